@@ -112,7 +112,7 @@ struct Group {
   DevBuf state;                  // KState [cap]
   DevBuf flags;                  // int [2][cap]
   DevBuf rhs_body, pol, ph;      // per right-hand side
-  DevBuf dirs, part, F, wd;      // far-field scratch
+  DevBuf ang, dirs, part, F, wd;  // far-field scratch
   // far-field voxel blocks per body (built on first use; the body never changes)
   struct Far {
     FarBlocks fb;
@@ -2374,10 +2374,11 @@ extern "C" int vie_get_current(vie_ctx* ctx, int32_t body, int32_t rhs, vie_c64*
 }
 
 // -------------------------------------------------------------- far field
-// Far field of every right-hand side of body B at ndir directions given as
-// (r-hat, e1, e2) triples (9 doubles each, e1 and e2 orthonormal and
-// perpendicular to r-hat): F[(rhs * ndir + d) * 2 + {0,1}] = (e1.F, e2.F).
-static int far_project(vie_ctx* ctx, BodyRec& B, const std::vector<double>& dirs, int ndir,
+// Far field of every right-hand side of body B at ndir directions, given as
+// angles (in = theta[ndir], phi[ndir]) or as (r-hat, e1, e2) triples (9 doubles
+// each, e1 and e2 orthonormal and perpendicular to r-hat):
+// F[(rhs * ndir + d) * 2 + {0,1}] = (e1.F, e2.F).
+static int far_project(vie_ctx* ctx, BodyRec& B, std::vector<double> in, bool angles, int ndir,
                        vie_c64* F) {
   Group& G = *ctx->groups[B.group];
   const size_t outn = (size_t)B.nrhs * ndir * 2;
@@ -2398,16 +2399,28 @@ static int far_project(vie_ctx* ctx, BodyRec& B, const std::vector<double>& dirs
     G.far[B.slot] = std::move(fr);
   }
   const Group::Far& fr = *G.far[B.slot];
-  const int ks = far_split_total(fr.fb, ndir);
-  VIE_HIP(G.dirs.reserve(dirs.size() * sizeof(double)));
-  VIE_HIP(G.part.reserve((size_t)ks * ndir * 3 * sizeof(c64)));
-  VIE_HIP(G.wd.reserve(far_pack_elems(fr.fb.ntiles) * sizeof(c64)));
+  const FarPlan pl = far_plan(fr.fb, B.nrhs, ndir);
+  // one upload: the directions, then the vector offsets of the right-hand
+  // sides (the solve's device copy may be gone: products share its storage)
+  const size_t nin = in.size();
+  in.resize(nin + B.nrhs);
+  memcpy(in.data() + nin, G.roff_host.data() + B.rhs0, B.nrhs * sizeof(int64_t));
+  VIE_HIP(G.dirs.reserve(((size_t)ndir * 9 + B.nrhs) * sizeof(double)));
+  VIE_HIP(G.part.reserve(pl.part * sizeof(c64)));
+  VIE_HIP(G.wd.reserve(pl.wd * sizeof(c64)));
   VIE_HIP(G.F.reserve(outn * sizeof(c64)));
-  VIE_HIP(hipMemcpyAsync(G.dirs.p, dirs.data(), dirs.size() * sizeof(double),
-                         hipMemcpyHostToDevice, ctx->stream));
+  if (angles) VIE_HIP(G.ang.reserve(in.size() * sizeof(double)));
+  double* din = angles ? G.ang.as<double>() : G.dirs.as<double>();
+  VIE_HIP(hipMemcpyAsync(din, in.data(), in.size() * sizeof(double), hipMemcpyHostToDevice,
+                         ctx->stream));
   VIE_HIP(timed(ctx, 12, [&] {
-    return launch_farfield_mfma(G.x.as<c64>(), G.roff_host.data() + B.rhs0, B.nrhs, B.nb, fr.fb,
-                                fr.vi.as<int>(), fr.org.as<int>(), G.dirs.as<double>(), ndir,
+    if (angles) {
+      const hipError_t fe =
+          launch_far_frames(G.ang.as<double>(), ndir, G.dirs.as<double>(), ctx->stream);
+      if (fe != hipSuccess) return fe;
+    }
+    return launch_farfield_mfma(G.x.as<c64>(), (const int64_t*)(din + nin), B.nrhs, B.nb, fr.fb,
+                                fr.vi.as<int>(), fr.org.as<int>(), pl, G.dirs.as<double>(), ndir,
                                 ctx->opt.k0, G.h, B.origin, G.wd.as<c64>(), G.part.as<c64>(),
                                 G.F.as<c64>(), ctx->stream);
   }));
@@ -2434,12 +2447,13 @@ extern "C" int vie_farfield(vie_ctx* ctx, int32_t body, const double* theta, con
     return VIE_EINVAL;
   BodyRec& B = *ctx->bodies[body];
   if (B.nrhs < 1) return VIE_ESTATE;
-  std::vector<double> dirs((size_t)ndir * 9);
+  std::vector<double> ang((size_t)ndir * 2);
   for (int d = 0; d < ndir; ++d) {
     if (!isfinite(theta[d]) || !isfinite(phi[d])) return VIE_EINVAL;
-    sph_frame(theta[d], phi[d], &dirs[(size_t)d * 9]);
+    ang[d] = theta[d];
+    ang[ndir + d] = phi[d];
   }
-  return far_project(ctx, B, dirs, ndir, F);
+  return far_project(ctx, B, std::move(ang), true, ndir, F);
 }
 
 // Gauss-Legendre nodes and weights on [-1, 1]: Newton iteration on P_n from
@@ -2527,7 +2541,7 @@ extern "C" int vie_transfer_na(vie_ctx* ctx, int32_t body, const vie_na_detector
   }
   const int nd = first[ndet];
   std::vector<vie_c64> F((size_t)B.nrhs * nd * 2);
-  const int rc = far_project(ctx, B, dirs, nd, F.data());
+  const int rc = far_project(ctx, B, std::move(dirs), false, nd, F.data());
   if (rc != VIE_OK) return rc;
   for (int q = 0; q < B.nrhs; ++q)
     for (int a = 0; a < ndet; ++a) {

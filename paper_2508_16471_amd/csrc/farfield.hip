@@ -25,8 +25,7 @@ namespace vie {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
-static constexpr int FF_RB = 1;          // right-hand sides per pass
-static constexpr int FF_QC = 3 * FF_RB;  // complex columns per block (rhs x component)
+static constexpr int FF_QC = 3;          // complex columns per block (components)
 static constexpr int FF_BS = 16;         // voxels per block (MFMA K = 4 per step, 4 steps)
 static constexpr int FF_TB = 16;         // blocks per tile (MFMA N)
 static constexpr int FF_WAVES = 4;       // waves per workgroup, 16 directions each
@@ -146,25 +145,41 @@ void far_blocks_build(const int* vox, int nb, const int N[3], FarBlocks& fb) {
 }
 
 // ------------------------------------------------------------ kernels
-struct RoffArg {
-  int64_t r[FF_RB];
-};
-
-// Wd[tile][qc][u][s] = w of right-hand side q, component c at offset u of
-// block tile*16 + s (zero where the block has no body voxel).
-__global__ void k_ff_pack(const c64* __restrict__ w, RoffArg ro, int nq, int nb,
+// Wd[q][tile][c][u][s] = w of right-hand side q (blockIdx.y), component c at
+// offset u of block tile*16 + s (zero where the block has no body voxel).
+__global__ void k_ff_pack(const c64* __restrict__ w, const int64_t* __restrict__ roff, int nb,
                           const int* __restrict__ blk_vi, int ntiles, c64* __restrict__ Wd) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= (int64_t)ntiles * FF_TILE) return;
   const int s = (int)(e % FF_TB);
   const int u = (int)((e / FF_TB) % FF_BS);
-  const int qc = (int)((e / (FF_TB * FF_BS)) % FF_QC);
+  const int c = (int)((e / (FF_TB * FF_BS)) % FF_QC);
   const int64_t tile = e / FF_TILE;
-  const int q = qc / 3, c = qc % 3;
   const int vi = blk_vi[(tile * FF_TB + s) * FF_BS + u];
   c64 v = mk(0.0, 0.0);
-  if (vi >= 0 && q < nq) v = w[ro.r[q] + (int64_t)c * nb + vi];
-  Wd[e] = v;
+  if (vi >= 0) v = w[roff[blockIdx.y] + (int64_t)c * nb + vi];
+  Wd[(int64_t)blockIdx.y * ntiles * FF_TILE + e] = v;
+}
+
+// dirs[d] = (r-hat, theta-hat, phi-hat) of the angles ang[0..nd) = theta,
+// ang[nd..2nd) = phi.  On the device because the host's trigonometry and a
+// 72-byte upload per direction cost more than the sweep's copies otherwise.
+__global__ void k_far_frames(const double* __restrict__ ang, int nd, double* __restrict__ dirs) {
+  const int d = blockIdx.x * blockDim.x + threadIdx.x;
+  if (d >= nd) return;
+  double st, ct, sp, cp;
+  sincos(ang[d], &st, &ct);
+  sincos(ang[nd + d], &sp, &cp);
+  double* D = dirs + (int64_t)d * 9;
+  D[0] = st * cp;
+  D[1] = st * sp;
+  D[2] = ct;
+  D[3] = ct * cp;
+  D[4] = ct * sp;
+  D[5] = -st;
+  D[6] = -sp;
+  D[7] = cp;
+  D[8] = 0.0;
 }
 
 struct FfGeom {
@@ -304,13 +319,15 @@ __device__ __forceinline__ void ff_accum(const d4 (&gR)[FF_QC], const d4 (&gI)[F
     for (int r = 0; r < 4; ++r) acc[r][qc] = cfma(S[r], mk(gR[qc][r], gI[qc][r]), acc[r][qc]);
 }
 
-// One workgroup: 64 directions (16 per wave) against the blocks of tiles
-// [t0, t1).  Tiles are double-buffered in LDS (one barrier per tile) with a
+// One workgroup: 64 directions (16 per wave) of right-hand side blockIdx.z
+// against the blocks of tiles [t0, t1).  Tiles are double-buffered in LDS (one barrier per tile) with a
 // register prefetch; two waves per SIMD so that one wave's scale-and-
 // accumulate and phase work runs while the other's matrix products execute.
 __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))) void k_ff_mfma(
-    const c64* __restrict__ Wd, const int4* __restrict__ org, int ntiles, int tiles_per_split,
-    const double* __restrict__ dirs, int nd, FfGeom fg, int nq, c64* __restrict__ part) {
+    const c64* __restrict__ Wd, int64_t wq, const int4* __restrict__ org, int ntiles,
+    int tiles_per_split, const double* __restrict__ dirs, int nd, FfGeom fg,
+    c64* __restrict__ part, int kst, int ks0) {
+  Wd += blockIdx.z * wq;
   __shared__ c64 sW[2][FF_TILE];
   __shared__ int4 sOrg[2][FF_TB];
   __shared__ c64 sT[FF_NT];
@@ -400,24 +417,41 @@ __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))
       const int d = dbase + (lane >> 4) + 4 * r;
       if (d >= nd) continue;
 #pragma unroll
-      for (int qc = 0; qc < FF_QC; ++qc) {
-        const int q = qc / 3, c = qc % 3;
-        if (q < nq) part[(((int64_t)blockIdx.y * nq + q) * nd + d) * 3 + c] = acc[r][qc];
-      }
+      for (int qc = 0; qc < FF_QC; ++qc)
+        part[(((int64_t)blockIdx.z * nd + d) * FF_QC + qc) * kst + ks0 + blockIdx.y] = acc[r][qc];
     }
   }
 }
 
-__global__ void k_farfield_project(const c64* __restrict__ part, int ksplit, int nr, int nd,
-                                   const double* __restrict__ dirs, double scale,
-                                   c64* __restrict__ F) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= nr * nd) return;
-  const int q = e / nd, d = e % nd;
-  c64 v[3] = {mk(0.0, 0.0), mk(0.0, 0.0), mk(0.0, 0.0)};
-  for (int k = 0; k < ksplit; ++k)
-    for (int c = 0; c < 3; ++c) v[c] = v[c] + part[(((int64_t)k * nr + q) * nd + d) * 3 + c];
-  const double* D = dirs + d * 9;
+// F = scale (theta-hat . S, phi-hat . S), S = the sum of the kst partials
+// of a (right-hand side, direction) pair, which are contiguous per
+// component.  L lanes share a pair: 64 where there are many partials (a
+// detector scan splits the voxels into hundreds; one thread walking them took
+// 190 us at 181 directions and 341 partials), 1 where a sweep leaves a few.
+// Fixed order either way.
+template <int L>
+__global__ __launch_bounds__(256) void k_farfield_project(const c64* __restrict__ part, int kst,
+                                                          int npair, int nd,
+                                                          const double* __restrict__ dirs,
+                                                          double scale, c64* __restrict__ F) {
+  const int e = (blockIdx.x * 256 + threadIdx.x) / L, lane = threadIdx.x % L;
+  if (e >= npair) return;
+  c64 v[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const c64* p = part + ((int64_t)e * 3 + c) * kst;
+    v[c] = mk(0.0, 0.0);
+    for (int k = lane; k < kst; k += L) v[c] = v[c] + p[k];
+  }
+#pragma unroll
+  for (int m = L / 2; m >= 1; m >>= 1)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      v[c].re += __shfl_xor(v[c].re, m, 64);
+      v[c].im += __shfl_xor(v[c].im, m, 64);
+    }
+  if (lane != 0) return;
+  const double* D = dirs + (int64_t)(e % nd) * 9;
   c64 ft = mk(0.0, 0.0), fp = mk(0.0, 0.0);
   for (int c = 0; c < 3; ++c) {
     ft = ft + D[3 + c] * v[c];
@@ -427,30 +461,58 @@ __global__ void k_farfield_project(const c64* __restrict__ part, int ksplit, int
   F[(int64_t)e * 2 + 1] = scale * fp;
 }
 
-static int far_split(int ntiles, int nd) {
+static hipError_t far_project_sums(const c64* part, int kst, int npair, int nd,
+                                   const double* dirs, double scale, c64* F, hipStream_t s) {
+  if (kst > 8)
+    k_farfield_project<64><<<(npair + 3) / 4, 256, 0, s>>>(part, kst, npair, nd, dirs, scale, F);
+  else
+    k_farfield_project<1><<<(npair + 255) / 256, 256, 0, s>>>(part, kst, npair, nd, dirs, scale,
+                                                              F);
+  return hipGetLastError();
+}
+
+// Workgroups wanted in one launch: the chip holds 512 (two per CU).
+static constexpr int kFarBlocks = 1024;
+
+// K-splits of `ntiles` tiles when `blocks` workgroups exist without a split.
+static int far_split(int ntiles, int blocks) {
   if (ntiles <= 0) return 0;
-  const int dblocks = (nd + FF_DIRS - 1) / FF_DIRS;
-  const int want = std::max(1, 1024 / dblocks);
+  const int want = std::max(1, kFarBlocks / std::max(1, blocks));
   const int ks = std::min(ntiles, want);
   const int tps = (ntiles + ks - 1) / ks;
   return (ntiles + tps - 1) / tps;
 }
 
-int far_split_total(const FarBlocks& fb, int nd) {
-  int ks = 0;
-  for (const FarGroup& gr : fb.groups) ks += far_split(gr.ntiles, nd);
-  return ks;
+FarPlan far_plan(const FarBlocks& fb, int nr, int nd) {
+  // right-hand sides per launch: as many as keep the packed operand and the
+  // partials within 64 MB each
+  constexpr int64_t kCap = (int64_t)64 << 20;
+  FarPlan p;
+  const int64_t wb = (int64_t)std::max(1, fb.ntiles) * FF_TILE * sizeof(c64);
+  const int db = (nd + FF_DIRS - 1) / FF_DIRS;
+  p.nq = (int)std::max<int64_t>(1, std::min<int64_t>(nr, kCap / wb));
+  for (;;) {
+    p.kst = 0;
+    for (const FarGroup& gr : fb.groups) p.kst += far_split(gr.ntiles, db * p.nq);
+    if (p.nq == 1 || (int64_t)p.nq * nd * FF_QC * p.kst * (int64_t)sizeof(c64) <= kCap) break;
+    p.nq = (p.nq + 1) / 2;
+  }
+  p.wd = (size_t)p.nq * fb.ntiles * FF_TILE;
+  p.part = (size_t)p.nq * nd * FF_QC * p.kst;
+  return p;
 }
 
-size_t far_pack_elems(int ntiles) { return (size_t)ntiles * FF_TILE; }
+hipError_t launch_far_frames(const double* ang, int nd, double* dirs, hipStream_t s) {
+  k_far_frames<<<(nd + 255) / 256, 256, 0, s>>>(ang, nd, dirs);
+  return hipGetLastError();
+}
 
-hipError_t launch_farfield_mfma(const c64* w, const int64_t* roff_host, int nr, int nb,
+hipError_t launch_farfield_mfma(const c64* w, const int64_t* roff, int nr, int nb,
                                 const FarBlocks& fb, const int* blk_vi, const int* blk_org,
-                                const double* dirs, int nd, double k0, double h,
+                                const FarPlan& pl, const double* dirs, int nd, double k0, double h,
                                 const double* origin, c64* Wd, c64* part, c64* F,
                                 hipStream_t s) {
   const int ntiles = fb.ntiles;
-  const int kst = far_split_total(fb, nd);
   FfGeom fg;
   fg.k0 = k0;
   fg.h = h;
@@ -458,33 +520,30 @@ hipError_t launch_farfield_mfma(const c64* w, const int64_t* roff_host, int nr, 
   fg.o[1] = origin[1];
   fg.o[2] = origin[2];
   const double scale = k0 * k0 * h * h * h / (4.0 * M_PI);
-  for (int q0 = 0; q0 < nr; q0 += FF_RB) {
-    const int nq = std::min(FF_RB, nr - q0);
-    RoffArg ro;
-    for (int q = 0; q < FF_RB; ++q) ro.r[q] = q < nq ? roff_host[q0 + q] : 0;
-    const int64_t tot = (int64_t)ntiles * FF_TILE;
-    k_ff_pack<<<(unsigned)((tot + 255) / 256), 256, 0, s>>>(w, ro, nq, nb, blk_vi, ntiles, Wd);
+  const int db = (nd + FF_DIRS - 1) / FF_DIRS;
+  const int64_t tot = (int64_t)ntiles * FF_TILE;
+  for (int q0 = 0; q0 < nr; q0 += pl.nq) {
+    const int nq = std::min(pl.nq, nr - q0);
+    k_ff_pack<<<dim3((unsigned)((tot + 255) / 256), nq), 256, 0, s>>>(w, roff + q0, nb, blk_vi,
+                                                                      ntiles, Wd);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // one launch per block shape; each writes its own range of K-split partials
     int ks0 = 0;
     for (const FarGroup& gr : fb.groups) {
-      const int ks = far_split(gr.ntiles, nd);
+      const int ks = far_split(gr.ntiles, db * pl.nq);
       if (ks == 0) continue;
       const int tps = (gr.ntiles + ks - 1) / ks;
       fg.bx = gr.shape[0];
       fg.by = gr.shape[1];
-      dim3 grid((nd + FF_DIRS - 1) / FF_DIRS, ks);
-      k_ff_mfma<<<grid, FF_DIRS * 4, 0, s>>>(
-          Wd + (int64_t)gr.tile0 * FF_TILE, (const int4*)blk_org + (int64_t)gr.tile0 * FF_TB,
-          gr.ntiles, tps, dirs, nd, fg, nq, part + (int64_t)ks0 * nq * nd * 3);
+      k_ff_mfma<<<dim3(db, ks, nq), FF_DIRS * 4, 0, s>>>(
+          Wd + (int64_t)gr.tile0 * FF_TILE, tot, (const int4*)blk_org + (int64_t)gr.tile0 * FF_TB,
+          gr.ntiles, tps, dirs, nd, fg, part, pl.kst, ks0);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
       ks0 += ks;
     }
-    k_farfield_project<<<(nq * nd + 255) / 256, 256, 0, s>>>(part, kst, nq, nd, dirs, scale,
-                                                              F + (int64_t)q0 * nd * 2);
-    e = hipGetLastError();
+    e = far_project_sums(part, pl.kst, nq * nd, nd, dirs, scale, F + (int64_t)q0 * nd * 2, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

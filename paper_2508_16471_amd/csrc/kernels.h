@@ -207,16 +207,23 @@ struct FarBlocks {
   std::vector<int> vi;   // [ntiles*16][16] compressed voxel index at offset u, -1 empty
 };
 void far_blocks_build(const int* vox, int nb, const int N[3], FarBlocks& fb);
-// Total K-split count over the groups, and packed-operand size (c64).
-int far_split_total(const FarBlocks& fb, int nd);
-size_t far_pack_elems(int ntiles);
+// Launch plan of nr right-hand sides at nd directions: right-hand sides per
+// launch, K-split partials per (right-hand side, direction, component), and
+// the scratch it needs (c64 counts of the packed operand and the partials).
+struct FarPlan {
+  int nq = 1, kst = 0;
+  size_t wd = 0, part = 0;
+};
+FarPlan far_plan(const FarBlocks& fb, int nr, int nd);
+// dirs[nd][9] = (r, theta-hat, phi-hat) of device angles ang = theta[nd], phi[nd].
+hipError_t launch_far_frames(const double* ang, int nd, double* dirs, hipStream_t s);
 // F[rhs][dir][2] = (F_theta, F_phi) for nr right-hand sides of one body; w
-// body-compressed with per-rhs offsets roff (host values), blk_vi / blk_org the
+// body-compressed with per-rhs offsets roff (device), blk_vi / blk_org the
 // device copies of fb.vi / fb.org; dirs[nd][9] = (r, theta-hat, phi-hat).
-// Scratch: Wd far_pack_elems(ntiles) c64, part far_split_total(..)*nd*3 c64.
-hipError_t launch_farfield_mfma(const c64* w, const int64_t* roff_host, int nr, int nb,
+// Scratch: Wd pl.wd c64, part pl.part c64.
+hipError_t launch_farfield_mfma(const c64* w, const int64_t* roff, int nr, int nb,
                                 const FarBlocks& fb, const int* blk_vi, const int* blk_org,
-                                const double* dirs, int nd, double k0, double h,
+                                const FarPlan& pl, const double* dirs, int nd, double k0, double h,
                                 const double* origin, c64* Wd, c64* part, c64* F,
                                 hipStream_t s);
 // ||v_rhs||^2 of body-compressed vectors into out[nrhs] (device).

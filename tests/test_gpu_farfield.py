@@ -124,3 +124,32 @@ def test_farfield_full_sweep_sphere_64(V):
         assert _relerr(F[:, row], F2) < 1e-13
     finally:
         V.vie_destroy(ctx)
+
+
+@pytest.mark.parametrize("nrhs,ndir", [(3, 5), (5, 40)])
+def test_farfield_right_hand_sides_in_several_launches(V, nrhs, ndir):
+    """Bodies whose packed operand exceeds the per-launch share: the
+    right-hand sides go out in launches of two with a remainder, the vector
+    offsets still hold after a product with more vectors has grown the
+    context's tables, and every one matches the direct sum (bar as above)."""
+    import torch
+
+    rng = np.random.default_rng(nrhs)
+    g = Grid.centred((96, 96, 64), 1 / 64)
+    eps = np.full((64, 96, 96), 1.05)
+    theta, phi = rng.uniform(0, np.pi, ndir), rng.uniform(-np.pi, np.pi, ndir)
+    ctx = V.vie_setup([(eps, g.h, g.origin)], V.make_options(K0, tol=1e-9, max_iter=2))
+    try:
+        V.vie_solve(ctx, _channels(rng, nrhs), [nrhs], allow_noconv=True)
+        x = torch.zeros((nrhs + 1, 3) + eps.shape, dtype=torch.complex128, device="cuda")
+        y = torch.empty_like(x)
+        V.vie_matvec_dev(ctx, 0, x.data_ptr(), y.data_ptr(), nrhs + 1)
+        F = V.vie_farfield(ctx, 0, theta, phi, nrhs)
+        pos = vd.voxel_centres(g.n, g.h, g.origin)
+        some = rng.choice(ndir, 4, replace=False)
+        for q in range(nrhs):
+            w = V.vie_get_current(ctx, 0, q, g.n).reshape(3, -1)
+            ft, fp = vd.farfield(w, pos, g.h, K0, theta[some], phi[some])
+            assert _relerr(F[q][some], np.stack([ft, fp], -1)) < 1e-12
+    finally:
+        V.vie_destroy(ctx)
