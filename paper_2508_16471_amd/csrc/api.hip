@@ -112,11 +112,14 @@ struct Group {
   DevBuf state;                  // KState [cap]
   DevBuf flags;                  // int [2][cap]
   DevBuf rhs_body, pol, ph;      // per right-hand side
-  DevBuf ang, dirs, part, F, wd;  // far-field scratch
+  DevBuf ang, dirs, part, F, wd, gidx;  // far-field scratch
   // far-field voxel blocks per body (built on first use; the body never changes)
   struct Far {
+    bool blocks = false, columns = false;  // built
     FarBlocks fb;
     DevBuf vi, org;
+    FarColumns fc;
+    DevBuf cptr, corg, cent;
   };
   std::vector<std::unique_ptr<Far>> far;  // [slot]
   // captured BiCGSTAB iterations (replayed while every pointer and the shape
@@ -2387,41 +2390,76 @@ static int far_project(vie_ctx* ctx, BodyRec& B, std::vector<double> in, bool an
     return VIE_OK;
   }
   if (G.far.size() < G.bodies.size()) G.far.resize(G.bodies.size());
-  if (!G.far[B.slot]) {
-    std::unique_ptr<Group::Far> fr(new Group::Far);
-    far_blocks_build(G.vox_host.data() + G.voff_host[B.slot], B.nb, G.g.N, fr->fb);
-    VIE_HIP(fr->vi.reserve(fr->fb.vi.size() * sizeof(int)));
-    VIE_HIP(fr->org.reserve(fr->fb.org.size() * sizeof(int)));
-    VIE_HIP(hipMemcpyAsync(fr->vi.p, fr->fb.vi.data(), fr->fb.vi.size() * sizeof(int),
-                           hipMemcpyHostToDevice, ctx->stream));
-    VIE_HIP(hipMemcpyAsync(fr->org.p, fr->fb.org.data(), fr->fb.org.size() * sizeof(int),
-                           hipMemcpyHostToDevice, ctx->stream));
-    G.far[B.slot] = std::move(fr);
+  if (!G.far[B.slot]) G.far[B.slot].reset(new Group::Far);
+  Group::Far& fr = *G.far[B.slot];
+  const int* vox = G.vox_host.data() + G.voff_host[B.slot];
+  auto up = [&](DevBuf& d, const std::vector<int>& v) -> hipError_t {
+    hipError_t e = d.reserve(std::max<size_t>(v.size(), 1) * sizeof(int));
+    if (e == hipSuccess && !v.empty())
+      e = hipMemcpyAsync(d.p, v.data(), v.size() * sizeof(int), hipMemcpyHostToDevice, ctx->stream);
+    return e;
+  };
+  // directions on a (theta, phi) grid go by theta groups where that pays
+  FarGroups gr;
+  bool sweep = angles && 1.25 * ndir * (double)B.nb > 3e7 && far_groups(in.data(), ndir, gr);
+  if (sweep) {
+    if (!fr.columns) {
+      far_columns_build(vox, B.nb, G.g.N, fr.fc);
+      VIE_HIP(up(fr.cptr, fr.fc.ptr));
+      VIE_HIP(up(fr.corg, fr.fc.org));
+      VIE_HIP(up(fr.cent, fr.fc.ent));
+      fr.columns = true;
+    }
+    sweep = far_by_columns(gr, ndir, fr.fc, B.nb);
   }
-  const Group::Far& fr = *G.far[B.slot];
-  const FarPlan pl = far_plan(fr.fb, B.nrhs, ndir);
+  if (!sweep && !fr.blocks) {
+    far_blocks_build(vox, B.nb, G.g.N, fr.fb);
+    VIE_HIP(up(fr.vi, fr.fb.vi));
+    VIE_HIP(up(fr.org, fr.fb.org));
+    fr.blocks = true;
+  }
+  FarPlan pl;
+  FarSweepPlan sp;
+  std::vector<int> gidx;  // sweep: perm, first, tile
+  if (sweep) {
+    sp = far_sweep_plan(gr, fr.fc, B.nrhs, ndir);
+    // the tile table first: its int4 rows want the buffer's alignment
+    gidx = gr.tile;
+    gidx.insert(gidx.end(), gr.perm.begin(), gr.perm.end());
+    gidx.insert(gidx.end(), gr.first.begin(), gr.first.end());
+    VIE_HIP(up(G.gidx, gidx));
+  } else {
+    pl = far_plan(fr.fb, B.nrhs, ndir);
+  }
   // one upload: the directions, then the vector offsets of the right-hand
   // sides (the solve's device copy may be gone: products share its storage)
   const size_t nin = in.size();
   in.resize(nin + B.nrhs);
   memcpy(in.data() + nin, G.roff_host.data() + B.rhs0, B.nrhs * sizeof(int64_t));
   VIE_HIP(G.dirs.reserve(((size_t)ndir * 9 + B.nrhs) * sizeof(double)));
-  VIE_HIP(G.part.reserve(pl.part * sizeof(c64)));
-  VIE_HIP(G.wd.reserve(pl.wd * sizeof(c64)));
+  VIE_HIP(G.part.reserve((sweep ? sp.part : pl.part) * sizeof(c64)));
+  VIE_HIP(G.wd.reserve((sweep ? sp.wd : pl.wd) * sizeof(c64)));
   VIE_HIP(G.F.reserve(outn * sizeof(c64)));
   if (angles) VIE_HIP(G.ang.reserve(in.size() * sizeof(double)));
   double* din = angles ? G.ang.as<double>() : G.dirs.as<double>();
   VIE_HIP(hipMemcpyAsync(din, in.data(), in.size() * sizeof(double), hipMemcpyHostToDevice,
                          ctx->stream));
+  const FarSrc src = {G.x.as<c64>(), (const int64_t*)(din + nin), B.nb, nullptr};
+  const FarGeom geo = {ctx->opt.k0, G.h, {B.origin[0], B.origin[1], B.origin[2]}, 0.0};
   VIE_HIP(timed(ctx, 12, [&] {
+    const int* perm = sweep ? G.gidx.as<int>() + gr.tile.size() : nullptr;
     if (angles) {
       const hipError_t fe =
-          launch_far_frames(G.ang.as<double>(), ndir, G.dirs.as<double>(), ctx->stream);
+          launch_far_frames(G.ang.as<double>(), perm, ndir, G.dirs.as<double>(), ctx->stream);
       if (fe != hipSuccess) return fe;
     }
-    return launch_farfield_mfma(G.x.as<c64>(), (const int64_t*)(din + nin), B.nrhs, B.nb, fr.fb,
-                                fr.vi.as<int>(), fr.org.as<int>(), pl, G.dirs.as<double>(), ndir,
-                                ctx->opt.k0, G.h, B.origin, G.wd.as<c64>(), G.part.as<c64>(),
+    if (sweep)
+      return launch_farfield_sweep(src, B.nrhs, fr.fc, fr.cptr.as<int>(), fr.corg.as<int>(),
+                                   fr.cent.as<int>(), gr, perm, perm + gr.perm.size(),
+                                   G.gidx.as<int>(), sp, G.dirs.as<double>(), ndir, G.g.N[2], geo,
+                                   G.wd.as<c64>(), G.part.as<c64>(), G.F.as<c64>(), ctx->stream);
+    return launch_farfield_mfma(src, B.nrhs, fr.fb, fr.vi.as<int>(), fr.org.as<int>(), pl,
+                                G.dirs.as<double>(), ndir, geo, G.wd.as<c64>(), G.part.as<c64>(),
                                 G.F.as<c64>(), ctx->stream);
   }));
   VIE_HIP(hipMemcpyAsync(F, G.F.p, outn * sizeof(c64), hipMemcpyDeviceToHost, ctx->stream));

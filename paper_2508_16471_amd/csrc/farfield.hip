@@ -16,6 +16,16 @@
 // The accumulation over blocks is split across workgroups (K-split) and
 // reduced in fixed order by a second kernel that projects onto theta-hat /
 // phi-hat and applies the constant.
+//
+// Directions that share theta share the phase's z factor exp(-i k0 h cos(theta) z),
+// so a sweep on a (theta, phi) grid needs the voxels only once per theta:
+//   U(theta, x, y) = sum_z w(x, y, z) exp(-i k0 h cos(theta) z)     (k_ff_columns)
+//   F(theta, phi)  = sum_xy U(theta, x, y) exp(-i k0 (r_x x + r_y y))
+// and the second sum is the same contraction over blocks of 16 columns.  On
+// the 128-cell metasurface (193,248 voxels in 16,384 columns) a 180 x 360
+// sweep of two channels does a twelfth of the contraction.
+#include <string.h>
+
 #include <algorithm>
 #include <vector>
 
@@ -144,11 +154,121 @@ void far_blocks_build(const int* vox, int nb, const int N[3], FarBlocks& fb) {
   fb.ntiles = tiles;
 }
 
+void far_columns_build(const int* vox, int nb, const int N[3], FarColumns& fc) {
+  const int plane = N[0] * N[1];
+  std::vector<int> cnt(plane, 0);
+  for (int k = 0; k < nb; ++k) ++cnt[vox[k] % plane];
+  // the lateral block shape that covers the columns with the fewest blocks
+  const int shapes[][2] = {{16, 1}, {8, 2}, {4, 4}, {2, 8}, {1, 16}};
+  int best = -1, nblk = 0;
+  for (int s = 0; s < 5; ++s) {
+    const int bx = shapes[s][0], by = shapes[s][1];
+    int n = 0;
+    for (int y0 = 0; y0 < N[1]; y0 += by)
+      for (int x0 = 0; x0 < N[0]; x0 += bx) {
+        bool any = false;
+        for (int y = y0; y < std::min(N[1], y0 + by) && !any; ++y)
+          for (int x = x0; x < std::min(N[0], x0 + bx) && !any; ++x) any = cnt[y * N[0] + x] > 0;
+        n += any;
+      }
+    if (best < 0 || n < nblk) {
+      best = s;
+      nblk = n;
+    }
+  }
+  fc.bx = shapes[best][0];
+  fc.by = shapes[best][1];
+  fc.ntiles = (nblk + FF_TB - 1) / FF_TB;
+  const size_t nslot = (size_t)fc.ntiles * FF_TB * FF_BS;
+  fc.org.assign((size_t)fc.ntiles * FF_TB * 4, 0);
+  fc.ptr.assign(nslot + 1, 0);
+  std::vector<int> slot(plane, -1);
+  int b = 0;
+  for (int y0 = 0; y0 < N[1]; y0 += fc.by)
+    for (int x0 = 0; x0 < N[0]; x0 += fc.bx) {
+      bool any = false;
+      for (int v = 0; v < fc.by; ++v)
+        for (int u = 0; u < fc.bx; ++u) {
+          const int x = x0 + u, y = y0 + v;
+          if (x >= N[0] || y >= N[1] || cnt[y * N[0] + x] == 0) continue;
+          any = true;
+          slot[y * N[0] + x] = b * FF_BS + v * fc.bx + u;
+        }
+      if (!any) continue;
+      fc.org[(size_t)b * 4 + 0] = x0;
+      fc.org[(size_t)b * 4 + 1] = y0;
+      ++b;
+    }
+  for (int c = 0; c < plane; ++c)
+    if (slot[c] >= 0) fc.ptr[slot[c] + 1] = cnt[c];
+  for (size_t k = 0; k < nslot; ++k) fc.ptr[k + 1] += fc.ptr[k];
+  fc.ent.resize((size_t)nb * 2);
+  std::vector<int> at(fc.ptr.begin(), fc.ptr.end() - 1);
+  for (int k = 0; k < nb; ++k) {  // ascending voxels: each column's entries ascend in z
+    const int e = at[slot[vox[k] % plane]]++;
+    fc.ent[(size_t)e * 2] = k;
+    fc.ent[(size_t)e * 2 + 1] = vox[k] / plane;
+  }
+}
+
+bool far_groups(const double* theta, int nd, FarGroups& fg) {
+  // open-addressed table of the distinct angles (by their bits), at most half
+  // as many as directions: beyond that nothing is shared
+  const int most = nd / 2;
+  if (most < 1) return false;
+  int cap = 16;
+  while (cap < 2 * most) cap <<= 1;
+  std::vector<uint64_t> key(cap);
+  std::vector<int> val(cap, -1), id(nd);
+  fg.first.assign(1, 0);
+  std::vector<int> cnt;
+  int last = -1;
+  uint64_t lastbits = 0;
+  for (int d = 0; d < nd; ++d) {
+    uint64_t b;
+    memcpy(&b, &theta[d], sizeof(b));
+    if (last < 0 || b != lastbits) {
+      uint64_t hsh = b * 0x9E3779B97F4A7C15ull;
+      int i = (int)((hsh >> 32) & (uint64_t)(cap - 1));
+      while (val[i] >= 0 && key[i] != b) i = (i + 1) & (cap - 1);
+      if (val[i] < 0) {
+        if ((int)cnt.size() >= most) return false;
+        key[i] = b;
+        val[i] = (int)cnt.size();
+        cnt.push_back(0);
+      }
+      last = val[i];
+      lastbits = b;
+    }
+    id[d] = last;
+    ++cnt[last];
+  }
+  const int ng = (int)cnt.size();
+  fg.first.resize(ng + 1);
+  for (int g = 0; g < ng; ++g) fg.first[g + 1] = fg.first[g] + cnt[g];
+  std::vector<int> at(fg.first.begin(), fg.first.end() - 1);
+  fg.perm.resize(nd);
+  for (int d = 0; d < nd; ++d) fg.perm[at[id[d]]++] = d;
+  // direction tiles: up to 64 directions of one group each
+  fg.tile.clear();
+  fg.tile0.assign(1, 0);
+  fg.rows = 0;
+  for (int g = 0; g < ng; ++g) {
+    for (int k = 0; k < cnt[g]; k += FF_DIRS) {
+      const int n = std::min(FF_DIRS, cnt[g] - k);
+      fg.tile.insert(fg.tile.end(), {fg.first[g] + k, n, g, 0});
+      fg.rows += (n + 15) / 16 * 16;
+    }
+    fg.tile0.push_back((int)(fg.tile.size() / 4));
+  }
+  return true;
+}
+
 // ------------------------------------------------------------ kernels
 // Wd[q][tile][c][u][s] = w of right-hand side q (blockIdx.y), component c at
 // offset u of block tile*16 + s (zero where the block has no body voxel).
-__global__ void k_ff_pack(const c64* __restrict__ w, const int64_t* __restrict__ roff, int nb,
-                          const int* __restrict__ blk_vi, int ntiles, c64* __restrict__ Wd) {
+__global__ void k_ff_pack(FarSrc f, const int* __restrict__ blk_vi, int ntiles,
+                          c64* __restrict__ Wd) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= (int64_t)ntiles * FF_TILE) return;
   const int s = (int)(e % FF_TB);
@@ -157,20 +277,22 @@ __global__ void k_ff_pack(const c64* __restrict__ w, const int64_t* __restrict__
   const int64_t tile = e / FF_TILE;
   const int vi = blk_vi[(tile * FF_TB + s) * FF_BS + u];
   c64 v = mk(0.0, 0.0);
-  if (vi >= 0) v = w[roff[blockIdx.y] + (int64_t)c * nb + vi];
+  if (vi >= 0) v = f.at(f.roff[blockIdx.y], c, vi);
   Wd[(int64_t)blockIdx.y * ntiles * FF_TILE + e] = v;
 }
 
-// dirs[d] = (r-hat, theta-hat, phi-hat) of the angles ang[0..nd) = theta,
-// ang[nd..2nd) = phi.  On the device because the host's trigonometry and a
+// dirs[p] = (r-hat, theta-hat, phi-hat) of the angles ang[d] = theta,
+// ang[nd + d] = phi of direction d = perm[p] (p itself without perm).  On the device because the host's trigonometry and a
 // 72-byte upload per direction cost more than the sweep's copies otherwise.
-__global__ void k_far_frames(const double* __restrict__ ang, int nd, double* __restrict__ dirs) {
-  const int d = blockIdx.x * blockDim.x + threadIdx.x;
-  if (d >= nd) return;
+__global__ void k_far_frames(const double* __restrict__ ang, const int* __restrict__ perm, int nd,
+                             double* __restrict__ dirs) {
+  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= nd) return;
+  const int d = perm ? perm[p] : p;
   double st, ct, sp, cp;
   sincos(ang[d], &st, &ct);
   sincos(ang[nd + d], &sp, &cp);
-  double* D = dirs + (int64_t)d * 9;
+  double* D = dirs + (int64_t)p * 9;
   D[0] = st * cp;
   D[1] = st * sp;
   D[2] = ct;
@@ -319,15 +441,76 @@ __device__ __forceinline__ void ff_accum(const d4 (&gR)[FF_QC], const d4 (&gI)[F
     for (int r = 0; r < 4; ++r) acc[r][qc] = cfma(S[r], mk(gR[qc][r], gI[qc][r]), acc[r][qc]);
 }
 
+// Sums over columns of z: U of theta group g0 + g (g < ng) and right-hand
+// side q, written as the packed operand Wd[q][g][tile] of the lateral
+// contraction.  One thread per column slot (16 of a block are neighbouring
+// lanes, so a block's loads are contiguous), FF_CG groups per pass over the
+// column's voxels, whose z factors sit in LDS; FP64 VALU bound (24 complex
+// multiply-adds per voxel and pass against 56 bytes read).
+constexpr int FF_CG = 8;
+constexpr int FF_NZ = 256;  // most z layers of a grid
+__global__ __launch_bounds__(256) void k_ff_columns(FarSrc f, const int* __restrict__ ptr,
+                                                    const int2* __restrict__ ent, int ntiles,
+                                                    const int* __restrict__ gfirst, int g0, int ng,
+                                                    const double* __restrict__ dirs, double k0h,
+                                                    int nz, c64* __restrict__ Wd) {
+  __shared__ c64 sT[FF_CG][FF_NZ];
+  const int gb = blockIdx.y * FF_CG;
+  for (int k = threadIdx.x; k < FF_CG * nz; k += 256) {
+    const int g = k / nz, z = k % nz;
+    double sn = 0.0, cs = 0.0;
+    if (gb + g < ng) ff_sincos(-k0h * dirs[(int64_t)gfirst[g0 + gb + g] * 9 + 2] * z, sn, cs);
+    sT[g][z] = mk(cs, sn);
+  }
+  __syncthreads();
+  const int p = blockIdx.x * 256 + threadIdx.x;
+  const int64_t off = f.roff[blockIdx.z];
+  c64 acc[FF_CG][FF_QC];
+#pragma unroll
+  for (int g = 0; g < FF_CG; ++g)
+#pragma unroll
+    for (int c = 0; c < FF_QC; ++c) acc[g][c] = mk(0.0, 0.0);
+  const int k1 = ptr[p + 1];
+  for (int k = ptr[p]; k < k1; ++k) {
+    const int2 e = ent[k];
+    c64 wv[FF_QC];
+#pragma unroll
+    for (int c = 0; c < FF_QC; ++c) wv[c] = f.at(off, c, e.x);
+#pragma unroll
+    for (int g = 0; g < FF_CG; ++g) {
+      const c64 t = sT[g][e.y];
+#pragma unroll
+      for (int c = 0; c < FF_QC; ++c) acc[g][c] = cfma(t, wv[c], acc[g][c]);
+    }
+  }
+  const int u = threadIdx.x & 15, s = threadIdx.x >> 4;
+#pragma unroll
+  for (int g = 0; g < FF_CG; ++g) {
+    if (gb + g >= ng) break;
+    c64* o = Wd + (((int64_t)blockIdx.z * ng + gb + g) * ntiles + blockIdx.x) * FF_TILE;
+#pragma unroll
+    for (int c = 0; c < FF_QC; ++c) o[(c * FF_BS + u) * FF_TB + s] = acc[g][c];
+  }
+}
+
 // One workgroup: 64 directions (16 per wave) of right-hand side blockIdx.z
-// against the blocks of tiles [t0, t1).  Tiles are double-buffered in LDS (one barrier per tile) with a
-// register prefetch; two waves per SIMD so that one wave's scale-and-
-// accumulate and phase work runs while the other's matrix products execute.
+// against the blocks of tiles [t0, t1); with a tile table dt (first direction,
+// count, theta group - g0) the directions of one theta group against that
+// group's packed columns.  Tiles are double-buffered in LDS (one barrier per
+// tile) with a register prefetch; two waves per SIMD so that one wave's scale-
+// and-accumulate and phase work runs while the other's matrix products execute.
 __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))) void k_ff_mfma(
     const c64* __restrict__ Wd, int64_t wq, const int4* __restrict__ org, int ntiles,
-    int tiles_per_split, const double* __restrict__ dirs, int nd, FfGeom fg,
-    c64* __restrict__ part, int kst, int ks0) {
+    int tiles_per_split, const double* __restrict__ dirs, const int4* __restrict__ dt, int g0,
+    int npos, FfGeom fg, c64* __restrict__ part, int kst, int ks0) {
   Wd += blockIdx.z * wq;
+  int first = blockIdx.x * FF_DIRS, nd = npos;
+  if (dt) {
+    const int4 t = dt[blockIdx.x];
+    first = t.x;
+    nd = t.x + t.y;  // positions past the group's last one are idle
+    Wd += (int64_t)(t.z - g0) * ntiles * FF_TILE;
+  }
   __shared__ c64 sW[2][FF_TILE];
   __shared__ int4 sOrg[2][FF_TB];
   __shared__ c64 sT[FF_NT];
@@ -337,7 +520,7 @@ __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))
     ff_sincos(k * (2.0 * M_PI / FF_NT), sn, cs);
     sT[k] = mk(cs, sn);
   }  // visible after the first barrier of the tile loop
-  const int dbase = blockIdx.x * FF_DIRS + wave * 16;
+  const int dbase = first + wave * 16;
   const int t0 = blockIdx.y * tiles_per_split;
   const int t1 = min(ntiles, t0 + tiles_per_split);
 
@@ -395,8 +578,10 @@ __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))
     ff_store(sW[cb], sOrg[cb], pre);
     if (t + 1 < t1) pre = ff_fetch(Wd, org, t + 1);
     __syncthreads();
-    ff_tile(sW[cb], sOrg[cb], sT, aR, aI, aIn, rw, lane, gR, gI, S);
-    ff_accum(gR, gI, S, acc);
+    if (dbase < nd) {
+      ff_tile(sW[cb], sOrg[cb], sT, aR, aI, aIn, rw, lane, gR, gI, S);
+      ff_accum(gR, gI, S, acc);
+    }
   }
   // sum over the 16 column blocks (lanes sharing lane / 16), fixed pattern
 #pragma unroll
@@ -418,14 +603,16 @@ __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))
       if (d >= nd) continue;
 #pragma unroll
       for (int qc = 0; qc < FF_QC; ++qc)
-        part[(((int64_t)blockIdx.z * nd + d) * FF_QC + qc) * kst + ks0 + blockIdx.y] = acc[r][qc];
+        part[(((int64_t)blockIdx.z * npos + d) * FF_QC + qc) * kst + ks0 + blockIdx.y] =
+            acc[r][qc];
     }
   }
 }
 
 // F = scale (theta-hat . S, phi-hat . S), S = the sum of the kst partials
-// of a (right-hand side, direction) pair, which are contiguous per
-// component.  L lanes share a pair: 64 where there are many partials (a
+// of a (right-hand side, direction position) pair, which are contiguous per
+// component; component c's points sit `half` / k0 off the block origins along
+// axis c (rooftop faces; 0 for voxels).  Position p is direction perm[p].  L lanes share a pair: 64 where there are many partials (a
 // detector scan splits the voxels into hundreds; one thread walking them took
 // 190 us at 181 directions and 341 partials), 1 where a sweep leaves a few.
 // Fixed order either way.
@@ -433,7 +620,9 @@ template <int L>
 __global__ __launch_bounds__(256) void k_farfield_project(const c64* __restrict__ part, int kst,
                                                           int npair, int nd,
                                                           const double* __restrict__ dirs,
-                                                          double scale, c64* __restrict__ F) {
+                                                          const int* __restrict__ perm,
+                                                          double scale, double half,
+                                                          c64* __restrict__ F) {
   const int e = (blockIdx.x * 256 + threadIdx.x) / L, lane = threadIdx.x % L;
   if (e >= npair) return;
   c64 v[3];
@@ -451,23 +640,35 @@ __global__ __launch_bounds__(256) void k_farfield_project(const c64* __restrict_
       v[c].im += __shfl_xor(v[c].im, m, 64);
     }
   if (lane != 0) return;
-  const double* D = dirs + (int64_t)(e % nd) * 9;
+  const int pos = e % nd, q = e / nd;
+  const double* D = dirs + (int64_t)pos * 9;
+  if (half != 0.0)
+    for (int c = 0; c < 3; ++c) {
+      double sn, cs;
+      ff_sincos(-half * D[c], sn, cs);
+      v[c] = v[c] * mk(cs, sn);
+    }
   c64 ft = mk(0.0, 0.0), fp = mk(0.0, 0.0);
   for (int c = 0; c < 3; ++c) {
     ft = ft + D[3 + c] * v[c];
     fp = fp + D[6 + c] * v[c];
   }
-  F[(int64_t)e * 2 + 0] = scale * ft;
-  F[(int64_t)e * 2 + 1] = scale * fp;
+  c64* o = F + ((int64_t)q * nd + (perm ? perm[pos] : pos)) * 2;
+  o[0] = scale * ft;
+  o[1] = scale * fp;
 }
 
 static hipError_t far_project_sums(const c64* part, int kst, int npair, int nd,
-                                   const double* dirs, double scale, c64* F, hipStream_t s) {
+                                   const double* dirs, const int* perm, const FarGeom& fg, c64* F,
+                                   hipStream_t s) {
+  const double scale = fg.k0 * fg.k0 * fg.h * fg.h * fg.h / (4.0 * M_PI);
+  const double half = fg.k0 * fg.half;
   if (kst > 8)
-    k_farfield_project<64><<<(npair + 3) / 4, 256, 0, s>>>(part, kst, npair, nd, dirs, scale, F);
+    k_farfield_project<64><<<(npair + 3) / 4, 256, 0, s>>>(part, kst, npair, nd, dirs, perm, scale,
+                                                           half, F);
   else
-    k_farfield_project<1><<<(npair + 255) / 256, 256, 0, s>>>(part, kst, npair, nd, dirs, scale,
-                                                              F);
+    k_farfield_project<1><<<(npair + 255) / 256, 256, 0, s>>>(part, kst, npair, nd, dirs, perm,
+                                                              scale, half, F);
   return hipGetLastError();
 }
 
@@ -502,30 +703,96 @@ FarPlan far_plan(const FarBlocks& fb, int nr, int nd) {
   return p;
 }
 
-hipError_t launch_far_frames(const double* ang, int nd, double* dirs, hipStream_t s) {
-  k_far_frames<<<(nd + 255) / 256, 256, 0, s>>>(ang, nd, dirs);
+// Whether a sweep goes by theta groups: complex multiply-adds of the lateral
+// contraction (whole 16-direction rows x column slots) plus the column sums,
+// which run on the VALU at about a quarter of the rate, against the direct
+// contraction of every voxel (1.25 slots per voxel).  Below about 3e7 direct
+// multiply-adds both are a few launches of latency, and the direct path has
+// two fewer.
+bool far_by_columns(const FarGroups& fg, int nd, const FarColumns& fc, int nb) {
+  const double direct = 1.25 * nd * (double)nb;
+  const double cols = (double)fg.rows * fc.ntiles * FF_TB * FF_BS +
+                      4.0 * (double)(fg.first.size() - 1) * nb;
+  return direct > 3e7 && cols < 0.8 * direct;
+}
+
+FarSweepPlan far_sweep_plan(const FarGroups& fg, const FarColumns& fc, int nr, int nd) {
+  constexpr int64_t kCap = (int64_t)64 << 20;  // packed operand and partials, as far_plan
+  FarSweepPlan p;
+  const int ng = (int)fg.first.size() - 1;
+  const int64_t gb = (int64_t)fc.ntiles * FF_TILE * sizeof(c64);
+  p.nq = (int)std::max<int64_t>(1, std::min<int64_t>(nr, kCap / std::max<int64_t>(gb, 1)));
+  for (;;) {
+    p.ngc = (int)std::max<int64_t>(1, std::min<int64_t>(ng, kCap / (gb * p.nq)));
+    const int64_t blocks = (int64_t)(fg.tile.size() / 4) * p.ngc / ng * p.nq;
+    p.kst = far_split(fc.ntiles, (int)std::min<int64_t>(blocks, kFarBlocks));
+    if (p.nq == 1 || (int64_t)p.nq * nd * FF_QC * p.kst * (int64_t)sizeof(c64) <= kCap) break;
+    p.nq = (p.nq + 1) / 2;
+  }
+  p.wd = (size_t)p.nq * p.ngc * fc.ntiles * FF_TILE;
+  p.part = (size_t)p.nq * nd * FF_QC * p.kst;
+  return p;
+}
+
+hipError_t launch_far_frames(const double* ang, const int* perm, int nd, double* dirs,
+                             hipStream_t s) {
+  k_far_frames<<<(nd + 255) / 256, 256, 0, s>>>(ang, perm, nd, dirs);
   return hipGetLastError();
 }
 
-hipError_t launch_farfield_mfma(const c64* w, const int64_t* roff, int nr, int nb,
-                                const FarBlocks& fb, const int* blk_vi, const int* blk_org,
-                                const FarPlan& pl, const double* dirs, int nd, double k0, double h,
-                                const double* origin, c64* Wd, c64* part, c64* F,
-                                hipStream_t s) {
+hipError_t launch_farfield_sweep(const FarSrc& src, int nr, const FarColumns& fc, const int* ptr,
+                                 const int* org, const int* ent, const FarGroups& gr,
+                                 const int* perm, const int* first, const int* tile,
+                                 const FarSweepPlan& pl, const double* dirs, int nd, int nz,
+                                 const FarGeom& geo, c64* Wd, c64* part, c64* F, hipStream_t s) {
+  if (nz > FF_NZ) return hipErrorInvalidValue;
+  const int ng = (int)gr.first.size() - 1;
+  const int tps = (fc.ntiles + pl.kst - 1) / pl.kst;
+  FfGeom fg;
+  fg.k0 = geo.k0;
+  fg.h = geo.h;
+  for (int a = 0; a < 3; ++a) fg.o[a] = geo.o[a];
+  fg.bx = fc.bx;
+  fg.by = fc.by;
+  for (int q0 = 0; q0 < nr; q0 += pl.nq) {
+    const int nq = std::min(pl.nq, nr - q0);
+    FarSrc f = src;
+    f.roff += q0;
+    for (int g0 = 0; g0 < ng; g0 += pl.ngc) {
+      const int n = std::min(pl.ngc, ng - g0);
+      k_ff_columns<<<dim3(fc.ntiles, (n + FF_CG - 1) / FF_CG, nq), 256, 0, s>>>(
+          f, ptr, (const int2*)ent, fc.ntiles, first, g0, n, dirs, geo.k0 * geo.h, nz, Wd);
+      hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      const int d0 = gr.tile0[g0], d1 = gr.tile0[g0 + n];
+      k_ff_mfma<<<dim3(d1 - d0, pl.kst, nq), FF_DIRS * 4, 0, s>>>(
+          Wd, (int64_t)n * fc.ntiles * FF_TILE, (const int4*)org, fc.ntiles, tps, dirs,
+          (const int4*)tile + d0, g0, nd, fg, part, pl.kst, 0);
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    const hipError_t e = far_project_sums(part, pl.kst, nq * nd, nd, dirs, perm, geo,
+                                          F + (int64_t)q0 * nd * 2, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_farfield_mfma(const FarSrc& src, int nr, const FarBlocks& fb, const int* blk_vi,
+                                const int* blk_org, const FarPlan& pl, const double* dirs, int nd,
+                                const FarGeom& geo, c64* Wd, c64* part, c64* F, hipStream_t s) {
   const int ntiles = fb.ntiles;
   FfGeom fg;
-  fg.k0 = k0;
-  fg.h = h;
-  fg.o[0] = origin[0];
-  fg.o[1] = origin[1];
-  fg.o[2] = origin[2];
-  const double scale = k0 * k0 * h * h * h / (4.0 * M_PI);
+  fg.k0 = geo.k0;
+  fg.h = geo.h;
+  for (int a = 0; a < 3; ++a) fg.o[a] = geo.o[a];
   const int db = (nd + FF_DIRS - 1) / FF_DIRS;
   const int64_t tot = (int64_t)ntiles * FF_TILE;
   for (int q0 = 0; q0 < nr; q0 += pl.nq) {
     const int nq = std::min(pl.nq, nr - q0);
-    k_ff_pack<<<dim3((unsigned)((tot + 255) / 256), nq), 256, 0, s>>>(w, roff + q0, nb, blk_vi,
-                                                                      ntiles, Wd);
+    FarSrc f = src;
+    f.roff += q0;
+    k_ff_pack<<<dim3((unsigned)((tot + 255) / 256), nq), 256, 0, s>>>(f, blk_vi, ntiles, Wd);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // one launch per block shape; each writes its own range of K-split partials
@@ -538,12 +805,13 @@ hipError_t launch_farfield_mfma(const c64* w, const int64_t* roff, int nr, int n
       fg.by = gr.shape[1];
       k_ff_mfma<<<dim3(db, ks, nq), FF_DIRS * 4, 0, s>>>(
           Wd + (int64_t)gr.tile0 * FF_TILE, tot, (const int4*)blk_org + (int64_t)gr.tile0 * FF_TB,
-          gr.ntiles, tps, dirs, nd, fg, part, pl.kst, ks0);
+          gr.ntiles, tps, dirs, nullptr, 0, nd, fg, part, pl.kst, ks0);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
       ks0 += ks;
     }
-    e = far_project_sums(part, pl.kst, nq * nd, nd, dirs, scale, F + (int64_t)q0 * nd * 2, s);
+    e = far_project_sums(part, pl.kst, nq * nd, nd, dirs, nullptr, geo, F + (int64_t)q0 * nd * 2,
+                         s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

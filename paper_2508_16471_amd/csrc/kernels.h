@@ -215,17 +215,66 @@ struct FarPlan {
   size_t wd = 0, part = 0;
 };
 FarPlan far_plan(const FarBlocks& fb, int nr, int nd);
-// dirs[nd][9] = (r, theta-hat, phi-hat) of device angles ang = theta[nd], phi[nd].
-hipError_t launch_far_frames(const double* ang, int nd, double* dirs, hipStream_t s);
-// F[rhs][dir][2] = (F_theta, F_phi) for nr right-hand sides of one body; w
-// body-compressed with per-rhs offsets roff (device), blk_vi / blk_org the
-// device copies of fb.vi / fb.org; dirs[nd][9] = (r, theta-hat, phi-hat).
-// Scratch: Wd pl.wd c64, part pl.part c64.
-hipError_t launch_farfield_mfma(const c64* w, const int64_t* roff, int nr, int nb,
-                                const FarBlocks& fb, const int* blk_vi, const int* blk_org,
-                                const FarPlan& pl, const double* dirs, int nd, double k0, double h,
-                                const double* origin, c64* Wd, c64* part, c64* F,
-                                hipStream_t s);
+// The currents: component c of point k of right-hand side q is
+// w[roff[q] + c cs + k], times scale[c cs + k] if given.  roff on the device.
+struct FarSrc {
+  const c64* w;
+  const int64_t* roff;
+  int64_t cs;
+  const double* scale;
+  __device__ __forceinline__ c64 at(int64_t off, int c, int k) const {
+    const c64 v = w[off + c * cs + k];
+    return scale ? scale[c * cs + k] * v : v;
+  }
+};
+// Point (i, j, l) at o + h (i, j, l), component c's moved by `half` along axis c.
+struct FarGeom {
+  double k0, h, o[3], half;
+};
+// dirs[p][9] = (r, theta-hat, phi-hat) of direction perm[p] (nullable: p) of
+// device angles ang = theta[nd], phi[nd].
+hipError_t launch_far_frames(const double* ang, const int* perm, int nd, double* dirs,
+                             hipStream_t s);
+// F[rhs][dir][2] = (F_theta, F_phi) for nr right-hand sides of one body;
+// blk_vi / blk_org the device copies of fb.vi / fb.org; dirs[nd][9] = (r,
+// theta-hat, phi-hat).  Scratch: Wd pl.wd c64, part pl.part c64.
+hipError_t launch_farfield_mfma(const FarSrc& src, int nr, const FarBlocks& fb, const int* blk_vi,
+                                const int* blk_org, const FarPlan& pl, const double* dirs, int nd,
+                                const FarGeom& geo, c64* Wd, c64* part, c64* F, hipStream_t s);
+
+// Sweeps: the body's voxel columns along z in lateral blocks of 16 (bx by =
+// 16), blocks in tiles of 16; slot p = 16 block + offset holds entries
+// ptr[p] .. ptr[p + 1] of ent = (voxel, z).
+struct FarColumns {
+  int bx = 16, by = 1, ntiles = 0;
+  std::vector<int> org;  // [ntiles*16][4] block origin (i, j, 0, 0)
+  std::vector<int> ptr;  // [ntiles*256 + 1]
+  std::vector<int> ent;  // [nb][2]
+};
+void far_columns_build(const int* vox, int nb, const int N[3], FarColumns& fc);
+// Directions grouped by equal theta: group g is positions first[g] ..
+// first[g + 1] of perm; tile = (first position, count <= 64, g, 0), those of
+// group g from tile0[g]; rows = directions rounded up to 16 per tile.  False
+// when more than half of the angles differ.
+struct FarGroups {
+  std::vector<int> perm, first, tile, tile0;
+  int64_t rows = 0;
+};
+bool far_groups(const double* theta, int nd, FarGroups& fg);
+bool far_by_columns(const FarGroups& fg, int nd, const FarColumns& fc, int nb);
+// Right-hand sides and theta groups per launch, K-splits, scratch (c64).
+struct FarSweepPlan {
+  int nq = 1, ngc = 1, kst = 1;
+  size_t wd = 0, part = 0;
+};
+FarSweepPlan far_sweep_plan(const FarGroups& fg, const FarColumns& fc, int nr, int nd);
+// As launch_farfield_mfma by theta groups: ptr, org, ent the device copies of
+// fc's, perm, first, tile those of gr's, dirs in perm order, nz <= 256 layers.
+hipError_t launch_farfield_sweep(const FarSrc& src, int nr, const FarColumns& fc, const int* ptr,
+                                 const int* org, const int* ent, const FarGroups& gr,
+                                 const int* perm, const int* first, const int* tile,
+                                 const FarSweepPlan& pl, const double* dirs, int nd, int nz,
+                                 const FarGeom& geo, c64* Wd, c64* part, c64* F, hipStream_t s);
 // ||v_rhs||^2 of body-compressed vectors into out[nrhs] (device).
 hipError_t launch_vec_norm2(int nrhs, const BodyIdx& bi, const c64* v, double* out,
                             hipStream_t s);

@@ -153,3 +153,47 @@ def test_farfield_right_hand_sides_in_several_launches(V, nrhs, ndir):
             assert _relerr(F[q][some], np.stack([ft, fp], -1)) < 1e-12
     finally:
         V.vie_destroy(ctx)
+
+
+@pytest.mark.parametrize("order", ["theta", "phi", "shuffled", "uneven"])
+@pytest.mark.parametrize("shape,window", [((21, 19, 13), 0), ((5, 70, 30), 1), ((97, 66, 1), 0)])
+def test_farfield_sweep_by_theta_matches_direct_path(V, order, shape, window):
+    """Directions sharing theta take the column path: same values as the
+    direct path (calls of few directions each) and as the oracle's sum, for
+    any order of the directions, group sizes around the 16- and 64-direction
+    tiles, flat and tall bodies with holes, with and without the z window
+    (bar as above)."""
+    rng = np.random.default_rng(shape[0])
+    g = Grid.centred(shape, 0.03)
+    eps = np.where(rng.random(shape[::-1]) < 0.7, 1.05, 1.0)
+    if window:
+        eps[:4] = eps[-7:] = 1.0
+    counts = np.full(67, 100) if order != "uneven" else np.array([1, 15, 16, 17, 63, 64, 65, 129,
+                                                                  2000, 3000, 1500])
+    theta = np.repeat(rng.uniform(0, np.pi, len(counts)), counts)
+    phi = np.concatenate([np.linspace(-np.pi, np.pi, n, endpoint=False) for n in counts])
+    if order == "phi":
+        at = np.argsort(phi, kind="stable")
+    elif order == "theta":
+        at = np.arange(theta.size)
+    else:
+        at = rng.permutation(theta.size)
+    theta, phi = theta[at], phi[at]
+    assert 1.25 * theta.size * (eps > 1).sum() > 3e7  # large enough for the column path
+    nrhs = 3
+    opt = V.make_options(K0, tol=1e-9, max_iter=2, flags=V.VIE_FLAG_Z_WINDOW if window else 0)
+    ctx = V.vie_setup([(eps, g.h, g.origin)], opt)
+    try:
+        V.vie_solve(ctx, _channels(rng, nrhs), [nrhs], allow_noconv=True)
+        F = V.vie_farfield(ctx, 0, theta, phi, nrhs)
+        D = np.concatenate([V.vie_farfield(ctx, 0, theta[a:a + 500], phi[a:a + 500], nrhs)
+                            for a in range(0, theta.size, 500)], axis=1)
+        pos = vd.voxel_centres(g.n, g.h, g.origin)
+        some = rng.choice(theta.size, 20, replace=False)
+        for q in range(nrhs):
+            assert _relerr(F[q], D[q]) < 1e-12
+            w = V.vie_get_current(ctx, 0, q, g.n).reshape(3, -1)
+            ft, fp = vd.farfield(w, pos, g.h, K0, theta[some], phi[some])
+            assert _relerr(F[q][some], np.stack([ft, fp], -1)) < 1e-12
+    finally:
+        V.vie_destroy(ctx)
