@@ -216,15 +216,17 @@ struct FarPlan {
 };
 FarPlan far_plan(const FarBlocks& fb, int nr, int nd);
 // The currents: component c of point k of right-hand side q is
-// w[roff[q] + c cs + k], times scale[c cs + k] if given.  roff on the device.
+// w[roff[q] + c cs + k], times scale[c cs + k] if given (0 where that is 0,
+// whatever w holds).  roff on the device.
 struct FarSrc {
   const c64* w;
   const int64_t* roff;
   int64_t cs;
   const double* scale;
   __device__ __forceinline__ c64 at(int64_t off, int c, int k) const {
-    const c64 v = w[off + c * cs + k];
-    return scale ? scale[c * cs + k] * v : v;
+    if (!scale) return w[off + c * cs + k];
+    const double a = scale[c * cs + k];
+    return a != 0.0 ? a * w[off + c * cs + k] : mk(0.0, 0.0);
   }
 };
 // Point (i, j, l) at o + h (i, j, l), component c's moved by `half` along axis c.
