@@ -3,18 +3,20 @@
 // v_mfma_f32_16x16x16_bf16 where a reduction step has only 16 channels), with
 // training kernels.
 //
-// Convolution (forward and backward-data): a workgroup of 4 waves computes
-// an 8x8x4 voxel tile (256 GEMM rows) x Cout, K = 27 taps x Cin.  The halo
-// tile (10x10x6 voxels, channels-last, padded channel stride) and the whole
-// weight tensor sit in LDS; blocks are persistent over tiles so the weights
-// are loaded once per block.  Wave w owns tile z-plane w: four 16-row MFMA
-// tiles (two y-rows of 8 x each) per output-channel tile.
+// Convolution (forward and backward-data): a workgroup marches a 16 x 16
+// lateral tile through its z layers, the layer's halo and the whole weight
+// tensor in LDS; every layer read feeds the three output layers it touches
+// (see k_conv3d).
 // Weight gradient: rows = Cout, columns = (tap, Cin), reduction over the
-// tile voxels; activations and gradients are staged channels-first in LDS so
-// that four consecutive voxels form one operand quad.  Per-block partials are
-// summed in fixed order by a second kernel (deterministic).
+// tile voxels; activations and gradients are staged channels-first in LDS,
+// the activations in three copies shifted along x, so that every operand is
+// one aligned 16-byte read.  Per-block partials are summed in fixed order by a
+// second kernel (deterministic).
 #include <math.h>
 #include <string.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "cnn.h"
 
@@ -56,261 +58,388 @@ CnnLayerOffsets cnn_offsets() {
   return o;
 }
 
-constexpr int TX = 8, TY = 8, TZ = 4;  // weight-gradient tile (256 voxels)
-constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2;
-constexpr int HV = HX * HY * HZ;
-// Convolution tile: 8 x 8 x FZ voxels, one z-plane per wave of an
-// 8-wave workgroup (two waves per SIMD).
-constexpr int FZ = 8, FNT = 64 * FZ;
-constexpr int HVF = HX * HY * (FZ + 2);
+// ------------------------------------------------------------ convolution
+constexpr int CT = 16;                 // lateral tile edge
+constexpr int CH = CT + 2;             // with its halo
+constexpr int CNT = 256;               // threads: four waves
 
 struct ConvDims {
+  int d0, d1, d2, tx, ty, zc;  // box, lateral tiles, z layers per workgroup
+};
+
+// MODE 0: + bias, ReLU -> bf16; MODE 1: + bias -> fp32; MODE 2: * (ref > 0) -> bf16
+//
+// One workgroup: outputs z0 .. z0 + zc - 1 of a 16 x 16 lateral tile.  It
+// walks the input layers z0 - 1 .. z0 + zc; layer p feeds output p + 1 with the
+// nine dz = -1 taps, p with dz = 0 and p - 1 with dz = +1, so each output sums
+// its taps in the order dz, dy, dx.  Waves split the tile's rows of 16 voxels
+// and the output channels in tiles of 16: with NS rows and three dz per
+// activation operand, a tap reads NS + 3 operands for 3 NS MFMAs (NS = 8:
+// 0.46 LDS reads per MFMA; one layer per wave and two 16-channel tiles took
+// 0.75).  LDS holds the weights and one layer (76 KB for 32 -> 32), the next
+// layer waits in registers: two workgroups share a CU, so one's staging and
+// stores run under the other's MFMAs.  Rows of 64 bytes are stored with
+// their 16-byte slots rotated by the voxel (row) index so that neighbouring
+// lanes hit different banks.  The voxels are the MFMA's columns: each lane
+// ends with four neighbouring channels of one voxel, one packed store.
+// 32 -> 32 channels on 128 x 128 x 37: 79 us before, see the note at the end of
+// the file for now.
+template <int CIN, int COUT, int MODE>
+__global__ __launch_bounds__(CNT) __attribute__((amdgpu_waves_per_eu(2))) void k_conv3d(
+    const bf16raw* __restrict__ in, const bf16raw* __restrict__ w, const float* __restrict__ bias,
+    bf16raw* __restrict__ outb, float* __restrict__ outf, const bf16raw* __restrict__ ref,
+    ConvDims cd) {
+  constexpr bool X32 = CIN == 32;
+  static_assert(CIN == 32 || CIN == 16, "channels");
+  constexpr int RB = 2 * CIN;       // bytes per voxel (weight row)
+  constexpr int SL = RB / 16;       // 16-byte slots per row
+  constexpr int NCT = COUT / 16;    // channel tiles
+  constexpr int NS = 4 * NCT;       // 16-voxel rows per wave
+  constexpr int NP = CH * CH * SL;  // 16-byte items of a layer
+  constexpr int PF = (NP + CNT - 1) / CNT;
+  constexpr int NW = 27 * COUT * SL;
+  __shared__ __align__(16) char s_w[NW * 16];
+  __shared__ __align__(16) char s_p[NP * 16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r = lane & 15, kq = lane >> 4;
+  const int ct = wave % NCT, row0 = (wave / NCT) * NS;
+  const int ntile = cd.tx * cd.ty;
+  const int tile = blockIdx.x % ntile, z0 = (blockIdx.x / ntile) * cd.zc;
+  const int z1 = min(cd.d2, z0 + cd.zc);
+  const int x0 = (tile % cd.tx) * CT, y0 = (tile / cd.tx) * CT;
+  auto swz = [](int v) { return X32 ? (v >> 1) & 3 : 0; };
+  for (int i = tid; i < NW; i += CNT) {
+    const int row = i / SL, sl = i % SL;
+    *(uint4*)&s_w[row * RB + ((sl ^ swz(row)) << 4)] = *(const uint4*)&w[(size_t)i * 8];
+  }
+  // this thread's items of every layer: offset inside the layer (-1: outside the box)
+  int goff[PF];
+#pragma unroll
+  for (int p = 0; p < PF; ++p) {
+    const int i = tid + p * CNT, v = i / SL;
+    const int gx = x0 + v % CH - 1, gy = y0 + v / CH - 1;
+    const bool ok = i < NP && gx >= 0 && gx < cd.d0 && gy >= 0 && gy < cd.d1;
+    goff[p] = ok ? (gy * cd.d0 + gx) * CIN + (i % SL) * 8 : -1;
+  }
+  const size_t layer = (size_t)cd.d0 * cd.d1;
+  uint4 pre[PF];
+  auto fetch = [&](int z) {
+    const bf16raw* src = in + (size_t)z * layer * CIN;
+#pragma unroll
+    for (int p = 0; p < PF; ++p) {
+      pre[p] = make_uint4(0u, 0u, 0u, 0u);
+      if (goff[p] >= 0) pre[p] = *(const uint4*)&src[goff[p]];
+    }
+  };
+  // operand addresses: activations of voxel (row0 + s + dy', r + dx'), dy', dx' = 0..2,
+  // = abase[c % 8] + c RB with c = (s + dy') CH + dx' known at compile time (row0 CH
+  // is a multiple of 8); weights of channel ct 16 + r likewise
+  int abase[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c)
+    abase[c] = (row0 * CH + r) * RB + (X32 ? (kq ^ swz(r + c)) << 4 : kq << 3);
+  const int wbase = (ct * 16 + r) * RB + (X32 ? (kq ^ swz(r)) << 4 : kq << 3);
+  using frag = typename std::conditional<X32, v8bf, v4s>::type;
+  auto mma = [](frag a, frag b, v4f c) {
+    if constexpr (X32)
+      return mfma32(a, b, c);
+    else
+      return mfma16(a, b, c);
+  };
+  float4 bv = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (MODE != 2) bv = *(const float4*)&bias[ct * 16 + 4 * kq];
+  auto emit = [&](const v4f (&acc)[NS], int z) {
+    const int gx = x0 + r;
+    if (gx >= cd.d0) return;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int gy = y0 + row0 + s;
+      if (gy >= cd.d1) break;
+      const size_t at = ((size_t)z * layer + (size_t)gy * cd.d0 + gx) * COUT + ct * 16 + 4 * kq;
+      float v[4] = {acc[s][0] + bv.x, acc[s][1] + bv.y, acc[s][2] + bv.z, acc[s][3] + bv.w};
+      if (MODE == 1) {
+        *(float4*)&outf[at] = make_float4(v[0], v[1], v[2], v[3]);
+      } else {
+        bf16raw h[4];
+        if (MODE == 0) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) h[i] = f2bf(v[i] > 0.f ? v[i] : 0.f);
+        } else {
+          const uint2 m = *(const uint2*)&ref[at];
+          const uint32_t mw[2] = {m.x, m.y};
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            h[i] = f2bf(bf2f((bf16raw)(mw[i / 2] >> (16 * (i & 1)))) > 0.f ? acc[s][i] : 0.f);
+        }
+        *(uint2*)&outb[at] = make_uint2((uint32_t)h[0] | (uint32_t)h[1] << 16,
+                                        (uint32_t)h[2] | (uint32_t)h[3] << 16);
+      }
+    }
+  };
+  const int p0 = max(0, z0 - 1), p1 = min(cd.d2 - 1, z1);
+  const v4f zero = {0.f, 0.f, 0.f, 0.f};
+  v4f am[NS], a0[NS], ap[NS];  // outputs p - 1, p, p + 1
+#pragma unroll
+  for (int s = 0; s < NS; ++s) am[s] = a0[s] = ap[s] = zero;
+  fetch(p0);
+  for (int p = p0; p <= p1; ++p) {
+    lds_barrier();  // the previous layer's operand reads are done
+#pragma unroll
+    for (int q = 0; q < PF; ++q) {
+      const int i = tid + q * CNT, v = i / SL;
+      if (i < NP) *(uint4*)&s_p[v * RB + (((i % SL) ^ swz(v)) << 4)] = pre[q];
+    }
+    if (p < p1) fetch(p + 1);
+    lds_barrier();
+    const bool up = p + 1 < z1, mid = p >= z0 && p < z1, dn = p > z0;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      frag b[NS], k0, k1, k2;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int c = (s + t / 3) * CH + t % 3;
+        b[s] = *(const frag*)&s_p[abase[c % 8] + c * RB];
+      }
+      k0 = *(const frag*)&s_w[wbase + t * COUT * RB];
+      k1 = *(const frag*)&s_w[wbase + (9 + t) * COUT * RB];
+      k2 = *(const frag*)&s_w[wbase + (18 + t) * COUT * RB];
+      if (up) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) ap[s] = mma(k0, b[s], ap[s]);
+      }
+      if (mid) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) a0[s] = mma(k1, b[s], a0[s]);
+      }
+      if (dn) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) am[s] = mma(k2, b[s], am[s]);
+      }
+    }
+    // output p - 1 is complete, and output p too at the top of the box
+    if (dn) emit(am, p - 1);
+    if (p + 1 == cd.d2 && mid) emit(a0, p);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      am[s] = a0[s];
+      a0[s] = ap[s];
+      ap[s] = zero;
+    }
+  }
+}
+
+// -------------------------------------------------------- weight gradient
+constexpr int TX = 8, TY = 8, TZ = 4;  // tile (256 voxels)
+constexpr int GNT = 768;               // threads: twelve waves
+
+struct GradDims {
   int d0, d1, d2, tx, ty, tz, ntiles;
 };
 
-// Tiles of tx x ty x tz voxels (tz = TZ for the weight gradient, FZ for the
-// convolutions) covering the box.
-static ConvDims conv_dims(const int d[3], int tdz) {
-  ConvDims c;
-  c.d0 = d[0];
-  c.d1 = d[1];
-  c.d2 = d[2];
-  c.tx = (d[0] + TX - 1) / TX;
-  c.ty = (d[1] + TY - 1) / TY;
-  c.tz = (d[2] + tdz - 1) / tdz;
-  c.ntiles = c.tx * c.ty * c.tz;
-  return c;
-}
-
-// MODE 0: + bias, ReLU -> bf16; MODE 1: + bias -> fp32; MODE 2: * (ref > 0) -> bf16
-// Persistent workgroups: the weights are staged once; every tile's halo is
-// fetched into registers while the previous tile's MFMAs run, then stored to
-// LDS between two barriers.
-template <int CIN, int COUT, int MODE>
-__global__ __launch_bounds__(FNT) void k_conv3d(const bf16raw* __restrict__ in,
-                                                const bf16raw* __restrict__ w,
-                                                const float* __restrict__ bias,
-                                                bf16raw* __restrict__ outb,
-                                                float* __restrict__ outf,
-                                                const bf16raw* __restrict__ ref, ConvDims cd) {
-  // 32-deep MFMA steps when the channels allow; padded channel stride keeps
-  // every operand slice 16-byte aligned (8-byte for the 16-deep form)
-  constexpr bool X32 = CIN % 32 == 0;
-  constexpr int KS = X32 ? 32 : 16;
-  constexpr int CP = X32 ? CIN + 8 : CIN + 4;
-  constexpr int NCT = COUT / 16;
-  constexpr int NQ = HVF * (CIN / 4);  // 8-byte halo items
-  constexpr int PF = (NQ + FNT - 1) / FNT;
-  __shared__ __align__(16) bf16raw s_in[HVF * CP];
-  __shared__ __align__(16) bf16raw s_w[27 * COUT * CP];
+// dW[tap][co][ci] = sum_m in[m + tap][ci] g[m][co];  db[co] = sum_m g[m][co]
+//
+// A reduction step is four x-rows of eight voxels.  An activation operand
+// (halo layer hz, rows shifted by dy, copy shifted by dx, 16 channels) meets
+// the gradient operands of layers hz - dz for the three dz and every
+// 16-channel tile of Cout: 3 COUT / 16 MFMAs per LDS read, the tile's
+// gradient operands kept in registers.  Wave (u, yg): units 3 u .. 3 u + 2 of the 18
+// (dy, dx, channel tile) combinations, rows 4 yg .. 4 yg + 3 of every layer; the
+// two halves are added through LDS at the end.  The next tile's voxels
+// wait in registers while this one's MFMAs run; a thread holds ten (eight)
+// neighbouring voxels of four channels and writes them transposed.  Channel
+// c of quad q is stored at index c (channels / 4) + q, which spreads the
+// writes over the banks; partials are written in operand order and
+// k_reduce_parts puts them in place.  With 8 two-byte LDS reads per operand and
+// one thread per channel summing the bias, 32 x 32 channels on 121 x 107 x 37
+// took 160 us, plus 121 us for the sum of 512 partials.
+template <int COUT>
+__global__ __launch_bounds__(GNT) void k_conv3d_wgrad(const bf16raw* __restrict__ in,
+                                                      const bf16raw* __restrict__ g,
+                                                      float* __restrict__ part, GradDims cd) {
+  constexpr int CIN = 32, NRT = COUT / 16;
+  constexpr int HR = (TY + 2) * (TZ + 2);  // halo rows
+  constexpr int HP = HR + 1;               // padded rows per channel (odd)
+  constexpr int MR = TY * TZ, MP = MR + 1;
+  constexpr int IN_B = 3 * CIN * HP * 16, G_B = COUT * MP * 16;
+  constexpr int NI = HR * (CIN / 4), NG = MR * (COUT / 4);
+  constexpr int NT = 27 * CIN * COUT;
+  static_assert(NI + NG <= GNT && HP % 2 == 1 && MP % 2 == 1, "staging");
+  constexpr int RED_B = 6 * 9 * NRT * 64 * 16;
+  constexpr int LDS_B = IN_B + G_B > RED_B ? IN_B + G_B : RED_B;
+  __shared__ __align__(16) char lds[LDS_B];
+  char* s_g = lds + IN_B;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, kq = lane >> 4;
-  for (int i = tid; i < 27 * COUT * (CIN / 4); i += FNT) {
-    const int c4 = i % (CIN / 4), row = i / (CIN / 4);
-    *(uint2*)&s_w[row * CP + 4 * c4] = *(const uint2*)&w[(size_t)row * CIN + 4 * c4];
-  }
-  uint2 pre[PF];
+  const int yg = wave & 1, u0 = (wave >> 1) * 3;
+  // staging item: row and channel quad
+  const bool is_in = tid < NI, is_g = !is_in && tid < NI + NG;
+  const int it = is_in ? tid : tid - NI;
+  const int quad = is_in ? it % (CIN / 4) : it % (COUT / 4);
+  const int row = is_in ? it / (CIN / 4) : it / (COUT / 4);
+  uint2 pre[TX + 2];
   auto fetch = [&](int tile) {
     const int tx = tile % cd.tx, ty = (tile / cd.tx) % cd.ty, tz = tile / (cd.tx * cd.ty);
-    const int x0 = tx * TX, y0 = ty * TY, z0 = tz * FZ;
+    const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
 #pragma unroll
-    for (int p = 0; p < PF; ++p) {
-      const int i = tid + p * FNT;
-      const int c4 = i % (CIN / 4), v = i / (CIN / 4);
-      const int hx = v % HX, hy = (v / HX) % HY, hz = v / (HX * HY);
-      const int gx = x0 + hx - 1, gy = y0 + hy - 1, gz = z0 + hz - 1;
-      pre[p] = make_uint2(0u, 0u);
-      if (i < NQ && gx >= 0 && gx < cd.d0 && gy >= 0 && gy < cd.d1 && gz >= 0 && gz < cd.d2)
-        pre[p] = *(const uint2*)&in[((size_t)(gz * cd.d1 + gy) * cd.d0 + gx) * CIN + 4 * c4];
+    for (int v = 0; v < TX + 2; ++v) pre[v] = make_uint2(0u, 0u);
+    if (is_in) {
+      const int gy = y0 + row % (TY + 2) - 1, gz = z0 + row / (TY + 2) - 1;
+      if (gy < 0 || gy >= cd.d1 || gz < 0 || gz >= cd.d2) return;
+      const bf16raw* src = in + ((size_t)gz * cd.d1 + gy) * cd.d0 * CIN + 4 * quad;
+#pragma unroll
+      for (int v = 0; v < TX + 2; ++v) {
+        const int gx = x0 + v - 1;
+        if (gx >= 0 && gx < cd.d0) pre[v] = *(const uint2*)&src[(size_t)gx * CIN];
+      }
+    } else if (is_g) {
+      const int gy = y0 + row % TY, gz = z0 + row / TY;
+      if (gy >= cd.d1 || gz >= cd.d2) return;
+      const bf16raw* src = g + ((size_t)gz * cd.d1 + gy) * cd.d0 * COUT + 4 * quad;
+#pragma unroll
+      for (int v = 0; v < TX; ++v)
+        if (x0 + v < cd.d0) pre[v] = *(const uint2*)&src[(size_t)(x0 + v) * COUT];
     }
   };
+  // channel c (of the quad) of voxels a .. a + 7, packed
+  auto pack8 = [&](int a, int c) {
+    uint32_t o[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t lo = c < 2 ? pre[a + 2 * k].x : pre[a + 2 * k].y;
+      const uint32_t hi = c < 2 ? pre[a + 2 * k + 1].x : pre[a + 2 * k + 1].y;
+      o[k] = (c & 1) ? (lo >> 16) | (hi & 0xFFFF0000u) : (lo & 0xFFFFu) | (hi << 16);
+    }
+    return make_uint4(o[0], o[1], o[2], o[3]);
+  };
+  v4f acc[3][3][NRT];
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+#pragma unroll
+    for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+      for (int rt = 0; rt < NRT; ++rt) acc[j][dz][rt] = v4f{0.f, 0.f, 0.f, 0.f};
+  float bs[4] = {0.f, 0.f, 0.f, 0.f};
+  const char* bp[3];  // this lane's activation operands of its units (layer hz: + 160 hz)
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    const int u = u0 + j, cit = u & 1, dy = (u >> 1) / 3, dx = (u >> 1) % 3;
+    bp[j] = lds + ((dx * CIN + cit * 16 + r) * HP + 4 * yg + kq + dy) * 16;
+  }
+  const char* ga = s_g + (r * MP + 4 * yg + kq) * 16;
   if ((int)blockIdx.x < cd.ntiles) fetch(blockIdx.x);
   for (int tile = blockIdx.x; tile < cd.ntiles; tile += gridDim.x) {
-    const int tx = tile % cd.tx, ty = (tile / cd.tx) % cd.ty, tz = tile / (cd.tx * cd.ty);
-    const int x0 = tx * TX, y0 = ty * TY, z0 = tz * FZ;
-    __syncthreads();  // the previous tile's operand reads are done
+    lds_barrier();  // the previous tile's operand reads are done
+    if (is_in) {
 #pragma unroll
-    for (int p = 0; p < PF; ++p) {
-      const int i = tid + p * FNT;
-      if (i < NQ) {
-        const int c4 = i % (CIN / 4), v = i / (CIN / 4);
-        *(uint2*)&s_in[v * CP + 4 * c4] = pre[p];
+      for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          *(uint4*)&lds[((dx * CIN + c * (CIN / 4) + quad) * HP + row) * 16] = pack8(dx, c);
+    } else if (is_g) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const uint4 v = pack8(0, c);
+        *(uint4*)&s_g[((c * (COUT / 4) + quad) * MP + row) * 16] = v;
+        const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
+        float t = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          t += bf2f((bf16raw)(wv[k] & 0xFFFFu)) + bf2f((bf16raw)(wv[k] >> 16));
+        bs[c] += t;
       }
     }
-    __syncthreads();
     if (tile + (int)gridDim.x < cd.ntiles) fetch(tile + gridDim.x);
-    v4f acc[4][NCT];
+    lds_barrier();
+    v8bf a[TZ][NRT];
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt)
-#pragma unroll
-      for (int ct = 0; ct < NCT; ++ct) acc[rt][ct] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 3
-    for (int tap = 0; tap < 27; ++tap) {
-      const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-#pragma unroll
-      for (int kc = 0; kc < CIN / KS; ++kc) {
-        const int ko = KS * kc + (KS / 4) * kq;  // this lane's K slice
-        if constexpr (X32) {
-          v8bf a[4], b[NCT];
-#pragma unroll
-          for (int rt = 0; rt < 4; ++rt) {
-            const int ly = 2 * rt + (r >> 3), lx = r & 7;
-            const int hv = ((wave + 1 + dz) * HY + (ly + 1 + dy)) * HX + (lx + 1 + dx);
-            a[rt] = *(const v8bf*)&s_in[hv * CP + ko];
-          }
-#pragma unroll
-          for (int ct = 0; ct < NCT; ++ct)
-            b[ct] = *(const v8bf*)&s_w[(tap * COUT + ct * 16 + r) * CP + ko];
-#pragma unroll
-          for (int rt = 0; rt < 4; ++rt)
-#pragma unroll
-            for (int ct = 0; ct < NCT; ++ct) acc[rt][ct] = mfma32(a[rt], b[ct], acc[rt][ct]);
-        } else {
-          v4s a[4], b[NCT];
-#pragma unroll
-          for (int rt = 0; rt < 4; ++rt) {
-            const int ly = 2 * rt + (r >> 3), lx = r & 7;
-            const int hv = ((wave + 1 + dz) * HY + (ly + 1 + dy)) * HX + (lx + 1 + dx);
-            a[rt] = *(const v4s*)&s_in[hv * CP + ko];
-          }
-#pragma unroll
-          for (int ct = 0; ct < NCT; ++ct)
-            b[ct] = *(const v4s*)&s_w[(tap * COUT + ct * 16 + r) * CP + ko];
-#pragma unroll
-          for (int rt = 0; rt < 4; ++rt)
-#pragma unroll
-            for (int ct = 0; ct < NCT; ++ct) acc[rt][ct] = mfma16(a[rt], b[ct], acc[rt][ct]);
-        }
-      }
-    }
-    // lane holds D[row = 4 kq + i][col = r]
-#pragma unroll
-    for (int rt = 0; rt < 4; ++rt)
-#pragma unroll
-      for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = 4 * kq + i;
-          const int gx = x0 + (row & 7), gy = y0 + 2 * rt + (row >> 3), gz = z0 + wave;
-          if (gx < cd.d0 && gy < cd.d1 && gz < cd.d2) {
-            const size_t vox = (size_t)(gz * cd.d1 + gy) * cd.d0 + gx;
-            const int co = ct * 16 + r;
-            float val = acc[rt][ct][i];
-            if (MODE == 0) {
-              val += bias[co];
-              outb[vox * COUT + co] = f2bf(val > 0.f ? val : 0.f);
-            } else if (MODE == 1) {
-              outf[vox * COUT + co] = val + bias[co];
-            } else {
-              outb[vox * COUT + co] = f2bf(bf2f(ref[vox * COUT + co]) > 0.f ? val : 0.f);
-            }
-          }
-        }
-  }
-}
-
-// dW[tap][co][ci] = sum_m in[m + tap][ci] g[m][co];  db[co] = sum_m g[m][co]
-template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void k_conv3d_wgrad(const bf16raw* __restrict__ in,
-                                                      const bf16raw* __restrict__ g,
-                                                      float* __restrict__ part, ConvDims cd) {
-  constexpr int NCOL = 27 * CIN / 16;
-  constexpr int NRT = COUT / 16;
-  constexpr int CPW = (NCOL + 3) / 4;
-  constexpr int HVP = HV + 4;
-  constexpr int MP = 256 + 8;  // 16-byte aligned gradient rows
-  constexpr int NW = 27 * COUT * CIN;
-  __shared__ __align__(16) bf16raw s_inT[CIN * HVP];
-  __shared__ __align__(16) bf16raw s_gT[COUT * MP];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r = lane & 15, kq = lane >> 4;
-  v4f acc[CPW][NRT];
-#pragma unroll
-  for (int j = 0; j < CPW; ++j)
-#pragma unroll
-    for (int rt = 0; rt < NRT; ++rt) acc[j][rt] = v4f{0.f, 0.f, 0.f, 0.f};
-  float bsum = 0.f;
-  for (int tile = blockIdx.x; tile < cd.ntiles; tile += gridDim.x) {
-    const int tx = tile % cd.tx, ty = (tile / cd.tx) % cd.ty, tz = tile / (cd.tx * cd.ty);
-    const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
-    __syncthreads();
-    for (int i = tid; i < HV * (CIN / 4); i += 256) {
-      const int c4 = i % (CIN / 4), v = i / (CIN / 4);
-      const int hx = v % HX, hy = (v / HX) % HY, hz = v / (HX * HY);
-      const int gx = x0 + hx - 1, gy = y0 + hy - 1, gz = z0 + hz - 1;
-      uint2 val = make_uint2(0u, 0u);
-      if (gx >= 0 && gx < cd.d0 && gy >= 0 && gy < cd.d1 && gz >= 0 && gz < cd.d2)
-        val = *(const uint2*)&in[((size_t)(gz * cd.d1 + gy) * cd.d0 + gx) * CIN + 4 * c4];
-      s_inT[(4 * c4 + 0) * HVP + v] = (bf16raw)(val.x & 0xFFFFu);
-      s_inT[(4 * c4 + 1) * HVP + v] = (bf16raw)(val.x >> 16);
-      s_inT[(4 * c4 + 2) * HVP + v] = (bf16raw)(val.y & 0xFFFFu);
-      s_inT[(4 * c4 + 3) * HVP + v] = (bf16raw)(val.y >> 16);
-    }
-    for (int i = tid; i < 256 * (COUT / 4); i += 256) {
-      const int c4 = i % (COUT / 4), m = i / (COUT / 4);
-      const int gx = x0 + (m & 7), gy = y0 + ((m >> 3) & 7), gz = z0 + (m >> 6);
-      uint2 val = make_uint2(0u, 0u);
-      if (gx < cd.d0 && gy < cd.d1 && gz < cd.d2)
-        val = *(const uint2*)&g[((size_t)(gz * cd.d1 + gy) * cd.d0 + gx) * COUT + 4 * c4];
-      s_gT[(4 * c4 + 0) * MP + m] = (bf16raw)(val.x & 0xFFFFu);
-      s_gT[(4 * c4 + 1) * MP + m] = (bf16raw)(val.x >> 16);
-      s_gT[(4 * c4 + 2) * MP + m] = (bf16raw)(val.y & 0xFFFFu);
-      s_gT[(4 * c4 + 3) * MP + m] = (bf16raw)(val.y >> 16);
-    }
-    __syncthreads();
-    if (tid < COUT) {
-      for (int m = 0; m < 256; ++m) bsum += bf2f(s_gT[tid * MP + m]);
-    }
-    for (int ks = 0; ks < 8; ++ks) {
-      const int m0 = 32 * ks + 8 * kq;  // this lane's 8 voxels m0..m0+7: one x-row
-      const int lz = m0 >> 6, ly = (m0 >> 3) & 7;
-      v8bf a[NRT];
-#pragma unroll
-      for (int rt = 0; rt < NRT; ++rt) a[rt] = *(const v8bf*)&s_gT[(rt * 16 + r) * MP + m0];
-#pragma unroll
-      for (int j = 0; j < CPW; ++j) {
-        const int c = wave + 4 * j;
-        if (c < NCOL) {
-          const int col = 16 * c + r;
-          const int tap = col / CIN, ci = col % CIN;
-          const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-          const int hv = ((lz + 1 + dz) * HY + (ly + 1 + dy)) * HX + (1 + dx);
-          const bf16raw* p = &s_inT[ci * HVP + hv];
-          v8bf b;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) b[e] = __builtin_bit_cast(__bf16, p[e]);
-#pragma unroll
-          for (int rt = 0; rt < NRT; ++rt) acc[j][rt] = mfma32(a[rt], b, acc[j][rt]);
-        }
-      }
-    }
-  }
-  float* pb = part + (size_t)blockIdx.x * (NW + COUT);
-#pragma unroll
-  for (int j = 0; j < CPW; ++j) {
-    const int c = wave + 4 * j;
-    if (c < NCOL) {
-      const int col = 16 * c + r;
-      const int tap = col / CIN, ci = col % CIN;
+    for (int lz = 0; lz < TZ; ++lz)
 #pragma unroll
       for (int rt = 0; rt < NRT; ++rt)
+        a[lz][rt] = *(const v8bf*)(ga + (rt * 16 * MP + lz * TY) * 16);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int co = rt * 16 + 4 * kq + i;
-          pb[((size_t)tap * COUT + co) * CIN + ci] = acc[j][rt][i];
-        }
-    }
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+      for (int hz = 0; hz < TZ + 2; ++hz) {
+        const v8bf b = *(const v8bf*)(bp[j] + hz * (TY + 2) * 16);
+#pragma unroll
+        for (int dz = 0; dz < 3; ++dz)
+          if (hz - dz >= 0 && hz - dz < TZ) {
+#pragma unroll
+            for (int rt = 0; rt < NRT; ++rt)
+              acc[j][dz][rt] = mfma32(a[hz - dz][rt], b, acc[j][dz][rt]);
+          }
+      }
   }
-  if (tid < COUT) pb[NW + tid] = bsum;
+  // the two row halves of every unit, then the partial in operand order
+  // [unit][dz][rt][lane][4]
+  __syncthreads();
+  v4f* red = (v4f*)lds;
+  if (yg) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+      for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+        for (int rt = 0; rt < NRT; ++rt)
+          red[((wave >> 1) * 9 * NRT + (j * 3 + dz) * NRT + rt) * 64 + lane] = acc[j][dz][rt];
+  }
+  __syncthreads();
+  float* pb = part + (size_t)blockIdx.x * (NT + COUT);
+  if (!yg) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+      for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+        for (int rt = 0; rt < NRT; ++rt)
+          *(v4f*)&pb[((((u0 + j) * 3 + dz) * NRT + rt) * 64 + lane) * 4] =
+              acc[j][dz][rt] +
+              red[((wave >> 1) * 9 * NRT + (j * 3 + dz) * NRT + rt) * 64 + lane];
+  }
+  __syncthreads();
+  float* sb = (float*)lds;  // [row][quad][4]
+  if (is_g)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sb[it * 4 + c] = bs[c];
+  __syncthreads();
+  if (tid < COUT) {
+    float t = 0.f;
+    for (int k = 0; k < MR; ++k) t += sb[(k * (COUT / 4) + tid / 4) * 4 + tid % 4];
+    pb[NT + tid] = t;
+  }
 }
 
-__global__ void k_reduce_parts(const float* __restrict__ part, int nblk, int n,
-                               float* __restrict__ out) {
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += gridDim.x * blockDim.x) {
-    float s = 0.f;
-    for (int b = 0; b < nblk; ++b) s += part[(size_t)b * n + j];
-    out[j] = s;
+// Sum of the weight-gradient partials, in fixed order, put in parameter order
+// ([tap][co][ci], then the biases): four waves take a quarter of the blocks
+// each for 64 neighbouring elements.
+template <int COUT>
+__global__ __launch_bounds__(256) void k_reduce_parts(const float* __restrict__ part, int nblk,
+                                                      float* __restrict__ out) {
+  constexpr int CIN = 32, NRT = COUT / 16, NT = 27 * CIN * COUT, N = NT + COUT;
+  __shared__ float red[4][64];
+  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + l;
+  const int b0 = (int)((int64_t)nblk * wv / 4), b1 = (int)((int64_t)nblk * (wv + 1) / 4);
+  float s = 0.f;
+  if (e < N) {
+#pragma unroll 8
+    for (int b = b0; b < b1; ++b) s += part[(size_t)b * N + e];
   }
+  red[wv][l] = s;
+  __syncthreads();
+  if (wv != 0 || e >= N) return;
+  s = (red[0][l] + red[1][l]) + (red[2][l] + red[3][l]);
+  if (e >= NT) {
+    out[e] = s;
+    return;
+  }
+  // e = (((unit * 3 + dz) * NRT + rt) * 64 + lane) * 4 + i: D[co index][ci index]
+  const int i = e & 3, lane = (e >> 2) & 63, f = e >> 8;
+  const int rt = f % NRT, dz = (f / NRT) % 3, u = f / (3 * NRT);
+  const int cit = u & 1, dy = (u >> 1) / 3, dx = (u >> 1) % 3;
+  const int coi = rt * 16 + 4 * (lane >> 4) + i, cii = cit * 16 + (lane & 15);
+  const int co = coi % (COUT / 4) * 4 + coi / (COUT / 4), ci = cii % (CIN / 4) * 4 + cii / (CIN / 4);
+  out[((size_t)(dz * 9 + dy * 3 + dx) * COUT + co) * CIN + ci] = s;
 }
 
 // masked relative L2 loss over outputs 0..5; mask = feature channel 0 > 0
@@ -346,16 +475,20 @@ __global__ __launch_bounds__(256) void k_loss_partial(const float* __restrict__ 
   }
 }
 
-__global__ void k_loss_final(const float* __restrict__ part, int nblk, float* __restrict__ loss) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    float n = 0.f, d = 0.f;
-    for (int b = 0; b < nblk; ++b) {
-      n += part[2 * b];
-      d += part[2 * b + 1];
-    }
-    loss[0] = n;
-    loss[1] = d;
-  }
+// The block sums in block order, one chain each (the order fixes the bits of
+// the loss, which scales a bfloat16 gradient), staged in LDS: read one by one
+// from memory the chain took 53 us.
+constexpr int kLossBlocks = 1024;
+__global__ __launch_bounds__(256) void k_loss_final(const float* __restrict__ part, int nblk,
+                                                    float* __restrict__ loss) {
+  __shared__ float s[2 * kLossBlocks];
+  for (int i = threadIdx.x; i < 2 * nblk; i += 256) s[i] = part[i];
+  __syncthreads();
+  if (threadIdx.x >= 2) return;
+  float t = 0.f;
+#pragma unroll 16
+  for (int b = 0; b < nblk; ++b) t += s[2 * b + threadIdx.x];
+  loss[threadIdx.x] = t;
 }
 
 __global__ __launch_bounds__(256) void k_loss_grad(const float* __restrict__ out,
@@ -547,17 +680,18 @@ hipError_t cnn_alloc(Cnn& c) {
 
 void cnn_free(Cnn& c) {
   void* ps[] = {c.p, c.m, c.v, c.g, c.wf, c.wb, c.out, c.wpart, c.loss, c.gbuf[0], c.gbuf[1],
-                c.act[1], c.act[2], c.act[3]};
+                c.act[1], c.act[2], c.act[3], c.fcopy};
   for (void* q : ps)
     if (q) (void)hipFree(q);
   if (c.hostloss) (void)hipHostFree(c.hostloss);
   c = Cnn();
 }
 
-// persistent grids: convolutions one 149 KB-LDS workgroup per CU, weight
-// gradients two 4-wave workgroups per CU (per-block partials: kMaxConvBlocks)
-static constexpr int kConvBlocks = 256;
-static constexpr int kMaxConvBlocks = 512;
+// Weight gradient: one persistent 12-wave workgroup per CU.
+static constexpr int kGradBlocks = 256;
+// Convolution: z layers per workgroup so that about two workgroups per CU
+// exist (each takes two more layers than it writes).
+static constexpr int kConvBlocks = 512;
 
 hipError_t cnn_ensure_ws(Cnn& c, size_t vox) {
   if (vox <= c.ws_vox) return hipSuccess;
@@ -575,7 +709,7 @@ hipError_t cnn_ensure_ws(Cnn& c, size_t vox) {
   for (int l = 1; l < kCnnLayers; ++l)
     if ((e = hipMalloc(&c.act[l], vox * kCnnCh[l] * 2)) != hipSuccess) return e;
   const size_t maxlayer = 27 * 32 * 32 + 32;
-  if ((e = hipMalloc(&c.wpart, (size_t)kMaxConvBlocks * maxlayer * 4)) != hipSuccess) return e;
+  if ((e = hipMalloc(&c.wpart, (size_t)kGradBlocks * maxlayer * 4)) != hipSuccess) return e;
   c.ws_vox = vox;
   return hipSuccess;
 }
@@ -585,26 +719,68 @@ hipError_t cnn_refresh_bf16(Cnn& c, hipStream_t s) {
   return hipGetLastError();
 }
 
+static ConvDims conv_dims(const int d[3]) {
+  ConvDims c;
+  c.d0 = d[0];
+  c.d1 = d[1];
+  c.d2 = d[2];
+  c.tx = (d[0] + CT - 1) / CT;
+  c.ty = (d[1] + CT - 1) / CT;
+  const int64_t nt = (int64_t)c.tx * c.ty;
+  c.zc = (int)std::min<int64_t>(d[2], (nt * d[2] + kConvBlocks - 1) / kConvBlocks);
+  return c;
+}
+
+static GradDims grad_dims(const int d[3]) {
+  GradDims c;
+  c.d0 = d[0];
+  c.d1 = d[1];
+  c.d2 = d[2];
+  c.tx = (d[0] + TX - 1) / TX;
+  c.ty = (d[1] + TY - 1) / TY;
+  c.tz = (d[2] + TZ - 1) / TZ;
+  c.ntiles = c.tx * c.ty * c.tz;
+  return c;
+}
+
 template <int CIN, int COUT, int MODE>
 static void conv(const ConvDims& cd, const bf16raw* in, const bf16raw* w, const float* bias,
                  bf16raw* ob, float* of, const bf16raw* ref, hipStream_t s) {
-  const int grid = cd.ntiles < kConvBlocks ? cd.ntiles : kConvBlocks;
-  k_conv3d<CIN, COUT, MODE><<<grid, FNT, 0, s>>>(in, w, bias, ob, of, ref, cd);
+  const int grid = cd.tx * cd.ty * ((cd.d2 + cd.zc - 1) / cd.zc);
+  k_conv3d<CIN, COUT, MODE><<<grid, CNT, 0, s>>>(in, w, bias, ob, of, ref, cd);
 }
 
-template <int CIN, int COUT>
-static void wgrad(const ConvDims& cd, const bf16raw* in, const bf16raw* g, float* part,
+template <int COUT>
+static void wgrad(const GradDims& cd, const bf16raw* in, const bf16raw* g, float* part,
                   float* out, hipStream_t s) {
-  const int grid = cd.ntiles < kMaxConvBlocks ? cd.ntiles : kMaxConvBlocks;
-  k_conv3d_wgrad<CIN, COUT><<<grid, 256, 0, s>>>(in, g, part, cd);
-  const int n = 27 * CIN * COUT + COUT;
-  k_reduce_parts<<<(n + 255) / 256, 256, 0, s>>>(part, grid, n, out);
+  const int grid = cd.ntiles < kGradBlocks ? cd.ntiles : kGradBlocks;
+  k_conv3d_wgrad<COUT><<<grid, GNT, 0, s>>>(in, g, part, cd);
+  const int n = 27 * 32 * COUT + COUT;
+  k_reduce_parts<COUT><<<(n + 63) / 64, 256, 0, s>>>(part, grid, out);
 }
 
 hipError_t cnn_forward(Cnn& c, const int d[3], const bf16raw* feat, float* out, hipStream_t s) {
-  const ConvDims cd = conv_dims(d, FZ);
-  hipError_t e = cnn_ensure_ws(c, (size_t)d[0] * d[1] * d[2]);
+  const ConvDims cd = conv_dims(d);
+  const size_t nv = (size_t)d[0] * d[1] * d[2];
+  hipError_t e = cnn_ensure_ws(c, nv);
   if (e != hipSuccess) return e;
+  // the convolutions move 16-byte items: a caller's tensor that does not start
+  // on such a boundary goes through the network's own buffers
+  float* dst = out ? out : c.out;
+  if ((uintptr_t)feat & 15) {
+    if (c.fcopy_vox < nv) {
+      if (c.fcopy) (void)hipFree(c.fcopy);
+      c.fcopy = nullptr;
+      c.fcopy_vox = 0;
+      if ((e = hipMalloc(&c.fcopy, nv * kCnnIn * sizeof(bf16raw))) != hipSuccess) return e;
+      c.fcopy_vox = nv;
+    }
+    if ((e = hipMemcpyAsync(c.fcopy, feat, nv * kCnnIn * sizeof(bf16raw),
+                            hipMemcpyDeviceToDevice, s)) != hipSuccess)
+      return e;
+    feat = c.fcopy;
+  }
+  if ((uintptr_t)dst & 15) dst = c.out;
   c.act[0] = const_cast<bf16raw*>(feat);
   conv<32, 32, 0>(cd, feat, c.wf + bf16_weight_offset(0), c.p + c.off.b[0], c.act[1], nullptr,
                   nullptr, s);
@@ -612,31 +788,35 @@ hipError_t cnn_forward(Cnn& c, const int d[3], const bf16raw* feat, float* out, 
                   nullptr, nullptr, s);
   conv<32, 32, 0>(cd, c.act[2], c.wf + bf16_weight_offset(2), c.p + c.off.b[2], c.act[3],
                   nullptr, nullptr, s);
-  conv<32, 16, 1>(cd, c.act[3], c.wf + bf16_weight_offset(3), c.p + c.off.b[3], nullptr,
-                  out ? out : c.out, nullptr, s);
-  return hipGetLastError();
+  conv<32, 16, 1>(cd, c.act[3], c.wf + bf16_weight_offset(3), c.p + c.off.b[3], nullptr, dst,
+                  nullptr, s);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (out && dst != out)
+    e = hipMemcpyAsync(out, dst, nv * 16 * sizeof(float), hipMemcpyDeviceToDevice, s);
+  return e;
 }
 
 hipError_t cnn_backward(Cnn& c, const int d[3], const float* target, float* loss_host,
                         hipStream_t s) {
-  const ConvDims cd = conv_dims(d, FZ), cw = conv_dims(d, TZ);
+  const ConvDims cd = conv_dims(d);
+  const GradDims cw = grad_dims(d);
   const size_t nv = (size_t)d[0] * d[1] * d[2];
-  const int lb = grid_for((int64_t)nv, 256) < 1024 ? grid_for((int64_t)nv, 256) : 1024;
+  const int lb = std::min(grid_for((int64_t)nv, 256), kLossBlocks);
   k_loss_partial<<<lb, 256, 0, s>>>(c.out, target, c.act[0], nv, c.loss + 2);
-  k_loss_final<<<1, 64, 0, s>>>(c.loss + 2, lb, c.loss);
+  k_loss_final<<<1, 256, 0, s>>>(c.loss + 2, lb, c.loss);
   k_loss_grad<<<grid_for((int64_t)nv * 16), 256, 0, s>>>(c.out, target, c.act[0], c.loss, nv,
                                                          c.gbuf[0]);
   // layer 4 (32 -> 16): weight gradient, then data gradient masked by ReLU'
-  wgrad<32, 16>(cw, c.act[3], c.gbuf[0], c.wpart, c.g + c.off.w[3], s);
+  wgrad<16>(cw, c.act[3], c.gbuf[0], c.wpart, c.g + c.off.w[3], s);
   conv<16, 32, 2>(cd, c.gbuf[0], c.wb + bf16_weight_offset(3), nullptr, c.gbuf[1], nullptr,
                   c.act[3], s);
-  wgrad<32, 32>(cw, c.act[2], c.gbuf[1], c.wpart, c.g + c.off.w[2], s);
+  wgrad<32>(cw, c.act[2], c.gbuf[1], c.wpart, c.g + c.off.w[2], s);
   conv<32, 32, 2>(cd, c.gbuf[1], c.wb + bf16_weight_offset(2), nullptr, c.gbuf[0], nullptr,
                   c.act[2], s);
-  wgrad<32, 32>(cw, c.act[1], c.gbuf[0], c.wpart, c.g + c.off.w[1], s);
+  wgrad<32>(cw, c.act[1], c.gbuf[0], c.wpart, c.g + c.off.w[1], s);
   conv<32, 32, 2>(cd, c.gbuf[0], c.wb + bf16_weight_offset(1), nullptr, c.gbuf[1], nullptr,
                   c.act[1], s);
-  wgrad<32, 32>(cw, c.act[0], c.gbuf[1], c.wpart, c.g + c.off.w[0], s);
+  wgrad<32>(cw, c.act[0], c.gbuf[1], c.wpart, c.g + c.off.w[0], s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (loss_host) {

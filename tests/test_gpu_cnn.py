@@ -91,6 +91,60 @@ def test_network_gradients_match_oracle(env):
         V.vie_cnn_destroy(net)
 
 
+@pytest.mark.parametrize("d,shift", [((40, 35, 70), 0), ((33, 17, 130), 0), ((16, 16, 1), 0),
+                                     ((17, 31, 5), 8)])
+def test_network_on_integers(env, d, shift):
+    """Boxes of several lateral tiles and several layers per workgroup (with a
+    remainder), exact tiles, a single layer, and tensors that start 8 bytes
+    off a 16-byte boundary.  Small integers throughout (sparse weights 0, +-1,
+    no biases, a power-of-two loss denominator): every product and FP32 sum of
+    the forward and data-gradient convolutions is exact, and both sides round
+    the same values to bfloat16, so the outputs are equal bit for bit.  The
+    weight gradients are FP32 sums of at most about 1e3 terms per chain: 1e-4."""
+    V, torch = env
+    rng = np.random.default_rng(sum(d))
+    layers = []
+    for (ws, bs) in V.cnn_param_shapes():
+        W = np.zeros(ws)
+        for co in range(ws[1]):
+            at = rng.choice(27 * ws[2], 3, replace=False)
+            W[at // ws[2], co, at % ws[2]] = [1, 1, -1]
+        layers.append((W, np.zeros(bs)))
+    net = V.vie_cnn_create(1)
+    try:
+        V.vie_cnn_params(net, np.concatenate([v.ravel() for W, b in layers for v in (W, b)]))
+        shape = d[::-1]
+        feat = np.zeros(shape + (32,))
+        feat[..., 1:25] = rng.integers(0, 3, shape + (24,))
+        feat[..., 0] = rng.random(shape) < 0.5
+        body = np.argwhere(feat[..., 0] > 0)
+        some = body[rng.choice(len(body), 1 << int(np.log2(len(body))), replace=False)]
+        tgt = np.zeros(shape + (6,))
+        tgt[some[:, 0], some[:, 1], some[:, 2], rng.integers(0, 6, len(some))] = 1
+
+        def dev(a, dtype):
+            flat = torch.zeros(a.size + 16, dtype=dtype, device="cuda")
+            k = shift // flat.element_size()
+            flat[k:k + a.size] = torch.tensor(a.ravel(), dtype=torch.float32).cuda().to(dtype)
+            return flat, flat.data_ptr() + shift
+
+        (fk, ft), (tk, tt) = dev(feat, torch.bfloat16), dev(tgt, torch.float32)
+        ok, op = dev(np.zeros(shape + (16,)), torch.float32)
+        V.vie_cnn_infer_dev(net, d, ft, op)
+        loss, g = V.vie_cnn_grad_dev(net, d, ft, tt)
+        out, acts = cr.forward(layers, feat, round_bf16=True)
+        got = ok.cpu().numpy()[shift // 4:][:out.size].reshape(out.shape)
+        assert np.any(out) and np.array_equal(got, out)
+        rloss, gout = cr.masked_rel_l2(out, tgt, feat[..., 0] > 0, 6)
+        assert abs(loss - rloss) < 1e-4 * rloss
+        for (gW, gb), (W_gpu, b_gpu) in zip(cr.backward(layers, acts, gout, round_bf16=True),
+                                            V.cnn_unpack(g)):
+            for x, ref in ((W_gpu, gW), (b_gpu, gb)):  # a dead layer's is exactly zero
+                assert np.linalg.norm(x - ref) <= 1e-4 * np.linalg.norm(ref)
+    finally:
+        V.vie_cnn_destroy(net)
+
+
 def test_training_reduces_loss(env):
     V, torch = env
     rng = np.random.default_rng(4)
