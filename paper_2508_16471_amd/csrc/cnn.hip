@@ -72,18 +72,18 @@ struct ConvDims {
 // One workgroup: outputs z0 .. z0 + zc - 1 of a 16 x 16 lateral tile.  It
 // walks the input layers z0 - 1 .. z0 + zc; layer p feeds output p + 1 with the
 // nine dz = -1 taps, p with dz = 0 and p - 1 with dz = +1, so each output sums
-// its taps in the order dz, dy, dx.  Waves split the tile's rows of 16 voxels
-// and the output channels in tiles of 16: with NS rows and three dz per
-// activation operand, a tap reads NS + 3 operands for 3 NS MFMAs (NS = 8:
-// 0.46 LDS reads per MFMA; one layer per wave and two 16-channel tiles took
-// 0.75).  LDS holds the weights and one layer (76 KB for 32 -> 32), the next
-// layer waits in registers: two workgroups share a CU, so one's staging and
-// stores run under the other's MFMAs.  Rows of 64 bytes are stored with
-// their 16-byte slots rotated by the voxel (row) index so that neighbouring
-// lanes hit different banks.  The voxels are the MFMA's columns: each lane
-// ends with four neighbouring channels of one voxel, one packed store.
-// 32 -> 32 channels on 128 x 128 x 37: 79 us before, see the note at the end of
-// the file for now.
+// its taps in the order dz, dy, dx.  A wave holds four rows of 16 voxels and
+// every output channel: with four activation operands and 3 x 2 weight
+// operands a tap reads 10 operands from LDS for 24 MFMAs (0.42 per MFMA; one
+// layer per wave took 0.75, eight rows and one channel tile 0.46).  LDS holds
+// the weights and one layer (76 KB for 32 -> 32), the next layer waits in
+// registers: two workgroups share a CU, so one's staging and stores run under
+// the other's MFMAs.  Rows of 64 bytes are stored with their 16-byte slots
+// rotated by the voxel (row) index so that neighbouring lanes hit different
+// banks.  The voxels are the MFMA's columns: each lane ends with four
+// neighbouring channels of one voxel, one packed store.  Bound by LDS reads
+// and MFMAs about equally (17 and 14 us of the 35 us per 32 -> 32 layer on
+// 128 x 128 x 37, where one layer per wave with 2-byte stores took 79 us).
 template <int CIN, int COUT, int MODE>
 __global__ __launch_bounds__(CNT) __attribute__((amdgpu_waves_per_eu(2))) void k_conv3d(
     const bf16raw* __restrict__ in, const bf16raw* __restrict__ w, const float* __restrict__ bias,
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(CNT) __attribute__((amdgpu_waves_per_eu(2))) void k
   constexpr int RB = 2 * CIN;       // bytes per voxel (weight row)
   constexpr int SL = RB / 16;       // 16-byte slots per row
   constexpr int NCT = COUT / 16;    // channel tiles
-  constexpr int NS = 4 * NCT;       // 16-voxel rows per wave
+  constexpr int NS = 4;             // 16-voxel rows per wave
   constexpr int NP = CH * CH * SL;  // 16-byte items of a layer
   constexpr int PF = (NP + CNT - 1) / CNT;
   constexpr int NW = 27 * COUT * SL;
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(CNT) __attribute__((amdgpu_waves_per_eu(2))) void k
   __shared__ __align__(16) char s_p[NP * 16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, kq = lane >> 4;
-  const int ct = wave % NCT, row0 = (wave / NCT) * NS;
+  const int row0 = wave * NS;
   const int ntile = cd.tx * cd.ty;
   const int tile = blockIdx.x % ntile, z0 = (blockIdx.x / ntile) * cd.zc;
   const int z1 = min(cd.d2, z0 + cd.zc);
@@ -133,12 +133,12 @@ __global__ __launch_bounds__(CNT) __attribute__((amdgpu_waves_per_eu(2))) void k
   };
   // operand addresses: activations of voxel (row0 + s + dy', r + dx'), dy', dx' = 0..2,
   // = abase[c % 8] + c RB with c = (s + dy') CH + dx' known at compile time (row0 CH
-  // is a multiple of 8); weights of channel ct 16 + r likewise
+  // is a multiple of 8); weights likewise
   int abase[8];
 #pragma unroll
   for (int c = 0; c < 8; ++c)
     abase[c] = (row0 * CH + r) * RB + (X32 ? (kq ^ swz(r + c)) << 4 : kq << 3);
-  const int wbase = (ct * 16 + r) * RB + (X32 ? (kq ^ swz(r)) << 4 : kq << 3);
+  const int wbase = r * RB + (X32 ? (kq ^ swz(r)) << 4 : kq << 3);
   using frag = typename std::conditional<X32, v8bf, v4s>::type;
   auto mma = [](frag a, frag b, v4f c) {
     if constexpr (X32)
@@ -146,41 +146,50 @@ __global__ __launch_bounds__(CNT) __attribute__((amdgpu_waves_per_eu(2))) void k
     else
       return mfma16(a, b, c);
   };
-  float4 bv = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (MODE != 2) bv = *(const float4*)&bias[ct * 16 + 4 * kq];
-  auto emit = [&](const v4f (&acc)[NS], int z) {
+  float4 bv[NCT];
+#pragma unroll
+  for (int ct = 0; ct < NCT; ++ct)
+    bv[ct] = MODE == 2 ? make_float4(0.f, 0.f, 0.f, 0.f)
+                       : *(const float4*)&bias[ct * 16 + 4 * kq];
+  auto emit = [&](const v4f (&acc)[NS][NCT], int z) {
     const int gx = x0 + r;
     if (gx >= cd.d0) return;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const int gy = y0 + row0 + s;
       if (gy >= cd.d1) break;
-      const size_t at = ((size_t)z * layer + (size_t)gy * cd.d0 + gx) * COUT + ct * 16 + 4 * kq;
-      float v[4] = {acc[s][0] + bv.x, acc[s][1] + bv.y, acc[s][2] + bv.z, acc[s][3] + bv.w};
-      if (MODE == 1) {
-        *(float4*)&outf[at] = make_float4(v[0], v[1], v[2], v[3]);
-      } else {
-        bf16raw h[4];
-        if (MODE == 0) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) h[i] = f2bf(v[i] > 0.f ? v[i] : 0.f);
+      for (int ct = 0; ct < NCT; ++ct) {
+        const size_t at = ((size_t)z * layer + (size_t)gy * cd.d0 + gx) * COUT + ct * 16 + 4 * kq;
+        const v4f c = acc[s][ct];
+        const float v[4] = {c[0] + bv[ct].x, c[1] + bv[ct].y, c[2] + bv[ct].z, c[3] + bv[ct].w};
+        if (MODE == 1) {
+          *(float4*)&outf[at] = make_float4(v[0], v[1], v[2], v[3]);
         } else {
-          const uint2 m = *(const uint2*)&ref[at];
-          const uint32_t mw[2] = {m.x, m.y};
+          bf16raw h[4];
+          if (MODE == 0) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            h[i] = f2bf(bf2f((bf16raw)(mw[i / 2] >> (16 * (i & 1)))) > 0.f ? acc[s][i] : 0.f);
+            for (int i = 0; i < 4; ++i) h[i] = f2bf(v[i] > 0.f ? v[i] : 0.f);
+          } else {
+            const uint2 m = *(const uint2*)&ref[at];
+            const uint32_t mw[2] = {m.x, m.y};
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              h[i] = f2bf(bf2f((bf16raw)(mw[i / 2] >> (16 * (i & 1)))) > 0.f ? c[i] : 0.f);
+          }
+          *(uint2*)&outb[at] = make_uint2((uint32_t)h[0] | (uint32_t)h[1] << 16,
+                                          (uint32_t)h[2] | (uint32_t)h[3] << 16);
         }
-        *(uint2*)&outb[at] = make_uint2((uint32_t)h[0] | (uint32_t)h[1] << 16,
-                                        (uint32_t)h[2] | (uint32_t)h[3] << 16);
       }
     }
   };
   const int p0 = max(0, z0 - 1), p1 = min(cd.d2 - 1, z1);
   const v4f zero = {0.f, 0.f, 0.f, 0.f};
-  v4f am[NS], a0[NS], ap[NS];  // outputs p - 1, p, p + 1
+  v4f am[NS][NCT], a0[NS][NCT], ap[NS][NCT];  // outputs p - 1, p, p + 1
 #pragma unroll
-  for (int s = 0; s < NS; ++s) am[s] = a0[s] = ap[s] = zero;
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) am[s][ct] = a0[s][ct] = ap[s][ct] = zero;
   fetch(p0);
   for (int p = p0; p <= p1; ++p) {
     lds_barrier();  // the previous layer's operand reads are done
@@ -194,37 +203,47 @@ __global__ __launch_bounds__(CNT) __attribute__((amdgpu_waves_per_eu(2))) void k
     const bool up = p + 1 < z1, mid = p >= z0 && p < z1, dn = p > z0;
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
-      frag b[NS], k0, k1, k2;
+      frag b[NS], k[3][NCT];
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         const int c = (s + t / 3) * CH + t % 3;
         b[s] = *(const frag*)&s_p[abase[c % 8] + c * RB];
       }
-      k0 = *(const frag*)&s_w[wbase + t * COUT * RB];
-      k1 = *(const frag*)&s_w[wbase + (9 + t) * COUT * RB];
-      k2 = *(const frag*)&s_w[wbase + (18 + t) * COUT * RB];
+#pragma unroll
+      for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct)
+          k[dz][ct] = *(const frag*)&s_w[wbase + ((9 * dz + t) * COUT + ct * 16) * RB];
       if (up) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) ap[s] = mma(k0, b[s], ap[s]);
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+          for (int ct = 0; ct < NCT; ++ct) ap[s][ct] = mma(k[0][ct], b[s], ap[s][ct]);
       }
       if (mid) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) a0[s] = mma(k1, b[s], a0[s]);
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+          for (int ct = 0; ct < NCT; ++ct) a0[s][ct] = mma(k[1][ct], b[s], a0[s][ct]);
       }
       if (dn) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) am[s] = mma(k2, b[s], am[s]);
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+          for (int ct = 0; ct < NCT; ++ct) am[s][ct] = mma(k[2][ct], b[s], am[s][ct]);
       }
     }
     // output p - 1 is complete, and output p too at the top of the box
     if (dn) emit(am, p - 1);
     if (p + 1 == cd.d2 && mid) emit(a0, p);
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      am[s] = a0[s];
-      a0[s] = ap[s];
-      ap[s] = zero;
-    }
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int ct = 0; ct < NCT; ++ct) {
+        am[s][ct] = a0[s][ct];
+        a0[s][ct] = ap[s][ct];
+        ap[s][ct] = zero;
+      }
   }
 }
 
