@@ -1559,94 +1559,67 @@ hipError_t launch_fft3d_full(c64* work, c64* tmp, const GroupGeom& g, const void
 }
 
 
-// ---------------------------- pruned x and y transforms of one field
-// For a field non-zero only on the first E[a] points of each axis
-// (E[a] <= P[a] / 2), the x and y stages of its forward 3-D transform, and
-// the y and x stages of a forward transform that keeps only the first E[1]
-// y and E[2] z outputs; both skip the zero halves like the operator's passes.
-template <typename T>
-static hipError_t px_pass(const cpx<T>* src, cpx<T>* dst, int n1, bool pad, const int E[3],
-                          const int P[3], const cpx<T>* tw0, hipStream_t s) {
-  const int P1 = P[0];
-  const int lines = E[1] * E[2];
-  const int L = lines_per_block<T>(P1);
-  const int bpr = (lines + L - 1) / L;
-  if (pad) {
-    VIE_DISPATCH_P(P1, (k_fft_x_fwd<T, T, PP, true><<<bpr, nt_lines_p<T>(PP), 0, s>>>(
-                           src, dst, tw0, n1, lines, bpr, nullptr)));
-  } else {
-    VIE_DISPATCH_P(P1, (k_fft_x_fwd<T, T, PP, false><<<bpr, nt_lines_p<T>(PP), 0, s>>>(
-                           src, dst, tw0, n1, lines, bpr, nullptr)));
-  }
-  return hipGetLastError();
-}
-
-template <typename T>
-static hipError_t py_pass(const cpx<T>* src, cpx<T>* dst, int rin, int rout, bool pad,
-                          const int E[3], const int P[3], const cpx<T>* tw1, hipStream_t s) {
-  const int P1 = P[0], P2 = P[1];
+// ---------------------------------- y stage of a batch of scalar fields
+// Forward: t1 [vec][fs fields][E3][E2][P1] -> t2 [vec][fs fields][E3][P2][P1] of
+// the first nf fields, zero rows skipped; inverse: back, kept rows only, into
+// t1 [vec][nf][E3][E2][P1].
+template <typename T, int PP>
+static void y_fields(const cpx<T>* in, cpx<T>* out, const int E[3], const int P[3],
+                     const cpx<T>* tw1, int nvec, int nf, int fs, bool inverse, const int* active,
+                     hipStream_t s) {
+  constexpr int ntY = y_threads<T, PP>();
+  constexpr int W = ntY / (PP / fft_e<PP>());
   StridedArgs a;
-  a.n_in_rows = rin;
-  a.n_out_rows = rout;
-  a.ncols = P1;
-  a.ncomp = 1;
+  a.ncols = P[0];
+  a.ncomp = nf;
   a.nz = E[2];
   a.zl = 1;
-  const int W = lines_per_block<T>(P2);
-  a.tiles = (P1 + W - 1) / W;
-  a.in.row = a.out.row = P1;
-  a.in.zhs = (int64_t)rin * P1;
-  a.out.zhs = (int64_t)rout * P1;
-  a.in.zls = a.out.zls = a.in.cs = a.out.cs = a.in.rs = a.out.rs = 0;
-  if (pad) {
-    VIE_DISPATCH_P(P2, (k_fft_strided<T, PP, true, false, false, nt_lines_p<T>(PP)>
-                        <<<a.tiles * E[2], nt_lines_p<T>(PP), 0, s>>>(src, dst, tw1, a, nullptr)));
+  a.tiles = (P[0] + W - 1) / W;
+  SideAddr t1, t2;
+  t1.row = t2.row = P[0];
+  t1.zls = t2.zls = 0;
+  t1.zhs = (int64_t)E[1] * P[0];
+  t2.zhs = (int64_t)P[1] * P[0];
+  t1.cs = t1.zhs * E[2];
+  t2.cs = t2.zhs * E[2];
+  t1.rs = t1.cs * (inverse ? nf : fs);
+  t2.rs = t2.cs * fs;
+  const dim3 grid(a.tiles * nf * E[2] * nvec);
+  if (!inverse) {
+    a.n_in_rows = E[1];
+    a.n_out_rows = PP;
+    a.in = t1;
+    a.out = t2;
+    k_fft_strided<T, PP, true, false, false, ntY><<<grid, ntY, 0, s>>>(in, out, tw1, a, active);
   } else {
-    VIE_DISPATCH_P(P2, (k_fft_strided<T, PP, false, true, false, nt_lines_p<T>(PP)>
-                        <<<a.tiles * E[2], nt_lines_p<T>(PP), 0, s>>>(src, dst, tw1, a, nullptr)));
+    a.n_in_rows = PP;
+    a.n_out_rows = E[1];
+    a.in = t2;
+    a.out = t1;
+    k_fft_strided<T, PP, false, true, true, ntY><<<grid, ntY, 0, s>>>(in, out, tw1, a, active);
   }
+}
+
+template <typename T>
+static hipError_t y_fields_t(const cpx<T>* in, cpx<T>* out, const int E[3], const int P[3],
+                             const cpx<T>* tw1, int nvec, int nf, int fs, bool inverse,
+                             const int* active, hipStream_t s) {
+  for (int a = 0; a < 3; ++a)
+    if (E[a] < 1 || 2 * E[a] > P[a]) return hipErrorInvalidValue;
+  VIE_DISPATCH_P(P[1],
+                 (y_fields<T, PP>(in, out, E, P, tw1, nvec, nf, fs, inverse, active, s)));
   return hipGetLastError();
 }
 
-static bool pruned_ok(const int E[3], const int P[3]) {
-  for (int a = 0; a < 3; ++a)
-    if (E[a] < 1 || 2 * E[a] > P[a]) return false;
-  return true;
+hipError_t launch_fft_y_fields(const c64* in, c64* out, const int E[3], const int P[3],
+                               const c64* tw1, int nvec, int nf, int fs, bool inverse,
+                               const int* active, hipStream_t s) {
+  return y_fields_t<double>(in, out, E, P, tw1, nvec, nf, fs, inverse, active, s);
 }
-
-template <typename T>
-static hipError_t xy_pad_t(const cpx<T>* in, cpx<T>* t1, cpx<T>* out, const int E[3],
-                           const int P[3], const void* tw[3], hipStream_t s) {
-  if (!pruned_ok(E, P)) return hipErrorInvalidValue;
-  hipError_t e = px_pass<T>(in, t1, E[0], true, E, P, (const cpx<T>*)tw[0], s);
-  if (e != hipSuccess) return e;
-  return py_pass<T>(t1, out, E[1], P[1], true, E, P, (const cpx<T>*)tw[1], s);
-}
-
-template <typename T>
-static hipError_t yx_trunc_t(const cpx<T>* in, cpx<T>* t1, cpx<T>* out, const int E[3],
-                             const int P[3], const void* tw[3], hipStream_t s) {
-  if (!pruned_ok(E, P)) return hipErrorInvalidValue;
-  hipError_t e = py_pass<T>(in, t1, P[1], E[1], false, E, P, (const cpx<T>*)tw[1], s);
-  if (e != hipSuccess) return e;
-  return px_pass<T>(t1, out, P[0], false, E, P, (const cpx<T>*)tw[0], s);
-}
-
-hipError_t launch_fft_xy_pad(const c64* in, c64* t1, c64* out, const int E[3], const int P[3],
-                             const void* tw[3], hipStream_t s) {
-  return xy_pad_t<double>(in, t1, out, E, P, tw, s);
-}
-hipError_t launch_fft_xy_pad(const c32* in, c32* t1, c32* out, const int E[3], const int P[3],
-                             const void* tw[3], hipStream_t s) {
-  return xy_pad_t<float>(in, t1, out, E, P, tw, s);
-}
-hipError_t launch_fft_yx_trunc(const c64* in, c64* t1, c64* out, const int E[3], const int P[3],
-                               const void* tw[3], hipStream_t s) {
-  return yx_trunc_t<double>(in, t1, out, E, P, tw, s);
-}
-hipError_t launch_fft_yx_trunc(const c32* in, c32* t1, c32* out, const int E[3], const int P[3],
-                               const void* tw[3], hipStream_t s) {
-  return yx_trunc_t<float>(in, t1, out, E, P, tw, s);
+hipError_t launch_fft_y_fields(const c32* in, c32* out, const int E[3], const int P[3],
+                               const c32* tw1, int nvec, int nf, int fs, bool inverse,
+                               const int* active, hipStream_t s) {
+  return y_fields_t<float>(in, out, E, P, tw1, nvec, nf, fs, inverse, active, s);
 }
 
 }  // namespace vie

@@ -108,293 +108,480 @@ __global__ void k_rt_octant(const c64* __restrict__ in, c64* __restrict__ out,
   }
 }
 
-// One input field of the product over the padded grid ([E3][E2][E1]): f < 3
-// the weighted current alpha W_f, f = 3 the cell charge rho.  Inactive faces
-// (alpha = 0) contribute nothing.
-template <typename T>
-__global__ void k_rt_gather(const c64* __restrict__ x, const double* __restrict__ alpha,
-                            cpx<T>* __restrict__ out, RtGeom q, int f, double inv_h) {
-  const int64_t step[3] = {1, q.E[0], (int64_t)q.E[0] * q.E[1]};
-  for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < q.m;
-       c += (int64_t)gridDim.x * blockDim.x) {
-    c64 v = mk(0.0, 0.0);
-    if (f < 3) {
-      v = alpha[f * q.m + c] * x[f * q.m + c];
-    } else {
-      const int pc[3] = {(int)(c % q.E[0]), (int)((c / q.E[0]) % q.E[1]),
-                         (int)(c / ((int64_t)q.E[0] * q.E[1]))};
-      for (int i = 0; i < 3; ++i) {
-        const int64_t o = i * q.m + c;
-        if (alpha[o] != 0.0) v = v + x[o];  // + face of the cell
-        if (pc[i] > 0 && alpha[o - step[i]] != 0.0) v = v - x[o - step[i]];  // - face
-      }
-      v = inv_h * v;
-    }
-    out[c] = cvt<T>(v);
+// ------------------------------------------------------- product passes
+// Fields f = 0..2: the weighted currents alpha W_f, f = 3: the cell charge.
+constexpr int kRtFields = 4;
+
+// Value of field f at cell c = (cx, cy, cz) of the vector x [3][m].  Inactive
+// faces (alpha = 0) contribute nothing, whatever x holds there.  Every load is
+// issued before the first is used (neighbours off the grid read the cell
+// itself): loading x only behind a test of alpha made the pass wait twice per
+// face.
+__device__ __forceinline__ c64 rt_field(const c64* __restrict__ x, const double* __restrict__ alpha,
+                                        const RtGeom& q, int f, int cx, int cy, int cz, int64_t c,
+                                        double inv_h) {
+  const c64 zero = mk(0.0, 0.0);
+  if (f < 3) {
+    const double a = alpha[f * q.m + c];
+    const c64 v = x[f * q.m + c];
+    return a != 0.0 ? a * v : zero;
   }
+  const int64_t step[3] = {1, q.E[0], (int64_t)q.E[0] * q.E[1]};
+  const int pc[3] = {cx, cy, cz};
+  double a[6];
+  c64 xv[6];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const int64_t o = i * q.m + c, lo = pc[i] > 0 ? o - step[i] : o;
+    a[2 * i] = alpha[o];
+    xv[2 * i] = x[o];
+    a[2 * i + 1] = alpha[lo];
+    xv[2 * i + 1] = x[lo];
+  }
+  c64 v = zero;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    v = v + (a[2 * i] != 0.0 ? xv[2 * i] : zero);                                   // + face
+    v = v - (pc[i] > 0 && a[2 * i + 1] != 0.0 ? xv[2 * i + 1] : zero);  // - face
+  }
+  return inv_h * v;
 }
 
-// The z stage with the kernel's spectrum, one workgroup per W neighbouring x
-// columns at one y of the y-transformed field t [E3][P2][P1] (rows z < E3
-// non-zero): forward z transform (zero half skipped), product with the
-// spectrum (1/M folded in), conjugate, forward z transform keeping rows
-// z < E3.  With the y and x stages run forward afterwards and a final
-// conjugate, that is the inverse transform of the product (the conjugate of
-// the forward transform of the conjugate).
+// x pass with the gather, over the lines (field, z, y) of every vector of a
+// batch: E1 gathered values -> P1 points of t1 [vector][field][z][y][P1].
+// HBM/L2 bound (one thread group per line, unit-stride reads and writes).
 template <typename T, int P>
-__global__ __launch_bounds__(nt_lines<T>()) void k_rt_zconv(
-    const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out, const cpx<T>* __restrict__ ghat,
-    const cpx<T>* __restrict__ tw, int E3, int P1, int P2, int tiles) {
-  constexpr int E = fft_e<P>(), TT = P / E, NT = nt_lines<T>(), W = NT / TT;
-  __shared__ cpx<T> lds[W * Pad<P>::LSTR];
-  const int b = xcd_remap(blockIdx.x, gridDim.x);
-  const int tile = b % tiles, y = b / tiles;
-  const int cw = threadIdx.x % W, t = threadIdx.x / W;
-  const int col = tile * W + cw;
-  const bool valid = col < P1;
-  const int64_t plane = (int64_t)P2 * P1;
-  const int64_t base = (int64_t)y * P1 + (valid ? col : 0);
-  // the spectrum's octant record of this column (mirrored x and y)
-  const int Q0 = P1 / 2 + 1, Q1 = P2 / 2 + 1;
-  const int xo = valid ? (col <= P1 / 2 ? col : P1 - col) : 0;
-  const int yo = y <= P2 / 2 ? y : P2 - y;
-  const cpx<T>* gcol = ghat + (int64_t)yo * Q0 + xo;
-  const int64_t gplane = (int64_t)Q0 * Q1;
+__global__ __launch_bounds__(nt_lines_p<T>(P)) void k_rt_xfwd(
+    const c64* __restrict__ x, const double* __restrict__ alpha, cpx<T>* __restrict__ t1,
+    const cpx<T>* __restrict__ tw, RtGeom q, double inv_h, int blocks_per_vec,
+    const int* __restrict__ active) {
+  constexpr int E = fft_e<P>(), TT = P / E, NT = nt_lines_p<T>(P), L = NT / TT,
+                LS = PadX<P, TT>::LSTR;
+  __shared__ cpx<T> lds[L * LS];
+  const int vec = blockIdx.x / blocks_per_vec, blk = blockIdx.x % blocks_per_vec;
+  if (active && !active[vec]) return;
+  const int li = threadIdx.x / TT, t = threadIdx.x % TT;
+  const int zy = q.E[1] * q.E[2], lines = kRtFields * zy;
+  const int line = blk * L + li;
+  const bool valid = line < lines;
+  const int f = valid ? line / zy : 0, yz = valid ? line % zy : 0;
+  const int cy = yz % q.E[1], cz = yz / q.E[1];
+  const c64* xv = x + (int64_t)vec * 3 * q.m;
   TwReg<T, P, E> tr;
   tr.load(t, tw);
   cpx<T> v[E];
 #pragma unroll
-  for (int q = 0; q < E; ++q) {
-    const int row = t + q * TT;
-    v[q] = (q < E / 2 && valid && row < E3) ? in[base + row * plane] : mk<T>(0, 0);
+  for (int k = 0; k < E; ++k) {
+    const int cx = t + k * TT;
+    if (k < E / 2 && valid && cx < q.E[0])
+      v[k] = cvt<T>(rt_field(xv, alpha, q, f, cx, cy, cz, (int64_t)yz * q.E[0] + cx, inv_h));
+    else
+      v[k] = mk<T>(0, 0);
   }
-  line_fft<T, P, false, true, false>(v, lds + cw * Pad<P>::LSTR, t, tr);
+  line_fft<T, P, false, true>(v, lds + li * LS, t, tr);
+  if (valid) {
+    cpx<T>* o = t1 + ((int64_t)vec * lines + line) * P;
 #pragma unroll
-  for (int q = 0; q < E; ++q) {
-    const int z = t + q * TT;
-    const cpx<T> p = v[q] * gcol[(int64_t)(z <= P / 2 ? z : P - z) * gplane];
-    v[q] = mk(p.re, -p.im);
+    for (int k = 0; k < E; ++k) o[t + k * TT] = v[k];
   }
-  line_fft<T, P, false, false, true>(v, lds + cw * Pad<P>::LSTR, t, tr);
+}
+
+// The z stage, in place on t2 [vector][field][z < E3][P2][P1]: forward z
+// transforms of the four fields of a column (zero half skipped), the three
+// components g (k0^2 F_i + D_i F_3) per point (1/M folded in g), inverse
+// transforms keeping z < E3, into fields 0..2.  Only the charge's transform
+// stays in registers; the components pass one by one, each one's points
+// requested while the one before is transformed, and the twiddles come from an
+// LDS table, so two waves share a SIMD.  Latency of the FP64 transforms' LDS
+// exchanges bounds it.  Microseconds per BiCGSTAB iteration of two channels on
+// 40^3 / 64^3 cells: 193 / 1077; four fields and register twiddles in one
+// wave's registers 217 / 1150; a launch per field, channel and pass 600 / 1430.
+template <int P>
+constexpr int rz_e() {
+  return P % 3 == 0 ? 12 : 8;
+}
+template <typename T, int P>
+constexpr int rz_threads() {
+  constexpr int n = (int)(128 / sizeof(cpx<T>)) * (P / rz_e<P>());  // 128-byte rows
+  return n < 64 ? 64 : n;
+}
+template <typename T, int P, int NT = rz_threads<T, P>()>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_rt_z(
+    cpx<T>* __restrict__ t2, const cpx<T>* __restrict__ ghat, const cpx<T>* __restrict__ tw,
+    const cpx<T>* __restrict__ dx, const cpx<T>* __restrict__ dy, const cpx<T>* __restrict__ dz,
+    int E3, int P1, int P2, int tiles, int nvec, T k0sq, const int* __restrict__ active) {
+  constexpr int E = rz_e<P>(), TT = P / E, W = NT / TT, LS = Pad<P>::LSTR;
+  __shared__ cpx<T> lds[W * LS];
+  // vectors innermost: they share the spectrum
+  const int b = xcd_remap(blockIdx.x, gridDim.x);
+  const int vec = b % nvec, rest = b / nvec;
+  if (active && !active[vec]) return;
+  const int tile = rest % tiles, y = rest / tiles;
+  const int cw = threadIdx.x % W, t = threadIdx.x / W;
+  const int col = tile * W + cw;
+  const bool valid = col < P1;
+  const int xc = valid ? col : 0;
+  const int64_t plane = (int64_t)P2 * P1, cs = plane * E3;
+  cpx<T>* base = t2 + (int64_t)vec * kRtFields * cs + (int64_t)y * P1 + xc;
+  __shared__ cpx<T> stw[P];
+  for (int k = threadIdx.x; k < P; k += NT) stw[k] = tw[k];
+  lds_barrier();
+  const LdsLine<T> ll{lds + cw * LS};
+  auto load = [&](int f, cpx<T> (&v)[E / 2]) {
+#pragma unroll
+    for (int k = 0; k < E / 2; ++k) {
+      const int z = t + k * TT;
+      v[k] = valid && z < E3 ? base[f * cs + z * plane] : mk<T>(0, 0);
+    }
+  };
+  // the spectrum's octant record of this column (mirrored x and y)
+  const int Q0 = P1 / 2 + 1, Q1 = P2 / 2 + 1;
+  const int xo = xc <= P1 / 2 ? xc : P1 - xc, yo = y <= P2 / 2 ? y : P2 - y;
+  const cpx<T>* gcol = ghat + (int64_t)yo * Q0 + xo;
+  const int64_t gplane = (int64_t)Q0 * Q1;
+  const cpx<T> fxy[2] = {dx[xc], dy[y]};
+  cpx<T> rho[E], v[E], nx[E / 2];
+  load(3, nx);
+#pragma unroll
+  for (int k = 0; k < E; ++k) rho[k] = k < E / 2 ? nx[k < E / 2 ? k : 0] : mk<T>(0, 0);
+  load(0, nx);
+  fft_stages_p<T, P, E, 1, false, 0, true, false, true>(rho, ll, t, stw);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+#pragma unroll
+    for (int k = 0; k < E; ++k) v[k] = k < E / 2 ? nx[k < E / 2 ? k : 0] : mk<T>(0, 0);
+    if (i < 2) load(i + 1, nx);
+    fft_stages_p<T, P, E, 1, false, 0, true, false, true>(v, ll, t, stw);
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const int z = t + k * TT;
+      const cpx<T> g = gcol[(int64_t)(z <= P / 2 ? z : P - z) * gplane];
+      const cpx<T> d = i < 2 ? fxy[i < 2 ? i : 0] : dz[z];
+      v[k] = g * cfma(d, rho[k], k0sq * v[k]);
+    }
+    fft_stages_p<T, P, E, 1, true, 0, false, true, true>(v, ll, t, stw);
+    if (valid) {
+#pragma unroll
+      for (int k = 0; k < E / 2; ++k) {
+        const int z = t + k * TT;
+        if (z < E3) base[i * cs + z * plane] = v[k];
+      }
+    }
+  }
+}
+
+// Last pass: inverse x transform of the lines (component, z, y), keeping
+// x < E1, then y = x - chi_f E (y = x on inactive faces) and the product's dot
+// partials, one pair per workgroup (fixed order):
+//   kEpiRhv: (aux, y);  kEpiTs: (y, x) and |y|^2;
+//   kEpiRes: out = aux - y, |out|^2
+enum { kEpiPlain = 0, kEpiRhv = 1, kEpiTs = 2, kEpiRes = 3 };
+template <typename T, int P, int MODE>
+__global__ __launch_bounds__(nt_lines_p<T>(P)) void k_rt_xinv(
+    const cpx<T>* __restrict__ t1, const c64* __restrict__ x, const double* __restrict__ chif,
+    const c64* __restrict__ aux, c64* __restrict__ out, c64* __restrict__ part,
+    const cpx<T>* __restrict__ tw, RtGeom q, int blocks_per_vec, const int* __restrict__ active) {
+  constexpr int E = fft_e<P>(), TT = P / E, NT = nt_lines_p<T>(P), L = NT / TT,
+                LS = PadX<P, TT>::LSTR;
+  __shared__ cpx<T> lds[L * LS];
+  __shared__ double red[4 * (NT / 64 + 1)];
+  const int vec = blockIdx.x / blocks_per_vec, blk = blockIdx.x % blocks_per_vec;
+  if (active && !active[vec]) return;
+  const int li = threadIdx.x / TT, t = threadIdx.x % TT;
+  const int lines = 3 * q.E[1] * q.E[2];
+  const int line = blk * L + li;
+  const bool valid = line < lines;
+  const cpx<T>* src = t1 + ((int64_t)vec * lines + (valid ? line : 0)) * P;
+  TwReg<T, P, E> tr;
+  tr.load(t, tw);
+  cpx<T> v[E];
+#pragma unroll
+  for (int k = 0; k < E; ++k) v[k] = valid ? src[t + k * TT] : mk<T>(0, 0);
+  line_fft<T, P, true, false, true>(v, lds + li * LS, t, tr);
+  c64 s0 = mk(0.0, 0.0), s1 = mk(0.0, 0.0);
   if (valid) {
 #pragma unroll
-    for (int q = 0; q < E / 2; ++q) {
-      const int row = t + q * TT;
-      if (row < E3) out[base + row * plane] = v[q];
+    for (int k = 0; k < E / 2; ++k) {
+      const int cx = t + k * TT;
+      if (cx >= q.E[0]) continue;
+      const int64_t e = (int64_t)line * q.E[0] + cx;  // within the vector
+      const int64_t g = (int64_t)vec * 3 * q.m + e;
+      const double cf = chif[e];
+      const c64 xv = x[g];
+      const c64 y = cf != 0.0 ? xv - cf * cvt<double>(v[k]) : xv;
+      if (MODE == kEpiRes) {
+        const c64 r = aux[g] - y;
+        out[g] = r;
+        s1.re += r.re * r.re + r.im * r.im;
+      } else {
+        out[g] = y;
+        if (MODE == kEpiRhv) s0 = s0 + cmulc(aux[g], y);
+        if (MODE == kEpiTs) {
+          s0 = s0 + cmulc(y, xv);
+          s1.re += y.re * y.re + y.im * y.im;
+        }
+      }
+    }
+  }
+  if (MODE != kEpiPlain) {
+    block_sum2(s0, s1, red);
+    if (threadIdx.x == 0) {
+      c64* pp = part + ((int64_t)vec * blocks_per_vec + blk) * 2;
+      pp[0] = s0;
+      pp[1] = s1;
     }
   }
 }
 
-// R[c] = conj(t) over the padded grid, t the truncated transform
-// [E3][E2][P1] (the inverse transform's result).
-template <typename T>
-__global__ void k_rt_store(const cpx<T>* __restrict__ t, c64* __restrict__ R, RtGeom q) {
-  for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < q.m;
-       c += (int64_t)gridDim.x * blockDim.x) {
-    const int x = (int)(c % q.E[0]);
-    const int64_t yz = c / q.E[0];  // z E2 + y
-    const cpx<T> v = t[yz * q.P[0] + x];
-    R[c] = mk((double)v.re, -(double)v.im);
-  }
-}
-
-// y = x - chi_f (k0^2 A_i + (phi(c + e_i) - phi(c)) / h) on active faces,
-// y = x on the others.  R holds A_x, A_y, A_z, phi (m each).
-__global__ void k_rt_epilogue(const c64* __restrict__ x, const c64* __restrict__ R,
-                              const double* __restrict__ chif, c64* __restrict__ y, RtGeom q,
-                              double k0sq, double inv_h) {
-  const int64_t step[3] = {1, q.E[0], (int64_t)q.E[0] * q.E[1]};
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < 3 * q.m;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const double cf = chif[e];
-    if (cf == 0.0) {
-      y[e] = x[e];
-      continue;
-    }
-    const int i = (int)(e / q.m);
-    const int64_t c = e - i * q.m;
-    // an active face has its upper cell on the padded grid (c + e_i < m)
-    const c64 grad = inv_h * (R[3 * q.m + c + step[i]] - R[3 * q.m + c]);
-    const c64 Es = k0sq * R[e] + grad;
-    y[e] = x[e] - cf * Es;
-  }
-}
-
-// b = chi_f pol_i e^{i k0 khat . r_f}, face i of padded cell c at
-// origin + h (c - 1) + (h/2) e_i.
-__global__ void k_rt_rhs(c64* __restrict__ b, const double* __restrict__ chif, RtGeom q, double h,
-                         double o0, double o1, double o2, double k0, double kx, double ky,
-                         double kz, c64 p0, c64 p1, c64 p2) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < 3 * q.m;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const double cf = chif[e];
-    if (cf == 0.0) {
-      b[e] = mk(0.0, 0.0);
-      continue;
-    }
-    const int i = (int)(e / q.m);
-    const int64_t c = e - i * q.m;
-    double r[3] = {o0 + h * ((int)(c % q.E[0]) - 1), o1 + h * ((int)((c / q.E[0]) % q.E[1]) - 1),
-                   o2 + h * ((int)(c / ((int64_t)q.E[0] * q.E[1])) - 1)};
-    r[i] += 0.5 * h;
-    double sn, cs;
-    sincos(k0 * (kx * r[0] + ky * r[1] + kz * r[2]), &sn, &cs);
-    const c64 pol = i == 0 ? p0 : (i == 1 ? p1 : p2);
-    b[e] = cf * (pol * mk(cs, sn));
-  }
-}
+// Incident channel of a batch.
+struct RtWave {
+  double k[3];
+  c64 p[3];
+};
 
 constexpr int kRtThreads = 256;
-constexpr int kRtDotBlocks = 256;
+constexpr int kRtFold = 64;  // partial pairs per vector that a vector kernel sums itself
 
-// Per-block partial sums of conj(a) . b (fixed reduction order).
-__global__ void __launch_bounds__(kRtThreads) k_rt_dot(const c64* __restrict__ a,
-                                                       const c64* __restrict__ b, int64_t n,
-                                                       c64* __restrict__ part) {
-  __shared__ double sr[kRtThreads], si[kRtThreads];
-  double re = 0.0, im = 0.0;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const c64 p = cmulc(a[e], b[e]);
-    re += p.re;
-    im += p.im;
+// Sum of n pairs of partials in a fixed order, to every thread.
+__device__ __forceinline__ void rt_sum(const c64* __restrict__ part, int n, c64& a, c64& b) {
+  __shared__ double red[kRtThreads / 64][4];
+  c64 s0 = mk(0.0, 0.0), s1 = mk(0.0, 0.0);
+  for (int k = threadIdx.x; k < n; k += kRtThreads) {
+    s0 = s0 + part[2 * k];
+    s1 = s1 + part[2 * k + 1];
   }
-  sr[threadIdx.x] = re;
-  si[threadIdx.x] = im;
+  for (int m = 32; m >= 1; m >>= 1) {
+    s0.re += __shfl_xor(s0.re, m, 64);
+    s0.im += __shfl_xor(s0.im, m, 64);
+    s1.re += __shfl_xor(s1.re, m, 64);
+    s1.im += __shfl_xor(s1.im, m, 64);
+  }
+  __syncthreads();  // red may still be read from an earlier sum
+  if ((threadIdx.x & 63) == 0) {
+    double* r = red[threadIdx.x >> 6];
+    r[0] = s0.re;
+    r[1] = s0.im;
+    r[2] = s1.re;
+    r[3] = s1.im;
+  }
   __syncthreads();
-  for (int s = kRtThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      sr[threadIdx.x] += sr[threadIdx.x + s];
-      si[threadIdx.x] += si[threadIdx.x + s];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = mk(sr[0], si[0]);
-}
-
-// out = a + ca b + cc c (c nullable)
-__global__ void k_rt_lin(c64* __restrict__ out, const c64* __restrict__ a, c64 cb,
-                         const c64* __restrict__ b, c64 cc, const c64* __restrict__ c, int64_t n) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    c64 v = cfma(cb, b[e], a[e]);
-    if (c) v = cfma(cc, c[e], v);
-    out[e] = v;
+  a = b = mk(0.0, 0.0);
+  for (int w = 0; w < kRtThreads / 64; ++w) {
+    a = a + mk(red[w][0], red[w][1]);
+    b = b + mk(red[w][2], red[w][3]);
   }
 }
 
-// BiCGSTAB scalars, kept on the device between host checks.
+// This thread's sums into the workgroup's partial pair.
+__device__ __forceinline__ void rt_partial(c64 s0, c64 s1, c64* __restrict__ out) {
+  __shared__ double red[4 * (kRtThreads / 64)];
+  block_sum2(s0, s1, red);
+  if (threadIdx.x == 0) {
+    out[0] = s0;
+    out[1] = s1;
+  }
+}
+
+// Many partials (one per workgroup of a large grid's last pass) folded to
+// kRtFold per vector.
+__global__ void __launch_bounds__(64) k_rt_fold(const c64* __restrict__ part, int n,
+                                                c64* __restrict__ out,
+                                                const int* __restrict__ active) {
+  const int vec = blockIdx.x / kRtFold, j = blockIdx.x % kRtFold;
+  if (!active[vec]) return;
+  const int k0 = (int)((int64_t)n * j / kRtFold), k1 = (int)((int64_t)n * (j + 1) / kRtFold);
+  const c64* p = part + (int64_t)vec * n * 2;
+  double v[4] = {0, 0, 0, 0};
+  for (int k = k0 + threadIdx.x; k < k1; k += 64) {
+    v[0] += p[2 * k].re;
+    v[1] += p[2 * k].im;
+    v[2] += p[2 * k + 1].re;
+    v[3] += p[2 * k + 1].im;
+  }
+  for (int m = 32; m >= 1; m >>= 1)
+    for (int c = 0; c < 4; ++c) v[c] += __shfl_xor(v[c], m, 64);
+  if (threadIdx.x == 0) {
+    c64* o = out + ((int64_t)vec * kRtFold + j) * 2;
+    o[0] = mk(v[0], v[1]);
+    o[1] = mk(v[2], v[3]);
+  }
+}
+
+// BiCGSTAB scalars of one vector, on the device between host checks.  A
+// vector kernel sums the partials it needs in every workgroup and one
+// workgroup per vector stores the results; no kernel stores a value that
+// another workgroup of the same launch reads (except `active`, cleared by the
+// same decision that every workgroup takes for itself).
 struct RtScal {
-  c64 rho, alpha, omega, beta, rho1;
-  double tol2;          // tol^2 ||b||^2 (recursive residual threshold)
-  int it, max_it;       // iterations done (all cycles), cap
-  int stop;             // 0 running, 1 recursive residual reached, 2 breakdown, 3 cap
+  c64 rho, rho1, alpha, omega;
+  double tol2;      // tol^2 ||b||^2 (recursive residual threshold)
+  int it, max_it;   // iterations done (all cycles), cap
+  int stop;         // 0 running, 1 recursive residual reached, 2 breakdown, 3 cap
 };
-enum { kScRho = 0, kScAlpha = 1, kScOmega = 2, kScRes = 3 };
 
 __device__ __forceinline__ c64 rt_cdiv(c64 a, c64 b) {
   const double d = b.re * b.re + b.im * b.im;
   return mk((a.re * b.re + a.im * b.im) / d, (a.im * b.re - a.re * b.im) / d);
 }
+__device__ __forceinline__ bool rt_zero(c64 a) { return a.re == 0.0 && a.im == 0.0; }
 
-__global__ void k_rt_sinit(RtScal* sc, double tol2, int it, int max_it) {
-  RtScal S;
-  S.rho = S.alpha = S.omega = S.beta = S.rho1 = mk(1.0, 0.0);
-  S.tol2 = tol2;
-  S.it = it;
-  S.max_it = max_it;
-  S.stop = 0;
-  *sc = S;
-}
-
-// Reduces the dot partials of slot 0 (and 1) in a fixed order and takes one
-// scalar step of the iteration:
-//   kScRho:   rho1 = (rh, r); beta = (rho1 / rho)(alpha / omega)
-//   kScAlpha: alpha = rho1 / (rh, v)
-//   kScOmega: omega = (t, s) / (t, t); rho = rho1; one iteration done
-//   kScRes:   stop when (r, r) <= tol^2 ||b||^2, or after omega = 0
-// A zero denominator stops the cycle (breakdown); so does the iteration cap.
-__global__ void __launch_bounds__(kRtThreads) k_rt_scal(const c64* __restrict__ part,
-                                                        RtScal* __restrict__ sc, int op) {
-  __shared__ double red[4][kRtThreads];
-  const int i = threadIdx.x;
-  const c64 a = part[i];
-  const c64 b = op == kScOmega ? part[kRtDotBlocks + i] : mk(0.0, 0.0);
-  red[0][i] = a.re;
-  red[1][i] = a.im;
-  red[2][i] = b.re;
-  red[3][i] = b.im;
-  __syncthreads();
-  for (int st = kRtThreads / 2; st > 0; st >>= 1) {
-    if (i < st)
-      for (int k = 0; k < 4; ++k) red[k][i] += red[k][i + st];
-    __syncthreads();
-  }
-  if (i != 0) return;
-  RtScal S = *sc;
-  if (S.stop) return;
-  const c64 d0 = mk(red[0][0], red[1][0]);
-  const bool zero0 = d0.re == 0.0 && d0.im == 0.0;
-  if (op == kScRho) {
-    if (S.it >= S.max_it) {
-      S.stop = 3;
-    } else if (zero0) {
-      S.stop = 2;
-    } else {
-      S.rho1 = d0;
-      S.beta = rt_cdiv(d0, S.rho) * rt_cdiv(S.alpha, S.omega);
+// b = chi_f pol_i e^{i k0 khat . r_f}, face i of padded cell c at
+// origin + h (c - 1) + (h/2) e_i; x = p = v = 0, r = rh = b, partials |b|^2.
+__global__ void __launch_bounds__(kRtThreads) k_rt_rhs(
+    c64* __restrict__ b, c64* __restrict__ x, c64* __restrict__ r, c64* __restrict__ rh,
+    c64* __restrict__ p, c64* __restrict__ v, const double* __restrict__ chif, RtGeom q, double h,
+    double o0, double o1, double o2, double k0, const RtWave* __restrict__ wave, int vb,
+    c64* __restrict__ part) {
+  const int vec = blockIdx.x / vb, blk = blockIdx.x % vb;
+  const RtWave w = wave[vec];
+  const int64_t n = 3 * q.m;
+  c64 s = mk(0.0, 0.0);
+  for (int64_t e = (int64_t)blk * kRtThreads + threadIdx.x; e < n; e += (int64_t)vb * kRtThreads) {
+    const double cf = chif[e];
+    c64 val = mk(0.0, 0.0);
+    if (cf != 0.0) {
+      const int i = (int)(e / q.m);
+      const int64_t c = e - i * q.m;
+      double rr[3] = {o0 + h * ((int)(c % q.E[0]) - 1),
+                      o1 + h * ((int)((c / q.E[0]) % q.E[1]) - 1),
+                      o2 + h * ((int)(c / ((int64_t)q.E[0] * q.E[1])) - 1)};
+      rr[i] += 0.5 * h;
+      double sn, cs;
+      sincos(k0 * (w.k[0] * rr[0] + w.k[1] * rr[1] + w.k[2] * rr[2]), &sn, &cs);
+      val = cf * (w.p[i] * mk(cs, sn));
     }
-  } else if (op == kScAlpha) {
-    if (zero0)
-      S.stop = 2;
-    else
-      S.alpha = rt_cdiv(S.rho1, d0);
-  } else if (op == kScOmega) {
-    const double tt = red[2][0];
-    S.omega = tt > 0 ? mk(d0.re / tt, d0.im / tt) : mk(0.0, 0.0);
-    S.rho = S.rho1;
-    S.it += 1;
-  } else {
-    if (d0.re <= S.tol2)
-      S.stop = 1;
-    else if (S.omega.re == 0.0 && S.omega.im == 0.0)
-      S.stop = 2;
+    const int64_t g = vec * n + e;
+    b[g] = r[g] = rh[g] = val;
+    x[g] = p[g] = v[g] = mk(0.0, 0.0);
+    s.re += val.re * val.re + val.im * val.im;
   }
-  *sc = S;
+  rt_partial(s, s, part + ((int64_t)vec * vb + blk) * 2);
 }
 
-// p = r + beta (p - omega v)
-__global__ void k_rt_pupd(c64* __restrict__ p, const c64* __restrict__ r,
-                          const c64* __restrict__ v, const RtScal* __restrict__ sc, int64_t n) {
-  if (sc->stop) return;
-  const c64 beta = sc->beta, om = sc->omega;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x)
-    p[e] = r[e] + beta * (p[e] - om * v[e]);
-}
-
-// s = r - alpha v
-__global__ void k_rt_supd(c64* __restrict__ s, const c64* __restrict__ r,
-                          const c64* __restrict__ v, const RtScal* __restrict__ sc, int64_t n) {
-  if (sc->stop) return;
-  const c64 al = sc->alpha;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x)
-    s[e] = r[e] - al * v[e];
-}
-
-// x = x + alpha p + omega s; r = s - omega t
-__global__ void k_rt_xrupd(c64* __restrict__ x, c64* __restrict__ r, const c64* __restrict__ p,
-                           const c64* __restrict__ s, const c64* __restrict__ t,
-                           const RtScal* __restrict__ sc, int64_t n) {
-  if (sc->stop) return;
-  const c64 al = sc->alpha, om = sc->omega;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const c64 se = s[e];
-    x[e] = x[e] + al * p[e] + om * se;
-    r[e] = se - om * t[e];
+// Restart of the marked vectors from their true residual t: r = rh = t,
+// p = v = 0, partials |t|^2.
+__global__ void __launch_bounds__(kRtThreads) k_rt_restart(
+    const c64* __restrict__ t, c64* __restrict__ r, c64* __restrict__ rh, c64* __restrict__ p,
+    c64* __restrict__ v, int64_t n, int vb, c64* __restrict__ part, const int* __restrict__ mark) {
+  const int vec = blockIdx.x / vb, blk = blockIdx.x % vb;
+  if (!mark[vec]) return;
+  c64 s = mk(0.0, 0.0);
+  for (int64_t e = (int64_t)blk * kRtThreads + threadIdx.x; e < n; e += (int64_t)vb * kRtThreads) {
+    const int64_t g = vec * n + e;
+    const c64 val = t[g];
+    r[g] = rh[g] = val;
+    p[g] = v[g] = mk(0.0, 0.0);
+    s.re += val.re * val.re + val.im * val.im;
   }
+  rt_partial(s, s, part + ((int64_t)vec * vb + blk) * 2);
+}
+
+// Ends or continues the iteration on the partials ((rh, r), (r, r)) of the
+// last residual update, then p = r + beta (p - omega v),
+// beta = (rho1 / rho)(alpha / omega).  A zero denominator stops the cycle
+// (breakdown); so does the iteration cap.
+__global__ void __launch_bounds__(kRtThreads) k_rt_pupd(
+    c64* __restrict__ p, const c64* __restrict__ r, const c64* __restrict__ v,
+    RtScal* __restrict__ scal, int* __restrict__ active, int64_t n, int vb,
+    const c64* __restrict__ part, int npart) {
+  const int vec = blockIdx.x / vb, blk = blockIdx.x % vb;
+  if (!active[vec]) return;
+  RtScal* S = scal + vec;
+  const c64 rho = S->rho, alpha = S->alpha, om = S->omega;
+  const double tol2 = S->tol2;
+  const int it = S->it, max_it = S->max_it;
+  c64 rho1, rr;
+  rt_sum(part + (int64_t)vec * npart * 2, npart, rho1, rr);
+  int stop = 0;
+  if (rr.re <= tol2)
+    stop = 1;
+  else if (rt_zero(om))
+    stop = 2;
+  else if (it >= max_it)
+    stop = 3;
+  else if (rt_zero(rho1))
+    stop = 2;
+  if (blk == 0 && threadIdx.x == 0) {
+    S->rho1 = rho1;
+    S->stop = stop;
+    if (stop) active[vec] = 0;
+  }
+  if (stop) return;
+  const c64 beta = rt_cdiv(rho1, rho) * rt_cdiv(alpha, om);
+  for (int64_t e = (int64_t)blk * kRtThreads + threadIdx.x; e < n; e += (int64_t)vb * kRtThreads) {
+    const int64_t g = vec * n + e;
+    p[g] = r[g] + beta * (p[g] - om * v[g]);
+  }
+}
+
+// alpha = rho1 / (rh, v); s = r - alpha v
+__global__ void __launch_bounds__(kRtThreads) k_rt_supd(
+    c64* __restrict__ s, const c64* __restrict__ r, const c64* __restrict__ v,
+    RtScal* __restrict__ scal, int* __restrict__ active, int64_t n, int vb,
+    const c64* __restrict__ part, int npart) {
+  const int vec = blockIdx.x / vb, blk = blockIdx.x % vb;
+  if (!active[vec]) return;
+  RtScal* S = scal + vec;
+  const c64 rho1 = S->rho1;
+  c64 rhv, none;
+  rt_sum(part + (int64_t)vec * npart * 2, npart, rhv, none);
+  const bool stop = rt_zero(rhv);
+  const c64 al = stop ? mk(0.0, 0.0) : rt_cdiv(rho1, rhv);
+  if (blk == 0 && threadIdx.x == 0) {
+    if (stop) {
+      S->stop = 2;
+      active[vec] = 0;
+    } else {
+      S->alpha = al;
+    }
+  }
+  if (stop) return;
+  for (int64_t e = (int64_t)blk * kRtThreads + threadIdx.x; e < n; e += (int64_t)vb * kRtThreads) {
+    const int64_t g = vec * n + e;
+    s[g] = r[g] - al * v[g];
+  }
+}
+
+// omega = (t, s) / (t, t); x += alpha p + omega s; r = s - omega t; one
+// iteration done; partials (rh, r), |r|^2.
+__global__ void __launch_bounds__(kRtThreads) k_rt_xrupd(
+    c64* __restrict__ x, c64* __restrict__ r, const c64* __restrict__ p,
+    const c64* __restrict__ s, const c64* __restrict__ t, const c64* __restrict__ rh,
+    RtScal* __restrict__ scal, const int* __restrict__ active, int64_t n, int vb,
+    const c64* __restrict__ part, int npart, c64* __restrict__ out) {
+  const int vec = blockIdx.x / vb, blk = blockIdx.x % vb;
+  if (!active[vec]) return;
+  RtScal* S = scal + vec;
+  const c64 al = S->alpha;
+  c64 ts, tt;
+  rt_sum(part + (int64_t)vec * npart * 2, npart, ts, tt);
+  const c64 om = tt.re > 0 ? mk(ts.re / tt.re, ts.im / tt.re) : mk(0.0, 0.0);
+  if (blk == 0 && threadIdx.x == 0) {
+    S->omega = om;
+    S->rho = S->rho1;
+    S->it += 1;
+  }
+  c64 s0 = mk(0.0, 0.0), s1 = mk(0.0, 0.0);
+  for (int64_t e = (int64_t)blk * kRtThreads + threadIdx.x; e < n; e += (int64_t)vb * kRtThreads) {
+    const int64_t g = vec * n + e;
+    const c64 se = s[g];
+    x[g] = x[g] + al * p[g] + om * se;
+    const c64 rn = se - om * t[g];
+    r[g] = rn;
+    s0 = s0 + cmulc(rh[g], rn);
+    s1.re += rn.re * rn.re + rn.im * rn.im;
+  }
+  rt_partial(s0, s1, out + ((int64_t)vec * vb + blk) * 2);
+}
+
+// The sums of one pair of partials per marked vector, for the host.
+__global__ void __launch_bounds__(kRtThreads) k_rt_total(const c64* __restrict__ part, int npart,
+                                                         double* __restrict__ out,
+                                                         const int* __restrict__ mark) {
+  if (mark && !mark[blockIdx.x]) return;
+  c64 a, b;
+  rt_sum(part + (int64_t)blockIdx.x * npart * 2, npart, a, b);
+  if (threadIdx.x == 0) out[blockIdx.x] = b.re;
 }
 
 }  // namespace vie
@@ -441,18 +628,11 @@ struct vie_rt {
   c32* ghat32 = nullptr;    // its FP32 copy
   c64* tw[3] = {nullptr, nullptr, nullptr};
   c32* tw32[3] = {nullptr, nullptr, nullptr};
-  c64* work = nullptr;  // [M]
-  c64* tmp = nullptr;   // [M]
-  c64* c0 = nullptr;    // [m] gathered field
-  c64* t1 = nullptr;    // [E3 E2 P1]
-  c64* t2 = nullptr;    // [E3 P2 P1]
-  c64* t3 = nullptr;    // [E3 P2 P1]
-  c64* c1 = nullptr;    // [E3 E2 P1]
-  c64* R = nullptr;     // [4][m]
-  c64* vec[9] = {};     // solver vectors [3m] each
-  c64* part = nullptr;  // dot partials, two slots
-  RtScal* sc = nullptr; // device-resident iteration scalars
-  std::vector<c64> hpart;
+  c64* df[3] = {nullptr, nullptr, nullptr};    // D_a(k) = (e^{2 pi i k / P_a} - 1) / h
+  c32* df32[3] = {nullptr, nullptr, nullptr};
+  // per batch of vectors (grown on first use): transform scratch
+  // [vec][4][E3][E2][P1] and [vec][4][E3][P2][P1], solver vectors, partials
+  RtBuf t1, t2, vecs, part[3], fold, scal, active, mark, wave, total;
   // far field: the cells with an active face (ascending), their blocks and
   // columns (built on first use), scratch
   std::vector<int> cells;
@@ -486,17 +666,8 @@ void rt_free(vie_rt* r) {
   f(r->ghat32);
   for (auto* t : r->tw32) f(t);
   for (auto* t : r->tw) f(t);
-  f(r->work);
-  f(r->tmp);
-  f(r->c0);
-  f(r->t1);
-  f(r->t2);
-  f(r->t3);
-  f(r->c1);
-  f(r->R);
-  for (auto* v : r->vec) f(v);
-  f(r->part);
-  f(r->sc);
+  for (auto* t : r->df) f(t);
+  for (auto* t : r->df32) f(t);
   if (r->stream) (void)hipStreamDestroy(r->stream);
 }
 
@@ -509,68 +680,107 @@ void rt_free(vie_rt* r) {
     }                                \
   } while (0)
 
-// y = A x for one full-layout vector (device pointers).  The transforms of
-// the four fields run in T (FP64, or FP32 for the inner products of a mixed
-// solve); gather, epilogue and y stay FP64.
+// Launch shapes of a vector kernel and of the last product pass: workgroups
+// (partial pairs) per vector.
+int vec_blocks(int64_t n) {
+  return (int)std::min<int64_t>(512, std::max<int64_t>(1, (n + 4 * kRtThreads - 1) /
+                                                              (4 * kRtThreads)));
+}
 template <typename T>
-int rt_apply_t(vie_rt* r, const c64* x, c64* y) {
+int xinv_blocks(const RtGeom& q) {
+  const int L = lines_per_block<T>(q.P[0]);
+  return (3 * q.E[1] * q.E[2] + L - 1) / L;
+}
+
+// Scratch for nvec vectors at once.
+hipError_t rt_ensure(vie_rt* r, int nvec) {
+  const RtGeom& q = r->q;
+  const size_t row = (size_t)kRtFields * q.E[2] * q.P[0] * sizeof(c64);
+  hipError_t e = r->t1.reserve(nvec * row * q.E[1]);
+  if (e == hipSuccess) e = r->t2.reserve(nvec * row * q.P[1]);
+  const size_t np = std::max(std::max(xinv_blocks<double>(q), xinv_blocks<float>(q)),
+                             vec_blocks(3 * q.m));
+  for (auto& p : r->part)
+    if (e == hipSuccess) e = p.reserve(nvec * np * 2 * sizeof(c64));
+  if (e == hipSuccess) e = r->fold.reserve((size_t)nvec * kRtFold * 2 * sizeof(c64));
+  return e;
+}
+
+// out = A x (kEpiRes: aux - A x) of nvec vectors [nvec][3][m] (device), with
+// the dot partials of `mode` in part.  The transforms run in T (FP64, or FP32
+// for the inner products of a mixed solve); gather, epilogue and out stay
+// FP64.  active (nullable): only the vectors with a non-zero flag.
+template <typename T>
+int rt_apply_t(vie_rt* r, const c64* x, c64* out, int nvec, int mode, const c64* aux, c64* part,
+               const int* active) {
   const RtGeom& q = r->q;
   const bool f64 = sizeof(T) == 8;
-  const void* tw[3];
-  for (int a = 0; a < 3; ++a) tw[a] = f64 ? (const void*)r->tw[a] : (const void*)r->tw32[a];
-  const cpx<T>* ghat = (const cpx<T>*)(f64 ? (const void*)r->ghat : (const void*)r->ghat32);
-  cpx<T>* c0 = (cpx<T>*)r->c0;
-  cpx<T>* t1 = (cpx<T>*)r->t1;
-  cpx<T>* t2 = (cpx<T>*)r->t2;
-  cpx<T>* t3 = (cpx<T>*)r->t3;
-  cpx<T>* c1 = (cpx<T>*)r->c1;
-  const double inv_h = 1.0 / r->h;
-  const int lpb = lines_per_block<T>(q.P[2]);
-  const int tiles = (q.P[0] + lpb - 1) / lpb;
-  for (int f = 0; f < 4; ++f) {
-    k_rt_gather<T><<<blocks_for(q.m), kRtThreads, 0, r->stream>>>(x, r->alpha, c0, q, f, inv_h);
-    RT_HIP(hipGetLastError());
-    RT_HIP(launch_fft_xy_pad(c0, t1, t2, q.E, q.P, tw, r->stream));
-    auto zconv = [&]() -> hipError_t {
-      VIE_DISPATCH_PZ(q.P[2], (k_rt_zconv<T, PP><<<tiles * q.P[1], nt_lines<T>(), 0, r->stream>>>(
-                                  t2, t3, ghat, (const cpx<T>*)tw[2], q.E[2], q.P[0], q.P[1],
-                                  tiles)));
-      return hipGetLastError();
-    };
-    RT_HIP(zconv());
-    RT_HIP(launch_fft_yx_trunc(t3, t1, c1, q.E, q.P, tw, r->stream));
-    k_rt_store<T><<<blocks_for(q.m), kRtThreads, 0, r->stream>>>(c1, r->R + f * q.m, q);
-    RT_HIP(hipGetLastError());
+  auto pick = [&](const void* a, const void* b) { return (const cpx<T>*)(f64 ? a : b); };
+  const cpx<T>* tw[3];
+  const cpx<T>* df[3];
+  for (int a = 0; a < 3; ++a) {
+    tw[a] = pick(r->tw[a], r->tw32[a]);
+    df[a] = pick(r->df[a], r->df32[a]);
   }
-  k_rt_epilogue<<<blocks_for(3 * q.m), kRtThreads, 0, r->stream>>>(x, r->R, r->chif, y, q,
-                                                                   r->k0 * r->k0, inv_h);
-  RT_HIP(hipGetLastError());
+  const cpx<T>* ghat = pick(r->ghat, r->ghat32);
+  cpx<T>* t1 = r->t1.as<cpx<T>>();
+  cpx<T>* t2 = r->t2.as<cpx<T>>();
+  const double inv_h = 1.0 / r->h;
+  const int L = lines_per_block<T>(q.P[0]);
+  const int bf = (kRtFields * q.E[1] * q.E[2] + L - 1) / L, bi = xinv_blocks<T>(q);
+  auto xf = [&]() -> hipError_t {
+    VIE_DISPATCH_P(q.P[0], (k_rt_xfwd<T, PP><<<bf * nvec, nt_lines_p<T>(PP), 0, r->stream>>>(
+                               x, r->alpha, t1, tw[0], q, inv_h, bf, active)));
+    return hipGetLastError();
+  };
+  auto zc = [&]() -> hipError_t {
+    VIE_DISPATCH_PZ(q.P[2], ({
+                      constexpr int NT = rz_threads<T, PP>();
+                      constexpr int W = NT / (PP / rz_e<PP>());
+                      const int tiles = (q.P[0] + W - 1) / W;
+                      k_rt_z<T, PP><<<tiles * q.P[1] * nvec, NT, 0, r->stream>>>(
+                          t2, ghat, tw[2], df[0], df[1], df[2], q.E[2], q.P[0], q.P[1], tiles,
+                          nvec, (T)(r->k0 * r->k0), active);
+                    }));
+    return hipGetLastError();
+  };
+#define RT_XINV(MODE_)                                                                     \
+  VIE_DISPATCH_P(q.P[0], (k_rt_xinv<T, PP, MODE_><<<bi * nvec, nt_lines_p<T>(PP), 0,         \
+                                                    r->stream>>>(t1, x, r->chif, aux, out, \
+                                                                 part, tw[0], q, bi, active)))
+  auto xi = [&]() -> hipError_t {
+    switch (mode) {
+      case kEpiPlain: RT_XINV(kEpiPlain); break;
+      case kEpiRhv: RT_XINV(kEpiRhv); break;
+      case kEpiTs: RT_XINV(kEpiTs); break;
+      default: RT_XINV(kEpiRes); break;
+    }
+    return hipGetLastError();
+  };
+#undef RT_XINV
+  RT_HIP(xf());
+  RT_HIP(launch_fft_y_fields(t1, t2, q.E, q.P, tw[1], nvec, kRtFields, kRtFields, false, active,
+                             r->stream));
+  RT_HIP(zc());
+  RT_HIP(launch_fft_y_fields(t2, t1, q.E, q.P, tw[1], nvec, 3, kRtFields, true, active,
+                             r->stream));
+  RT_HIP(xi());
   return VIE_OK;
 }
 
-int rt_apply(vie_rt* r, const c64* x, c64* y, bool fp32 = false) {
-  return fp32 ? rt_apply_t<float>(r, x, y) : rt_apply_t<double>(r, x, y);
+int rt_apply(vie_rt* r, const c64* x, c64* out, int nvec, bool fp32, int mode = kEpiPlain,
+             const c64* aux = nullptr, c64* part = nullptr, const int* active = nullptr) {
+  return fp32 ? rt_apply_t<float>(r, x, out, nvec, mode, aux, part, active)
+              : rt_apply_t<double>(r, x, out, nvec, mode, aux, part, active);
 }
 
-// conj(a) . b over n entries (synchronous).
-int rt_dot(vie_rt* r, const c64* a, const c64* b, int64_t n, c64* out) {
-  k_rt_dot<<<kRtDotBlocks, kRtThreads, 0, r->stream>>>(a, b, n, r->part);
-  RT_HIP(hipGetLastError());
-  RT_HIP(hipMemcpyAsync(r->hpart.data(), r->part, kRtDotBlocks * sizeof(c64),
-                        hipMemcpyDeviceToHost, r->stream));
-  RT_HIP(hipStreamSynchronize(r->stream));
-  c64 s = mk(0.0, 0.0);
-  for (int k = 0; k < kRtDotBlocks; ++k) s = s + r->hpart[k];
-  *out = s;
-  return VIE_OK;
-}
-
-int rt_lin(vie_rt* r, c64* out, const c64* a, c64 cb, const c64* b, c64 cc, const c64* c,
-           int64_t n) {
-  k_rt_lin<<<blocks_for(n), kRtThreads, 0, r->stream>>>(out, a, cb, b, cc, c, n);
-  RT_HIP(hipGetLastError());
-  return VIE_OK;
-}
+// an allocation that fails leaves the operator usable
+#define RT_ALLOC(call)                                  \
+  do {                                                  \
+    hipError_t ea_ = (call);                            \
+    if (ea_ == hipErrorOutOfMemory) return VIE_ENOMEM;  \
+    RT_HIP(ea_);                                        \
+  } while (0)
 
 #define RT_TRY(call)          \
   do {                        \
@@ -660,35 +870,36 @@ extern "C" int vie_rt_setup(const vie_body* body, double k0, vie_rt** out) {
   const int64_t noct = (int64_t)(q.P[0] / 2 + 1) * (q.P[1] / 2 + 1) * (q.P[2] / 2 + 1);
   chk(dalloc(&r->ghat, noct));
   chk(dalloc(&r->ghat32, noct));
-  chk(dalloc(&r->work, M));
-  chk(dalloc(&r->tmp, M));
-  chk(dalloc(&r->R, 4 * m));
-  chk(dalloc(&r->c0, m));
-  chk(dalloc(&r->t1, (size_t)q.E[2] * q.E[1] * q.P[0]));
-  chk(dalloc(&r->t2, (size_t)q.E[2] * q.P[1] * q.P[0]));
-  chk(dalloc(&r->t3, (size_t)q.E[2] * q.P[1] * q.P[0]));
-  chk(dalloc(&r->c1, (size_t)q.E[2] * q.E[1] * q.P[0]));
-  for (auto& v : r->vec) chk(dalloc(&v, 3 * m));
-  chk(dalloc(&r->part, 2 * kRtDotBlocks));
-  chk(dalloc(&r->sc, 1));
+  RtBuf work, tmp;  // the full circulant, for the spectrum only
+  chk(work.reserve(M * sizeof(c64)));
+  chk(tmp.reserve(M * sizeof(c64)));
   for (int a = 0; a < 3; ++a) chk(dalloc(&r->tw[a], q.P[a]));
   for (int a = 0; a < 3; ++a) chk(dalloc(&r->tw32[a], q.P[a]));
+  for (int a = 0; a < 3; ++a) chk(dalloc(&r->df[a], q.P[a]));
+  for (int a = 0; a < 3; ++a) chk(dalloc(&r->df32[a], q.P[a]));
   if (e != hipSuccess) {
     rt_free(r);
     delete r;
     return e == hipErrorOutOfMemory ? VIE_ENOMEM : VIE_EDEVICE;
   }
-  r->hpart.resize(kRtDotBlocks);
   for (int a = 0; a < 3; ++a) {
-    std::vector<c64> t(q.P[a]);
-    std::vector<c32> t32(q.P[a]);
+    std::vector<c64> t(q.P[a]), d(q.P[a]);
+    std::vector<c32> t32(q.P[a]), d32(q.P[a]);
     for (int k = 0; k < q.P[a]; ++k) {
-      const long double ang = -2.0L * 3.14159265358979323846264338327950288L * k / q.P[a];
+      const long double pi = 3.14159265358979323846264338327950288L;
+      const long double ang = -2.0L * pi * k / q.P[a];
       t[k] = mk((double)cosl(ang), (double)sinl(ang));
       t32[k] = mk((float)cosl(ang), (float)sinl(ang));
+      // e^{i a} - 1 = -2 sin(a/2)^2 + i sin a: no cancellation at small k
+      const long double sh = sinl(pi * k / q.P[a]);
+      const long double dr = -2.0L * sh * sh / r->h, di = -sinl(ang) / r->h;
+      d[k] = mk((double)dr, (double)di);
+      d32[k] = mk((float)dr, (float)di);
     }
     chk(hipMemcpy(r->tw[a], t.data(), q.P[a] * sizeof(c64), hipMemcpyHostToDevice));
     chk(hipMemcpy(r->tw32[a], t32.data(), q.P[a] * sizeof(c32), hipMemcpyHostToDevice));
+    chk(hipMemcpy(r->df[a], d.data(), q.P[a] * sizeof(c64), hipMemcpyHostToDevice));
+    chk(hipMemcpy(r->df32[a], d32.data(), q.P[a] * sizeof(c32), hipMemcpyHostToDevice));
   }
   chk(hipMemcpy(r->alpha, alpha.data(), 3 * m * sizeof(double), hipMemcpyHostToDevice));
   chk(hipMemcpy(r->chif, chif.data(), 3 * m * sizeof(double), hipMemcpyHostToDevice));
@@ -696,13 +907,14 @@ extern "C" int vie_rt_setup(const vie_body* body, double k0, vie_rt** out) {
   cube_green_integral(k0, r->h, &s_re, &s_im);
   const void* tw[3] = {r->tw[0], r->tw[1], r->tw[2]};
   if (e == hipSuccess) {
-    k_rt_green<<<blocks_for(M), kRtThreads, 0, r->stream>>>(r->work, q, r->h, k0, s_re, s_im);
+    k_rt_green<<<blocks_for(M), kRtThreads, 0, r->stream>>>(work.as<c64>(), q, r->h, k0, s_re,
+                                                            s_im);
     chk(hipGetLastError());
   }
-  if (e == hipSuccess) chk(launch_fft3d_full(r->work, r->tmp, r->g, tw, r->stream));
+  if (e == hipSuccess) chk(launch_fft3d_full(work.as<c64>(), tmp.as<c64>(), r->g, tw, r->stream));
   if (e == hipSuccess) {
-    k_rt_octant<<<blocks_for(noct), kRtThreads, 0, r->stream>>>(r->tmp, r->ghat, r->ghat32, q,
-                                                                   1.0 / (double)M);
+    k_rt_octant<<<blocks_for(noct), kRtThreads, 0, r->stream>>>(tmp.as<c64>(), r->ghat,
+                                                                r->ghat32, q, 1.0 / (double)M);
     chk(hipGetLastError());
   }
   if (e == hipSuccess) chk(hipStreamSynchronize(r->stream));
@@ -711,10 +923,6 @@ extern "C" int vie_rt_setup(const vie_body* body, double k0, vie_rt** out) {
     delete r;
     return VIE_EDEVICE;
   }
-  // the full circulant buffers serve the spectrum only
-  (void)hipFree(r->work);
-  (void)hipFree(r->tmp);
-  r->work = r->tmp = nullptr;
   *out = r;
   return VIE_OK;
 }
@@ -734,13 +942,171 @@ extern "C" int vie_rt_matvec(vie_rt* r, const vie_c64* x, vie_c64* y, int32_t nv
     return VIE_EINVAL;
   if (r->poisoned) return VIE_ESTATE;
   const int64_t n = 3 * r->q.m;
+  RT_ALLOC(rt_ensure(r, 1));
+  RT_ALLOC(r->vecs.reserve((size_t)2 * n * sizeof(c64)));
+  c64 *dx = r->vecs.as<c64>(), *dy = dx + n;
   for (int v = 0; v < nvec; ++v) {
-    RT_HIP(hipMemcpyAsync(r->vec[0], x + v * n, n * sizeof(c64), hipMemcpyHostToDevice,
-                          r->stream));
-    RT_TRY(rt_apply(r, r->vec[0], r->vec[1], precision == VIE_MIXED));
-    RT_HIP(hipMemcpyAsync(y + v * n, r->vec[1], n * sizeof(c64), hipMemcpyDeviceToHost,
+    RT_HIP(hipMemcpyAsync(dx, x + v * n, n * sizeof(c64), hipMemcpyHostToDevice, r->stream));
+    RT_TRY(rt_apply(r, dx, dy, 1, precision == VIE_MIXED));
+    RT_HIP(hipMemcpyAsync(y + v * n, dy, n * sizeof(c64), hipMemcpyDeviceToHost, r->stream));
+    RT_HIP(hipStreamSynchronize(r->stream));
+  }
+  return VIE_OK;
+}
+
+// Solves nc channels as one batch (host driver of the iteration): chunks of
+// iterations run on the device, the host looks at the scalars once per chunk
+// and, for every vector whose cycle ended, takes the true residual and
+// restarts it from there unless it converged, hit the cap or took no step.
+static int rt_solve_batch(vie_rt* r, const vie_planewave* inc, int nc, double tol, int max_iter,
+                          bool mixed, vie_c64* w, vie_stats* stats, bool* all) {
+  constexpr double kInnerTol = 1e-3;  // residual reduction per refinement cycle (mixed)
+  constexpr int kChunk = 8;
+  const RtGeom& q = r->q;
+  const int64_t n = 3 * q.m;
+  const auto t0 = std::chrono::steady_clock::now();
+  RT_ALLOC(rt_ensure(r, nc));
+  RT_ALLOC(r->vecs.reserve((size_t)8 * nc * n * sizeof(c64)));
+  RT_ALLOC(r->scal.reserve(nc * sizeof(RtScal)));
+  RT_ALLOC(r->active.reserve(nc * sizeof(int)));
+  RT_ALLOC(r->mark.reserve(nc * sizeof(int)));
+  RT_ALLOC(r->wave.reserve(nc * sizeof(RtWave)));
+  RT_ALLOC(r->total.reserve(nc * sizeof(double)));
+  c64* vec[8];
+  for (int k = 0; k < 8; ++k) vec[k] = r->vecs.as<c64>() + (int64_t)k * nc * n;
+  c64 *x = vec[0], *b = vec[1], *rr = vec[2], *rh = vec[3], *p = vec[4], *v = vec[5], *s = vec[6],
+      *t = vec[7];
+  RtScal* sc = r->scal.as<RtScal>();
+  int* active = r->active.as<int>();
+  int* mark = r->mark.as<int>();
+  c64 *pr = r->part[0].as<c64>(), *pv = r->part[1].as<c64>(), *pt = r->part[2].as<c64>();
+  const int vb = vec_blocks(n);
+  const int bi64 = xinv_blocks<double>(q), bi = mixed ? xinv_blocks<float>(q) : bi64;
+  // a product's partials: folded first when every consumer would sum many
+  auto fold = [&](c64* part, int& np, const int* act) -> c64* {
+    if (np <= 512) return part;
+    k_rt_fold<<<kRtFold * nc, 64, 0, r->stream>>>(part, np, r->fold.as<c64>(), act);
+    np = kRtFold;
+    return r->fold.as<c64>();
+  };
+  std::vector<RtWave> hw(nc);
+  for (int k = 0; k < nc; ++k)
+    for (int a = 0; a < 3; ++a) {
+      hw[k].k[a] = inc[k].khat[a];
+      hw[k].p[a] = mk(inc[k].pol[a].re, inc[k].pol[a].im);
+    }
+  RT_HIP(hipMemcpyAsync(r->wave.p, hw.data(), nc * sizeof(RtWave), hipMemcpyHostToDevice,
+                        r->stream));
+  k_rt_rhs<<<vb * nc, kRtThreads, 0, r->stream>>>(b, x, rr, rh, p, v, r->chif, q, r->h,
+                                                  r->origin[0], r->origin[1], r->origin[2], r->k0,
+                                                  r->wave.as<RtWave>(), vb, pr);
+  k_rt_total<<<nc, kRtThreads, 0, r->stream>>>(pr, vb, r->total.as<double>(), nullptr);
+  RT_HIP(hipGetLastError());
+  std::vector<double> bb(nc), r2(nc);
+  RT_HIP(hipMemcpyAsync(bb.data(), r->total.p, nc * sizeof(double), hipMemcpyDeviceToHost,
+                        r->stream));
+  RT_HIP(hipStreamSynchronize(r->stream));
+  std::vector<RtScal> hs(nc);
+  std::vector<int> run(nc), mk_(nc), it0(nc, 0);
+  std::vector<vie_stats> st(nc);
+  // the cycle's target: tol ||b||, and for a mixed solve no deeper than
+  // kInnerTol times its starting residual (the FP32 products' accuracy)
+  auto start_cycle = [&](int k, double r0, int it) {
+    RtScal S;
+    S.rho = S.rho1 = S.alpha = S.omega = mk(1.0, 0.0);
+    S.tol2 = tol * tol * bb[k];
+    if (mixed) S.tol2 = std::max(S.tol2, kInnerTol * kInnerTol * r0);
+    S.it = it0[k] = it;
+    S.max_it = max_iter;
+    S.stop = 0;
+    hs[k] = S;
+    run[k] = 1;
+    ++st[k].cycles;
+  };
+  for (int k = 0; k < nc; ++k) {
+    st[k] = vie_stats{};
+    st[k].rel_res_x0 = 1.0;
+    st[k].rel_res = bb[k] > 0 ? 1.0 : 0.0;
+    run[k] = 0;
+    if (bb[k] > 0)
+      start_cycle(k, bb[k], 0);
+    else
+      st[k].converged = 1;
+  }
+  auto any = [&]() { return std::find(run.begin(), run.end(), 1) != run.end(); };
+  bool fresh = true;  // hs and run are newer than the device's copies
+  while (any()) {
+    if (fresh) {
+      RT_HIP(hipMemcpyAsync(sc, hs.data(), nc * sizeof(RtScal), hipMemcpyHostToDevice, r->stream));
+      RT_HIP(hipMemcpyAsync(active, run.data(), nc * sizeof(int), hipMemcpyHostToDevice,
+                            r->stream));
+      fresh = false;
+    }
+    for (int j = 0; j < kChunk; ++j) {
+      k_rt_pupd<<<vb * nc, kRtThreads, 0, r->stream>>>(p, rr, v, sc, active, n, vb, pr, vb);
+      RT_TRY(rt_apply(r, p, v, nc, mixed, kEpiRhv, rh, pv, active));
+      int np = bi;
+      const c64* fv = fold(pv, np, active);
+      k_rt_supd<<<vb * nc, kRtThreads, 0, r->stream>>>(s, rr, v, sc, active, n, vb, fv, np);
+      RT_TRY(rt_apply(r, s, t, nc, mixed, kEpiTs, nullptr, pt, active));
+      np = bi;
+      const c64* ft = fold(pt, np, active);
+      k_rt_xrupd<<<vb * nc, kRtThreads, 0, r->stream>>>(x, rr, p, s, t, rh, sc, active, n, vb, ft,
+                                                        np, pr);
+      RT_HIP(hipGetLastError());
+    }
+    RT_HIP(hipMemcpyAsync(hs.data(), sc, nc * sizeof(RtScal), hipMemcpyDeviceToHost, r->stream));
+    RT_HIP(hipStreamSynchronize(r->stream));
+    bool ended = false;
+    for (int k = 0; k < nc; ++k) {
+      mk_[k] = run[k] && hs[k].stop != 0;
+      ended |= mk_[k] != 0;
+    }
+    if (!ended) continue;
+    // the true residual decides
+    RT_HIP(hipMemcpyAsync(mark, mk_.data(), nc * sizeof(int), hipMemcpyHostToDevice, r->stream));
+    RT_TRY(rt_apply(r, x, t, nc, false, kEpiRes, b, pt, mark));
+    int np = bi64;
+    const c64* ft = fold(pt, np, mark);
+    k_rt_total<<<nc, kRtThreads, 0, r->stream>>>(ft, np, r->total.as<double>(), mark);
+    RT_HIP(hipGetLastError());
+    RT_HIP(hipMemcpyAsync(r2.data(), r->total.p, nc * sizeof(double), hipMemcpyDeviceToHost,
                           r->stream));
     RT_HIP(hipStreamSynchronize(r->stream));
+    bool again = false;
+    for (int k = 0; k < nc; ++k) {
+      if (!mk_[k]) continue;
+      const int it = hs[k].it;
+      st[k].iters = it;
+      st[k].matvecs += 2 * (it - it0[k]) + 1;
+      st[k].rel_res = sqrt(r2[k]) / sqrt(bb[k]);
+      st[k].converged = st[k].rel_res <= tol ? 1 : 0;
+      run[k] = 0;
+      if (st[k].converged)
+        st[k].seconds =
+            std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+      // the cap, or a cycle that could not take a single step, ends the solve
+      if (st[k].converged || hs[k].stop == 3 || it == it0[k] || it >= max_iter) {
+        mk_[k] = 0;
+      } else {
+        start_cycle(k, r2[k], it);
+        again = true;
+      }
+    }
+    if (again) {
+      // the running vectors' scalars go back as they came
+      RT_HIP(hipMemcpyAsync(mark, mk_.data(), nc * sizeof(int), hipMemcpyHostToDevice, r->stream));
+      k_rt_restart<<<vb * nc, kRtThreads, 0, r->stream>>>(t, rr, rh, p, v, n, vb, pr, mark);
+      RT_HIP(hipGetLastError());
+      RT_HIP(hipStreamSynchronize(r->stream));  // mk_ is reused
+      fresh = true;
+    }
+  }
+  RT_HIP(hipMemcpyAsync(w, x, (size_t)nc * n * sizeof(c64), hipMemcpyDeviceToHost, r->stream));
+  RT_HIP(hipStreamSynchronize(r->stream));
+  for (int k = 0; k < nc; ++k) {
+    if (stats) stats[k] = st[k];
+    *all &= st[k].converged != 0;
   }
   return VIE_OK;
 }
@@ -751,117 +1117,22 @@ extern "C" int vie_rt_solve(vie_rt* r, const vie_planewave* inc, int32_t nrhs, d
   if (!r || !inc || !w || nrhs < 1 || !(tol > 0) || !(tol < 1) || max_iter < 1 ||
       (precision != VIE_FP64 && precision != VIE_MIXED))
     return VIE_EINVAL;
-  const bool mixed = precision == VIE_MIXED;
-  constexpr double kInnerTol = 1e-3;  // residual reduction per refinement cycle (mixed)
   if (r->poisoned) return VIE_ESTATE;
   for (int k = 0; k < nrhs; ++k)
     for (int a = 0; a < 3; ++a)
       if (!std::isfinite(inc[k].khat[a]) || !std::isfinite(inc[k].pol[a].re) ||
           !std::isfinite(inc[k].pol[a].im))
         return VIE_EINVAL;
+  // channels per batch: 1 GB of transform scratch
   const RtGeom& q = r->q;
-  const int64_t n = 3 * q.m;
-  c64 *x = r->vec[0], *b = r->vec[1], *rr = r->vec[2], *rh = r->vec[3], *p = r->vec[4],
-      *v = r->vec[5], *s = r->vec[6], *t = r->vec[7];
-  const c64 zero = mk(0.0, 0.0);
-  int status = VIE_OK;
-  for (int k = 0; k < nrhs; ++k) {
-    const auto t0 = std::chrono::steady_clock::now();
-    const vie_planewave& pw = inc[k];
-    k_rt_rhs<<<blocks_for(n), kRtThreads, 0, r->stream>>>(
-        b, r->chif, q, r->h, r->origin[0], r->origin[1], r->origin[2], r->k0, pw.khat[0],
-        pw.khat[1], pw.khat[2], mk(pw.pol[0].re, pw.pol[0].im), mk(pw.pol[1].re, pw.pol[1].im),
-        mk(pw.pol[2].re, pw.pol[2].im));
-    RT_HIP(hipGetLastError());
-    RT_HIP(hipMemsetAsync(x, 0, n * sizeof(c64), r->stream));
-    c64 bb;
-    RT_TRY(rt_dot(r, b, b, n, &bb));
-    const double bnorm = sqrt(bb.re);
-    vie_stats st{};
-    st.rel_res_x0 = 1.0;
-    st.cycles = 0;
-    double rel = bnorm > 0 ? 1.0 : 0.0;
-    int it = 0, mv = 0;
-    bool conv = bnorm == 0.0;
-    while (!conv && it < max_iter) {
-      // (re)start from the true residual
-      if (st.cycles > 0) {
-        RT_TRY(rt_apply(r, x, t));
-        ++mv;
-        RT_TRY(rt_lin(r, rr, b, mk(-1.0, 0.0), t, zero, nullptr, n));
-      } else {
-        RT_HIP(hipMemcpyAsync(rr, b, n * sizeof(c64), hipMemcpyDeviceToDevice, r->stream));
-      }
-      ++st.cycles;
-      RT_HIP(hipMemcpyAsync(rh, rr, n * sizeof(c64), hipMemcpyDeviceToDevice, r->stream));
-      RT_HIP(hipMemsetAsync(p, 0, n * sizeof(c64), r->stream));
-      RT_HIP(hipMemsetAsync(v, 0, n * sizeof(c64), r->stream));
-      // the cycle's target: tol ||b||, and for a mixed solve no deeper than
-      // kInnerTol times its starting residual (the FP32 products' accuracy)
-      double tol2 = tol * tol * bb.re;
-      if (mixed) {
-        c64 r0;
-        RT_TRY(rt_dot(r, rr, rr, n, &r0));
-        tol2 = std::max(tol2, kInnerTol * kInnerTol * r0.re);
-      }
-      k_rt_sinit<<<1, 1, 0, r->stream>>>(r->sc, tol2, it, max_iter);
-      RT_HIP(hipGetLastError());
-      // iterations run in chunks with the scalars on the device; the host
-      // looks at them once per chunk (iterations after a stop are no-ops)
-      constexpr int kChunk = 8;
-      const int it0 = it;
-      RtScal S{};
-      for (;;) {
-        for (int j = 0; j < kChunk; ++j) {
-          k_rt_dot<<<kRtDotBlocks, kRtThreads, 0, r->stream>>>(rh, rr, n, r->part);
-          k_rt_scal<<<1, kRtThreads, 0, r->stream>>>(r->part, r->sc, kScRho);
-          k_rt_pupd<<<blocks_for(n), kRtThreads, 0, r->stream>>>(p, rr, v, r->sc, n);
-          RT_HIP(hipGetLastError());
-          RT_TRY(rt_apply(r, p, v, mixed));
-          k_rt_dot<<<kRtDotBlocks, kRtThreads, 0, r->stream>>>(rh, v, n, r->part);
-          k_rt_scal<<<1, kRtThreads, 0, r->stream>>>(r->part, r->sc, kScAlpha);
-          k_rt_supd<<<blocks_for(n), kRtThreads, 0, r->stream>>>(s, rr, v, r->sc, n);
-          RT_HIP(hipGetLastError());
-          RT_TRY(rt_apply(r, s, t, mixed));
-          k_rt_dot<<<kRtDotBlocks, kRtThreads, 0, r->stream>>>(t, s, n, r->part);
-          k_rt_dot<<<kRtDotBlocks, kRtThreads, 0, r->stream>>>(t, t, n, r->part + kRtDotBlocks);
-          k_rt_scal<<<1, kRtThreads, 0, r->stream>>>(r->part, r->sc, kScOmega);
-          k_rt_xrupd<<<blocks_for(n), kRtThreads, 0, r->stream>>>(x, rr, p, s, t, r->sc, n);
-          k_rt_dot<<<kRtDotBlocks, kRtThreads, 0, r->stream>>>(rr, rr, n, r->part);
-          k_rt_scal<<<1, kRtThreads, 0, r->stream>>>(r->part, r->sc, kScRes);
-          RT_HIP(hipGetLastError());
-        }
-        RT_HIP(hipMemcpyAsync(&S, r->sc, sizeof(RtScal), hipMemcpyDeviceToHost, r->stream));
-        RT_HIP(hipStreamSynchronize(r->stream));
-        if (S.stop) break;
-      }
-      it = S.it;
-      mv += 2 * (it - it0);
-      // true residual decides
-      RT_TRY(rt_apply(r, x, t));
-      ++mv;
-      RT_TRY(rt_lin(r, t, b, mk(-1.0, 0.0), t, zero, nullptr, n));
-      c64 r2;
-      RT_TRY(rt_dot(r, t, t, n, &r2));
-      rel = sqrt(r2.re) / bnorm;
-      conv = rel <= tol;
-      // the cap, or a cycle that could not take a single step, ends the solve;
-      // otherwise restart from the true residual
-      if (S.stop == 3 || it == it0) break;
-    }
-    RT_HIP(hipMemcpyAsync(w + k * n, x, n * sizeof(c64), hipMemcpyDeviceToHost, r->stream));
-    RT_HIP(hipStreamSynchronize(r->stream));
-    const double sec =
-        std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-    st.iters = it;
-    st.matvecs = mv;
-    st.converged = conv ? 1 : 0;
-    st.rel_res = rel;
-    st.seconds = conv ? sec : 0.0;
-    if (stats) stats[k] = st;
-    if (!conv) status = VIE_ENOCONV;
-  }
-  return status;
+  const int64_t one = (int64_t)kRtFields * q.E[2] * q.P[1] * q.P[0] * sizeof(c64);
+  const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(nrhs, ((int64_t)1 << 30) / one));
+  bool all = true;
+  for (int k = 0; k < nrhs; k += nb)
+    RT_TRY(rt_solve_batch(r, inc + k, std::min(nb, nrhs - k), tol, max_iter,
+                          precision == VIE_MIXED, w + k * 3 * q.m, stats ? stats + k : nullptr,
+                          &all));
+  return all ? VIE_OK : VIE_ENOCONV;
 }
 
 extern "C" int vie_rt_farfield(vie_rt* r, const vie_c64* w, int32_t nrhs, const double* theta,

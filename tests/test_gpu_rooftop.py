@@ -314,3 +314,53 @@ def test_farfield_matches_oracle_sum(V, n, ntheta, nphi):
             assert np.linalg.norm(F[q][some] - ref) <= 1e-12 * np.linalg.norm(ref)
     finally:
         V.vie_rt_destroy(h)
+
+
+@pytest.mark.parametrize("prec,tol", [(0, 1e-11), (1, 1e-10)])
+def test_batched_channels_match_lu(V, prec, tol):
+    """Three channels of one body advance as one batch, each with its own
+    cycles (mixed: several) and its own end, against the oracle's LU solution
+    (bar: the condition number of this body is below 1e2, so 1e3 tol); a dark
+    channel (zero polarisation) has the zero solution; the products counted
+    are two per iteration and one residual per cycle."""
+    name, g, chi, k0 = next(b for b in _bodies() if b[0] == "two_material")
+    chans = [([0, 0, 1], [1, 0, 0]), ([1, 0, 0], [0, 1j, 0.5]), ([0, 1, 0], [0, 0, 0]),
+             ([0, -1, 0], [0.3, 0, 1])]
+    h = V.vie_rt_setup(chi + 1, g.h, g.origin, k0)
+    try:
+        rc, w, st = V.vie_rt_solve(h, chans, tol=tol, max_iter=4000, precision=prec)
+        assert rc == V.VIE_OK
+        for (k, p), x, s in zip(chans, w, st):
+            assert s["converged"] and s["rel_res"] <= tol
+            assert s["matvecs"] == 2 * s["iters"] + s["cycles"]
+            ref = rt.solve_lu(chi, g.h, g.origin, k0, np.array(k, float), np.array(p, complex))
+            assert np.linalg.norm(x.reshape(3, -1) - ref) <= 1e3 * tol * np.linalg.norm(ref)
+        assert prec == 0 or st[0]["cycles"] > 1
+        assert not np.any(w[2])
+    finally:
+        V.vie_rt_destroy(h)
+
+
+def test_batches_of_channels_equal_single_channels(V):
+    """More channels than one batch holds (47 MB of scratch each, 1 GB a
+    batch), on a grid whose last pass leaves more partial sums than a vector
+    kernel folds: every channel's iterate after three iterations equals the
+    one it has alone, bit for bit (fixed reduction orders)."""
+    g = Grid.centred((128, 128, 3), 1.0 / 32)
+    rng = np.random.default_rng(5)
+    eps = np.where(rng.random((3, 128, 128)) < 0.5, 2.25, 1.0)
+    chans = []
+    for _ in range(23):
+        k = rng.standard_normal(3)
+        k /= np.linalg.norm(k)
+        p = np.cross(k, rng.standard_normal(3))
+        chans.append((k, p / np.linalg.norm(p)))
+    h = V.vie_rt_setup(eps, g.h, g.origin, K0)
+    try:
+        _, w, st = V.vie_rt_solve(h, chans, tol=1e-12, max_iter=3, allow_noconv=True)
+        assert all(s["iters"] == 3 for s in st)
+        for q in (0, 11, 21, 22):
+            _, one, _ = V.vie_rt_solve(h, [chans[q]], tol=1e-12, max_iter=3, allow_noconv=True)
+            assert np.any(one) and np.array_equal(one[0], w[q])
+    finally:
+        V.vie_rt_destroy(h)
