@@ -108,7 +108,8 @@ struct Group {
   bool samples_ready = false;            // r = b and v = A b hold for every rhs
   DevBuf bufA, bufB;             // FFT scratch (sized for FP64)
   DevBuf boxX, boxY;             // compute-window copies of box-layout product vectors
-  DevBuf partials;               // c64 [cap][maxblk][2]
+  DevBuf partials;               // c64 [3][cap][maxblk][2]
+  int maxblk = 1;
   DevBuf state;                  // KState [cap]
   DevBuf flags;                  // int [2][cap]
   DevBuf rhs_body, pol, ph;      // per right-hand side
@@ -703,9 +704,10 @@ static int ensure_solve_storage(vie_ctx* ctx, Group& G, int nrhs) {
   const size_t bb = (size_t)bufB_elems(G.g) * sizeof(c64);
   VIE_HIP(G.bufA.reserve(a * nrhs));
   VIE_HIP(G.bufB.reserve(bb * nrhs));
-  const int maxblk = std::max(std::max(part_blocks_xinv(G.g, 0), part_blocks_xinv(G.g, 1)),
+  const int maxblk = std::max(std::max(part_blocks_product(G.g, 0), part_blocks_product(G.g, 1)),
                               vec_blocks_group(G));
-  VIE_HIP(G.partials.reserve((size_t)nrhs * maxblk * 2 * sizeof(c64)));
+  G.maxblk = maxblk;
+  VIE_HIP(G.partials.reserve((size_t)3 * nrhs * maxblk * 2 * sizeof(c64)));
   VIE_HIP(G.state.reserve((size_t)nrhs * sizeof(KState)));
   VIE_HIP(G.flags.reserve((size_t)3 * nrhs * sizeof(int)));  // active, not done, pending
   VIE_HIP(G.rhs_body.reserve((size_t)nrhs * sizeof(int)));
@@ -733,8 +735,7 @@ static MatvecArgs matvec_args(Group& G, int precision, const int* active) {
   MatvecArgs m;
   m.zvar = G.zvar[precision] < 0 ? 0 : G.zvar[precision];
   m.g = &G.g;
-  m.chi = G.chi.as<double>();
-  m.rhs_body = G.rhs_body.as<int>();
+  m.chi = nullptr;
   m.spec = precision == 0 ? G.spec64.p : G.spec32.p;
   for (int a = 0; a < 3; ++a) m.tw[a] = precision == 0 ? G.tw64[a].p : G.tw32[a].p;
   if (precision == 1 && G.zh) {
@@ -856,14 +857,20 @@ static hipError_t tune_z(vie_ctx* ctx, Group& G, int precision) {
 }
 
 // x, y: c64 vectors, or c32 with io32 (FP32 product, compressed, plain).
+// box_chi: box vectors of the body with this chi instead of compressed ones.
+// upd: x is the result of this update, made by the product's first pass.
 static hipError_t run_matvec(vie_ctx* ctx, Group& G, int precision, const void* x, void* y,
-                             EpiArgs& e, const int* active, bool compressed = true,
-                             int io32 = 0) {
+                             EpiArgs& e, const int* active, const double* box_chi = nullptr,
+                             int io32 = 0, const UpdArgs* upd = nullptr) {
   hipError_t te = tune_z(ctx, G, precision);
   if (te != hipSuccess) return te;
   MatvecArgs m = matvec_args(G, precision, active);
-  if (compressed) m.bi = &G.bi;
+  if (box_chi)
+    m.chi = box_chi;
+  else
+    m.bi = &G.bi;
   m.io32 = io32;
+  m.upd = upd;
   return launch_matvec(m, precision, x, y, e, ctx->stream, timing_on(ctx) ? timing_cb : nullptr,
                        ctx);
 }
@@ -1043,6 +1050,10 @@ static int warm_start_init(vie_ctx* ctx, Group& G, const FinParams& fp,
   return VIE_OK;
 }
 
+// Circulant points of all right-hand sides up to which solve_group reads the
+// flags of every chunk before it queues the next one.
+static constexpr int64_t kLagPoints = (int64_t)1 << 20;
+
 static int solve_group(vie_ctx* ctx, Group& G, bool warm, std::vector<int>& fallback_out) {
   TraceRange trace_("solve_group");
   const GroupGeom& g = G.g;
@@ -1056,7 +1067,10 @@ static int solve_group(vie_ctx* ctx, Group& G, bool warm, std::vector<int>& fall
   KState* st = G.state.as<KState>();
   int* flags = G.flags.as<int>();
   int* active = flags;
+  // dot partials of the products v and t and of the residual update
   c64* part = G.partials.as<c64>();
+  c64* tpart = part + (int64_t)nrhs * G.maxblk * 2;
+  c64* rpart = tpart + (int64_t)nrhs * G.maxblk * 2;
   const int vb = vec_blocks_group(G);
   const BodyIdx& bi = G.bi;
   c64 *x = G.x.as<c64>(), *r = G.r.as<c64>(), *rh = G.rh.as<c64>(), *p = G.p.as<c64>(),
@@ -1082,38 +1096,57 @@ static int solve_group(vie_ctx* ctx, Group& G, bool warm, std::vector<int>& fall
   int rc = ensure_hflags(ctx, 3 * nrhs);
   if (rc != VIE_OK) return rc;
 
-  // one BiCGSTAB iteration for every active right-hand side
-  auto iteration = [&]() -> hipError_t {
+  // `iters` BiCGSTAB iterations for every active right-hand side.  The vector
+  // updates of p and s run inside the products' first passes; while a pass has
+  // at most kFoldMax partials to fold it also takes the scalar step that
+  // k_finalize would (3 launches of 16 fewer per iteration), except after the
+  // last iteration, whose decision must be in the flags the host reads.
+  const int npx = part_blocks_product(g, prec);
+  const bool fold_x = npx <= kFoldMax, fold_r = vb <= kFoldMax;
+  auto iteration = [&](int iters) -> hipError_t {
     hipError_t he;
-    if ((he = timed(ctx, 10, [&] {
-           return launch_update_p(g, bi, vb, st, active, r, p, v, ctx->stream);
-         })) != hipSuccess)
-      return he;
-    EpiArgs e1{EPI_RHV, rh, part, 0, pol, ph};
-    if ((he = run_matvec(ctx, G, prec, p, v, e1, active)) != hipSuccess) return he;
-    if ((he = timed(ctx, 11, [&] {
-           return launch_finalize(FIN_ALPHA, nrhs, e1.part_blocks, part, st, flags, fp,
-                                  ctx->stream);
-         })) != hipSuccess)
-      return he;
-    if ((he = timed(ctx, 10, [&] {
-           return launch_update_s(g, bi, vb, st, active, r, v, s, ctx->stream);
-         })) != hipSuccess)
-      return he;
-    EpiArgs e2{EPI_TS, nullptr, part, 0, pol, ph};
-    if ((he = run_matvec(ctx, G, prec, s, t, e2, active)) != hipSuccess) return he;
-    if ((he = timed(ctx, 11, [&] {
-           return launch_finalize(FIN_OMEGA, nrhs, e2.part_blocks, part, st, flags, fp,
-                                  ctx->stream);
-         })) != hipSuccess)
-      return he;
-    if ((he = timed(ctx, 10, [&] {
-           return launch_update_xr(g, bi, vb, st, active, x, r, p, s, t, rh, part, ctx->stream);
-         })) != hipSuccess)
-      return he;
-    return timed(ctx, 11, [&] {
-      return launch_finalize(FIN_RHO, nrhs, vb, part, st, flags, fp, ctx->stream);
-    });
+    UpdArgs u;
+    u.st = st;
+    u.flags = flags;
+    u.nrhs = nrhs;
+    u.max_iter = fp.max_iter;
+    u.r = r;
+    u.v = v;
+    for (int i = 0; i < iters; ++i) {
+      u.mode = UPD_P;
+      u.part = rpart;
+      u.npart = fold_r && i > 0 ? vb : 0;
+      u.out = p;
+      EpiArgs e1{EPI_RHV, rh, part, 0, pol, ph};
+      if ((he = run_matvec(ctx, G, prec, p, v, e1, active, nullptr, 0, &u)) != hipSuccess) return he;
+      if (!fold_x && (he = timed(ctx, 11, [&] {
+                        return launch_finalize(FIN_ALPHA, nrhs, npx, part, st, flags, fp,
+                                               ctx->stream);
+                      })) != hipSuccess)
+        return he;
+      u.mode = UPD_S;
+      u.part = part;
+      u.npart = fold_x ? npx : 0;
+      u.out = s;
+      EpiArgs e2{EPI_TS, nullptr, tpart, 0, pol, ph};
+      if ((he = run_matvec(ctx, G, prec, s, t, e2, active, nullptr, 0, &u)) != hipSuccess) return he;
+      if (!fold_x && (he = timed(ctx, 11, [&] {
+                        return launch_finalize(FIN_OMEGA, nrhs, npx, tpart, st, flags, fp,
+                                               ctx->stream);
+                      })) != hipSuccess)
+        return he;
+      if ((he = timed(ctx, 10, [&] {
+             return launch_update_xr(g, bi, vb, st, active, x, r, p, s, t, rh, tpart,
+                                     fold_x ? npx : 0, rpart, ctx->stream);
+           })) != hipSuccess)
+        return he;
+      if ((!fold_r || i + 1 == iters) && (he = timed(ctx, 11, [&] {
+                                            return launch_finalize(FIN_RHO, nrhs, vb, rpart, st,
+                                                                   flags, fp, ctx->stream);
+                                          })) != hipSuccess)
+        return he;
+    }
+    return hipSuccess;
   };
   // Graph mode: capture VIE_GRAPH_ITERS iterations once and replay them.  Every
   // launch reads its scalars from device state and skips inactive right-hand
@@ -1141,7 +1174,7 @@ static int solve_group(vie_ctx* ctx, Group& G, bool warm, std::vector<int>& fall
       hipGraph_t graph = nullptr;
       VIE_HIP(hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
       hipError_t ce = hipSuccess;
-      for (int i = 0; i < VIE_GRAPH_ITERS && ce == hipSuccess; ++i) ce = iteration();
+      ce = iteration(VIE_GRAPH_ITERS);
       hipError_t ee = hipStreamEndCapture(ctx->stream, &graph);
       if (ce == hipSuccess) ce = ee;
       if (ce == hipSuccess) ce = hipGraphInstantiate(&G.iter_graph.exec, graph, nullptr, nullptr, 0);
@@ -1173,24 +1206,31 @@ static int solve_group(vie_ctx* ctx, Group& G, bool warm, std::vector<int>& fall
       return launch_finalize(FIN_PENDING, nrhs, e.part_blocks, part, st, flags, fp, ctx->stream);
     });
   };
+  // Short chunks are read at once: a wait costs the device some 15 us, a chunk
+  // queued past the end of the last cycle eight iterations of empty launches
+  // (about 120 us on 16^3 voxels, and it is paid again after a restart).
+  const bool lag = !use_graph || (int64_t)nrhs * g.P[0] * g.P[1] * g.P[2] > kLagPoints;
   for (int64_t k = 0;; ++k) {
     if (use_graph) {
       VIE_HIP(hipGraphLaunch(G.iter_graph.exec, ctx->stream));
     } else {
-      VIE_HIP(iteration());
+      VIE_HIP(iteration(1));
     }
     const int slot = (int)(k & 1);
     VIE_HIP(hipMemcpyAsync(ctx->hflags[slot], flags, 3 * nrhs * sizeof(int),
                            hipMemcpyDeviceToHost, ctx->stream));
     VIE_HIP(hipEventRecord(ctx->flag_ev[slot], ctx->stream));
-    if (!have_prev) {
+    if (!lag) {
+      restart_queued = false;  // what was queued came before this chunk
+      prev = slot;
+    } else if (!have_prev) {
       have_prev = true;
       prev = slot;
       continue;
     }
     const int* hf = ctx->hflags[prev];
     VIE_HIP(hipEventSynchronize(ctx->flag_ev[prev]));
-    prev = slot;
+    if (lag) prev = slot;
     bool any_active = false, any_pending = false;
     for (int i = 0; i < nrhs; ++i) {
       any_active |= hf[i] != 0;
@@ -1759,7 +1799,7 @@ static int bj_apply(vie_ctx* ctx, BlockPrec& P, const vie_fgmres_options* fo, co
       VIE_HIP(run_matvec_nrm(sub, Gp, A.w.p, A.w.p, A.at(A.V, j, tot), A.npart.as<double>(),
                              S.nblk, NR + j, ldn, A.act.as<int>()));
     else
-      VIE_HIP(run_matvec(sub, Gp, ip, A.at(A.V, j, tot), A.w.p, e, A.act.as<int>(), true, A.v32));
+      VIE_HIP(run_matvec(sub, Gp, ip, A.at(A.V, j, tot), A.w.p, e, A.act.as<int>(), nullptr, A.v32));
     VIE_HIP(timed(ctx, kArnoldiKind,
                   [&] { return arnoldi_orth(ctx, A, S, tot, k, j, eta2, nrm_in); }));
   }
@@ -1959,7 +1999,7 @@ static int fgmres_group(vie_ctx* ctx, Group& G, BlockPrec* P, const vie_fgmres_o
     }
     // mixed: the FP32 product reads z_j and writes w in FP32
     EpiArgs e{EPI_PLAIN, nullptr, nullptr, 0, nullptr, nullptr};
-    VIE_HIP(run_matvec(ctx, G, prec, zj, A.w.p, e, A.act.as<int>(), true, A.v32));
+    VIE_HIP(run_matvec(ctx, G, prec, zj, A.w.p, e, A.act.as<int>(), nullptr, A.v32));
     VIE_HIP(timed(ctx, kArnoldiKind, [&] { return arnoldi_orth(ctx, A, S, tot, m, j, eta2); }));
     VIE_HIP(launch_ls_step(nrhs, j, A.H1.as<c64>(), A.H2.as<c64>(), eta2 > 0 ? 1 : 0, m + 1, NR,
                            m + 1, st, half_tol, A.act.as<int>(), steps, mc, L, anyf,
@@ -2226,9 +2266,6 @@ extern "C" int vie_matvec_dev(vie_ctx* ctx, int32_t body, int32_t precision, con
     G.g.nrhs = saved;
     return rc;
   }
-  std::vector<int> rb(nvec, B.slot);
-  VIE_HIP(hipMemcpyAsync(G.rhs_body.p, rb.data(), nvec * sizeof(int), hipMemcpyHostToDevice,
-                         ctx->stream));
   // Box vectors come in the bodies' grid; the product runs on the compute
   // window.  Outside the window chi = 0, so there y = x.
   const bool window = G.g.n != G.n0;
@@ -2250,7 +2287,8 @@ extern "C" int vie_matvec_dev(vie_ctx* ctx, int32_t body, int32_t precision, con
     ys = G.boxY.as<c64>();
   }
   EpiArgs e{EPI_PLAIN, nullptr, nullptr, 0, nullptr, nullptr};
-  hipError_t err = run_matvec(ctx, G, precision == VIE_MIXED ? 1 : 0, xs, ys, e, nullptr, false);
+  hipError_t err = run_matvec(ctx, G, precision == VIE_MIXED ? 1 : 0, xs, ys, e, nullptr,
+                              G.chi.as<double>() + (int64_t)B.slot * G.g.n);
   G.g.nrhs = saved;
   VIE_HIP(err);
   if (window) {
@@ -2265,11 +2303,10 @@ extern "C" int vie_matvec_dev(vie_ctx* ctx, int32_t body, int32_t precision, con
 }
 
 // The product of vie_matvec_dev with every scratch buffer (FFT work arrays,
-// the right-hand-side table, window copies) carved out of the static scratch
-// array instead of memory the context allocates: no allocation, no host
-// copy, no memset.  Layout, each part 256-byte aligned: bufA, bufB, the
-// body table, then the two window copies.  The z-pass shape is the one tuned
-// for this group if any, else the default.
+// window copies) carved out of the static scratch array instead of memory the
+// context allocates: no allocation, no host copy, no memset.  Layout, each part
+// 256-byte aligned: bufA, bufB, then the two window copies.  The z-pass shape
+// is the one tuned for this group if any, else the default.
 extern "C" int vie_matvec_dev_static(vie_ctx* ctx, int32_t body, int32_t precision,
                                      const void* x, void* y, int32_t nvec) {
   if (!ctx) return VIE_EINVAL;
@@ -2284,7 +2321,7 @@ extern "C" int vie_matvec_dev_static(vie_ctx* ctx, int32_t body, int32_t precisi
   auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
   const size_t a_b = al((size_t)nvec * 3 * G.g.N[2] * G.g.N[1] * G.g.P[0] * cb);
   const size_t b_b = al((size_t)nvec * (size_t)bufB_elems(G.g) * cb);
-  const size_t r_b = al((size_t)nvec * sizeof(int));
+  const size_t r_b = al((size_t)nvec * sizeof(int));  // in the documented size; unused
   const size_t w_b = window ? al((size_t)nvec * 3 * G.g.n * sizeof(c64)) : 0;
   const size_t need = a_b + b_b + r_b + 2 * w_b;
   if (need > (size_t)VIE_STATIC_SCRATCH_BYTES) {
@@ -2295,7 +2332,6 @@ extern "C" int vie_matvec_dev_static(vie_ctx* ctx, int32_t body, int32_t precisi
   }
   char* base = (char*)g_scratch_ptr[ctx->dev];
   if (!base) return VIE_ESTATE;  // the look-up at setup failed (vie_setup would have said so)
-  int* rb = (int*)(base + a_b + b_b);
   c64* boxX = (c64*)(base + a_b + b_b + r_b);
   c64* boxY = (c64*)(base + a_b + b_b + r_b + w_b);
   const int saved = G.g.nrhs;
@@ -2303,9 +2339,9 @@ extern "C" int vie_matvec_dev_static(vie_ctx* ctx, int32_t body, int32_t precisi
   MatvecArgs m = matvec_args(G, prec, nullptr);
   m.bufA = base;
   m.bufB = base + a_b;
-  m.rhs_body = rb;
+  m.chi = G.chi.as<double>() + (int64_t)B.slot * G.g.n;
   m.zvar = G.zvar[prec] >= 0 ? G.zvar[prec] : 0;
-  hipError_t err = launch_fill_int(rb, nvec, B.slot, ctx->stream);
+  hipError_t err = hipSuccess;
   const c64* xs = (const c64*)x;
   c64* ys = (c64*)y;
   const int64_t shift = (int64_t)G.g.N[0] * G.g.N[1] * B.zoff;

@@ -359,8 +359,7 @@ struct XinvArgs {
 template <typename T, int P, int MODE>
 __global__ __launch_bounds__(nt_lines_p<T>(P)) void k_fft_x_inv(
     const cpx<T>* __restrict__ A, const c64* __restrict__ xin, c64* __restrict__ yout,
-    const double* __restrict__ chi, const int* __restrict__ rhs_body,
-    const cpx<T>* __restrict__ tw, XinvArgs a, c64* __restrict__ aux, c64* __restrict__ partials,
+    const double* __restrict__ chi, const cpx<T>* __restrict__ tw, XinvArgs a, c64* __restrict__ aux, c64* __restrict__ partials,
     const c64* __restrict__ pol, const c64* __restrict__ ph, const int* __restrict__ active) {
   constexpr int E = fft_e<P>(), TT = P / E, NT = nt_lines_p<T>(P), L = NT / TT;
   __shared__ cpx<T> lds[L * Pad<P>::LSTR];
@@ -384,7 +383,7 @@ __global__ __launch_bounds__(nt_lines_p<T>(P)) void k_fft_x_inv(
   }
   line_fft<T, P, true, false, true>(v, lds + li * Pad<P>::LSTR, t, tr);  // only x < N1 kept
   const int comp = lc / a.lines_per_comp, sp = lc % a.lines_per_comp;  // sp = z*N2 + y
-  const double* chib = chi + (int64_t)rhs_body[rhs] * a.n + (int64_t)sp * a.N1;
+  const double* chib = chi + (int64_t)sp * a.N1;
   c64 s0 = mk(0.0, 0.0), s1 = mk(0.0, 0.0);
   c64 phyz = mk(0.0, 0.0), pc = mk(0.0, 0.0);
   if (MODE == EPI_RESID && valid) {
@@ -1380,7 +1379,8 @@ hipError_t launch_tw_h2(const void* tw32, void* tw16, int n, hipStream_t s) {
   return hipGetLastError();
 }
 
-int part_blocks_xinv(const GroupGeom& g, int precision) {
+int part_blocks_product(const GroupGeom& g, int precision) {
+  if (plane_ok(g)) return 3 * g.N[2];
   const int lines = 3 * g.N[1] * g.N[2];
   const int L = precision == 0 ? lines_per_block<double>(g.P[0]) : lines_per_block<float>(g.P[0]);
   return (lines + L - 1) / L;
@@ -1388,8 +1388,8 @@ int part_blocks_xinv(const GroupGeom& g, int precision) {
 
 template <typename T>
 static hipError_t x_inv(const GroupGeom& g, const cpx<T>* A, const c64* x, c64* y,
-                        const double* chi, const int* rhs_body, const cpx<T>* tw, EpiArgs& e,
-                        const int* active, hipStream_t s) {
+                        const double* chi, const cpx<T>* tw, EpiArgs& e, const int* active,
+                        hipStream_t s) {
   XinvArgs a;
   a.N1 = g.N[0];
   a.N2 = g.N[1];
@@ -1403,7 +1403,7 @@ static hipError_t x_inv(const GroupGeom& g, const cpx<T>* A, const c64* x, c64* 
   const dim3 grid(a.blocks_per_rhs * g.nrhs);
 #define VIE_XINV(MODE_)                                                                    \
   VIE_DISPATCH_P(g.P[0], (k_fft_x_inv<T, PP, MODE_><<<grid, nt_lines_p<T>(PP), 0, s>>>(       \
-                             A, x, y, chi, rhs_body, tw, a, e.aux, e.partials, e.pol, e.ph, \
+                             A, x, y, chi, tw, a, e.aux, e.partials, e.pol, e.ph,           \
                              active)))
   switch (e.mode) {
     case EPI_PLAIN: VIE_XINV(EPI_PLAIN); break;
@@ -1419,11 +1419,22 @@ static hipError_t x_inv(const GroupGeom& g, const cpx<T>* A, const c64* x, c64* 
 // hs > 0: packed FP16 lines on the scratch side (see the x passes)
 template <typename T>
 hipError_t x_fwd_c(const GroupGeom& g, const void* xc, int in32, cpx<T>* A, const cpx<T>* tw,
-                   const BodyIdx& bi, const int* active, hipStream_t s, float hs = 0.f);
+                   const BodyIdx& bi, const int* active, hipStream_t s, float hs = 0.f,
+                   const UpdArgs* upd = nullptr);
 template <typename T>
 hipError_t x_inv_c(const GroupGeom& g, const cpx<T>* A, const void* x, void* y, int io32,
                    const cpx<T>* tw, const BodyIdx& bi, EpiArgs& e, const int* active,
                    hipStream_t s, float hs = 0.f);
+
+// fused x-y passes of short lines (fft_plane.hip)
+template <typename T>
+hipError_t plane_fwd(const GroupGeom& g, const c64* x, cpx<T>* B, const cpx<T>* tw1,
+                     const cpx<T>* tw2, const BodyIdx* bi, const int* active, const UpdArgs* upd,
+                     hipStream_t s);
+template <typename T>
+hipError_t plane_inv(const GroupGeom& g, const cpx<T>* B, const c64* x, c64* y, const double* chi,
+                     const cpx<T>* tw1, const cpx<T>* tw2, const BodyIdx* bi, EpiArgs& e,
+                     const int* active, hipStream_t s);
 
 template <typename T>
 static hipError_t matvec_t(const MatvecArgs& m, const void* xv, void* yv, EpiArgs& e,
@@ -1472,8 +1483,15 @@ static hipError_t matvec_t(const MatvecArgs& m, const void* xv, void* yv, EpiArg
       return hipErrorInvalidValue;
     }
   }
+  if (m.upd && (!m.bi || m.io32)) return hipErrorInvalidValue;
+  if (plane_ok(g) && !m.io32) {  // short lines, FP64 vectors
+    STEP(0, plane_fwd<T>(g, x, B, tw0, tw1, m.bi, m.active, m.upd, s));
+    STEP(2, z_pass<T>(g, B, (const cpx<T>*)m.spec, tw2, m.active, s, m.zvar));
+    STEP(4, plane_inv<T>(g, B, m.upd ? m.upd->out : x, y, m.chi, tw0, tw1, m.bi, e, m.active, s));
+    return hipSuccess;
+  }
   if (m.bi) {
-    STEP(0, x_fwd_c<T>(g, xv, m.io32, A, tw0, *m.bi, m.active, s));
+    STEP(0, x_fwd_c<T>(g, xv, m.io32, A, tw0, *m.bi, m.active, s, 0.f, m.upd));
   } else {
     STEP(0, x_fwd<T>(g, x, A, tw0, m.active, s));
   }
@@ -1481,9 +1499,9 @@ static hipError_t matvec_t(const MatvecArgs& m, const void* xv, void* yv, EpiArg
   STEP(2, z_pass<T>(g, B, (const cpx<T>*)m.spec, tw2, m.active, s, m.zvar));
   STEP(3, y_pass<T>(g, B, A, tw1, true, m.active, s));
   if (m.bi) {
-    STEP(4, x_inv_c<T>(g, A, xv, yv, m.io32, tw0, *m.bi, e, m.active, s));
+    STEP(4, x_inv_c<T>(g, A, m.upd ? m.upd->out : xv, yv, m.io32, tw0, *m.bi, e, m.active, s));
   } else {
-    STEP(4, x_inv<T>(g, A, x, y, m.chi, m.rhs_body, tw0, e, m.active, s));
+    STEP(4, x_inv<T>(g, A, x, y, m.chi, tw0, e, m.active, s));
   }
 #undef STEP
   return hipSuccess;

@@ -9,7 +9,7 @@
 // (zeros elsewhere) before transforming, and the inverse x pass gathers the
 // convolution at the line's voxels after transforming.  The y and z passes
 // and their scratch are unchanged (full FFT box).
-#include "fft_common.h"
+#include "fft_plane.h"
 #include "kernels.h"
 
 namespace vie {
@@ -18,11 +18,13 @@ namespace vie {
 // H (FP32 only): the transformed lines are stored as packed FP16 column
 // pairs scaled by hs (cpx<h2> per pair of neighbouring points of a line);
 // lanes t and t + 1 of a line exchange one point per pair of registers.
-template <typename T, int P, typename TI, bool H = false>
+// U: the vector is the result of the update u, made here: the update's own
+// launch and its write and read back of the vector's lines are saved.
+template <typename T, int P, typename TI, bool H = false, bool U = false>
 __global__ __launch_bounds__(nt_lines_p<T>(P)) void k_fft_x_fwd_c(
     const cpx<TI>* __restrict__ xc, void* __restrict__ outv, const cpx<T>* __restrict__ tw,
     BodyIdx bi, int N1, int N2, int N3, int blocks_per_rhs, const int* __restrict__ active,
-    float hs) {
+    float hs, UpdArgs u) {
   constexpr int E = fft_e<P>(), TT = P / E, NT = nt_lines_p<T>(P), L = NT / TT,
                 LS = PadX<P, P / fft_e<P>()>::LSTR;
   __shared__ cpx<T> lds[L * LS];
@@ -32,6 +34,11 @@ __global__ __launch_bounds__(nt_lines_p<T>(P)) void k_fft_x_fwd_c(
   const int b = blockIdx.x;
   const int rhs = b / blocks_per_rhs, blk = b % blocks_per_rhs;
   if (active && !active[rhs]) return;
+  UpdScal us;
+  if constexpr (U) {
+    __shared__ double red[16];
+    if (!upd_scalars<NT>(u, rhs, blk == 0, red, us)) return;
+  }
   const int lines_per_rhs = 3 * N2 * N3, lpc = N2 * N3;
   const int li = threadIdx.x / TT, t = threadIdx.x % TT;
   const int line = blk * L + li;
@@ -42,7 +49,8 @@ __global__ __launch_bounds__(nt_lines_p<T>(P)) void k_fft_x_fwd_c(
   const int nb = bi.nb[body];
   const int* vox = bi.vox + bi.voff[body];
   const int* lp = bi.line_ptr + (int64_t)body * (lpc + 1);
-  const cpx<TI>* xv = xc + bi.roff[rhs] + (int64_t)comp * nb;
+  const int64_t vb = bi.roff[rhs] + (int64_t)comp * nb;
+  const cpx<TI>* xv = xc + vb;
   TwReg<T, P, E> tr;
   tr.load(t, tw);
   cpx<T>* myl = lds + li * LS;
@@ -64,6 +72,25 @@ __global__ __launch_bounds__(nt_lines_p<T>(P)) void k_fft_x_fwd_c(
         kv[i] = vox[k];
         xr[i] = xv[k];
       }
+    }
+    if constexpr (U) {
+      const bool needv = !(u.mode == UPD_P && us.first);
+      c64 pr[E / 2], vr[E / 2];
+#pragma unroll
+      for (int i = 0; i < E / 2; ++i) {
+        const int64_t k = vb + k0 + i * TT;
+        pr[i] = vr[i] = mk(0.0, 0.0);
+        if (k0 + i * TT < k1 && needv) {
+          vr[i] = u.v[k];
+          if (u.mode == UPD_P) pr[i] = u.out[k];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < E / 2; ++i)
+        if (k0 + i * TT < k1) {
+          xr[i] = upd_value(u, us, xr[i], pr[i], vr[i]);
+          u.out[vb + k0 + i * TT] = xr[i];
+        }
     }
 #pragma unroll
     for (int i = 0; i < E / 2; ++i)
@@ -225,18 +252,28 @@ bool x_packed_ok(int P1) { return (P1 / fft_e_of(P1)) % 2 == 0; }
 
 template <typename T>
 hipError_t x_fwd_c(const GroupGeom& g, const void* xc, int in32, cpx<T>* A, const cpx<T>* tw,
-                   const BodyIdx& bi, const int* active, hipStream_t s, float hs) {
+                   const BodyIdx& bi, const int* active, hipStream_t s, float hs,
+                   const UpdArgs* upd) {
   const int lines = 3 * g.N[1] * g.N[2];
   const int L = lines_per_block<T>(g.P[0]);
   const int bpr = (lines + L - 1) / L;
   const dim3 grid(bpr * g.nrhs);
+  const UpdArgs none;
+  if (upd) {
+    if (hs > 0.f || in32) return hipErrorInvalidValue;
+    VIE_DISPATCH_P(g.P[0], (k_fft_x_fwd_c<T, PP, double, false, true>
+                            <<<grid, nt_lines_p<T>(PP), 0, s>>>(upd->r, A, tw, bi, g.N[0], g.N[1],
+                                                                g.N[2], bpr, active, 0.f, *upd)));
+    return hipGetLastError();
+  }
   if (hs > 0.f) {  // packed FP16 output from bfloat16 input (FP32 arithmetic)
     if constexpr (sizeof(T) == 4) {
       if (in32 != 2) return hipErrorInvalidValue;
       VIE_DISPATCH_P(g.P[0], ({
                        if constexpr (packed_lines_ok<PP>()) {
                          k_fft_x_fwd_c<T, PP, __bf16, true><<<grid, nt_lines_p<T>(PP), 0, s>>>(
-                             (const cb16*)xc, A, tw, bi, g.N[0], g.N[1], g.N[2], bpr, active, hs);
+                             (const cb16*)xc, A, tw, bi, g.N[0], g.N[1], g.N[2], bpr, active, hs,
+                             none);
                        } else {
                          return hipErrorInvalidValue;
                        }
@@ -250,18 +287,18 @@ hipError_t x_fwd_c(const GroupGeom& g, const void* xc, int in32, cpx<T>* A, cons
     if constexpr (sizeof(T) == 4) {
       VIE_DISPATCH_P(g.P[0], (k_fft_x_fwd_c<T, PP, __bf16><<<grid, nt_lines_p<T>(PP), 0, s>>>(
                                  (const cb16*)xc, A, tw, bi, g.N[0], g.N[1], g.N[2], bpr, active,
-                                 0.f)));
+                                 0.f, none)));
     } else {
       return hipErrorInvalidValue;
     }
   } else if (in32) {
     VIE_DISPATCH_P(g.P[0], (k_fft_x_fwd_c<T, PP, float><<<grid, nt_lines_p<T>(PP), 0, s>>>(
                                (const c32*)xc, A, tw, bi, g.N[0], g.N[1], g.N[2], bpr, active,
-                               0.f)));
+                               0.f, none)));
   } else {
     VIE_DISPATCH_P(g.P[0], (k_fft_x_fwd_c<T, PP, double><<<grid, nt_lines_p<T>(PP), 0, s>>>(
                                (const c64*)xc, A, tw, bi, g.N[0], g.N[1], g.N[2], bpr, active,
-                               0.f)));
+                               0.f, none)));
   }
   return hipGetLastError();
 }
@@ -327,9 +364,11 @@ hipError_t x_inv_c(const GroupGeom& g, const cpx<T>* A, const void* x, void* y, 
 }
 
 template hipError_t x_fwd_c<double>(const GroupGeom&, const void*, int, c64*, const c64*,
-                                    const BodyIdx&, const int*, hipStream_t, float);
+                                    const BodyIdx&, const int*, hipStream_t, float,
+                                    const UpdArgs*);
 template hipError_t x_fwd_c<float>(const GroupGeom&, const void*, int, c32*, const c32*,
-                                   const BodyIdx&, const int*, hipStream_t, float);
+                                   const BodyIdx&, const int*, hipStream_t, float,
+                                   const UpdArgs*);
 template hipError_t x_inv_c<double>(const GroupGeom&, const c64*, const void*, void*, int,
                                     const c64*, const BodyIdx&, EpiArgs&, const int*, hipStream_t,
                                     float);

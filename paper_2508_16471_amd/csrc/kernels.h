@@ -12,7 +12,9 @@ namespace vie {
 
 // Per-right-hand-side BiCGSTAB state, resident in device memory.
 struct KState {
-  c64 rho, rho_prev, alpha, omega, beta;
+  c64 rho, alpha, omega, beta;
+  c64 rho1;        // (rhat, r) of the current residual; rho: of the one before (the
+                   // residual update makes it rho)
   double bnorm2;   // ||b||^2
   double rnorm2;   // ||r||^2 (recursive inside a cycle, true after a restart)
   double target2;  // stop the current cycle when rnorm2 <= target2
@@ -56,11 +58,31 @@ struct BodyIdx {
   const int* rhs_body;   // [rhs] body of each right-hand side
 };
 
+// Krylov update fused into the pass that starts a product of body-compressed
+// FP64 vectors: the multiplied vector is p = r + beta (p - omega v) or s = r -
+// alpha v, stored in `out` on the way.  With npart > 0 the pass folds the
+// partials [nrhs][npart][2] that the scalars need (FIN_RHO's, FIN_ALPHA's) and
+// takes the decisions of k_finalize; with npart = 0 they are in the state.
+enum UpdMode { UPD_NONE = 0, UPD_P = 1, UPD_S = 2 };
+struct UpdArgs {
+  int mode = UPD_NONE;
+  KState* st = nullptr;
+  int* flags = nullptr;  // as k_finalize's
+  int nrhs = 0, max_iter = 0;
+  const c64* part = nullptr;
+  int npart = 0;
+  const c64* r = nullptr;
+  const c64* v = nullptr;
+  c64* out = nullptr;  // p (read and written) or s
+};
+// Partials a fused update may fold itself: beyond, every workgroup reading
+// them all costs more than the launch of k_finalize it saves.
+static constexpr int kFoldMax = 512;
+
 // Device pointers used by one operator product of a group.
 struct MatvecArgs {
   const GroupGeom* g;
-  const double* chi;       // [body][n]
-  const int* rhs_body;     // [nrhs] body index of each right-hand side
+  const double* chi;       // [n] of the body, for box vectors (all of one body)
   const void* spec;        // octant spectrum, c64 or c32 per precision
   const void* tw[3];       // twiddle tables per axis (c64 or c32)
   void* bufA;              // x-transformed scratch [nrhs][3][N3][N2][P1]
@@ -68,6 +90,7 @@ struct MatvecArgs {
   const int* active;       // [nrhs] or nullptr
   int zvar = 0;            // launch shape of the z pass (autotuned per group/precision)
   const BodyIdx* bi = nullptr;  // non-null: x and y are body-compressed
+  const UpdArgs* upd = nullptr;  // update that makes x (then x itself is not read)
   int io32 = 0;  // compressed x and y stored in FP32 (FP32 passes, plain epilogue only);
                  // 2: x stored in bfloat16, y in FP32
   // Approximate products (FP32, bfloat16 x, FP32 y, plain epilogue): with
@@ -104,7 +127,10 @@ struct EpiArgs {
   const c64* ph;    // [nrhs][N1 + N2 + N3]  exp(i k0 khat_a (o_a + h idx))
 };
 
-int part_blocks_xinv(const GroupGeom& g, int precision);
+// Dot partials (pairs per right-hand side) of a product's last pass.
+int part_blocks_product(const GroupGeom& g, int precision);
+// Whether a grid takes the fused x-y passes of short lines (fft_plane.hip).
+bool plane_ok(const GroupGeom& g);
 int z_block(const GroupGeom& g);        // z planes kept adjacent in the y/z scratch
 int64_t bufB_elems(const GroupGeom& g);  // y/z scratch elements per right-hand side
 int vec_blocks(const GroupGeom& g);
@@ -158,14 +184,13 @@ int vec_blocks_n(int64_t max_len);
 hipError_t launch_init_zero_guess(const GroupGeom& g, const BodyIdx& bi, int vb,
                                   const c64* pol, const c64* ph, c64* x, c64* r, c64* rh,
                                   c64* partials, int keep_x, const int* mask, hipStream_t s);
-hipError_t launch_update_p(const GroupGeom& g, const BodyIdx& bi, int vb, const KState* st,
-                           const int* active, const c64* r, c64* p, const c64* v, hipStream_t s);
-hipError_t launch_update_s(const GroupGeom& g, const BodyIdx& bi, int vb, const KState* st,
-                           const int* active, const c64* r, const c64* v, c64* s_out,
-                           hipStream_t s);
-hipError_t launch_update_xr(const GroupGeom& g, const BodyIdx& bi, int vb, const KState* st,
+// x += alpha p + omega s, r = s - omega t, one iteration done, partials
+// ((rhat, r), |r|^2); omega from the product's partials tpart (ntpart pairs per
+// right-hand side) or, with ntpart = 0, from the state.
+hipError_t launch_update_xr(const GroupGeom& g, const BodyIdx& bi, int vb, KState* st,
                             const int* active, c64* x, c64* r, const c64* p, const c64* sv,
-                            const c64* t, const c64* rh, c64* partials, hipStream_t s);
+                            const c64* t, const c64* rh, const c64* tpart, int ntpart,
+                            c64* partials, hipStream_t s);
 // Finalize reductions (one workgroup per right-hand side, fixed order):
 // FIN_RESTART acts on the right-hand sides not done; FIN_PENDING (the same
 // restart) on those whose cycle has ended and waits for its true residual.

@@ -7,6 +7,7 @@
 //
 // Vectors: FP64 complex, [rhs][3][N3][N2][N1] (3n per right-hand side).
 // flags[rhs] = active (iterating), flags[nrhs + rhs] = not yet converged.
+#include "fft_plane.h"
 #include "kernels.h"
 
 namespace vie {
@@ -101,51 +102,37 @@ __global__ __launch_bounds__(VT) void k_init_zero(GroupGeom g, BodyIdx bi,
   }
 }
 
-// p = r + beta (p - omega v); p = r at the start of a cycle
-__global__ __launch_bounds__(VT) void k_update_p(BodyIdx bi, const KState* __restrict__ st,
-                                                 const int* __restrict__ active,
-                                                 const c64* __restrict__ r, c64* __restrict__ p,
-                                                 const c64* __restrict__ v, int vb) {
-  const int rhs = blockIdx.x / vb, blk = blockIdx.x % vb;
-  if (!active[rhs]) return;
-  const VecRange R = vrange(bi, rhs);
-  const bool first = st[rhs].it_cycle == 0;
-  const c64 beta = st[rhs].beta, om = st[rhs].omega;
-  for (int64_t e = (int64_t)blk * VT + threadIdx.x; e < R.len; e += (int64_t)vb * VT) {
-    const int64_t k = R.base + e;
-    p[k] = first ? r[k] : r[k] + beta * (p[k] - om * v[k]);
-  }
-}
-
-// s = r - alpha v
-__global__ __launch_bounds__(VT) void k_update_s(BodyIdx bi, const KState* __restrict__ st,
-                                                 const int* __restrict__ active,
-                                                 const c64* __restrict__ r,
-                                                 const c64* __restrict__ v, c64* __restrict__ s,
-                                                 int vb) {
-  const int rhs = blockIdx.x / vb, blk = blockIdx.x % vb;
-  if (!active[rhs]) return;
-  const VecRange R = vrange(bi, rhs);
-  const c64 al = st[rhs].alpha;
-  for (int64_t e = (int64_t)blk * VT + threadIdx.x; e < R.len; e += (int64_t)vb * VT) {
-    const int64_t k = R.base + e;
-    s[k] = r[k] - al * v[k];
-  }
-}
-
 // x += alpha p + omega s; r = s - omega t; partials (rhat.r, |r|^2)
-__global__ __launch_bounds__(VT) void k_update_xr(BodyIdx bi, const KState* __restrict__ st,
+// (p and s are updated by the passes that multiply them, see UpdArgs).
+__global__ __launch_bounds__(VT) void k_update_xr(BodyIdx bi, KState* __restrict__ st,
                                                   const int* __restrict__ active,
                                                   c64* __restrict__ x, c64* __restrict__ r,
                                                   const c64* __restrict__ p,
                                                   const c64* __restrict__ s,
                                                   const c64* __restrict__ t,
                                                   const c64* __restrict__ rh,
+                                                  const c64* __restrict__ tpart, int ntpart,
                                                   c64* __restrict__ partials, int vb) {
+  __shared__ double red[16];
   const int rhs = blockIdx.x / vb, blk = blockIdx.x % vb;
   if (!active[rhs]) return;
   const VecRange R = vrange(bi, rhs);
-  const c64 al = st[rhs].alpha, om = st[rhs].omega;
+  KState& S = st[rhs];
+  const c64 al = S.alpha;
+  c64 om;
+  if (ntpart) {
+    c64 ts, tt;
+    fold_pairs<VT>(tpart + (int64_t)rhs * ntpart * 2, ntpart, red, ts, tt);
+    om = tt.re > 0 ? mk(ts.re / tt.re, ts.im / tt.re) : mk(0.0, 0.0);
+  } else {
+    om = S.omega;
+  }
+  if (blk == 0 && threadIdx.x == 0) {  // nothing stored here is read in this launch
+    if (ntpart) S.omega = om;
+    S.rho = S.rho1;
+    S.iters += 1;
+    S.it_cycle += 1;
+  }
   c64 s0 = mk(0.0, 0.0), s1 = mk(0.0, 0.0);
   for (int64_t e = (int64_t)blk * VT + threadIdx.x; e < R.len; e += (int64_t)vb * VT) {
     const int64_t k = R.base + e;
@@ -188,12 +175,6 @@ __global__ __launch_bounds__(VT) void k_compress(const c64* __restrict__ box, c6
   }
 }
 
-__device__ __forceinline__ c64 cdiv(c64 a, c64 b) {
-  const double d = b.re * b.re + b.im * b.im;
-  return mk((a.re * b.re + a.im * b.im) / d, (a.im * b.re - a.re * b.im) / d);
-}
-__device__ __forceinline__ double cabs2(c64 a) { return a.re * a.re + a.im * a.im; }
-
 __global__ __launch_bounds__(VT) void k_finalize(int which, int nrhs, int nblk,
                                                  const c64* __restrict__ partials,
                                                  KState* __restrict__ st, int* __restrict__ flags,
@@ -207,12 +188,9 @@ __global__ __launch_bounds__(VT) void k_finalize(int which, int nrhs, int nblk,
                     : (which == FIN_INIT)    ? true
                                              : flags[rhs] != 0;
   if (!gate) return;
-  c64 a = mk(0.0, 0.0), b = mk(0.0, 0.0);
-  for (int k = threadIdx.x; k < nblk; k += VT) {
-    a = a + partials[((size_t)rhs * nblk + k) * 2 + 0];
-    b = b + partials[((size_t)rhs * nblk + k) * 2 + 1];
-  }
-  block_reduce2(a, b);
+  __shared__ double red[16];
+  c64 a, b;
+  fold_pairs<VT>(partials + (size_t)rhs * nblk * 2, nblk, red, a, b);
   if (threadIdx.x != 0) return;
   switch (which) {
     case FIN_ALPHA: {
@@ -222,13 +200,13 @@ __global__ __launch_bounds__(VT) void k_finalize(int which, int nrhs, int nblk,
       // |rhat| |r| decays geometrically in a healthy iteration and any fixed
       // relative threshold would restart it (losing the Krylov space) for
       // no reason on slowly converging problems.
-      if (cabs2(rhv) == 0.0 || !(cabs2(rhv) < 1e300)) {
+      if (kcabs2(rhv) == 0.0 || !(kcabs2(rhv) < 1e300)) {
         S.breakdown = 1;  // rhat . A p vanished
         S.active = 0;
         flags[rhs] = 0;
         flags[2 * nrhs + rhs] = 1;
       } else {
-        S.alpha = cdiv(S.rho, rhv);
+        S.alpha = kcdiv(S.rho1, rhv);
       }
       break;
     }
@@ -238,29 +216,16 @@ __global__ __launch_bounds__(VT) void k_finalize(int which, int nrhs, int nblk,
       break;
     }
     case FIN_RHO: {
-      S.rho_prev = S.rho;
-      S.rho = a;
+      S.rho1 = a;
       S.rnorm2 = b.re;
-      S.iters += 1;
-      S.it_cycle += 1;
-      int stop = 0;
-      if (!(S.rnorm2 <= 1e300)) {  // NaN / overflow: end the cycle, restart from x
-        stop = 1;
-        S.breakdown = 4;
-      } else if (S.rnorm2 <= S.target2) {
-        stop = 1;
-      } else if (S.iters >= fp.max_iter) {
-        stop = 1;
-      } else if (cabs2(S.rho) == 0.0 || cabs2(S.omega) == 0.0) {
-        stop = 1;
-        S.breakdown = cabs2(S.omega) == 0.0 ? 3 : 2;  // omega = 0 / rhat . r vanished
-      } else {
-        S.beta = cdiv(S.rho, S.rho_prev) * cdiv(S.alpha, S.omega);
-      }
-      if (stop) {
+      int bd;
+      if (rho_decision(a, b.re, S.omega, S.iters, S.target2, fp.max_iter, bd)) {
+        if (bd) S.breakdown = bd;
         S.active = 0;
         flags[rhs] = 0;
         flags[2 * nrhs + rhs] = 1;
+      } else {
+        S.beta = kcdiv(a, S.rho) * kcdiv(S.alpha, S.omega);
       }
       break;
     }
@@ -276,8 +241,8 @@ __global__ __launch_bounds__(VT) void k_finalize(int which, int nrhs, int nblk,
       }
       S.rnorm2 = b.re;
       S.rh2 = b.re;
-      S.rho = mk(b.re, 0.0);  // rhat = r
-      S.rho_prev = S.alpha = S.omega = S.beta = mk(1.0, 0.0);
+      S.rho = S.rho1 = mk(b.re, 0.0);  // rhat = r
+      S.alpha = S.omega = S.beta = mk(1.0, 0.0);
       S.it_cycle = 0;
       S.breakdown = 0;
       const double done2 = fp.tol2_done * S.bnorm2;
@@ -308,21 +273,12 @@ hipError_t launch_init_zero_guess(const GroupGeom& g, const BodyIdx& bi, int vb,
   k_init_zero<<<vb * g.nrhs, VT, 0, s>>>(g, bi, pol, ph, x, r, rh, partials, vb, keep_x, mask);
   return hipGetLastError();
 }
-hipError_t launch_update_p(const GroupGeom& g, const BodyIdx& bi, int vb, const KState* st,
-                           const int* active, const c64* r, c64* p, const c64* v, hipStream_t s) {
-  k_update_p<<<vb * g.nrhs, VT, 0, s>>>(bi, st, active, r, p, v, vb);
-  return hipGetLastError();
-}
-hipError_t launch_update_s(const GroupGeom& g, const BodyIdx& bi, int vb, const KState* st,
-                           const int* active, const c64* r, const c64* v, c64* so,
-                           hipStream_t s) {
-  k_update_s<<<vb * g.nrhs, VT, 0, s>>>(bi, st, active, r, v, so, vb);
-  return hipGetLastError();
-}
-hipError_t launch_update_xr(const GroupGeom& g, const BodyIdx& bi, int vb, const KState* st,
+hipError_t launch_update_xr(const GroupGeom& g, const BodyIdx& bi, int vb, KState* st,
                             const int* active, c64* x, c64* r, const c64* p, const c64* sv,
-                            const c64* t, const c64* rh, c64* partials, hipStream_t s) {
-  k_update_xr<<<vb * g.nrhs, VT, 0, s>>>(bi, st, active, x, r, p, sv, t, rh, partials, vb);
+                            const c64* t, const c64* rh, const c64* tpart, int ntpart,
+                            c64* partials, hipStream_t s) {
+  k_update_xr<<<vb * g.nrhs, VT, 0, s>>>(bi, st, active, x, r, p, sv, t, rh, tpart, ntpart,
+                                         partials, vb);
   return hipGetLastError();
 }
 hipError_t launch_vec_norm2(int nrhs, const BodyIdx& bi, const c64* v, double* out,
