@@ -364,3 +364,25 @@ def test_batches_of_channels_equal_single_channels(V):
             assert np.any(one) and np.array_equal(one[0], w[q])
     finally:
         V.vie_rt_destroy(h)
+
+
+@pytest.mark.parametrize("n", [(41, 42, 40), (44, 44, 44), (60, 57, 50)])
+def test_outputs_through_staging_equal_pinned_outputs(V, n):
+    """Outputs of 4 MB and more reach a pageable array in pieces; a pinned one takes the
+    runtime's own copy.  Same bytes, for vectors below and above the limit, with remainders."""
+    import torch
+
+    print(f"rooftop outputs n={n}", flush=True)
+    rng = np.random.default_rng(5)
+    eps = np.where(rng.random(n[::-1]) < 0.7, 2.5, 1.0)
+    r = V.vie_rt_setup(eps, 1.0 / 64, (0.0, 0.0, 0.0), K0)
+    try:
+        E, _ = V.vie_rt_grid(r)
+        x = _random_x(rng, (2, 3) + E[::-1])
+        want = torch.empty(x.shape, dtype=torch.complex128, pin_memory=True).numpy()
+        V._check(V.lib().vie_rt_matvec(r, V._cptr(x), V._cptr(want), 2, V.VIE_FP64), "product")
+        for _ in range(2):
+            assert np.array_equal(V.vie_rt_matvec(r, x), want)
+        assert np.abs(want).max() > 0
+    finally:
+        V.vie_rt_destroy(r)
