@@ -136,7 +136,7 @@ struct Group {
   int zvar_nrhs[2] = {0, 0};     // right-hand-side count it was tuned for
   // packed-FP16 y and z passes of approximate FP32 products (block solves):
   // tables, spectrum scale gs, forward scales along x, y, z, scale back, on/off
-  DevBuf spec16, tw16y, tw16z, gmax;
+  DevBuf spec16, tw16y, tw16z, dft16, gmax;
   float zh_gs = 0.f, hs[3] = {0.f, 0.f, 0.f}, hout = 0.f;
   int zh = 0;
 };
@@ -742,6 +742,7 @@ static MatvecArgs matvec_args(Group& G, int precision, const int* active) {
     m.spec16 = G.spec16.p;
     m.tw16[0] = G.tw16y.p;
     m.tw16[1] = G.tw16z.p;
+    m.dft16 = G.dft16.p;
     for (int d = 0; d < 3; ++d) m.hs[d] = G.hs[d];
     m.hout = G.hout;
   }
@@ -1851,6 +1852,10 @@ static int bj_prepare(vie_ctx* ctx, BlockPrec& P, const vie_fgmres_options* fo) 
         VIE_HIP(launch_tw_h2(Gs.tw32[1].p, Gs.tw16y.p, g.P[1], ctx->stream));
         VIE_HIP(Gs.tw16z.reserve((size_t)g.P[2] * 8));
         VIE_HIP(launch_tw_h2(Gs.tw32[2].p, Gs.tw16z.p, g.P[2], ctx->stream));
+        if (xy_fused_ok(g)) {
+          VIE_HIP(Gs.dft16.reserve(xy16_table_bytes(g)));
+          VIE_HIP(launch_xy16_tables(Gs.dft16.p, g, ctx->stream));
+        }
         Gs.zh_gs = gs;
       }
     }
@@ -1884,7 +1889,7 @@ static void key_group(std::vector<const void*>& k, const Group& G) {
   const int ints[] = {G.g.nrhs, G.zvar[0], G.zvar[1], G.g.N[0], G.g.N[1], G.g.N[2], G.g.P[0],
                       G.g.P[1], G.g.P[2], G.zh};
   for (int v : ints) k.push_back((const void*)(intptr_t)v);
-  key_bufs(k, {&G.spec16, &G.tw16y, &G.tw16z});
+  key_bufs(k, {&G.spec16, &G.tw16y, &G.tw16z, &G.dft16});
   for (float f : {G.hs[0], G.hs[1], G.hs[2], G.hout}) {
     uint32_t b = 0;
     memcpy(&b, &f, sizeof(b));

@@ -758,283 +758,6 @@ __global__ __launch_bounds__(NTB) void k_fft_y_h2(const cpx<h2>* __restrict__ in
   }
 }
 
-// Fused x and y passes of the packed path: one workgroup per (right-hand
-// side, component, z) plane keeps the plane's x-transformed lines in LDS as
-// packed pairs (N2 rows of P1 / 2 pairs), so the x-y scratch never goes to
-// HBM.  Forward: the plane's x lines are scattered from the compressed
-// bfloat16 vector and transformed in FP32 (L1 lines at a time), converted
-// into the plane (scale h1), then the column pairs are transformed along y in
-// packed FP16 (W2 at a time, scale h2) and written to the y/z scratch.
-// Inverse: the reverse, ending in the compressed product epilogue
-// y = x - chi (conv / (h1 h2 h3 gs)).  The x and y phases share one LDS
-// buffer for their transform lines.
-template <int P1, int P2>
-struct XYShape {
-  static constexpr int NT = 256;
-  // 8 points per thread on 128-point lines (16 threads a line): fewer lines
-  // in flight per phase, so three workgroups share a CU
-  static constexpr int E1 = P1 == 128 ? 8 : fft_e<P1>(), TT1 = P1 / E1, L1 = NT / TT1;
-  static constexpr int E2 = P2 == 128 ? 8 : fft_e<P2>(), TT2 = P2 / E2, W2 = NT / TT2;
-  static constexpr int PS = P1 / 2;               // packed pairs per plane row
-  static constexpr int NBX = (P2 / 2 + L1 - 1) / L1;  // x-line batches (N2 <= P2 / 2)
-  static constexpr int NP = P1 / 2;               // column pairs
-  static constexpr int PLANE = (P2 / 2) * PS;     // rows N2 <= P2 / 2
-  static constexpr int XLS = PadX<P1, TT1>::LSTR;  // x-line stride
-  static constexpr int XB = L1 * XLS * (int)sizeof(c32);
-  static constexpr int YB = W2 * Pad<P2>::LSTR * (int)sizeof(cpx<h2>);
-  static constexpr int UB = XB > YB ? XB : YB;
-  static_assert(NT % TT1 == 0 && NT % TT2 == 0 && TT1 % 2 == 0, "fused x-y shape");
-};
-
-// NRM: the input is an FP32 work vector, normalised per right-hand side
-// (see MatvecArgs::npart) into the bfloat16 vector vout on the way in.
-template <int P1, int P2, bool NRM>
-__global__ __launch_bounds__(256) void k_fft_xy_fwd_h2(
-    const void* __restrict__ xcv, cpx<h2>* __restrict__ B, const c32* __restrict__ tw1,
-    const cpx<h2>* __restrict__ tw2, BodyIdx bi, int N1, int N2, int N3, SideAddr sb, int zl,
-    float hs1, float hs2, const int* __restrict__ active, const double* __restrict__ npart,
-    int nblk, double* __restrict__ nrm, int ldn, cb16* __restrict__ vout) {
-  using TXI = typename std::conditional<NRM, c32, cb16>::type;
-  using S = XYShape<P1, P2>;
-  __shared__ cpx<h2> plane[S::PLANE];
-  __shared__ __align__(16) char ubuf[S::UB];
-  const int nrhs = gridDim.x / (3 * N3);
-  const int rhs = blockIdx.x % nrhs, cz = blockIdx.x / nrhs;
-  if (active && !active[rhs]) return;
-  const int comp = cz / N3, z = cz % N3;
-  const int body = bi.rhs_body[rhs];
-  const int nb = bi.nb[body];
-  const int* vox = bi.vox + bi.voff[body];
-  const int* lp = bi.line_ptr + (int64_t)body * (N2 * N3 + 1);
-  const TXI* xv = reinterpret_cast<const TXI*>(xcv) + bi.roff[rhs] + (int64_t)comp * nb;
-  cb16* vo = NRM ? vout + bi.roff[rhs] + (int64_t)comp * nb : nullptr;
-  double sc = 1.0;
-  if constexpr (NRM) {
-    // ||w||^2 of this right-hand side: every wave sums the partials in the
-    // order of the separate reduction (lane-strided, then a fixed butterfly)
-    double t2 = 0.0;
-    for (int k = threadIdx.x & 63; k < nblk; k += 64) t2 += npart[(int64_t)rhs * nblk + k];
-    for (int mk = 32; mk >= 1; mk >>= 1) t2 += __shfl_xor(t2, mk);
-    sc = t2 > 0.0 ? 1.0 / sqrt(t2) : 0.0;
-    if (comp == 0 && z == 0 && threadIdx.x == 0) nrm[(int64_t)rhs * ldn] = t2;
-  }
-  {  // x: FP32 lines into the plane, S::L1 lines a batch
-    constexpr int E = S::E1, TT = S::TT1;
-    const int li = threadIdx.x / TT, t = threadIdx.x % TT, odd = t & 1;
-    cpx<float>* myl = reinterpret_cast<cpx<float>*>(ubuf) + li * S::XLS;
-    TwReg<float, P1, E> tr;
-    tr.load(t, tw1);
-    // the line pointers of this thread's line in every batch, in one round of
-    // loads; each batch's voxels (at most P1 / 2 a line, so E / 2 a thread)
-    // are requested while the previous batch is transformed
-    int lpa[S::NBX], lpb[S::NBX];
-#pragma unroll
-    for (int n = 0; n < S::NBX; ++n) {
-      const int y = n * S::L1 + li;
-      lpa[n] = lpb[n] = 0;
-      if (y < N2) {
-        lpa[n] = lp[z * N2 + y];
-        lpb[n] = lp[z * N2 + y + 1];
-      }
-    }
-    int kv[E / 2];
-    TXI xr[E / 2];
-    auto fetch = [&](int n) {
-      const int k0 = lpa[n] + t, k1 = lpb[n];
-#pragma unroll
-      for (int i = 0; i < E / 2; ++i) {
-        const int k = k0 + i * TT;
-        if (k < k1) {
-          kv[i] = vox[k];
-          xr[i] = xv[k];
-        }
-      }
-    };
-    fetch(0);
-#pragma unroll
-    for (int n = 0; n < S::NBX; ++n) {
-      if (n * S::L1 >= N2) break;
-      const int y = n * S::L1 + li;
-      const bool valid = y < N2;
-      lds_barrier();  // the previous lines' last transform stage has read the buffer
-#pragma unroll
-      for (int q = 0; q < E / 2; ++q) myl[pidx(t + q * TT)] = mk<float>(0, 0);
-      lds_barrier();
-      {
-        const int k0 = lpa[n] + t, k1 = lpb[n], base = (z * N2 + y) * N1;
-#pragma unroll
-        for (int i = 0; i < E / 2; ++i) {
-          if (k0 + i * TT >= k1) continue;
-          if constexpr (NRM) {
-            // the basis vector as stored (bfloat16 through FP32) is what is multiplied
-            const c64 wn = sc * cvt<double>(xr[i]);
-            cb16 b16;
-            b16.re = (__bf16)(float)wn.re;
-            b16.im = (__bf16)(float)wn.im;
-            vo[k0 + i * TT] = b16;
-            myl[pidx(kv[i] - base)] = cvt<float>(b16);
-          } else {
-            myl[pidx(kv[i] - base)] = cvt<float>(xr[i]);
-          }
-        }
-      }
-      lds_barrier();
-      if (n + 1 < S::NBX) fetch(n + 1);
-      cpx<float> v[E];
-#pragma unroll
-      for (int q = 0; q < E; ++q) v[q] = (q < E / 2) ? myl[pidx(t + q * TT)] : mk<float>(0, 0);
-      line_fft_e<float, P1, E, false, true, false>(v, myl, t, tr);
-      // lanes t, t + 1 hold neighbouring points: one exchange packs a pair
-#pragma unroll
-      for (int q = 0; q < E; q += 2) {
-        const float4 f = pair_out(odd, v[q], v[q + 1]);
-        if (valid)
-          plane[y * S::PS + ((t - odd + (q + odd) * TT) >> 1)] =
-              pack2(f.x * hs1, f.y * hs1, f.z * hs1, f.w * hs1);
-      }
-    }
-  }
-  lds_barrier();  // the plane is complete and the line buffer free
-  {  // y: packed column pairs from the plane to the y/z scratch
-    constexpr int E = S::E2, TT = S::TT2;
-    const int cw = threadIdx.x % S::W2, t = threadIdx.x / S::W2;
-    cpx<h2>* myl = reinterpret_cast<cpx<h2>*>(ubuf) + cw * Pad<P2>::LSTR;
-    TwReg<h2, P2, E> tr;
-    tr.load(t, tw2);
-    const h2 sc = {(_Float16)hs2, (_Float16)hs2};
-    cpx<h2>* po = B + slab_base(sb, rhs, comp, z, zl);
-    for (int p0 = 0; p0 < S::NP; p0 += S::W2) {
-      const int p = p0 + cw;
-      const bool valid = p < S::NP;
-      cpx<h2> v[E];
-#pragma unroll
-      for (int q = 0; q < E; ++q) {
-        const int row = t + q * TT;
-        v[q] = (q < E / 2 && valid && row < N2) ? hscale(plane[row * S::PS + p], sc)
-                                               : mk<h2>(h2{0, 0}, h2{0, 0});
-      }
-      line_fft_e<h2, P2, E, false, true, false>(v, myl, t, tr);
-      if (valid) {
-#pragma unroll
-        for (int q = 0; q < E; ++q) po[(int64_t)(t + q * TT) * sb.row + p] = v[q];
-      }
-    }
-  }
-}
-
-template <int P1, int P2>
-__global__ __launch_bounds__(256) void k_fft_yx_inv_h2(
-    const cpx<h2>* __restrict__ B, const cb16* __restrict__ xin, c32* __restrict__ yout,
-    const c32* __restrict__ tw1, const cpx<h2>* __restrict__ tw2, BodyIdx bi, int N1, int N2,
-    int N3, SideAddr sb, int zl, float hs, const int* __restrict__ active) {
-  using S = XYShape<P1, P2>;
-  __shared__ cpx<h2> plane[S::PLANE];
-  __shared__ __align__(16) char ubuf[S::UB];
-  const int nrhs = gridDim.x / (3 * N3);
-  const int rhs = blockIdx.x % nrhs, cz = blockIdx.x / nrhs;
-  if (active && !active[rhs]) return;
-  const int comp = cz / N3, z = cz % N3;
-  // The epilogue's operands of this thread's x line in every batch (line
-  // pointers first, in one round; then each batch's voxels, at most P1 / 2 a
-  // line, so E1 / 2 a thread) are requested ahead: the first batch's before
-  // the y phase, each next one while the current batch is finished.
-  const int body = bi.rhs_body[rhs];
-  const int nb = bi.nb[body];
-  const int* vox = bi.vox + bi.voff[body];
-  const double* chic = bi.chic + bi.voff[body];
-  const int* lp = bi.line_ptr + (int64_t)body * (N2 * N3 + 1);
-  const int64_t vb = bi.roff[rhs] + (int64_t)comp * nb;
-  const int lix = threadIdx.x / S::TT1, tx = threadIdx.x % S::TT1;
-  int lpa[S::NBX], lpb[S::NBX];
-#pragma unroll
-  for (int n = 0; n < S::NBX; ++n) {
-    const int y = n * S::L1 + lix;
-    lpa[n] = lpb[n] = 0;
-    if (y < N2) {
-      lpa[n] = lp[z * N2 + y];
-      lpb[n] = lp[z * N2 + y + 1];
-    }
-  }
-  int kv[S::E1 / 2];
-  double cv[S::E1 / 2];
-  cb16 xr[S::E1 / 2];
-  auto fetch = [&](int n) {
-    const int k0 = lpa[n] + tx, k1 = lpb[n];
-#pragma unroll
-    for (int i = 0; i < S::E1 / 2; ++i) {
-      const int k = k0 + i * S::TT1;
-      if (k < k1) {
-        kv[i] = vox[k];
-        cv[i] = chic[k];
-        xr[i] = xin[vb + k];
-      }
-    }
-  };
-  fetch(0);
-  {  // inverse y: packed column pairs from the y/z scratch into the plane (rows < N2)
-    constexpr int E = S::E2, TT = S::TT2;
-    const int cw = threadIdx.x % S::W2, t = threadIdx.x / S::W2;
-    cpx<h2>* myl = reinterpret_cast<cpx<h2>*>(ubuf) + cw * Pad<P2>::LSTR;
-    TwReg<h2, P2, E> tr;
-    tr.load(t, tw2);
-    const cpx<h2>* pin = B + slab_base(sb, rhs, comp, z, zl);
-    for (int p0 = 0; p0 < S::NP; p0 += S::W2) {
-      const int p = p0 + cw;
-      const bool valid = p < S::NP;
-      cpx<h2> v[E];
-#pragma unroll
-      for (int q = 0; q < E; ++q)
-        v[q] = valid ? pin[(int64_t)(t + q * TT) * sb.row + p] : mk<h2>(h2{0, 0}, h2{0, 0});
-      line_fft_e<h2, P2, E, true, false, true>(v, myl, t, tr);
-      if (valid) {
-#pragma unroll
-        for (int q = 0; q < E / 2; ++q) {
-          const int row = t + q * TT;
-          if (row < N2) plane[row * S::PS + p] = v[q];
-        }
-      }
-    }
-  }
-  lds_barrier();  // the plane is complete and the line buffer free
-  {  // inverse x in FP32 and the compressed epilogue, L1 lines at a time
-    constexpr int E = S::E1, TT = S::TT1;
-    const int li = lix, t = tx, odd = t & 1;
-    cpx<float>* myl = reinterpret_cast<cpx<float>*>(ubuf) + li * S::XLS;
-    TwReg<float, P1, E> tr;
-    tr.load(t, tw1);
-#pragma unroll
-    for (int n = 0; n < S::NBX; ++n) {
-      if (n * S::L1 >= N2) break;
-      const int y = n * S::L1 + li;
-      const bool valid = y < N2;
-      cpx<float> v[E];
-#pragma unroll
-      for (int q = 0; q < E; q += 2) {
-        float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (valid) f = unpack2(plane[y * S::PS + ((t - odd + (q + odd) * TT) >> 1)]);
-        pair_in(f, odd, v[q], v[q + 1]);
-      }
-      line_fft_e<float, P1, E, true, false, true>(v, myl, t, tr);  // only x < N1 is used
-      lds_barrier();  // every thread has left the transform's last LDS read
-#pragma unroll
-      for (int q = 0; q < E / 2; ++q) myl[pidx(t + q * TT)] = v[q];
-      lds_barrier();
-      {
-        const int k0 = lpa[n] + t, k1 = lpb[n], base = (z * N2 + y) * N1;
-#pragma unroll
-        for (int i = 0; i < E / 2; ++i) {
-          const int k = k0 + i * TT;
-          if (k >= k1) continue;
-          const c64 conv = (double)hs * cvt<double>(myl[pidx(kv[i] - base)]);
-          const c64 r = cvt<double>(xr[i]) - cv[i] * conv;
-          yout[vb + k] = cvt<float>(r);
-        }
-      }
-      if (n + 1 < S::NBX) fetch(n + 1);
-    }
-  }
-}
-
 __device__ __forceinline__ void load_g6h(const cpx<h2>* __restrict__ r, cpx<h2> (&g)[6]) {
 #pragma unroll
   for (int k = 0; k < 6; ++k) g[k] = r[k];
@@ -1225,61 +948,6 @@ static hipError_t y_pass_h2(const GroupGeom& g, const cpx<h2>* in, cpx<h2>* out,
   return hipGetLastError();
 }
 
-// The fused x-y passes take FFT lengths 64, 96 and 128 along x and y (the
-// plane and one set of transform lines fit a quarter of the LDS).
-static bool xy_len_ok(int p) { return p == 64 || p == 96 || p == 128; }
-bool xy_fused_ok(const GroupGeom& g) { return xy_len_ok(g.P[0]) && xy_len_ok(g.P[1]); }
-
-#define VIE_DISPATCH_XY(P_, CALL)                    \
-  switch (P_) {                                      \
-    case 64: { constexpr int PP = 64; CALL; break; } \
-    case 96: { constexpr int PP = 96; CALL; break; } \
-    case 128: { constexpr int PP = 128; CALL; break; } \
-    default: return hipErrorInvalidValue;            \
-  }
-
-// m.npart set: normalising FP32 input (see MatvecArgs), else bfloat16 input
-static hipError_t xy_fwd_h2(const GroupGeom& g, const void* xc, cpx<h2>* B, const c32* tw1,
-                            const cpx<h2>* tw2, const BodyIdx& bi, float hs1, float hs2,
-                            const MatvecArgs& m, hipStream_t s) {
-  if (!xy_fused_ok(g)) return hipErrorInvalidValue;
-  const int zl = z_block(g);
-  const SideAddr sb = halved(side_B(g, zl));
-  const dim3 grid(g.nrhs * 3 * g.N[2]);
-  VIE_DISPATCH_XY(g.P[0], ({
-                    constexpr int Q1 = PP;
-                    VIE_DISPATCH_XY(g.P[1], ({
-                                      if (m.npart)
-                                        k_fft_xy_fwd_h2<Q1, PP, true><<<grid, 256, 0, s>>>(
-                                            xc, B, tw1, tw2, bi, g.N[0], g.N[1], g.N[2], sb, zl,
-                                            hs1, hs2, m.active, m.npart, m.nblk, m.nrm, m.ldn,
-                                            (cb16*)m.vout);
-                                      else
-                                        k_fft_xy_fwd_h2<Q1, PP, false><<<grid, 256, 0, s>>>(
-                                            xc, B, tw1, tw2, bi, g.N[0], g.N[1], g.N[2], sb, zl,
-                                            hs1, hs2, m.active, nullptr, 0, nullptr, 0, nullptr);
-                                    }));
-                  }));
-  return hipGetLastError();
-}
-
-static hipError_t yx_inv_h2(const GroupGeom& g, const cpx<h2>* B, const void* x, void* y,
-                            const c32* tw1, const cpx<h2>* tw2, const BodyIdx& bi, float hs,
-                            const int* active, hipStream_t s) {
-  if (!xy_fused_ok(g)) return hipErrorInvalidValue;
-  const int zl = z_block(g);
-  const SideAddr sb = halved(side_B(g, zl));
-  const dim3 grid(g.nrhs * 3 * g.N[2]);
-  VIE_DISPATCH_XY(g.P[0], ({
-                    constexpr int Q1 = PP;
-                    VIE_DISPATCH_XY(g.P[1], (k_fft_yx_inv_h2<Q1, PP><<<grid, 256, 0, s>>>(
-                                                B, (const cb16*)x, (c32*)y, tw1, tw2, bi, g.N[0],
-                                                g.N[1], g.N[2], sb, zl, hs, active)));
-                  }));
-  return hipGetLastError();
-}
-#undef VIE_DISPATCH_XY
-
 static hipError_t z_pass_h2(const GroupGeom& g, cpx<h2>* B, const cpx<h2>* spec,
                             const cpx<h2>* tw, float hs, const int* active, hipStream_t s) {
   if (!h16_ok(g)) return hipErrorInvalidValue;
@@ -1426,6 +1094,10 @@ hipError_t x_inv_c(const GroupGeom& g, const cpx<T>* A, const void* x, void* y, 
                    const cpx<T>* tw, const BodyIdx& bi, EpiArgs& e, const int* active,
                    hipStream_t s, float hs = 0.f);
 
+// fused x-y passes of the packed products (fft_xy16.hip)
+hipError_t xy_fwd_h2(const MatvecArgs& m, const void* xc, void* B, hipStream_t s);
+hipError_t yx_inv_h2(const MatvecArgs& m, const void* B, const void* x, void* y, hipStream_t s);
+
 // fused x-y passes of short lines (fft_plane.hip)
 template <typename T>
 hipError_t plane_fwd(const GroupGeom& g, const c64* x, cpx<T>* B, const cpx<T>* tw1,
@@ -1465,11 +1137,10 @@ static hipError_t matvec_t(const MatvecArgs& m, const void* xv, void* yv, EpiArg
       const cpx<h2>* twz = (const cpx<h2>*)m.tw16[1];
       base = kH16Kind0;
       if (xy_fused_ok(g)) {  // x and y fused per plane: no x-y scratch traffic
-        STEP(5, xy_fwd_h2(g, xv, Bh, (const c32*)tw0, twy, *m.bi, m.hs[0], m.hs[1], m, s));
+        STEP(5, xy_fwd_h2(m, xv, Bh, s));
         STEP(2, z_pass_h2(g, Bh, (const cpx<h2>*)m.spec16, twz, m.hs[2], m.active, s));
         // with a normalised input the epilogue's x is the stored bfloat16 vector
-        STEP(6, yx_inv_h2(g, Bh, m.npart ? m.vout : xv, yv, (const c32*)tw0, twy, *m.bi, m.hout,
-                          m.active, s));
+        STEP(6, yx_inv_h2(m, Bh, m.npart ? m.vout : xv, yv, s));
         return hipSuccess;
       }
       if (m.npart) return hipErrorInvalidValue;

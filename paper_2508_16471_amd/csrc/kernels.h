@@ -100,6 +100,7 @@ struct MatvecArgs {
   // scales along x, y, z, hout the inverse x pass's scale back.
   const void* spec16 = nullptr;
   const void* tw16[2] = {nullptr, nullptr};
+  const void* dft16 = nullptr;  // operand tables of the fused x-y passes (xy_fused_ok)
   float hs[3] = {0.f, 0.f, 0.f};
   float hout = 0.f;
   // Fused packed passes only (xy_fused_ok), with npart set: x is an FP32 work
@@ -155,6 +156,8 @@ hipError_t launch_spec_absmax(const void* spec32, int64_t n, unsigned* dmax, hip
 hipError_t launch_spec_pairs(const void* spec32, void* spec16, const GroupGeom& g, float gs,
                              hipStream_t s);
 hipError_t launch_tw_h2(const void* tw32, void* tw16, int n, hipStream_t s);
+size_t xy16_table_bytes(const GroupGeom& g);
+hipError_t launch_xy16_tables(void* tab, const GroupGeom& g, hipStream_t s);
 
 // Green spectrum: sample the circulant kernel of component ab into
 // work[P3][P2][P1] (c64).

@@ -314,3 +314,36 @@ def test_packed_fp16_block_products(V, n, fused):
     res = float(np.linalg.norm(b - aw) / np.linalg.norm(b))
     print("sampled residual", res)
     assert res < 2e-6
+
+
+# block boxes at the edges of the fused x-y lengths (64: 25..32 cells, 96: 33..48, 128: 49..64),
+# uneven in x and y, with z lines that are full (16, 32, 48 cells) or padded (29, 33, 40)
+@pytest.mark.parametrize("n", [(50, 50, 29), (64, 50, 32), (63, 96, 40), (66, 128, 33),
+                               (96, 50, 48), (97, 70, 16), (128, 98, 32), (128, 128, 29)])
+def test_packed_fp16_planes_of_every_length(V, n):
+    """Two block GMRES steps against FP64 ones.  The basis is rounded to bfloat16 (2^-9 a
+    vector, two vectors, once more through the product of the first), the FP16 transforms add
+    a few 2^-11: below 1e-2 in all."""
+    print("packed planes", n, flush=True)
+    rng = np.random.default_rng(7)
+    h = 0.03
+    g = Grid.centred(n, h)
+    eps = 1.0 + rng.uniform(0.5, 2.0, size=n[::-1])
+    eps[rng.random(eps.shape) < 0.3] = 1.0
+    r = rng.standard_normal((2, 3) + n[::-1]) + 1j * rng.standard_normal((2, 3) + n[::-1])
+    out = {}
+    for prec, inner in ((V.VIE_FP64, V.VIE_FP64), (V.VIE_MIXED, V.VIE_MIXED_BF16)):
+        ctx = V.vie_setup([(eps, h, g.origin)],
+                          V.make_options(K0, precision=prec, flags=V.VIE_FLAG_TIMING))
+        try:
+            out[inner] = V.vie_precond_apply(
+                ctx, V.fgmres_options(blocks=(2, 2), inner_iters=2, inner_precision=inner), r)
+            t = V.vie_kernel_times(ctx, reset=True)
+        finally:
+            V.vie_destroy(ctx)
+        assert (t["block_fft_xy_fwd_h16"][1] > 0) == (inner == V.VIE_MIXED_BF16)
+    for q in range(2):
+        e = (np.linalg.norm(out[V.VIE_MIXED_BF16][q] - out[V.VIE_FP64][q])
+             / np.linalg.norm(out[V.VIE_FP64][q]))
+        print("error", q, e)
+        assert e < 1e-2
