@@ -154,16 +154,19 @@ def kernel_bytes(kind, N, P, Q, epi_extra=0, nb=None, vb=16, vin=None):
     FGMRES products); vin: bytes of an input-vector element when it differs
     (4 for the bfloat16 basis vectors the block products read).  Kinds
     ending in h16 are the packed-FP16 passes: FP16 scratch (4 bytes a
-    point), FP32 vectors."""
+    point), FP32 vectors; grids of short lines (columns_h16) keep only the
+    x-transformed field in it."""
     N1, N2, N3 = N
     P1, P2, P3 = P
     n = N1 * N2 * N3
     c = 16 if kind.endswith("f64") else (4 if kind.endswith("h16") else 8)
     A = 3 * N3 * N2 * P1
     B = 3 * N3 * P2 * P1
-    if kind.startswith("fft_xy_fwd"):  # fused packed x-y: compressed input to y/z scratch
+    if columns_h16(kind, P):
+        B = 3 * N3 * (P2 // 2) * P1
+    if kind.startswith("fft_xy_fwd"):  # compressed input to the x-transformed scratch
         return 3 * nb * ((vin or vb) + 4) + 3 * (N2 * N3 + 1) * 4 + B * c
-    if kind.startswith("fft_yx_inv"):  # fused packed y-x: y/z scratch to compressed output
+    if kind.startswith("fft_yx_inv"):  # and back to the compressed output
         return B * c + 3 * nb * (vb + (vin or vb) + 8 + 4) + 3 * (N2 * N3 + 1) * 4 + epi_extra
     if kind.startswith("fft_x_fwd"):
         if nb is not None:
@@ -182,7 +185,15 @@ def kernel_bytes(kind, N, P, Q, epi_extra=0, nb=None, vb=16, vin=None):
     raise KeyError(kind)
 
 
+def columns_h16(kind, P):
+    """Whether a packed-FP16 pass belongs to the three-pass products of short lines."""
+    short = (64, 96, 128)
+    return kind.endswith("h16") and P[0] in short and P[1] in short and P[2] in (32,) + short
+
+
 def spectrum_bytes(kind, Q):
+    if columns_h16(kind, [2 * (q - 1) for q in Q]):  # FP16 records, four z together
+        return 6 * Q[0] * Q[1] * (Q[2] + 3) // 4 * 16
     if kind.endswith("h16"):  # pair-packed FP16 copy: six 8-byte records per column pair
         return 6 * Q[1] * Q[2] * (Q[0] - 1) * 8
     c = 16 if kind.endswith("f64") else 8

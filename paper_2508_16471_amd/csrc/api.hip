@@ -1834,6 +1834,11 @@ static int bj_prepare(vie_ctx* ctx, BlockPrec& P, const vie_fgmres_options* fo) 
   Gs.zh = 0;
   if (fo->inner_precision == VIE_MIXED_BF16 && h16_ok(Gs.g)) {
     const GroupGeom& g = Gs.g;
+    for (int d = 0; d < 3; ++d) {
+      int e = 0;
+      while (((int64_t)1 << (2 * e)) < g.N[d]) ++e;
+      Gs.hs[d] = ldexpf(1.f, -e);
+    }
     if (!(Gs.zh_gs > 0)) {
       VIE_HIP(Gs.gmax.reserve(sizeof(unsigned)));
       VIE_HIP(hipMemsetAsync(Gs.gmax.p, 0, sizeof(unsigned), ctx->stream));
@@ -1846,27 +1851,25 @@ static int bj_prepare(vie_ctx* ctx, BlockPrec& P, const vie_fgmres_options* fo) 
       memcpy(&mx, &bits, sizeof(mx));
       if (mx > 0.f && std::isfinite(mx)) {
         const float gs = exp2f(-ceilf(log2f(mx)));
-        VIE_HIP(Gs.spec16.reserve((size_t)6 * g.Q[1] * g.Q[2] * (g.P[0] / 2) * 8));
-        VIE_HIP(launch_spec_pairs(Gs.spec32.p, Gs.spec16.p, g, gs, ctx->stream));
-        VIE_HIP(Gs.tw16y.reserve((size_t)g.P[1] * 8));
-        VIE_HIP(launch_tw_h2(Gs.tw32[1].p, Gs.tw16y.p, g.P[1], ctx->stream));
-        VIE_HIP(Gs.tw16z.reserve((size_t)g.P[2] * 8));
-        VIE_HIP(launch_tw_h2(Gs.tw32[2].p, Gs.tw16z.p, g.P[2], ctx->stream));
         if (xy_fused_ok(g)) {
-          VIE_HIP(Gs.dft16.reserve(xy16_table_bytes(g)));
-          VIE_HIP(launch_xy16_tables(Gs.dft16.p, g, ctx->stream));
+          VIE_HIP(Gs.spec16.reserve(spec_cols_bytes(g)));
+          VIE_HIP(launch_spec_cols(Gs.spec32.p, Gs.spec16.p, g, gs, ctx->stream));
+          VIE_HIP(Gs.dft16.reserve(dft16_table_bytes(g)));
+          VIE_HIP(launch_dft16_tables(Gs.dft16.p, g, Gs.hs, ctx->stream));
+        } else {
+          VIE_HIP(Gs.spec16.reserve((size_t)6 * g.Q[1] * g.Q[2] * (g.P[0] / 2) * 8));
+          VIE_HIP(launch_spec_pairs(Gs.spec32.p, Gs.spec16.p, g, gs, ctx->stream));
+          VIE_HIP(Gs.tw16y.reserve((size_t)g.P[1] * 8));
+          VIE_HIP(launch_tw_h2(Gs.tw32[1].p, Gs.tw16y.p, g.P[1], ctx->stream));
+          VIE_HIP(Gs.tw16z.reserve((size_t)g.P[2] * 8));
+          VIE_HIP(launch_tw_h2(Gs.tw32[2].p, Gs.tw16z.p, g.P[2], ctx->stream));
         }
         Gs.zh_gs = gs;
       }
     }
     if (Gs.zh_gs > 0) {
       float prod = Gs.zh_gs;
-      for (int d = 0; d < 3; ++d) {
-        int e = 0;
-        while (((int64_t)1 << (2 * e)) < Gs.g.N[d]) ++e;
-        Gs.hs[d] = ldexpf(1.f, -e);
-        prod *= Gs.hs[d];
-      }
+      for (int d = 0; d < 3; ++d) prod *= Gs.hs[d];
       Gs.hout = 1.f / prod;  // a power of two: exact
       Gs.zh = 1;
     }

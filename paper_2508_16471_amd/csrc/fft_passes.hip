@@ -695,7 +695,9 @@ static hipError_t z_pass(const GroupGeom& g, cpx<T>* B, const cpx<T>* spec, cons
 // the FP32 rate) with both scratch buffers in FP16: a cpx<h2> holds columns
 // 2p and 2p + 1 of one row, so the FP32 layouts apply with every stride
 // halved and pair indices for columns.  The x passes transform in FP32 and
-// convert at the scratch side.
+// convert at the scratch side.  Grids of short lines (xy_fused_ok) run the same
+// transforms, at the same scales, in three passes on the matrix cores instead
+// (fft_mm16.hip); the passes here take the others (FFT 64 x 48, say).
 //
 // Range: the input is a unit-norm basis vector x.  Each forward pass scales
 // its input by a power of two h_d <= 1 / sqrt(N_d) (N_d the box extent along
@@ -1094,9 +1096,10 @@ hipError_t x_inv_c(const GroupGeom& g, const cpx<T>* A, const void* x, void* y, 
                    const cpx<T>* tw, const BodyIdx& bi, EpiArgs& e, const int* active,
                    hipStream_t s, float hs = 0.f);
 
-// fused x-y passes of the packed products (fft_xy16.hip)
-hipError_t xy_fwd_h2(const MatvecArgs& m, const void* xc, void* B, hipStream_t s);
-hipError_t yx_inv_h2(const MatvecArgs& m, const void* B, const void* x, void* y, hipStream_t s);
+// packed products of short lines on the matrix cores (fft_mm16.hip)
+hipError_t x16_fwd(const MatvecArgs& m, const void* xc, void* A, hipStream_t s);
+hipError_t yz16_green(const MatvecArgs& m, void* A, hipStream_t s);
+hipError_t x16_inv(const MatvecArgs& m, const void* A, const void* x, void* y, hipStream_t s);
 
 // fused x-y passes of short lines (fft_plane.hip)
 template <typename T>
@@ -1136,11 +1139,11 @@ static hipError_t matvec_t(const MatvecArgs& m, const void* xv, void* yv, EpiArg
       const cpx<h2>* twy = (const cpx<h2>*)m.tw16[0];
       const cpx<h2>* twz = (const cpx<h2>*)m.tw16[1];
       base = kH16Kind0;
-      if (xy_fused_ok(g)) {  // x and y fused per plane: no x-y scratch traffic
-        STEP(5, xy_fwd_h2(m, xv, Bh, s));
-        STEP(2, z_pass_h2(g, Bh, (const cpx<h2>*)m.spec16, twz, m.hs[2], m.active, s));
+      if (xy_fused_ok(g)) {  // three passes over an x-transformed scratch
+        STEP(5, x16_fwd(m, xv, Ah, s));
+        STEP(2, yz16_green(m, Ah, s));
         // with a normalised input the epilogue's x is the stored bfloat16 vector
-        STEP(6, yx_inv_h2(m, Bh, m.npart ? m.vout : xv, yv, s));
+        STEP(6, x16_inv(m, Ah, m.npart ? m.vout : xv, yv, s));
         return hipSuccess;
       }
       if (m.npart) return hipErrorInvalidValue;

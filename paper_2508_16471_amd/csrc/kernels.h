@@ -94,16 +94,17 @@ struct MatvecArgs {
   int io32 = 0;  // compressed x and y stored in FP32 (FP32 passes, plain epilogue only);
                  // 2: x stored in bfloat16, y in FP32
   // Approximate products (FP32, bfloat16 x, FP32 y, plain epilogue): with
-  // spec16 set the y and z passes run in packed FP16 arithmetic on FP16
-  // scratch (see h16_ok for the grids this takes): spec16 the scaled
-  // pair-packed spectrum, tw16 the splatted y and z twiddles, hs the forward
-  // scales along x, y, z, hout the inverse x pass's scale back.
+  // spec16 set the y and z transforms are FP16 transforms on FP16 scratch (see
+  // h16_ok for the grids this takes): spec16 the scaled FP16 spectrum, hs the
+  // forward scales along x, y, z, hout the inverse x pass's scale back.  Grids
+  // of short lines (xy_fused_ok) run three passes on the matrix cores with the
+  // operand tables dft16, others five with the splatted twiddles tw16.
   const void* spec16 = nullptr;
   const void* tw16[2] = {nullptr, nullptr};
-  const void* dft16 = nullptr;  // operand tables of the fused x-y passes (xy_fused_ok)
+  const void* dft16 = nullptr;
   float hs[3] = {0.f, 0.f, 0.f};
   float hout = 0.f;
-  // Fused packed passes only (xy_fused_ok), with npart set: x is an FP32 work
+  // Three-pass products only (xy_fused_ok), with npart set: x is an FP32 work
   // vector w; right-hand side q of it is scaled by 1 / ||w_q|| (||w_q||^2
   // summed from the nblk partials npart[q nblk ..] in a fixed order and
   // stored at nrm[q ldn]) and rounded to bfloat16, that vector is stored at
@@ -142,22 +143,28 @@ hipError_t launch_matvec(const MatvecArgs& a, int precision, const void* x, void
 int z_variants(int precision);  // z-pass launch shapes (0 = FP64, 1 = FP32)
 // z pass alone on bufB (autotuning; contents are scratch)
 hipError_t launch_z_only(const MatvecArgs& a, int precision, hipStream_t s);
-// Packed-FP16 y and z passes of approximate FP32 products: whether the grid
-// takes them, and their tables: max |re|, |im| of an FP32 octant spectrum (n
-// complex values) as float bits atomically maxed into *dmax (zeroed by the
-// caller), the pair-packed FP16 copy scaled by gs (Q2 Q3 P1/2 6 packed
-// pairs, 8 bytes each), the splatted FP16 twiddles of n points.
+// Packed-FP16 transforms of approximate FP32 products: whether the grid takes
+// them, and whether in three passes on the matrix cores (fft_mm16.hip).
 bool h16_ok(const GroupGeom& g);
-// timing kinds of their passes: the five separate ones (26..30), then the
-// fused x-y forward and inverse passes (31, 32) of grids xy_fused_ok takes
-static constexpr int kH16Kind0 = 26;
 bool xy_fused_ok(const GroupGeom& g);
+// timing kinds: the five separate passes (26..30); the three passes are z (28)
+// between xy_fwd and yx_inv (31, 32), the x passes before and after it
+static constexpr int kH16Kind0 = 26;
+// max |re|, |im| of an FP32 octant spectrum (n complex values) as float bits
+// atomically maxed into *dmax (zeroed by the caller)
 hipError_t launch_spec_absmax(const void* spec32, int64_t n, unsigned* dmax, hipStream_t s);
+// Tables of the five passes: the pair-packed FP16 spectrum scaled by gs (Q2 Q3
+// P1/2 6 packed pairs, 8 bytes each), the splatted FP16 twiddles of n points.
 hipError_t launch_spec_pairs(const void* spec32, void* spec16, const GroupGeom& g, float gs,
                              hipStream_t s);
 hipError_t launch_tw_h2(const void* tw32, void* tw16, int n, hipStream_t s);
-size_t xy16_table_bytes(const GroupGeom& g);
-hipError_t launch_xy16_tables(void* tab, const GroupGeom& g, hipStream_t s);
+// Tables of the three passes: DFT operands (with the forward scales) and the
+// FP16 spectrum scaled by gs, four z of an entry together.
+size_t dft16_table_bytes(const GroupGeom& g);
+hipError_t launch_dft16_tables(void* tab, const GroupGeom& g, const float hs[3], hipStream_t s);
+size_t spec_cols_bytes(const GroupGeom& g);
+hipError_t launch_spec_cols(const void* spec32, void* out, const GroupGeom& g, float gs,
+                            hipStream_t s);
 
 // Green spectrum: sample the circulant kernel of component ab into
 // work[P3][P2][P1] (c64).
