@@ -339,25 +339,39 @@ __global__ __launch_bounds__(256, 4) void k_x16_fwd(
 //
 // What bounds it is arithmetic: vector instructions (the spectrum's 18 dot
 // products a point, conversions) take half of its time, the matrix cores a
-// quarter, and two waves a SIMD overlap them only in part.  Few wide waves (61
-// KB of LDS a workgroup of four for 128 x 64) load each table and record for
-// twice the points; eight narrow ones, each with one of j, -j, were bound by the
-// vector cache.  128 x 128 x 64, 29 planes, 32 right-hand sides: 126 us (153
-// with narrow waves; 137 with pairs formed before the spectrum), x passes 48 and
-// 51 us.  Before, with the y lines in HBM: packed Stockham passes x-y 102, z
-// 137, y-x 101 us; the same with x and y on the matrix cores 82, 139, 82 us.
+// quarter, and few waves overlap them only in part.  Wide waves load each table
+// and record for twice the points (narrow ones, each with one of j, -j, were
+// bound by the vector cache); the two of a pair go through the spectrum one
+// after the other and rows are not padded, so that three workgroups of four
+// waves share a CU (49 KB of LDS, 168 registers, for 128 x 64).  128 x 128 x 64,
+// 29 planes, 32 right-hand sides: 116 us (153 with narrow waves; 137 with the
+// pairs kz, -kz formed before the spectrum, 126 without; two workgroups until
+// here), x passes 50 and 52 us.  Before, with the y lines in HBM: packed
+// Stockham passes x-y 102, z 137, y-x 101 us; the same with x and y on the
+// matrix cores 82, 139, 82 us.
 template <int P2, int P3>
 struct Yz16 {
   static constexpr int H2 = P2 / 2, H3 = P3 / 2;
   static constexpr int TY = H2 / 16, TZ = H3 / 16;
   static constexpr int NW = TY, NT = 64 * NW;
   static constexpr int KY = (H2 + 31) / 32, KZ = (H3 + 31) / 32, KI = P2 / 32;
-  // rows 16 bytes apart in the banks: the column as loaded, the z lines, the y lines
-  static constexpr int CS = P2 + 8, ZS = H3 + 8, KS = P2 + 8;
-  static constexpr int L0 = 3 * H3 * CS, L1 = 6 * P2 * ZS, L2 = 6 * H3 * KS;
+  // the column as loaded, the z lines, the y lines.  16-byte pieces of a row are
+  // rotated by the row where its length is a power of two, else rows are padded
+  // by one piece: neighbouring rows' pieces lie in different banks
+  static constexpr bool YR = P2 != 96, ZR = H3 != 48;
+  static constexpr int CS = YR ? P2 : P2 + 8, ZS = ZR ? H3 : H3 + 8;
+  static constexpr int L0 = 3 * H3 * CS, L1 = 6 * P2 * ZS, L2 = 6 * H3 * CS;
+  static __device__ __forceinline__ int ypos(int row, int y) {  // of L0, L2
+    return row * CS + (YR ? y ^ ((row & 7) << 3) : y);
+  }
+  static __device__ __forceinline__ int zpos(int row, int z) {
+    constexpr int M = H3 / 8 - 1;  // pieces of a row - 1
+    return row * ZS + (ZR ? z ^ (((row / (8 / (M < 7 ? M + 1 : 8))) & M) << 3) : z);
+  }
   static constexpr int LDS = L1 > L2 ? (L1 > L0 ? L1 : L0) : (L2 > L0 ? L2 : L0);
   static constexpr int FIT = 160 * 1024 / (2 * LDS) * NW / 4;  // waves per SIMD the LDS holds
-  static constexpr int WPE = FIT > 2 ? 2 : FIT < 1 ? 1 : FIT;  // and the registers
+  static constexpr int CAP = TZ > 2 ? 1 : 3;                   // and the registers
+  static constexpr int WPE = FIT > CAP ? CAP : FIT < 1 ? 1 : FIT;
 };
 
 // o += g v in FP32, from g' = (g.re, -g.im): v = (re, im) gives the real part,
@@ -435,7 +449,7 @@ __global__ __launch_bounds__(NT, WPE) void k_yz16_green(
 #pragma unroll
     for (int n = 0; n < (N + S::NT - 1) / S::NT; ++n) {
       const int i = min(tid + n * S::NT, N - 1);
-      *reinterpret_cast<half8*>(buf + i / C * S::CS + i % C * 8) = v[n];
+      *reinterpret_cast<half8*>(buf + S::ypos(i / C, i % C * 8)) = v[n];
     }
   }
   lds_barrier();
@@ -445,9 +459,9 @@ __global__ __launch_bounds__(NT, WPE) void k_yz16_green(
     for (int t = 0; t < 3 * TZ; ++t)
 #pragma unroll
       for (int ks = 0; ks < S::KY; ++ks) {
-        const _Float16* row = buf + (t * 16 + l16) * S::CS + min(ks * 32 + 8 * quad, H2 - 8);
-        re[t][ks] = *reinterpret_cast<const half8*>(row);
-        im[t][ks] = *reinterpret_cast<const half8*>(row + H2);
+        const int y = min(ks * 32 + 8 * quad, H2 - 8);
+        re[t][ks] = *reinterpret_cast<const half8*>(buf + S::ypos(t * 16 + l16, y));
+        im[t][ks] = *reinterpret_cast<const half8*>(buf + S::ypos(t * 16 + l16, H2 + y));
       }
     const half8* tb = a.tab + off.yf + wave * S::KY * 64 + lane;
     half8 c[S::KY], sn[S::KY];
@@ -475,7 +489,8 @@ __global__ __launch_bounds__(NT, WPE) void k_yz16_green(
         hr = round4(u);
         hi = round4(q);
       }
-      _Float16* o = buf + (t / TZ * 2 * P2 + j) * S::ZS + t % TZ * 16 + 4 * quad;
+      // (H2 and P2 rows further the rotation is the same)
+      _Float16* o = buf + S::zpos(t / TZ * 2 * P2 + j, t % TZ * 16 + 8 * (quad / 2)) + 4 * (quad & 1);
       *reinterpret_cast<half4*>(o) = lr;
       *reinterpret_cast<half4*>(o + H2 * S::ZS) = hr;
       *reinterpret_cast<half4*>(o + P2 * S::ZS) = li;
@@ -500,34 +515,33 @@ __global__ __launch_bounds__(NT, WPE) void k_yz16_green(
   for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int comp = 0; comp < 3; ++comp) {
-      const _Float16* row = buf + (comp * 2 * P2 + h * H2 + yo) * S::ZS;
 #pragma unroll
       for (int ks = 0; ks < KZ; ++ks) {
-        const int z = min(ks * 32 + 8 * quad, H3 - 8);
-        vr[h][comp][ks] = *reinterpret_cast<const half8*>(row + z);
-        vi[h][comp][ks] = *reinterpret_cast<const half8*>(row + P2 * S::ZS + z);
+        const _Float16* row =
+            buf + S::zpos(comp * 2 * P2 + h * H2 + yo, min(ks * 32 + 8 * quad, H3 - 8));
+        vr[h][comp][ks] = *reinterpret_cast<const half8*>(row);
+        vi[h][comp][ks] = *reinterpret_cast<const half8*>(row + P2 * S::ZS);
       }
     }
   lds_barrier();  // every wave has read its lines
   // half the sum (re, im) and half the difference (re, -im) of each component's
   // pair, two points a register; X[0] and X[P3 / 2] (im, re) in the first
-  unsigned op[2][3][4][4 * KZ];
-  if constexpr (TZ & 1) {
 #pragma unroll
-    for (int c = 0; c < 24; ++c)
-      op[c / 12][c / 4 % 3][c % 4][4 * KZ - 2] = op[c / 12][c / 4 % 3][c % 4][4 * KZ - 1] = 0;
-  }
+  for (int h = 0; h < 2; ++h) {
+    unsigned op[3][4][4 * KZ];
+    if constexpr (TZ & 1) {
 #pragma unroll
-  for (int zt = 0; zt < TZ; ++zt) {
-    const half8* tb = a.tab + off.zf + zt * KZ * 64 + lane;
-    half8 tc[KZ], ts[KZ];
-#pragma unroll
-    for (int ks = 0; ks < KZ; ++ks) {
-      tc[ks] = tb[ks * 64];
-      ts[ks] = tb[(TZ * KZ + ks) * 64];
+      for (int c = 0; c < 12; ++c) op[c / 4][c % 4][4 * KZ - 2] = op[c / 4][c % 4][4 * KZ - 1] = 0;
     }
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int zt = 0; zt < TZ; ++zt) {
+      const half8* tb = a.tab + off.zf + zt * KZ * 64 + lane;
+      half8 tc[KZ], ts[KZ];
+#pragma unroll
+      for (int ks = 0; ks < KZ; ++ks) {
+        tc[ks] = tb[ks * 64];
+        ts[ks] = tb[(TZ * KZ + ks) * 64];
+      }
       unsigned lo[3][4], hi[3][4];
 #pragma unroll
       for (int comp = 0; comp < 3; ++comp) {
@@ -553,10 +567,6 @@ __global__ __launch_bounds__(NT, WPE) void k_yz16_green(
 #pragma unroll
       for (int c = 0; c < 12; ++c)
         asm volatile("" : "+v"(lo[c / 4][c % 4]), "+v"(hi[c / 4][c % 4]));
-      if (h == 1 && wave == 0) {  // the record of P2 / 2 in lane 0's slot of -0
-#pragma unroll
-        for (int c = 0; c < 6; ++c) rec[c] = sp[((zt * 4 + quad) * 6 + c) * Q2 + skip];
-      }
       unsigned gn[6];
       if (zt == 0) {
 #pragma unroll
@@ -617,34 +627,33 @@ __global__ __launch_bounds__(NT, WPE) void k_yz16_green(
         }
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
-          unsigned& w = op[h][c / 4][c % 4][2 * zt + i / 2];
+          unsigned& w = op[c / 4][c % 4][2 * zt + i / 2];
           w = pack_c(o[0][c / 4][c % 4], o[1][c / 4][c % 4]);
           asm volatile("" : "+v"(w));
         }
       }
+      // the next records; P2 / 2's in lane 0's slot of -0
+      if (zt + 1 < TZ || h == 0) {
+        const int zn = zt + 1 < TZ ? zt + 1 : 0, at = h == 1 || zt + 1 == TZ ? skip : 0;
+#pragma unroll
+        for (int c = 0; c < 6; ++c) rec[c] = sp[((zn * 4 + quad) * 6 + c) * Q2 + at];
+      }
     }
-    if (zt + 1 < TZ) {
+    // z inverse, into [component][re, im][z][y slot]
 #pragma unroll
-      for (int c = 0; c < 6; ++c) rec[c] = sp[(((zt + 1) * 4 + quad) * 6 + c) * Q2];
-    }
-  }
-  // z inverse, into [component][re, im][z][y slot]
+    for (int zt = 0; zt < TZ; ++zt) {
+      const half8* tb = a.tab + off.zi + zt * KZ * 64 + lane;
+      half8 tc[KZ], ts[KZ];
 #pragma unroll
-  for (int zt = 0; zt < TZ; ++zt) {
-    const half8* tb = a.tab + off.zi + zt * KZ * 64 + lane;
-    half8 tc[KZ], ts[KZ];
-#pragma unroll
-    for (int ks = 0; ks < KZ; ++ks) {
-      tc[ks] = tb[ks * 64];
-      ts[ks] = tb[(TZ * KZ + ks) * 64];
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
+      for (int ks = 0; ks < KZ; ++ks) {
+        tc[ks] = tb[ks * 64];
+        ts[ks] = tb[(TZ * KZ + ks) * 64];
+      }
 #pragma unroll
       for (int comp = 0; comp < 3; ++comp) {
         f32x4 re = 0.f, im = 0.f;
         auto frag = [&](int k, int ks) {
-          const unsigned* o = op[h][comp][k] + 4 * ks;
+          const unsigned* o = op[comp][k] + 4 * ks;
           return __builtin_bit_cast(half8, u32x4{o[0], o[1], o[2], o[3]});
         };
 #pragma unroll
@@ -654,10 +663,11 @@ __global__ __launch_bounds__(NT, WPE) void k_yz16_green(
           re = mma16(frag(3, ks), ts[ks], re);
           im = mma16(frag(2, ks), ts[ks], im);
         }
-        _Float16* o = buf + (comp * 2 * H3 + zt * 16 + l16) * S::KS + h * H2 + wave * 16 + 4 * quad;
-        *reinterpret_cast<half4*>(o) = round4(re);
-        *reinterpret_cast<half4*>(o + H3 * S::KS) = round4(im);
+        const int z = comp * 2 * H3 + zt * 16 + l16, k = h * H2 + wave * 16 + 8 * (quad / 2);
+        *reinterpret_cast<half4*>(buf + S::ypos(z, k) + 4 * (quad & 1)) = round4(re);
+        *reinterpret_cast<half4*>(buf + S::ypos(z + H3, k) + 4 * (quad & 1)) = round4(im);
       }
+    }
   }
   {  // y inverse: the wave's 16 points
     const half8* tb = a.tab + off.yi + wave * S::KI * 64 + lane;
@@ -671,12 +681,12 @@ __global__ __launch_bounds__(NT, WPE) void k_yz16_green(
 #pragma unroll
     for (int t = 0; t < 3 * TZ; ++t) {
       const int comp = t / TZ, z = t % TZ * 16 + l16;
-      const _Float16* row = buf + (comp * 2 * H3 + z) * S::KS + 8 * quad;
       f32x4 r1 = 0.f, r2 = 0.f, i1 = 0.f, i2 = 0.f;
 #pragma unroll
       for (int ks = 0; ks < S::KI; ++ks) {
-        const half8 gr = *reinterpret_cast<const half8*>(row + ks * 32);
-        const half8 gi = *reinterpret_cast<const half8*>(row + H3 * S::KS + ks * 32);
+        const int k = ks * 32 + 8 * quad;
+        const half8 gr = *reinterpret_cast<const half8*>(buf + S::ypos(comp * 2 * H3 + z, k));
+        const half8 gi = *reinterpret_cast<const half8*>(buf + S::ypos(comp * 2 * H3 + H3 + z, k));
         r1 = mma16(c[ks], gr, r1);
         r2 = mma16(sn[ks], gi, r2);
         i1 = mma16(c[ks], gi, i1);
@@ -813,8 +823,8 @@ bool xy_fused_ok(const GroupGeom& g) {
 
 // The lengths divide into the products' tiles, and a plane and a column fit the
 // LDS.  (Three passes, us, before and after, FFT lengths x, y, z with 32
-// right-hand sides: 64 96 96: 234, 180; 96 64 96: 241, 173; 96 128 96: 415, 284;
-// 128 64 64: 160, 127; 128 128 64: 340, 225; 64 64 64 with 8: 51, 35.)
+// right-hand sides: 64 96 96: 234, 180; 96 64 96: 241, 178; 96 128 96: 415, 300;
+// 128 64 64: 160, 125; 128 128 64: 340, 218; 64 64 64 with 8: 51, 35.)
 static bool x16_args(const MatvecArgs& m, X16Args* a) {
   const GroupGeom& g = *m.g;
   if (!xy_fused_ok(g) || !m.dft16 || !m.bi) return false;
