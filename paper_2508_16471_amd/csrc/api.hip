@@ -223,8 +223,8 @@ struct BlockPrec {
 // block-Jacobi sub-context (15..24, same order as 0..9), the Arnoldi
 // vector kernels of FGMRES (25), and the packed-FP16 passes of approximate
 // FP32 products (26..32 the context's own: the five passes in the order of
-// 0..4, then the fused x-y forward and inverse passes; 33..39 the block
-// solves').
+// 0..4, then the x passes of the three-pass products, whose y-z pass counts
+// as z; 33..39 the block solves').
 static const char* kKindNames[] = {
     "fft_x_fwd_f64",       "fft_y_fwd_f64",       "fft_z_green_f64",       "fft_y_inv_f64",
     "fft_x_inv_f64",       "fft_x_fwd_f32",       "fft_y_fwd_f32",         "fft_z_green_f32",

@@ -337,18 +337,17 @@ __global__ __launch_bounds__(256, 4) void k_x16_fwd(
 // next one's operand layout with its k permuted, so nothing is exchanged but
 // the y-z transpositions.
 //
-// What bounds it is arithmetic: vector instructions (the spectrum's 18 dot
-// products a point, conversions) take half of its time, the matrix cores a
-// quarter, and few waves overlap them only in part.  Wide waves load each table
-// and record for twice the points (narrow ones, each with one of j, -j, were
-// bound by the vector cache); the two of a pair go through the spectrum one
-// after the other and rows are not padded, so that three workgroups of four
-// waves share a CU (49 KB of LDS, 168 registers, for 128 x 64).  128 x 128 x 64,
-// 29 planes, 32 right-hand sides: 116 us (153 with narrow waves; 137 with the
-// pairs kz, -kz formed before the spectrum, 126 without; two workgroups until
-// here), x passes 50 and 52 us.  Before, with the y lines in HBM: packed
-// Stockham passes x-y 102, z 137, y-x 101 us; the same with x and y on the
-// matrix cores 82, 139, 82 us.
+// What bounds it is instruction issue: vector instructions (the spectrum's 18
+// dot products a point, conversions) take 64 % of its cycles, the matrix cores
+// 30 %, and the two add up.  Wide waves load each table and record for twice
+// the points (narrow ones, each with one of j, -j, were bound by the vector
+// cache); the two of a pair go through the spectrum one after the other and
+// rows are not padded, so that three workgroups of four waves share a CU (49 KB
+// of LDS, 168 registers, for 128 x 64).  128 x 128 x 64, 29 planes, 32 right-
+// hand sides: 116 us (153 with narrow waves; 137 with the pairs kz, -kz formed
+// before the spectrum, 126 without; two workgroups until here), x passes 50 and
+// 52 us.  Before, with the y lines in HBM: packed Stockham passes x-y 102, z
+// 137, y-x 101 us; the same with x and y on the matrix cores 82, 139, 82 us.
 template <int P2, int P3>
 struct Yz16 {
   static constexpr int H2 = P2 / 2, H3 = P3 / 2;
