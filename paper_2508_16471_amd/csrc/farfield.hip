@@ -306,7 +306,13 @@ __global__ void k_far_frames(const double* __restrict__ ang, const int* __restri
 
 struct FfGeom {
   double k0, h, o[3];
-  int bx, by;
+};
+
+// The tile groups of one launch: group g's K-splits start at ks0[g] and end at
+// the next group's, its tiles are tile0[g] .. + ntiles[g] - 1, its blocks bx[g] x by[g] x (16 / bx / by).
+struct FfGroups {
+  int n;
+  int ks0[kNumShapes], tile0[kNumShapes], ntiles[kNumShapes], bx[kNumShapes], by[kNumShapes];
 };
 
 // sin and cos of x for |x| < 1e9: Cody-Waite reduction by pi/2 with a two-part
@@ -500,10 +506,21 @@ __global__ __launch_bounds__(256) void k_ff_columns(FarSrc f, const int* __restr
 // tile) with a register prefetch; two waves per SIMD so that one wave's scale-
 // and-accumulate and phase work runs while the other's matrix products execute.
 __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))) void k_ff_mfma(
-    const c64* __restrict__ Wd, int64_t wq, const int4* __restrict__ org, int ntiles,
+    const c64* __restrict__ Wd, int64_t wq, const int4* __restrict__ org, FfGroups gs,
     int tiles_per_split, const double* __restrict__ dirs, const int4* __restrict__ dt, int g0,
-    int npos, FfGeom fg, c64* __restrict__ part, int kst, int ks0) {
-  Wd += blockIdx.z * wq;
+    int npos, FfGeom fg, c64* __restrict__ part, int kst) {
+  int ks0 = 0, ntiles = gs.ntiles[0], bx = gs.bx[0], by = gs.by[0], tile0 = gs.tile0[0];
+#pragma unroll
+  for (int g = 1; g < kNumShapes; ++g)
+    if (g < gs.n && (int)blockIdx.y >= gs.ks0[g]) {
+      ks0 = gs.ks0[g];
+      ntiles = gs.ntiles[g];
+      bx = gs.bx[g];
+      by = gs.by[g];
+      tile0 = gs.tile0[g];
+    }
+  Wd += blockIdx.z * wq + (int64_t)tile0 * FF_TILE;
+  org += (int64_t)tile0 * FF_TB;
   int first = blockIdx.x * FF_DIRS, nd = npos;
   if (dt) {
     const int4 t = dt[blockIdx.x];
@@ -521,7 +538,7 @@ __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))
     sT[k] = mk(cs, sn);
   }  // visible after the first barrier of the tile loop
   const int dbase = first + wave * 16;
-  const int t0 = blockIdx.y * tiles_per_split;
+  const int t0 = ((int)blockIdx.y - ks0) * tiles_per_split;
   const int t1 = min(ntiles, t0 + tiles_per_split);
 
   // left operand A(r, u): direction dbase + lane%16, offsets u = 4 ks + lane/16
@@ -537,7 +554,7 @@ __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       const int u = 4 * ks + (lane >> 4);
-      const int du = u % fg.bx, dv = (u / fg.bx) % fg.by, dw = u / (fg.bx * fg.by);
+      const int du = u % bx, dv = (u / bx) % by, dw = u / (bx * by);
       const double ang = -fg.k0 * fg.h * (rx * du + ry * dv + rz * dw);
       double sn, cs;
       ff_sincos(ang, sn, cs);
@@ -603,8 +620,7 @@ __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))
       if (d >= nd) continue;
 #pragma unroll
       for (int qc = 0; qc < FF_QC; ++qc)
-        part[(((int64_t)blockIdx.z * npos + d) * FF_QC + qc) * kst + ks0 + blockIdx.y] =
-            acc[r][qc];
+        part[(((int64_t)blockIdx.z * npos + d) * FF_QC + qc) * kst + blockIdx.y] = acc[r][qc];
     }
   }
 }
@@ -672,8 +688,11 @@ static hipError_t far_project_sums(const c64* part, int kst, int npair, int nd,
   return hipGetLastError();
 }
 
-// Workgroups wanted in one launch: the chip holds 512 (two per CU).
-static constexpr int kFarBlocks = 1024;
+// Workgroups wanted in one launch: the chip holds 512 (two per CU), and a
+// workgroup's own tables cost about as much as three tiles.  181 directions of
+// two channels of the 128-cell metasurface: 94 us a call with 512, 104 with
+// 1024, 107 with 2048.
+static constexpr int kFarBlocks = 512;
 
 // K-splits of `ntiles` tiles when `blocks` workgroups exist without a split.
 static int far_split(int ntiles, int blocks) {
@@ -682,6 +701,14 @@ static int far_split(int ntiles, int blocks) {
   const int ks = std::min(ntiles, want);
   const int tps = (ntiles + ks - 1) / ks;
   return (ntiles + tps - 1) / tps;
+}
+
+// Tiles per split of a launch over every group of `fb`.
+static int far_tps(const FarBlocks& fb, int blocks) {
+  int nt = 0;
+  for (const FarGroup& gr : fb.groups) nt += gr.ntiles;
+  const int want = std::max(1, kFarBlocks / std::max(1, blocks));
+  return std::max(1, (nt + want - 1) / want);
 }
 
 FarPlan far_plan(const FarBlocks& fb, int nr, int nd) {
@@ -693,8 +720,9 @@ FarPlan far_plan(const FarBlocks& fb, int nr, int nd) {
   const int db = (nd + FF_DIRS - 1) / FF_DIRS;
   p.nq = (int)std::max<int64_t>(1, std::min<int64_t>(nr, kCap / wb));
   for (;;) {
+    p.tps = far_tps(fb, db * p.nq);
     p.kst = 0;
-    for (const FarGroup& gr : fb.groups) p.kst += far_split(gr.ntiles, db * p.nq);
+    for (const FarGroup& gr : fb.groups) p.kst += (gr.ntiles + p.tps - 1) / p.tps;
     if (p.nq == 1 || (int64_t)p.nq * nd * FF_QC * p.kst * (int64_t)sizeof(c64) <= kCap) break;
     p.nq = (p.nq + 1) / 2;
   }
@@ -752,8 +780,11 @@ hipError_t launch_farfield_sweep(const FarSrc& src, int nr, const FarColumns& fc
   fg.k0 = geo.k0;
   fg.h = geo.h;
   for (int a = 0; a < 3; ++a) fg.o[a] = geo.o[a];
-  fg.bx = fc.bx;
-  fg.by = fc.by;
+  FfGroups gs = {};
+  gs.n = 1;
+  gs.ntiles[0] = fc.ntiles;
+  gs.bx[0] = fc.bx;
+  gs.by[0] = fc.by;
   for (int q0 = 0; q0 < nr; q0 += pl.nq) {
     const int nq = std::min(pl.nq, nr - q0);
     FarSrc f = src;
@@ -766,8 +797,8 @@ hipError_t launch_farfield_sweep(const FarSrc& src, int nr, const FarColumns& fc
       if (e != hipSuccess) return e;
       const int d0 = gr.tile0[g0], d1 = gr.tile0[g0 + n];
       k_ff_mfma<<<dim3(d1 - d0, pl.kst, nq), FF_DIRS * 4, 0, s>>>(
-          Wd, (int64_t)n * fc.ntiles * FF_TILE, (const int4*)org, fc.ntiles, tps, dirs,
-          (const int4*)tile + d0, g0, nd, fg, part, pl.kst, 0);
+          Wd, (int64_t)n * fc.ntiles * FF_TILE, (const int4*)org, gs, tps, dirs,
+          (const int4*)tile + d0, g0, nd, fg, part, pl.kst);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
@@ -788,6 +819,23 @@ hipError_t launch_farfield_mfma(const FarSrc& src, int nr, const FarBlocks& fb, 
   for (int a = 0; a < 3; ++a) fg.o[a] = geo.o[a];
   const int db = (nd + FF_DIRS - 1) / FF_DIRS;
   const int64_t tot = (int64_t)ntiles * FF_TILE;
+  // every block shape in one launch, all splits equally long: launched one
+  // after the other, each split to fill the chip, the three shapes of the
+  // 128-cell metasurface took 85 us of a 146 us call (181 directions, two
+  // channels), mostly the workgroups' own tables for 2 tiles each; 94 us a call now
+  FfGroups gs = {};
+  int ks = 0;
+  for (const FarGroup& gr : fb.groups) {
+    if (gr.ntiles < 1) continue;
+    if (gs.n == kNumShapes) return hipErrorInvalidValue;
+    gs.ks0[gs.n] = ks;
+    gs.tile0[gs.n] = gr.tile0;
+    gs.ntiles[gs.n] = gr.ntiles;
+    gs.bx[gs.n] = gr.shape[0];
+    gs.by[gs.n++] = gr.shape[1];
+    ks += (gr.ntiles + pl.tps - 1) / pl.tps;
+  }
+  if (ks != pl.kst) return hipErrorInvalidValue;
   for (int q0 = 0; q0 < nr; q0 += pl.nq) {
     const int nq = std::min(pl.nq, nr - q0);
     FarSrc f = src;
@@ -795,20 +843,12 @@ hipError_t launch_farfield_mfma(const FarSrc& src, int nr, const FarBlocks& fb, 
     k_ff_pack<<<dim3((unsigned)((tot + 255) / 256), nq), 256, 0, s>>>(f, blk_vi, ntiles, Wd);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // one launch per block shape; each writes its own range of K-split partials
-    int ks0 = 0;
-    for (const FarGroup& gr : fb.groups) {
-      const int ks = far_split(gr.ntiles, db * pl.nq);
-      if (ks == 0) continue;
-      const int tps = (gr.ntiles + ks - 1) / ks;
-      fg.bx = gr.shape[0];
-      fg.by = gr.shape[1];
-      k_ff_mfma<<<dim3(db, ks, nq), FF_DIRS * 4, 0, s>>>(
-          Wd + (int64_t)gr.tile0 * FF_TILE, tot, (const int4*)blk_org + (int64_t)gr.tile0 * FF_TB,
-          gr.ntiles, tps, dirs, nullptr, 0, nd, fg, part, pl.kst, ks0);
+    if (pl.kst > 0) {
+      k_ff_mfma<<<dim3(db, pl.kst, nq), FF_DIRS * 4, 0, s>>>(Wd, tot, (const int4*)blk_org, gs,
+                                                             pl.tps, dirs, nullptr, 0, nd, fg, part,
+                                                             pl.kst);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
-      ks0 += ks;
     }
     e = far_project_sums(part, pl.kst, nq * nd, nd, dirs, nullptr, geo, F + (int64_t)q0 * nd * 2,
                          s);

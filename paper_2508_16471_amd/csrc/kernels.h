@@ -241,7 +241,7 @@ void far_blocks_build(const int* vox, int nb, const int N[3], FarBlocks& fb);
 // launch, K-split partials per (right-hand side, direction, component), and
 // the scratch it needs (c64 counts of the packed operand and the partials).
 struct FarPlan {
-  int nq = 1, kst = 0;
+  int nq = 1, kst = 0, tps = 1;  // tps: tiles per split
   size_t wd = 0, part = 0;
 };
 FarPlan far_plan(const FarBlocks& fb, int nr, int nd);

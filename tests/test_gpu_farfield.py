@@ -197,3 +197,30 @@ def test_farfield_sweep_by_theta_matches_direct_path(V, order, shape, window):
             assert _relerr(F[q][some], np.stack([ft, fp], -1)) < 1e-12
     finally:
         V.vie_destroy(ctx)
+
+
+@pytest.mark.parametrize("ndir", [1, 64, 65, 333])
+def test_farfield_block_shapes_share_a_launch(V, ndir):
+    """A slab, y lines and z columns in separate bands of layers: block shapes of one launch
+    with different tile counts, the last split of each shape shorter than the others."""
+    print(f"farfield shapes ndir={ndir}", flush=True)
+    rng = np.random.default_rng(19)
+    g = Grid.centred((45, 43, 40), 0.03)
+    eps = np.ones(g.n[::-1])
+    eps[0:4, 3:41, 2:44] = 2.0
+    eps[8:12, :, 5::7] = 2.5
+    eps[20:40, 4::6, 3::5] = 3.0
+    ctx = V.vie_setup([(eps, g.h, g.origin)], V.make_options(K0, tol=1e-2, max_iter=3))
+    try:
+        chans = _channels(rng, 2)
+        V.vie_solve(ctx, chans, [2], allow_noconv=True)
+        th = np.arccos(rng.uniform(-1, 1, ndir))
+        ph = rng.uniform(-np.pi, np.pi, ndir)
+        F = V.vie_farfield(ctx, 0, th, ph, 2)
+        pos = vd.voxel_centres(g.n, g.h, g.origin)
+        for q in range(2):
+            w = V.vie_get_current(ctx, 0, q, g.n).reshape(3, -1)
+            ft, fp = vd.farfield(w, pos, g.h, K0, th, ph)
+            assert _relerr(F[q], np.stack([ft, fp], -1)) < 1e-12
+    finally:
+        V.vie_destroy(ctx)
