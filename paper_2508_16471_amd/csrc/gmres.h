@@ -96,7 +96,7 @@ hipError_t launch_seg_act_map(int nseg, const int* seg_rhs, const int* act_rhs, 
 // ---------------------------------------------------------------------------
 // Least-squares part of GMRES on the device: the Hessenberg matrix of every
 // segment reduced column by column by complex Givens rotations (c real,
-// s complex), then the triangular solve.  One thread per segment; the
+// s complex), then the triangular solve.  One lane walks a segment's chain; the
 // Hessenberg columns come from the Arnoldi kernels above: column j of all
 // segments at H + j * nseg * ldh, entry i of segment s at [s * ldh + i]
 // (H1 + H2 when both Gram-Schmidt passes ran, use_h2), the subdiagonal as

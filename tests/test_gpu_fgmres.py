@@ -347,3 +347,50 @@ def test_packed_fp16_planes_of_every_length(V, n):
              / np.linalg.norm(out[V.VIE_FP64][q]))
         print("error", q, e)
         assert e < 1e-2
+
+
+@pytest.mark.parametrize("k", [1, 31, 32, 33])
+def test_block_least_squares_of_every_size(V, k):
+    """Block solves whose least squares fit one wave's LDS (k <= 32) and one that does not,
+    against the oracle's k-step GMRES (bar as the other FP64 block solves)."""
+    print("block steps", k, flush=True)
+    g, eps, chi, pos, A, body = _case(11)
+    rng = np.random.default_rng(8)
+    r = rng.standard_normal((2, 3) + g.n[::-1]) + 1j * rng.standard_normal((2, 3) + g.n[::-1])
+    bset = pc.block_index_sets(pc.lateral_blocks(g.n, 3, 2)[body])
+    ctx = _ctx(V, g, eps, V.VIE_FP64)
+    try:
+        z = V.vie_precond_apply(ctx, V.fgmres_options(blocks=(3, 2), inner_iters=k,
+                                                      inner_precision=V.VIE_FP64), r)
+    finally:
+        V.vie_destroy(ctx)
+    for q in range(2):
+        want = pc.block_jacobi(A, bset, _body_vec(r[q], body), k=k)
+        err = np.linalg.norm(_body_vec(z[q], body) - want) / np.linalg.norm(want)
+        print(q, err)
+        assert err < 1e-9
+
+
+def test_steps_of_few_and_many_right_hand_sides(V):
+    """16 right-hand sides take a wave each, 17 a lane each: the same iterates after six steps
+    (FP64 roundings of the products, at most 1e-14 a step, through six steps)."""
+    g, eps, chi, pos, A, body = _case(13)
+    rng = np.random.default_rng(9)
+    chans = []
+    for _ in range(17):
+        k = rng.standard_normal(3)
+        k /= np.linalg.norm(k)
+        p = np.cross(k, rng.standard_normal(3)) + 0j
+        chans.append((k, p / np.linalg.norm(p)))
+    w = {}
+    for n in (1, 16, 17):
+        ctx = _ctx(V, g, eps, V.VIE_FP64, tol=1e-15, max_iter=6)
+        try:
+            V.vie_solve_fgmres(ctx, chans[:n], [n], V.fgmres_options(4, (0, 0), 1, V.VIE_FP64),
+                               allow_noconv=True)
+            w[n] = [V.vie_get_current(ctx, 0, q, g.n) for q in range(n)]
+        finally:
+            V.vie_destroy(ctx)
+    for q in range(16):
+        assert np.linalg.norm(w[16][q] - w[17][q]) <= 1e-11 * np.linalg.norm(w[17][q])
+    assert np.linalg.norm(w[1][0] - w[17][0]) <= 1e-11 * np.linalg.norm(w[17][0])
