@@ -41,13 +41,9 @@ struct DevBuf {
   hipError_t reserve(size_t b) {
     if (b <= bytes) return hipSuccess;
     release();
-    hipError_t e = hipMalloc(&p, b);
-    if (e != hipSuccess) {
-      p = nullptr;
-      return e;
-    }
-    bytes = b;
-    return hipSuccess;
+    const hipError_t e = dev_malloc(&p, b);
+    if (e == hipSuccess) bytes = b;
+    return e;
   }
   template <typename T>
   T* as() const {
@@ -91,15 +87,14 @@ struct Group {
   DevBuf vox_all, chic_all, line_ptr_all, nb_arr, voff_arr;
   std::vector<int> vox_host, nb_host, voff_host;
   int max_nb = 0;
-  // per-solve storage (capacity in right-hand sides / compressed elements)
-  int cap = 0;
-  int64_t vec_cap = 0;
-  DevBuf roff;                   // int64 [cap] vector offset of each right-hand side
+  // per-solve storage; no count of what it holds is kept beside the buffers' own
+  // sizes: one that did not fit has given up its old memory
+  DevBuf roff;                   // int64 [nrhs] vector offset of each right-hand side
   std::vector<int64_t> roff_host;
   BodyIdx bi;
   DevBuf x, r, rh, p, v, s, t;   // c64, body-compressed, all right-hand sides
-  DevBuf mask;                   // int [cap] scratch mask
-  DevBuf knorm;                  // double [4][cap] norms of the network's Krylov inputs
+  DevBuf mask;                   // int [nrhs] scratch mask
+  DevBuf knorm;                  // double [4][nrhs] norms of the network's Krylov inputs
   std::vector<double> knorm_host;
   // learned warm start: per body, network box = bounding box + 4-voxel halo
   std::vector<int> box_lo, box_d;        // [slot][3]
@@ -108,10 +103,10 @@ struct Group {
   bool samples_ready = false;            // r = b and v = A b hold for every rhs
   DevBuf bufA, bufB;             // FFT scratch (sized for FP64)
   DevBuf boxX, boxY;             // compute-window copies of box-layout product vectors
-  DevBuf partials;               // c64 [3][cap][maxblk][2]
+  DevBuf partials;               // c64 [3][nrhs][maxblk][2]
   int maxblk = 1;
-  DevBuf state;                  // KState [cap]
-  DevBuf flags;                  // int [2][cap]
+  DevBuf state;                  // KState [nrhs]
+  DevBuf flags;                  // int [3][nrhs]
   DevBuf rhs_body, pol, ph;      // per right-hand side
   DevBuf ang, dirs, part, F, wd, gidx;  // far-field scratch
   // far-field voxel blocks per body (built on first use; the body never changes)
@@ -306,7 +301,9 @@ static hipError_t scratch_init(int dev) {
       if (getenv("VIE_LOG"))                                                          \
         fprintf(stderr, "vie: %s failed: %s (%s:%d)\n", #call, hipGetErrorString(e_), \
                 __FILE__, __LINE__);                                                  \
-      return e_ == hipErrorOutOfMemory ? VIE_ENOMEM : fail_device(ctx);               \
+      if (e_ != hipErrorOutOfMemory) return fail_device(ctx);                         \
+      (void)hipGetLastError(); /* the context stays usable */                         \
+      return VIE_ENOMEM;                                                              \
     }                                                                                 \
   } while (0)
 
@@ -690,16 +687,13 @@ static int vec_blocks_group(const Group& G) { return vec_blocks_n(3 * (int64_t)G
 
 // Krylov vectors of all right-hand sides (body-compressed, vec_len elements).
 static int ensure_vectors(vie_ctx* ctx, Group& G, int64_t vec_len) {
-  if (vec_len <= G.vec_cap) return VIE_OK;
   DevBuf* vs[] = {&G.x, &G.r, &G.rh, &G.p, &G.v, &G.s, &G.t};
   for (DevBuf* b : vs) VIE_HIP(b->reserve((size_t)vec_len * sizeof(c64)));
-  G.vec_cap = vec_len;
   return VIE_OK;
 }
 
 // Scratch and per-right-hand-side arrays for nrhs right-hand sides.
 static int ensure_solve_storage(vie_ctx* ctx, Group& G, int nrhs) {
-  if (nrhs <= G.cap) return VIE_OK;
   const size_t a = (size_t)3 * G.g.N[2] * G.g.N[1] * G.g.P[0] * sizeof(c64);
   const size_t bb = (size_t)bufB_elems(G.g) * sizeof(c64);
   VIE_HIP(G.bufA.reserve(a * nrhs));
@@ -716,12 +710,12 @@ static int ensure_solve_storage(vie_ctx* ctx, Group& G, int nrhs) {
   VIE_HIP(G.roff.reserve((size_t)nrhs * sizeof(int64_t)));
   VIE_HIP(G.mask.reserve((size_t)nrhs * sizeof(int)));
   VIE_HIP(G.knorm.reserve((size_t)4 * nrhs * sizeof(double)));
-  G.cap = nrhs;
   return VIE_OK;
 }
 
 static int ensure_hflags(vie_ctx* ctx, int n) {
   if (n <= ctx->hflags_cap) return VIE_OK;
+  ctx->hflags_cap = 0;
   for (int k = 0; k < 2; ++k) {
     if (ctx->hflags[k]) (void)hipHostFree(ctx->hflags[k]);
     ctx->hflags[k] = nullptr;
@@ -1320,8 +1314,14 @@ static int bind_rhs(vie_ctx* ctx, Group& G, const vie_planewave* inc,
   }
   G.g.nrhs = nr;
   if (nr == 0) return VIE_OK;
+  // without storage the bodies have no solution, not even the last one
+  auto unbind = [&](int code) {
+    for (int b : G.bodies) ctx->bodies[b]->nrhs = 0;
+    G.g.nrhs = 0;
+    return code;
+  };
   int rc = ensure_solve_storage(ctx, G, nr);
-  if (rc != VIE_OK) return rc;
+  if (rc != VIE_OK) return unbind(rc);
   G.roff_host.assign(nr, 0);
   int64_t vlen = 0;
   for (int b : G.bodies) {
@@ -1332,7 +1332,7 @@ static int bind_rhs(vie_ctx* ctx, Group& G, const vie_planewave* inc,
     }
   }
   rc = ensure_vectors(ctx, G, std::max<int64_t>(vlen, 1));
-  if (rc != VIE_OK) return rc;
+  if (rc != VIE_OK) return unbind(rc);
   VIE_HIP(hipMemcpyAsync(G.roff.p, G.roff_host.data(), nr * sizeof(int64_t),
                          hipMemcpyHostToDevice, ctx->stream));
   G.bi.vox = G.vox_all.as<int>();

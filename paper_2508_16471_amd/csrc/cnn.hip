@@ -683,16 +683,16 @@ hipError_t cnn_alloc(Cnn& c) {
   c.off = cnn_offsets();
   const size_t np = (size_t)c.off.total;
   hipError_t e;
-  if ((e = hipMalloc(&c.p, np * 4)) != hipSuccess) return e;
-  if ((e = hipMalloc(&c.m, np * 4)) != hipSuccess) return e;
-  if ((e = hipMalloc(&c.v, np * 4)) != hipSuccess) return e;
-  if ((e = hipMalloc(&c.g, np * 4)) != hipSuccess) return e;
+  if ((e = dev_malloc(&c.p, np * 4)) != hipSuccess) return e;
+  if ((e = dev_malloc(&c.m, np * 4)) != hipSuccess) return e;
+  if ((e = dev_malloc(&c.v, np * 4)) != hipSuccess) return e;
+  if ((e = dev_malloc(&c.g, np * 4)) != hipSuccess) return e;
   if ((e = hipMemset(c.m, 0, np * 4)) != hipSuccess) return e;
   if ((e = hipMemset(c.v, 0, np * 4)) != hipSuccess) return e;
   const size_t nw = (size_t)bf16_weights_total();
-  if ((e = hipMalloc(&c.wf, nw * 2)) != hipSuccess) return e;
-  if ((e = hipMalloc(&c.wb, nw * 2)) != hipSuccess) return e;
-  if ((e = hipMalloc(&c.loss, 4 * 4096 * 2)) != hipSuccess) return e;
+  if ((e = dev_malloc(&c.wf, nw * 2)) != hipSuccess) return e;
+  if ((e = dev_malloc(&c.wb, nw * 2)) != hipSuccess) return e;
+  if ((e = dev_malloc(&c.loss, 4 * 4096 * 2)) != hipSuccess) return e;
   if ((e = hipHostMalloc(&c.hostloss, 2 * sizeof(float))) != hipSuccess) return e;
   return hipSuccess;
 }
@@ -722,13 +722,13 @@ hipError_t cnn_ensure_ws(Cnn& c, size_t vox) {
   c.wpart = nullptr;
   c.ws_vox = 0;
   hipError_t e;
-  if ((e = hipMalloc(&c.out, vox * 16 * 4)) != hipSuccess) return e;
+  if ((e = dev_malloc(&c.out, vox * 16 * 4)) != hipSuccess) return e;
   for (int k = 0; k < 2; ++k)
-    if ((e = hipMalloc(&c.gbuf[k], vox * 32 * 2)) != hipSuccess) return e;
+    if ((e = dev_malloc(&c.gbuf[k], vox * 32 * 2)) != hipSuccess) return e;
   for (int l = 1; l < kCnnLayers; ++l)
-    if ((e = hipMalloc(&c.act[l], vox * kCnnCh[l] * 2)) != hipSuccess) return e;
+    if ((e = dev_malloc(&c.act[l], vox * kCnnCh[l] * 2)) != hipSuccess) return e;
   const size_t maxlayer = 27 * 32 * 32 + 32;
-  if ((e = hipMalloc(&c.wpart, (size_t)kGradBlocks * maxlayer * 4)) != hipSuccess) return e;
+  if ((e = dev_malloc(&c.wpart, (size_t)kGradBlocks * maxlayer * 4)) != hipSuccess) return e;
   c.ws_vox = vox;
   return hipSuccess;
 }
@@ -791,7 +791,7 @@ hipError_t cnn_forward(Cnn& c, const int d[3], const bf16raw* feat, float* out, 
       if (c.fcopy) (void)hipFree(c.fcopy);
       c.fcopy = nullptr;
       c.fcopy_vox = 0;
-      if ((e = hipMalloc(&c.fcopy, nv * kCnnIn * sizeof(bf16raw))) != hipSuccess) return e;
+      if ((e = dev_malloc(&c.fcopy, nv * kCnnIn * sizeof(bf16raw))) != hipSuccess) return e;
       c.fcopy_vox = nv;
     }
     if ((e = hipMemcpyAsync(c.fcopy, feat, nv * kCnnIn * sizeof(bf16raw),

@@ -6,6 +6,18 @@
 
 namespace vie {
 
+// Device allocation whose failure is only returned: the runtime would keep the
+// error and hand it to the check after the next launch, however well that went.
+template <typename T>
+inline hipError_t dev_malloc(T** p, size_t bytes) {
+  const hipError_t e = hipMalloc((void**)p, bytes);
+  if (e != hipSuccess) {
+    *p = nullptr;
+    (void)hipGetLastError();
+  }
+  return e;
+}
+
 // Interleaved complex; 2*sizeof(T) alignment so a value moves in one
 // dwordx4 (FP64) or dwordx2 (FP32) memory instruction.
 template <typename T>

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/vie.h"
+#include "common.h"
 
 namespace {
 
@@ -51,8 +52,8 @@ extern "C" int vie_hbm_probe(int64_t bytes, int32_t reps, double* gbps) {
     grid = cus * 16;  // 16 workgroups per CU, grid-stride over the buffer
   }
   int rc = VIE_OK;
-  if (hipMalloc(&a, n * 16) != hipSuccess || hipMalloc(&b, n * 16) != hipSuccess ||
-      hipMalloc(&part, (size_t)grid * (PT / 64) * sizeof(float)) != hipSuccess) {
+  if (vie::dev_malloc(&a, n * 16) != hipSuccess || vie::dev_malloc(&b, n * 16) != hipSuccess ||
+      vie::dev_malloc(&part, (size_t)grid * (PT / 64) * sizeof(float)) != hipSuccess) {
     rc = VIE_ENOMEM;
   } else if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
     rc = VIE_EDEVICE;

@@ -604,7 +604,7 @@ struct RtBuf {
     if (p) (void)hipFree(p);
     p = nullptr;
     bytes = 0;
-    const hipError_t e = hipMalloc(&p, b);
+    const hipError_t e = dev_malloc(&p, b);
     if (e == hipSuccess) bytes = b;
     return e;
   }
@@ -720,7 +720,7 @@ int blocks_for(int64_t n) {
 
 template <typename T>
 hipError_t dalloc(T** p, size_t count) {
-  return hipMalloc((void**)p, count * sizeof(T));
+  return dev_malloc(p, count * sizeof(T));
 }
 
 void rt_free(vie_rt* r) {
