@@ -692,12 +692,19 @@ static int ensure_vectors(vie_ctx* ctx, Group& G, int64_t vec_len) {
   return VIE_OK;
 }
 
-// Scratch and per-right-hand-side arrays for nrhs right-hand sides.
-static int ensure_solve_storage(vie_ctx* ctx, Group& G, int nrhs) {
+// FFT scratch of a product of nrhs vectors.
+static int ensure_product_storage(vie_ctx* ctx, Group& G, int nrhs) {
   const size_t a = (size_t)3 * G.g.N[2] * G.g.N[1] * G.g.P[0] * sizeof(c64);
   const size_t bb = (size_t)bufB_elems(G.g) * sizeof(c64);
   VIE_HIP(G.bufA.reserve(a * nrhs));
   VIE_HIP(G.bufB.reserve(bb * nrhs));
+  return VIE_OK;
+}
+
+// Scratch and per-right-hand-side arrays for nrhs right-hand sides of a solve.
+static int ensure_solve_storage(vie_ctx* ctx, Group& G, int nrhs) {
+  const int rc = ensure_product_storage(ctx, G, nrhs);
+  if (rc != VIE_OK) return rc;
   const int maxblk = std::max(std::max(part_blocks_product(G.g, 0), part_blocks_product(G.g, 1)),
                               vec_blocks_group(G));
   G.maxblk = maxblk;
@@ -2269,7 +2276,9 @@ extern "C" int vie_matvec_dev(vie_ctx* ctx, int32_t body, int32_t precision, con
   Group& G = *ctx->groups[B.group];
   const int saved = G.g.nrhs;
   G.g.nrhs = nvec;
-  int rc = ensure_solve_storage(ctx, G, nvec);
+  // the scratch alone: the last solve's tables stay as they are for
+  // vie_cnn_sample_dev, which reads them after any number of products
+  int rc = ensure_product_storage(ctx, G, nvec);
   if (rc != VIE_OK) {
     G.g.nrhs = saved;
     return rc;
@@ -2475,8 +2484,7 @@ static int far_project(vie_ctx* ctx, BodyRec& B, std::vector<double> in, bool an
   } else {
     pl = far_plan(fr.fb, B.nrhs, ndir);
   }
-  // one upload: the directions, then the vector offsets of the right-hand
-  // sides (the solve's device copy may be gone: products share its storage)
+  // one upload: the directions, then the vector offsets of the right-hand sides
   const size_t nin = in.size();
   in.resize(nin + B.nrhs);
   memcpy(in.data() + nin, G.roff_host.data() + B.rhs0, B.nrhs * sizeof(int64_t));

@@ -140,3 +140,35 @@ def test_network_after_a_box_that_does_not_fit(V):
         assert torch.equal(out.ravel()[:n], again.ravel()[:n])
     finally:
         V.vie_cnn_destroy(net)
+
+
+def test_sample_after_products_of_more_vectors(V, monkeypatch):
+    """Products between a solve and its training sample, with more vectors than
+    the solve had channels: the sample is that of the solve, bit for bit."""
+    import torch
+
+    monkeypatch.setenv("VIE_DETERMINISTIC", "1")
+
+    g = Grid.centred(20, 1 / 16)
+    eps = sphere(g, 0.55, 2.25)
+    x = torch.randn((40, 3) + eps.shape, dtype=torch.complex128, device="cuda")
+    y = torch.empty_like(x)
+    got = []
+    for products in (0, 1, 40):
+        print("sample after a product of", products, flush=True)
+        ctx = V.vie_setup([(eps, g.h, g.origin)], V.make_options(K0, tol=1e-8, max_iter=2000))
+        try:
+            V.vie_solve(ctx, _channels(2), [2])
+            if products:
+                V.vie_matvec_dev(ctx, 0, x.data_ptr(), y.data_ptr(), products)
+            d = V.vie_cnn_sample_dev(ctx, 0, 1)
+            feat = torch.zeros(d[::-1] + (32,), dtype=torch.bfloat16, device="cuda")
+            target = torch.zeros(d[::-1] + (6,), device="cuda")
+            V.vie_cnn_sample_dev(ctx, 0, 1, feat.data_ptr(), target.data_ptr())
+            torch.cuda.synchronize()
+            got.append((feat, target))
+        finally:
+            V.vie_destroy(ctx)
+    assert got[0][1].abs().max() > 0
+    for feat, target in got[1:]:
+        assert torch.equal(feat, got[0][0]) and torch.equal(target, got[0][1])
