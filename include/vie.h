@@ -297,13 +297,15 @@ typedef struct vie_rt vie_rt;
 /* Build the operator of one body (n: 1..128 per axis, VIE_ENOTSUP above;
  * eps_r as vie_body) at wavenumber k0: face data, the spectrum of the scalar
  * kernel's circulant (length P >= 2 E - 1 per axis; kept on its octant,
- * (P1/2 + 1)(P2/2 + 1)(P3/2 + 1) complex doubles and an FP32 copy); setup
- * needs two P1 P2 P3 complex arrays for the duration of the call.  The first
- * call that needs them allocates, and the operator keeps: transform scratch
- * (4 E3 P2 P1 + 4 E3 E2 P1 complex, in a solve per channel of a batch, up to 1
- * GB of the former), the solver's vectors (24 E1 E2 E3 complex per channel of a
- * batch) and the far field's buffers (up to 256 MB of currents).
- * VIE_EINVAL on bad values. */
+ * (P1/2 + 1)(P2/2 + 1)(P3/2 + 1) complex doubles and an FP32 copy), and the
+ * workspace of one vector: transform scratch (4 E3 P2 P1 + 4 E3 E2 P1 complex)
+ * and the solver's vectors (24 E1 E2 E3 complex); setup needs two P1 P2 P3
+ * complex arrays for the duration of the call.  With that, products and solves
+ * never run out of memory: a solve of several channels takes the workspace of
+ * a batch (up to 1 GB of the 4 E3 P2 P1 arrays) and keeps it, and where it does
+ * not fit makes do with a smaller batch.  The far field's buffers (up to 256 MB
+ * each of currents and of results) are made by the first call that needs them
+ * (VIE_ENOMEM) and kept.  VIE_EINVAL on bad values. */
 int vie_rt_setup(const vie_body *body, double k0, vie_rt **out);
 
 /* Padded grid E[3] and circulant lengths P[3]; either may be NULL. */
@@ -316,15 +318,17 @@ int vie_rt_matvec(vie_rt *rt, const vie_c64 *x, vie_c64 *y, int32_t nvec, int32_
 
 /* Solve for nrhs plane-wave channels (b = chi_f e(r_f)) with BiCGSTAB from
  * w = 0 (channels advance together in batches; scalars on the device, the host
- * checking them every 8 iterations), each channel restarted from the FP64 true residual when the recursive one reaches its
- * target or the iteration breaks down (a zero denominator); the true residual
- * ||b - A w|| / ||b|| <= tol decides.  precision VIE_FP64: FP64 products;
- * VIE_MIXED: FP32 products inside FP64 iterative refinement, every cycle
+ * checking them every 8 iterations), each channel restarted from the FP64 true
+ * residual when the recursive one reaches its target or the iteration breaks
+ * down (a zero denominator); the true residual ||b - A w|| / ||b|| <= tol
+ * decides.  precision VIE_FP64: FP64 products; VIE_MIXED: FP32 products inside
+ * FP64 iterative refinement, every cycle
  * reducing its starting residual by 1e-3 (or to tol), the vectors and dots
  * FP64.  w: nrhs vectors.  stats (nullable, one per channel): iters (all
  * cycles), matvecs, cycles, converged, rel_res; seconds = host wall time from
- * the start of the channel's batch to its convergence (0 if not converged).  VIE_ENOCONV if a channel missed
- * tol in max_iter iterations (its best iterate is still returned). */
+ * the start of the channel's batch to its convergence (0 if not converged).
+ * VIE_ENOCONV if a channel missed tol in max_iter iterations (its best iterate
+ * is still returned). */
 int vie_rt_solve(vie_rt *rt, const vie_planewave *inc, int32_t nrhs, double tol,
                  int32_t max_iter, int32_t precision, vie_c64 *w, vie_stats *stats);
 

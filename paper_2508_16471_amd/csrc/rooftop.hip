@@ -30,6 +30,7 @@
 #include <chrono>
 #include <cmath>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/vie.h"
@@ -596,14 +597,15 @@ struct RtBuf {
   RtBuf() = default;
   RtBuf(const RtBuf&) = delete;
   RtBuf& operator=(const RtBuf&) = delete;
-  ~RtBuf() {
-    if (p) (void)hipFree(p);
-  }
-  hipError_t reserve(size_t b) {
-    if (b <= bytes) return hipSuccess;
+  ~RtBuf() { release(); }
+  void release() {
     if (p) (void)hipFree(p);
     p = nullptr;
     bytes = 0;
+  }
+  hipError_t reserve(size_t b) {
+    if (b <= bytes) return hipSuccess;
+    release();
     const hipError_t e = dev_malloc(&p, b);
     if (e == hipSuccess) bytes = b;
     return e;
@@ -681,6 +683,19 @@ struct RtStage {
   }
 };
 
+// Workspace of `cap` vectors, one allocation: transform scratch
+// [vec][4][E3][E2][P1] and [vec][4][E3][P2][P1], eight solver vectors, dot
+// partials, the solver's scalars and flags.
+struct RtWork {
+  char* base = nullptr;
+  int cap = 0;
+  c64 *t1, *t2, *vecs, *part[3], *fold;
+  RtScal* scal;
+  RtWave* wave;
+  double* total;
+  int *active, *mark;
+};
+
 struct vie_rt {
   int N[3] = {0, 0, 0};
   double h = 0, k0 = 0, origin[3] = {0, 0, 0};
@@ -696,9 +711,8 @@ struct vie_rt {
   c32* tw32[3] = {nullptr, nullptr, nullptr};
   c64* df[3] = {nullptr, nullptr, nullptr};    // D_a(k) = (e^{2 pi i k / P_a} - 1) / h
   c32* df32[3] = {nullptr, nullptr, nullptr};
-  // per batch of vectors (grown on first use): transform scratch
-  // [vec][4][E3][E2][P1] and [vec][4][E3][P2][P1], solver vectors, partials
-  RtBuf t1, t2, vecs, part[3], fold, scal, active, mark, wave, total;
+  int dev = 0;  // HIP device current at setup
+  RtWork w;     // of the largest batch of vectors so far, one from setup on
   // far field: the cells with an active face (ascending), their blocks and
   // columns (built on first use), scratch
   std::vector<int> cells;
@@ -735,6 +749,7 @@ void rt_free(vie_rt* r) {
   for (auto* t : r->tw) f(t);
   for (auto* t : r->df) f(t);
   for (auto* t : r->df32) f(t);
+  f(r->w.base);
   if (r->stream) (void)hipStreamDestroy(r->stream);
 }
 
@@ -759,18 +774,56 @@ int xinv_blocks(const RtGeom& q) {
   return (3 * q.E[1] * q.E[2] + L - 1) / L;
 }
 
-// Scratch for nvec vectors at once.
-hipError_t rt_ensure(vie_rt* r, int nvec) {
+// Makes the handle's device the current one for a call: the calls allocate.
+struct RtDevice {
+  int prev = -1;
+  explicit RtDevice(int dev) {
+    int cur = dev;
+    if (hipGetDevice(&cur) == hipSuccess && cur != dev && hipSetDevice(dev) == hipSuccess)
+      prev = cur;
+  }
+  ~RtDevice() {
+    if (prev >= 0) (void)hipSetDevice(prev);
+  }
+};
+
+// Workspace for nvec vectors at once.  Where it cannot grow the old one stays
+// in place (setup makes one for a single vector), so a product always runs and
+// a solve always fits one channel.
+hipError_t rt_reserve(vie_rt* r, int nvec) {
+  if (nvec <= r->w.cap) return hipSuccess;
   const RtGeom& q = r->q;
-  const size_t row = (size_t)kRtFields * q.E[2] * q.P[0] * sizeof(c64);
-  hipError_t e = r->t1.reserve(nvec * row * q.E[1]);
-  if (e == hipSuccess) e = r->t2.reserve(nvec * row * q.P[1]);
+  RtWork w;
+  size_t bytes = 0;
+  auto lay = [&](auto*& p, size_t count) {  // the first pass counts, the second places
+    using T = std::remove_reference_t<decltype(*p)>;
+    p = w.base ? (T*)(w.base + bytes) : nullptr;
+    bytes += (nvec * count * sizeof(T) + 255) / 256 * 256;
+  };
+  const size_t row = (size_t)kRtFields * q.E[2] * q.P[0];
   const size_t np = std::max(std::max(xinv_blocks<double>(q), xinv_blocks<float>(q)),
                              vec_blocks(3 * q.m));
-  for (auto& p : r->part)
-    if (e == hipSuccess) e = p.reserve(nvec * np * 2 * sizeof(c64));
-  if (e == hipSuccess) e = r->fold.reserve((size_t)nvec * kRtFold * 2 * sizeof(c64));
-  return e;
+  for (int pass = 0; pass < 2; ++pass) {
+    bytes = 0;
+    lay(w.t1, row * q.E[1]);
+    lay(w.t2, row * q.P[1]);
+    lay(w.vecs, (size_t)8 * 3 * q.m);
+    for (auto& p : w.part) lay(p, np * 2);
+    lay(w.fold, (size_t)kRtFold * 2);
+    lay(w.scal, 1);
+    lay(w.wave, 1);
+    lay(w.total, 1);
+    lay(w.active, 1);
+    lay(w.mark, 1);
+    if (pass == 0) {
+      const hipError_t e = dev_malloc(&w.base, bytes);
+      if (e != hipSuccess) return e;
+    }
+  }
+  w.cap = nvec;
+  if (r->w.base) (void)hipFree(r->w.base);
+  r->w = w;
+  return hipSuccess;
 }
 
 // out = A x (kEpiRes: aux - A x) of nvec vectors [nvec][3][m] (device), with
@@ -790,8 +843,8 @@ int rt_apply_t(vie_rt* r, const c64* x, c64* out, int nvec, int mode, const c64*
     df[a] = pick(r->df[a], r->df32[a]);
   }
   const cpx<T>* ghat = pick(r->ghat, r->ghat32);
-  cpx<T>* t1 = r->t1.as<cpx<T>>();
-  cpx<T>* t2 = r->t2.as<cpx<T>>();
+  cpx<T>* t1 = (cpx<T>*)r->w.t1;
+  cpx<T>* t2 = (cpx<T>*)r->w.t2;
   const double inv_h = 1.0 / r->h;
   const int L = lines_per_block<T>(q.P[0]);
   const int bf = (kRtFields * q.E[1] * q.E[2] + L - 1) / L, bi = xinv_blocks<T>(q);
@@ -840,14 +893,6 @@ int rt_apply(vie_rt* r, const c64* x, c64* out, int nvec, bool fp32, int mode = 
   return fp32 ? rt_apply_t<float>(r, x, out, nvec, mode, aux, part, active)
               : rt_apply_t<double>(r, x, out, nvec, mode, aux, part, active);
 }
-
-// an allocation that fails leaves the operator usable
-#define RT_ALLOC(call)                                  \
-  do {                                                  \
-    hipError_t ea_ = (call);                            \
-    if (ea_ == hipErrorOutOfMemory) return VIE_ENOMEM;  \
-    RT_HIP(ea_);                                        \
-  } while (0)
 
 #define RT_TRY(call)          \
   do {                        \
@@ -931,6 +976,7 @@ extern "C" int vie_rt_setup(const vie_body* body, double k0, vie_rt** out) {
   auto chk = [&](hipError_t x) {
     if (e == hipSuccess) e = x;
   };
+  chk(hipGetDevice(&r->dev));
   chk(hipStreamCreate(&r->stream));
   chk(dalloc(&r->alpha, 3 * m));
   chk(dalloc(&r->chif, 3 * m));
@@ -985,10 +1031,13 @@ extern "C" int vie_rt_setup(const vie_body* body, double k0, vie_rt** out) {
     chk(hipGetLastError());
   }
   if (e == hipSuccess) chk(hipStreamSynchronize(r->stream));
+  work.release();
+  tmp.release();
+  if (e == hipSuccess) chk(rt_reserve(r, 1));
   if (e != hipSuccess) {
     rt_free(r);
     delete r;
-    return VIE_EDEVICE;
+    return e == hipErrorOutOfMemory ? VIE_ENOMEM : VIE_EDEVICE;
   }
   *out = r;
   return VIE_OK;
@@ -1008,10 +1057,9 @@ extern "C" int vie_rt_matvec(vie_rt* r, const vie_c64* x, vie_c64* y, int32_t nv
   if (!r || !x || !y || nvec < 1 || (precision != VIE_FP64 && precision != VIE_MIXED))
     return VIE_EINVAL;
   if (r->poisoned) return VIE_ESTATE;
+  const RtDevice on(r->dev);
   const int64_t n = 3 * r->q.m;
-  RT_ALLOC(rt_ensure(r, 1));
-  RT_ALLOC(r->vecs.reserve((size_t)2 * n * sizeof(c64)));
-  c64 *dx = r->vecs.as<c64>(), *dy = dx + n;
+  c64 *dx = r->w.vecs, *dy = dx + n;
   for (int v = 0; v < nvec; ++v) {
     RT_HIP(hipMemcpyAsync(dx, x + v * n, n * sizeof(c64), hipMemcpyHostToDevice, r->stream));
     RT_TRY(rt_apply(r, dx, dy, 1, precision == VIE_MIXED));
@@ -1031,29 +1079,22 @@ static int rt_solve_batch(vie_rt* r, const vie_planewave* inc, int nc, double to
   const RtGeom& q = r->q;
   const int64_t n = 3 * q.m;
   const auto t0 = std::chrono::steady_clock::now();
-  RT_ALLOC(rt_ensure(r, nc));
-  RT_ALLOC(r->vecs.reserve((size_t)8 * nc * n * sizeof(c64)));
-  RT_ALLOC(r->scal.reserve(nc * sizeof(RtScal)));
-  RT_ALLOC(r->active.reserve(nc * sizeof(int)));
-  RT_ALLOC(r->mark.reserve(nc * sizeof(int)));
-  RT_ALLOC(r->wave.reserve(nc * sizeof(RtWave)));
-  RT_ALLOC(r->total.reserve(nc * sizeof(double)));
   c64* vec[8];
-  for (int k = 0; k < 8; ++k) vec[k] = r->vecs.as<c64>() + (int64_t)k * nc * n;
+  for (int k = 0; k < 8; ++k) vec[k] = r->w.vecs + (int64_t)k * nc * n;
   c64 *x = vec[0], *b = vec[1], *rr = vec[2], *rh = vec[3], *p = vec[4], *v = vec[5], *s = vec[6],
       *t = vec[7];
-  RtScal* sc = r->scal.as<RtScal>();
-  int* active = r->active.as<int>();
-  int* mark = r->mark.as<int>();
-  c64 *pr = r->part[0].as<c64>(), *pv = r->part[1].as<c64>(), *pt = r->part[2].as<c64>();
+  RtScal* sc = r->w.scal;
+  int* active = r->w.active;
+  int* mark = r->w.mark;
+  c64 *pr = r->w.part[0], *pv = r->w.part[1], *pt = r->w.part[2];
   const int vb = vec_blocks(n);
   const int bi64 = xinv_blocks<double>(q), bi = mixed ? xinv_blocks<float>(q) : bi64;
   // a product's partials: folded first when every consumer would sum many
   auto fold = [&](c64* part, int& np, const int* act) -> c64* {
     if (np <= 512) return part;
-    k_rt_fold<<<kRtFold * nc, 64, 0, r->stream>>>(part, np, r->fold.as<c64>(), act);
+    k_rt_fold<<<kRtFold * nc, 64, 0, r->stream>>>(part, np, r->w.fold, act);
     np = kRtFold;
-    return r->fold.as<c64>();
+    return r->w.fold;
   };
   std::vector<RtWave> hw(nc);
   for (int k = 0; k < nc; ++k)
@@ -1061,15 +1102,15 @@ static int rt_solve_batch(vie_rt* r, const vie_planewave* inc, int nc, double to
       hw[k].k[a] = inc[k].khat[a];
       hw[k].p[a] = mk(inc[k].pol[a].re, inc[k].pol[a].im);
     }
-  RT_HIP(hipMemcpyAsync(r->wave.p, hw.data(), nc * sizeof(RtWave), hipMemcpyHostToDevice,
+  RT_HIP(hipMemcpyAsync(r->w.wave, hw.data(), nc * sizeof(RtWave), hipMemcpyHostToDevice,
                         r->stream));
   k_rt_rhs<<<vb * nc, kRtThreads, 0, r->stream>>>(b, x, rr, rh, p, v, r->chif, q, r->h,
                                                   r->origin[0], r->origin[1], r->origin[2], r->k0,
-                                                  r->wave.as<RtWave>(), vb, pr);
-  k_rt_total<<<nc, kRtThreads, 0, r->stream>>>(pr, vb, r->total.as<double>(), nullptr);
+                                                  r->w.wave, vb, pr);
+  k_rt_total<<<nc, kRtThreads, 0, r->stream>>>(pr, vb, r->w.total, nullptr);
   RT_HIP(hipGetLastError());
   std::vector<double> bb(nc), r2(nc);
-  RT_HIP(hipMemcpyAsync(bb.data(), r->total.p, nc * sizeof(double), hipMemcpyDeviceToHost,
+  RT_HIP(hipMemcpyAsync(bb.data(), r->w.total, nc * sizeof(double), hipMemcpyDeviceToHost,
                         r->stream));
   RT_HIP(hipStreamSynchronize(r->stream));
   std::vector<RtScal> hs(nc);
@@ -1134,9 +1175,9 @@ static int rt_solve_batch(vie_rt* r, const vie_planewave* inc, int nc, double to
     RT_TRY(rt_apply(r, x, t, nc, false, kEpiRes, b, pt, mark));
     int np = bi64;
     const c64* ft = fold(pt, np, mark);
-    k_rt_total<<<nc, kRtThreads, 0, r->stream>>>(ft, np, r->total.as<double>(), mark);
+    k_rt_total<<<nc, kRtThreads, 0, r->stream>>>(ft, np, r->w.total, mark);
     RT_HIP(hipGetLastError());
-    RT_HIP(hipMemcpyAsync(r2.data(), r->total.p, nc * sizeof(double), hipMemcpyDeviceToHost,
+    RT_HIP(hipMemcpyAsync(r2.data(), r->w.total, nc * sizeof(double), hipMemcpyDeviceToHost,
                           r->stream));
     RT_HIP(hipStreamSynchronize(r->stream));
     bool again = false;
@@ -1188,10 +1229,18 @@ extern "C" int vie_rt_solve(vie_rt* r, const vie_planewave* inc, int32_t nrhs, d
       if (!std::isfinite(inc[k].khat[a]) || !std::isfinite(inc[k].pol[a].re) ||
           !std::isfinite(inc[k].pol[a].im))
         return VIE_EINVAL;
-  // channels per batch: 1 GB of transform scratch
+  const RtDevice on(r->dev);
+  // channels per batch: 1 GB of y/z scratch, fewer where their workspace does
+  // not fit (the iterates are the same)
   const RtGeom& q = r->q;
   const int64_t one = (int64_t)kRtFields * q.E[2] * q.P[1] * q.P[0] * sizeof(c64);
-  const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(nrhs, ((int64_t)1 << 30) / one));
+  int nb = (int)std::max<int64_t>(1, std::min<int64_t>(nrhs, ((int64_t)1 << 30) / one));
+  while (nb > r->w.cap) {
+    const hipError_t e = rt_reserve(r, nb);
+    if (e == hipSuccess) break;
+    if (e != hipErrorOutOfMemory) RT_HIP(e);
+    nb = std::max(r->w.cap, nb / 2);
+  }
   bool all = true;
   for (int k = 0; k < nrhs; k += nb)
     RT_TRY(rt_solve_batch(r, inc + k, std::min(nb, nrhs - k), tol, max_iter,
@@ -1208,6 +1257,7 @@ extern "C" int vie_rt_farfield(vie_rt* r, const vie_c64* w, int32_t nrhs, const 
   for (int d = 0; d < ndir; ++d)
     if (!std::isfinite(theta[d]) || !std::isfinite(phi[d])) return VIE_EINVAL;
   if ((int64_t)nrhs * ndir > (int64_t)1 << 30) return VIE_EINVAL;
+  const RtDevice on(r->dev);
   // Component i of cell c is its face c + e_i / 2: the voxel contraction over
   // the cells with an active face, weights alpha, and one half-cell phase per
   // component and direction at the end (a direct sum over the faces took
@@ -1247,9 +1297,10 @@ extern "C" int vie_rt_farfield(vie_rt* r, const vie_c64* w, int32_t nrhs, const 
     up(r->forg, r->fb.org);
     r->far_blocks = e == hipSuccess;
   }
-  // right-hand sides per upload: 256 MB of currents
-  const int per = (int)std::max<int64_t>(1, std::min<int64_t>(nrhs, ((int64_t)256 << 20) /
-                                                                        (n * (int64_t)sizeof(c64))));
+  // right-hand sides per upload: 256 MB of currents and of results
+  const int64_t each = std::max<int64_t>(n, (int64_t)ndir * 2) * (int64_t)sizeof(c64);
+  const int per =
+      (int)std::max<int64_t>(1, std::min<int64_t>(nrhs, ((int64_t)256 << 20) / each));
   FarPlan pl;
   FarSweepPlan sp;
   std::vector<int> idx;

@@ -172,3 +172,31 @@ def test_sample_after_products_of_more_vectors(V, monkeypatch):
     assert got[0][1].abs().max() > 0
     for feat, target in got[1:]:
         assert torch.equal(feat, got[0][0]) and torch.equal(target, got[0][1])
+
+
+def test_rooftop_calls_need_no_memory_beyond_setup(V):
+    """A rooftop operator that could be set up multiplies and solves, whatever
+    memory is left: 40 channels of 21 MB each run in smaller batches, to the
+    same iterates."""
+    g = Grid.centred((30, 28, 26), 1 / 16)
+    eps = sphere(g, 0.7, 2.25)
+    rng = np.random.default_rng(2)
+    x = rng.standard_normal((2, 3, 28, 30, 32)) + 0j
+    chans = _channels(40)
+    r = V.vie_rt_setup(eps, g.h, g.origin, K0)
+    try:
+        print("rooftop calls with memory", flush=True)
+        y = V.vie_rt_matvec(r, x)
+        _, w, st = V.vie_rt_solve(r, chans, tol=1e-8, max_iter=500)
+    finally:
+        V.vie_rt_destroy(r)
+    r = V.vie_rt_setup(eps, g.h, g.origin, K0)
+    try:
+        with short_of_memory(128 * MIB):
+            print("rooftop calls without memory", flush=True)
+            assert np.array_equal(V.vie_rt_matvec(r, x), y)
+            _, w2, st2 = V.vie_rt_solve(r, chans, tol=1e-8, max_iter=500)
+        assert np.array_equal(w2, w)
+        assert [s["iters"] for s in st2] == [s["iters"] for s in st]
+    finally:
+        V.vie_rt_destroy(r)
