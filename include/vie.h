@@ -299,8 +299,8 @@ typedef struct vie_rt vie_rt;
  * kernel's circulant (length P >= 2 E - 1 per axis; kept on its octant,
  * (P1/2 + 1)(P2/2 + 1)(P3/2 + 1) complex doubles and an FP32 copy), and the
  * workspace of one vector: transform scratch (4 E3 P2 P1 + 4 E3 E2 P1 complex)
- * and the solver's vectors (24 E1 E2 E3 complex); setup needs two P1 P2 P3
- * complex arrays for the duration of the call.  With that, products and solves
+ * and the solver's vectors (24 E1 E2 E3 complex), or two P1 P2 P3 complex
+ * arrays where those are larger.  With that, products and solves
  * never run out of memory: a solve of several channels takes the workspace of
  * a batch (up to 1 GB of the 4 E3 P2 P1 arrays) and keeps it, and where it does
  * not fit makes do with a smaller batch.  The far field's buffers (up to 256 MB

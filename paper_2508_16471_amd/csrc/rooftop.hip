@@ -597,15 +597,14 @@ struct RtBuf {
   RtBuf() = default;
   RtBuf(const RtBuf&) = delete;
   RtBuf& operator=(const RtBuf&) = delete;
-  ~RtBuf() { release(); }
-  void release() {
+  ~RtBuf() {
     if (p) (void)hipFree(p);
-    p = nullptr;
-    bytes = 0;
   }
   hipError_t reserve(size_t b) {
     if (b <= bytes) return hipSuccess;
-    release();
+    if (p) (void)hipFree(p);
+    p = nullptr;
+    bytes = 0;
     const hipError_t e = dev_malloc(&p, b);
     if (e == hipSuccess) bytes = b;
     return e;
@@ -703,10 +702,12 @@ struct vie_rt {
   GroupGeom g{};
   hipStream_t stream = nullptr;
   bool poisoned = false;
+  // one allocation each: the faces, the spectrum, the tables
   double* alpha = nullptr;  // [3][m]
   double* chif = nullptr;   // [3][m]
   c64* ghat = nullptr;      // spectrum / M on the octant [0, P/2]^3
   c32* ghat32 = nullptr;    // its FP32 copy
+  c64* tables = nullptr;    // per axis tw, df, then their FP32 copies
   c64* tw[3] = {nullptr, nullptr, nullptr};
   c32* tw32[3] = {nullptr, nullptr, nullptr};
   c64* df[3] = {nullptr, nullptr, nullptr};    // D_a(k) = (e^{2 pi i k / P_a} - 1) / h
@@ -742,13 +743,8 @@ void rt_free(vie_rt* r) {
     if (p) (void)hipFree(p);
   };
   f(r->alpha);
-  f(r->chif);
   f(r->ghat);
-  f(r->ghat32);
-  for (auto* t : r->tw32) f(t);
-  for (auto* t : r->tw) f(t);
-  for (auto* t : r->df) f(t);
-  for (auto* t : r->df32) f(t);
+  f(r->tables);
   f(r->w.base);
   if (r->stream) (void)hipStreamDestroy(r->stream);
 }
@@ -789,8 +785,8 @@ struct RtDevice {
 
 // Workspace for nvec vectors at once.  Where it cannot grow the old one stays
 // in place (setup makes one for a single vector), so a product always runs and
-// a solve always fits one channel.
-hipError_t rt_reserve(vie_rt* r, int nvec) {
+// a solve always fits one channel.  least: bytes wanted for another use.
+hipError_t rt_reserve(vie_rt* r, int nvec, size_t least = 0) {
   if (nvec <= r->w.cap) return hipSuccess;
   const RtGeom& q = r->q;
   RtWork w;
@@ -816,7 +812,7 @@ hipError_t rt_reserve(vie_rt* r, int nvec) {
     lay(w.active, 1);
     lay(w.mark, 1);
     if (pass == 0) {
-      const hipError_t e = dev_malloc(&w.base, bytes);
+      const hipError_t e = dev_malloc(&w.base, std::max(bytes, least));
       if (e != hipSuccess) return e;
     }
   }
@@ -940,7 +936,8 @@ extern "C" int vie_rt_setup(const vie_body* body, double k0, vie_rt** out) {
   const int64_t m = r->q.m, M = r->q.M;
 
   // face data: chi on the padded grid, then alpha and chi_f per face
-  std::vector<double> chi(m, 0.0), alpha(3 * m, 0.0), chif(3 * m, 0.0);
+  std::vector<double> chi(m, 0.0), faces(6 * m, 0.0);
+  double *alpha = faces.data(), *chif = alpha + 3 * m;
   for (int z = 0; z < r->N[2]; ++z)
     for (int y = 0; y < r->N[1]; ++y)
       for (int x = 0; x < r->N[0]; ++x)
@@ -978,66 +975,62 @@ extern "C" int vie_rt_setup(const vie_body* body, double k0, vie_rt** out) {
   };
   chk(hipGetDevice(&r->dev));
   chk(hipStreamCreate(&r->stream));
-  chk(dalloc(&r->alpha, 3 * m));
-  chk(dalloc(&r->chif, 3 * m));
+  chk(dalloc(&r->alpha, 6 * m));
+  r->chif = r->alpha + 3 * m;
   const int64_t noct = (int64_t)(q.P[0] / 2 + 1) * (q.P[1] / 2 + 1) * (q.P[2] / 2 + 1);
-  chk(dalloc(&r->ghat, noct));
-  chk(dalloc(&r->ghat32, noct));
-  RtBuf work, tmp;  // the full circulant, for the spectrum only
-  chk(work.reserve(M * sizeof(c64)));
-  chk(tmp.reserve(M * sizeof(c64)));
-  for (int a = 0; a < 3; ++a) chk(dalloc(&r->tw[a], q.P[a]));
-  for (int a = 0; a < 3; ++a) chk(dalloc(&r->tw32[a], q.P[a]));
-  for (int a = 0; a < 3; ++a) chk(dalloc(&r->df[a], q.P[a]));
-  for (int a = 0; a < 3; ++a) chk(dalloc(&r->df32[a], q.P[a]));
+  chk(dalloc(&r->ghat, noct + (noct + 1) / 2));
+  r->ghat32 = (c32*)(r->ghat + noct);
+  const int sum = q.P[0] + q.P[1] + q.P[2];
+  chk(dalloc(&r->tables, 3 * sum));
+  for (int a = 0, at = 0; a < 3; at += q.P[a++]) {
+    r->tw[a] = r->tables + at;
+    r->df[a] = r->tables + sum + at;
+    r->tw32[a] = (c32*)(r->tables + 2 * sum) + at;
+    r->df32[a] = (c32*)(r->tables + 2 * sum) + sum + at;
+  }
+  // the circulant and its transform, for the spectrum only, then the workspace:
+  // whichever is larger is the one allocation
+  chk(rt_reserve(r, 1, 2 * M * sizeof(c64)));
   if (e != hipSuccess) {
     rt_free(r);
     delete r;
     return e == hipErrorOutOfMemory ? VIE_ENOMEM : VIE_EDEVICE;
   }
-  for (int a = 0; a < 3; ++a) {
-    std::vector<c64> t(q.P[a]), d(q.P[a]);
-    std::vector<c32> t32(q.P[a]), d32(q.P[a]);
+  c64 *work = (c64*)r->w.base, *tmp = work + M;
+  std::vector<c64> tab(3 * sum);
+  c32* tab32 = (c32*)(tab.data() + 2 * sum);
+  for (int a = 0, at = 0; a < 3; at += q.P[a++])
     for (int k = 0; k < q.P[a]; ++k) {
       const long double pi = 3.14159265358979323846264338327950288L;
-      const long double ang = -2.0L * pi * k / q.P[a];
-      t[k] = mk((double)cosl(ang), (double)sinl(ang));
-      t32[k] = mk((float)cosl(ang), (float)sinl(ang));
+      const long double ang = -2.0L * pi * k / q.P[a], cs = cosl(ang), sn = sinl(ang);
+      tab[at + k] = mk((double)cs, (double)sn);
+      tab32[at + k] = mk((float)cs, (float)sn);
       // e^{i a} - 1 = -2 sin(a/2)^2 + i sin a: no cancellation at small k
       const long double sh = sinl(pi * k / q.P[a]);
-      const long double dr = -2.0L * sh * sh / r->h, di = -sinl(ang) / r->h;
-      d[k] = mk((double)dr, (double)di);
-      d32[k] = mk((float)dr, (float)di);
+      const long double dr = -2.0L * sh * sh / r->h, di = -sn / r->h;
+      tab[sum + at + k] = mk((double)dr, (double)di);
+      tab32[sum + at + k] = mk((float)dr, (float)di);
     }
-    chk(hipMemcpy(r->tw[a], t.data(), q.P[a] * sizeof(c64), hipMemcpyHostToDevice));
-    chk(hipMemcpy(r->tw32[a], t32.data(), q.P[a] * sizeof(c32), hipMemcpyHostToDevice));
-    chk(hipMemcpy(r->df[a], d.data(), q.P[a] * sizeof(c64), hipMemcpyHostToDevice));
-    chk(hipMemcpy(r->df32[a], d32.data(), q.P[a] * sizeof(c32), hipMemcpyHostToDevice));
-  }
-  chk(hipMemcpy(r->alpha, alpha.data(), 3 * m * sizeof(double), hipMemcpyHostToDevice));
-  chk(hipMemcpy(r->chif, chif.data(), 3 * m * sizeof(double), hipMemcpyHostToDevice));
+  chk(hipMemcpy(r->tables, tab.data(), tab.size() * sizeof(c64), hipMemcpyHostToDevice));
+  chk(hipMemcpy(r->alpha, faces.data(), faces.size() * sizeof(double), hipMemcpyHostToDevice));
   double s_re, s_im;
   cube_green_integral(k0, r->h, &s_re, &s_im);
   const void* tw[3] = {r->tw[0], r->tw[1], r->tw[2]};
   if (e == hipSuccess) {
-    k_rt_green<<<blocks_for(M), kRtThreads, 0, r->stream>>>(work.as<c64>(), q, r->h, k0, s_re,
-                                                            s_im);
+    k_rt_green<<<blocks_for(M), kRtThreads, 0, r->stream>>>(work, q, r->h, k0, s_re, s_im);
     chk(hipGetLastError());
   }
-  if (e == hipSuccess) chk(launch_fft3d_full(work.as<c64>(), tmp.as<c64>(), r->g, tw, r->stream));
+  if (e == hipSuccess) chk(launch_fft3d_full(work, tmp, r->g, tw, r->stream));
   if (e == hipSuccess) {
-    k_rt_octant<<<blocks_for(noct), kRtThreads, 0, r->stream>>>(tmp.as<c64>(), r->ghat,
-                                                                r->ghat32, q, 1.0 / (double)M);
+    k_rt_octant<<<blocks_for(noct), kRtThreads, 0, r->stream>>>(tmp, r->ghat, r->ghat32, q,
+                                                                1.0 / (double)M);
     chk(hipGetLastError());
   }
   if (e == hipSuccess) chk(hipStreamSynchronize(r->stream));
-  work.release();
-  tmp.release();
-  if (e == hipSuccess) chk(rt_reserve(r, 1));
   if (e != hipSuccess) {
     rt_free(r);
     delete r;
-    return e == hipErrorOutOfMemory ? VIE_ENOMEM : VIE_EDEVICE;
+    return VIE_EDEVICE;
   }
   *out = r;
   return VIE_OK;
