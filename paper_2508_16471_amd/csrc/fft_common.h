@@ -211,6 +211,18 @@ constexpr int nt_lines_p(int P) {
 }
 
 
+// *flag, read once for the whole workgroup, in kernels whose leading workgroup
+// may clear it meanwhile.  Either value will do then, as every workgroup that
+// goes on takes the leading one's decision for itself -- but not one for some
+// waves of a workgroup and the other for the rest: those that left would be
+// missing at its barriers and from its sums.
+__device__ __forceinline__ bool group_flag(const int* flag) {
+  __shared__ int s;
+  if (threadIdx.x == 0) s = *flag;
+  __syncthreads();
+  return s != 0;
+}
+
 __device__ __forceinline__ void block_sum2(c64& a, c64& b, double* red) {
   // wave64 butterfly then across waves through LDS (fixed order: deterministic)
 #pragma unroll

@@ -77,8 +77,8 @@ __device__ __forceinline__ int rho_decision(c64 a, double rr, c64 omega, int ite
 // Scalars of the fused update of right-hand side rhs.  With u.npart the
 // workgroup folds the partials itself (and, as `lead`, records the outcome);
 // otherwise they are in the state.  Returns false when the right-hand side
-// stopped.  The state's fields written here are not read here, except the
-// activity flag, which every workgroup also decides for itself.
+// stopped.  The state's fields written here are not read here; the activity
+// flag is, before (group_flag), and every workgroup comes to the same decision.
 struct UpdScal {
   c64 beta, om, al;
   bool first;

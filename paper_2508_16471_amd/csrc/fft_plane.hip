@@ -103,15 +103,14 @@ struct PlaneArgs {
 template <typename T, int P1, bool COMP, int NT = plane_threads(P1)>
 __global__ __launch_bounds__(NT) void k_plane_fwd(
     const c64* __restrict__ x, cpx<T>* __restrict__ B, const cpx<T>* __restrict__ tw1,
-    const cpx<T>* __restrict__ tw2, BodyIdx bi, PlaneArgs a, const int* __restrict__ active,
-    UpdArgs u) {
+    const cpx<T>* __restrict__ tw2, BodyIdx bi, PlaneArgs a, const int* active, UpdArgs u) {
   using X = PlaneLine<P1, NT>;
   extern __shared__ __align__(16) char smem[];
   __shared__ double red[16];
   cpx<T>* plane = reinterpret_cast<cpx<T>*>(smem);
   cpx<T>* ubuf = plane + a.ubuf;
   const int rhs = blockIdx.x % a.nrhs, cz = blockIdx.x / a.nrhs;
-  if (active && !active[rhs]) return;
+  if (active && !group_flag(active + rhs)) return;
   const int comp = cz / a.N3, z = cz % a.N3;
   UpdScal us;
   if (COMP && u.mode != UPD_NONE) {

@@ -23,8 +23,8 @@ namespace vie {
 template <typename T, int P, typename TI, bool H = false, bool U = false>
 __global__ __launch_bounds__(nt_lines_p<T>(P)) void k_fft_x_fwd_c(
     const cpx<TI>* __restrict__ xc, void* __restrict__ outv, const cpx<T>* __restrict__ tw,
-    BodyIdx bi, int N1, int N2, int N3, int blocks_per_rhs, const int* __restrict__ active,
-    float hs, UpdArgs u) {
+    BodyIdx bi, int N1, int N2, int N3, int blocks_per_rhs, const int* active, float hs,
+    UpdArgs u) {
   constexpr int E = fft_e<P>(), TT = P / E, NT = nt_lines_p<T>(P), L = NT / TT,
                 LS = PadX<P, P / fft_e<P>()>::LSTR;
   __shared__ cpx<T> lds[L * LS];
@@ -33,10 +33,12 @@ __global__ __launch_bounds__(nt_lines_p<T>(P)) void k_fft_x_fwd_c(
   // leave none idle, and concurrently running blocks touch neighbouring lines.
   const int b = blockIdx.x;
   const int rhs = b / blocks_per_rhs, blk = b % blocks_per_rhs;
-  if (active && !active[rhs]) return;
   UpdScal us;
-  if constexpr (U) {
+  if constexpr (!U) {
+    if (active && !active[rhs]) return;
+  } else {
     __shared__ double red[16];
+    if (active && !group_flag(active + rhs)) return;
     if (!upd_scalars<NT>(u, rhs, blk == 0, red, us)) return;
   }
   const int lines_per_rhs = 3 * N2 * N3, lpc = N2 * N3;

@@ -412,7 +412,7 @@ __global__ void __launch_bounds__(64) k_rt_fold(const c64* __restrict__ part, in
 // vector kernel sums the partials it needs in every workgroup and one
 // workgroup per vector stores the results; no kernel stores a value that
 // another workgroup of the same launch reads (except `active`, cleared by the
-// same decision that every workgroup takes for itself).
+// same decision that every workgroup takes for itself, see group_flag).
 struct RtScal {
   c64 rho, rho1, alpha, omega;
   double tol2;      // tol^2 ||b||^2 (recursive residual threshold)
@@ -483,10 +483,10 @@ __global__ void __launch_bounds__(kRtThreads) k_rt_restart(
 // (breakdown); so does the iteration cap.
 __global__ void __launch_bounds__(kRtThreads) k_rt_pupd(
     c64* __restrict__ p, const c64* __restrict__ r, const c64* __restrict__ v,
-    RtScal* __restrict__ scal, int* __restrict__ active, int64_t n, int vb,
+    RtScal* __restrict__ scal, int* active, int64_t n, int vb,
     const c64* __restrict__ part, int npart) {
   const int vec = blockIdx.x / vb, blk = blockIdx.x % vb;
-  if (!active[vec]) return;
+  if (!group_flag(active + vec)) return;
   RtScal* S = scal + vec;
   const c64 rho = S->rho, alpha = S->alpha, om = S->omega;
   const double tol2 = S->tol2;
@@ -518,10 +518,10 @@ __global__ void __launch_bounds__(kRtThreads) k_rt_pupd(
 // alpha = rho1 / (rh, v); s = r - alpha v
 __global__ void __launch_bounds__(kRtThreads) k_rt_supd(
     c64* __restrict__ s, const c64* __restrict__ r, const c64* __restrict__ v,
-    RtScal* __restrict__ scal, int* __restrict__ active, int64_t n, int vb,
+    RtScal* __restrict__ scal, int* active, int64_t n, int vb,
     const c64* __restrict__ part, int npart) {
   const int vec = blockIdx.x / vb, blk = blockIdx.x % vb;
-  if (!active[vec]) return;
+  if (!group_flag(active + vec)) return;
   RtScal* S = scal + vec;
   const c64 rho1 = S->rho1;
   c64 rhv, none;
