@@ -211,6 +211,14 @@ constexpr int nt_lines_p(int P) {
 }
 
 
+// Orders the LDS accesses of one wave's lanes before and after it: lanes that
+// share a line run in step, but the compiler orders only what one lane reads
+// and writes itself.  A fence to the compiler, no instruction.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // *flag, read once for the whole workgroup, in kernels whose leading workgroup
 // may clear it meanwhile.  Either value will do then, as every workgroup that
 // goes on takes the leading one's decision for itself -- but not one for some

@@ -179,7 +179,8 @@ __global__ __launch_bounds__(NT) void k_plane_fwd(
       }
     }
     plane_fft<T, P1, false, true, false>(v, line, t, tr);
-    if (valid) {  // the line's own threads (one wave) have done its last reads
+    wave_fence();  // the line's own threads (one wave) have done its last reads
+    if (valid) {
 #pragma unroll
       for (int q = 0; q < X::E; ++q) line[pidx(t + q * X::TT)] = v[q];
     }
@@ -220,6 +221,7 @@ __global__ __launch_bounds__(NT) void k_plane_inv(
     for (int q = 0; q < X::E; ++q) v[q] = valid ? line[pidx(t + q * X::TT)] : mk<T>(0, 0);
     plane_fft<T, P1, true, false, true>(v, line, t, tr);  // only x < N1 is used
     if constexpr (COMP) {
+      wave_fence();          // as in the forward pass
       if (!valid) continue;  // no barrier below
       // the line's own threads (one wave) exchange the result
 #pragma unroll
@@ -251,8 +253,7 @@ __global__ __launch_bounds__(NT) void k_plane_inv(
           if (mode == EPI_RHV) ar[i] = aux[vb + k];
         }
       }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+      wave_fence();
 #pragma unroll
       for (int i = 0; i < X::E / 2; ++i) {
         const int k = k0 + i * X::TT;

@@ -39,3 +39,21 @@ def test_gates_that_a_launch_clears_are_read_once_per_workgroup():
         assert "group_flag(active + " in gate, name
         assert "int* __restrict__ active" not in text, name
     assert sorted(names) == ["k_fft_x_fwd_c", "k_plane_fwd", "k_rt_pupd", "k_rt_supd"]
+
+
+def test_lines_written_over_their_transform_are_fenced():
+    """The plane passes put a line back into the LDS that its own wave has just
+    transformed it in, without a barrier: each write comes after a wave fence."""
+    writes = 0
+    for name, text in _kernels():
+        if name not in ("k_plane_fwd", "k_plane_inv"):
+            continue
+        after = text.split("plane_fft<")[1:]
+        assert len(after) == 1, name
+        at = after[0].index("line[pidx(t + q * X::TT)] = v[q];")
+        assert "wave_fence();" in after[0][:at], name
+        writes += 1
+        reads = after[0][at:].find("line[pidx(xi)]")
+        if reads >= 0:
+            assert "wave_fence();" in after[0][at:at + reads], name
+    assert writes == 2
