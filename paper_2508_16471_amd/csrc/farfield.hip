@@ -315,15 +315,24 @@ struct FfGroups {
   int ks0[kNumShapes], tile0[kNumShapes], ntiles[kNumShapes], bx[kNumShapes], by[kNumShapes];
 };
 
-// sin and cos of x for |x| < 1e9: Cody-Waite reduction by pi/2 with a two-part
+// The integer nearest x s, as a double and its low bits: adding 3/2 2^52 leaves
+// it in the low mantissa bits for |x s| < 2^51 (a conversion to int would end
+// at 2^31).
+__device__ __forceinline__ double ff_round(double x, double s, int& low) {
+  const double t = fma(x, s, 6755399441055744.0);
+  low = (int)(unsigned)__double_as_longlong(t);
+  return t - 6755399441055744.0;
+}
+
+// sin and cos of x for |x| < 1e15: Cody-Waite reduction by pi/2 with a two-part
 // constant (FMA), then Taylor polynomials on |r| <= pi/4 through r^17 (sin)
 // and r^16 (cos); absolute error about 2e-16.  Branch-free, so it schedules
 // between the matrix instructions.
 __device__ __forceinline__ void ff_sincos(double x, double& sn, double& cs) {
-  const double n = rint(x * 0.63661977236758134308);
+  int q;
+  const double n = ff_round(x, 0.63661977236758134308, q);  // 2 / pi
   double r = fma(-n, 1.5707963267948966192, x);
   r = fma(-n, 6.123233995736766036e-17, r);
-  const int q = (int)n;
   const double r2 = r * r;
   double ps = 2.8114572543455207632e-15;    // 1/17!
   ps = fma(ps, r2, -7.6471637318198164759e-13);  // -1/15!
@@ -349,16 +358,17 @@ __device__ __forceinline__ void ff_sincos(double x, double& sn, double& cs) {
   cs = ((q + 1) & 2) ? -c1 : c1;
 }
 
-// exp(i x) from a 256-entry table of exp(2 pi i k / 256) in LDS: x = k pi/128
+// exp(i x), |x| < 1e13, from a 256-entry table of exp(2 pi i k / 256) in LDS: x = k pi/128
 // + e with |e| <= pi/256 (two-part FMA reduction), then Taylor polynomials of
 // cos e through e^6 and sin e through e^7 (truncation below 1e-19) and one
 // complex product with the table entry.
 constexpr int FF_NT = 256;
 __device__ __forceinline__ c64 ff_expi(double x, const c64* sT) {
-  const double kf = rint(x * 40.743665431525205957);  // 128 / pi
+  int k;
+  const double kf = ff_round(x, 40.743665431525205957, k);  // 128 / pi
   double e = fma(-kf, 2.4543692606170259375e-02, x);  // fl(pi) / 128
   e = fma(-kf, 9.5675531183386971e-19, e);            // (pi - fl(pi)) / 128
-  const c64 t = sT[(int)kf & (FF_NT - 1)];
+  const c64 t = sT[k & (FF_NT - 1)];
   const double e2 = e * e;
   double pc = fma(e2, -1.3888888888888888889e-03, 4.1666666666666666667e-02);
   pc = fma(e2, pc, -0.5);

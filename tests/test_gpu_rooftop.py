@@ -386,3 +386,47 @@ def test_outputs_through_staging_equal_pinned_outputs(V, n):
         assert np.abs(want).max() > 0
     finally:
         V.vie_rt_destroy(r)
+
+
+def _farfield_long(alpha, pos, h, k0, w, theta, phi):
+    """The face sum in extended precision, from the angles on."""
+    t, p = np.asarray(theta, np.longdouble), np.asarray(phi, np.longdouble)
+    st, ct, sp, cp = np.sin(t), np.cos(t), np.sin(p), np.cos(p)
+    r = np.stack([st * cp, st * sp, ct], -1)
+    S = []
+    for i in range(3):
+        m = alpha[i] > 0
+        ang = -np.longdouble(k0) * (r @ pos[i][m].astype(np.longdouble).T)
+        re, im = (alpha[i][m] * w[i][m]).real, (alpha[i][m] * w[i][m]).imag
+        c, s = np.cos(ang), np.sin(ang)
+        S.append((c @ re - s @ im) + 1j * (c @ im + s @ re).astype(np.clongdouble))
+    C = np.longdouble(k0) ** 2 * np.longdouble(h) ** 3 / (16 * np.arctan(np.longdouble(1)))
+    return C * np.stack([ct * cp * S[0] + ct * sp * S[1] - st * S[2], cp * S[1] - sp * S[0]], -1)
+
+
+@pytest.mark.parametrize("ntheta,nphi", [(11, 1), (60, 130)])
+def test_farfield_of_a_body_far_away(V, ntheta, nphi):
+    """A body 2^28 wavelengths from the coordinate origin (positions exact): its
+    phases are of 2e9 rad, beyond a 32-bit number of table steps.  Bar: a phase
+    of that size carries 8 roundings of 2^-53 (three per direction cosine, the
+    products and sums), 2e-6."""
+    print("rooftop far field far away", ntheta, flush=True)
+    rng = np.random.default_rng(6)
+    n, h = (20, 17, 23), 1.0 / 32
+    origin = (2.0 ** 28, 2.0 ** 27, -(2.0 ** 26))
+    chi = np.where(rng.random(n[::-1]) < 0.6, 1.5, 0.0)
+    active, alpha, _, pos = rt.face_data(chi, h, origin)
+    w = np.where(active, rng.standard_normal(active.shape) + 1j, 0)
+    theta, phi = np.meshgrid(rng.uniform(0, np.pi, ntheta), np.linspace(-3, 3, nphi), indexing="ij")
+    theta, phi = theta.ravel(), phi.ravel()
+    r = V.vie_rt_setup(chi + 1, h, origin, K0)
+    try:
+        ext, _ = V.vie_rt_grid(r)
+        F = V.vie_rt_farfield(r, w.reshape((1, 3) + ext[::-1]), theta, phi)[0]
+    finally:
+        V.vie_rt_destroy(r)
+    some = rng.choice(theta.size, 10, replace=False)
+    ref = _farfield_long(alpha, pos, h, K0, w, theta[some], phi[some])
+    err = float(np.max(np.abs(F[some] - ref)) / np.max(np.abs(ref)))
+    print(err)
+    assert err < 2e-6
