@@ -2497,7 +2497,7 @@ static int far_project(vie_ctx* ctx, BodyRec& B, std::vector<double> in, bool an
   VIE_HIP(hipMemcpyAsync(din, in.data(), in.size() * sizeof(double), hipMemcpyHostToDevice,
                          ctx->stream));
   const FarSrc src = {G.x.as<c64>(), (const int64_t*)(din + nin), B.nb, nullptr};
-  const FarGeom geo = {ctx->opt.k0, G.h, {B.origin[0], B.origin[1], B.origin[2]}, 0.0};
+  const FarGeom geo = far_geom(ctx->opt.k0, G.h, B.origin, 0, G.g.N, 0.0);
   VIE_HIP(timed(ctx, 12, [&] {
     const int* perm = sweep ? G.gidx.as<int>() + gr.tile.size() : nullptr;
     if (angles) {

@@ -7,19 +7,20 @@
 // never stored: the body voxels are grouped into aligned blocks of 16 voxels
 // (shape bx x by x bz, chosen per body to minimise padding), and for a voxel
 // at block origin o_b plus offset u the phase factors as
-//   exp(-i k0 r.(o + h(o_b + u))) = S(r, b) A(r, u),
-// S(r, b) = exp(-i k0 r.(o + h o_b)),   A(r, u) = exp(-i k0 h r.u).
+//   exp(-i k0 r.(o + h(o_b + u - c))) = P(r) S(r, b) A(r, u),
+// P(r) = exp(-i k0 r.o),  S(r, b) = exp(-i k0 h r.(o_b - c)),  A(r, u) = exp(-i k0 h r.u)
+// (c the reference point, see FarGeom).
 // A is the same for every block, so it stays in registers as the MFMA's left
 // operand for the whole kernel; each block contributes
 //   G(r, b, qc) = sum_u A(r, u) W(b, u, qc)   (16x16x16 complex tiles on MFMA)
 // and is scaled by S(r, b) (one sincos per direction and block) and summed.
 // The accumulation over blocks is split across workgroups (K-split) and
 // reduced in fixed order by a second kernel that projects onto theta-hat /
-// phi-hat and applies the constant.
+// phi-hat and applies P and the constant.
 //
 // Directions that share theta share the phase's z factor exp(-i k0 h cos(theta) z),
 // so a sweep on a (theta, phi) grid needs the voxels only once per theta:
-//   U(theta, x, y) = sum_z w(x, y, z) exp(-i k0 h cos(theta) z)     (k_ff_columns)
+//   U(theta, x, y) = sum_z w(x, y, z) exp(-i k0 h cos(theta) (z - c_z))   (k_ff_columns)
 //   F(theta, phi)  = sum_xy U(theta, x, y) exp(-i k0 (r_x x + r_y y))
 // and the second sum is the same contraction over blocks of 16 columns.  On
 // the 128-cell metasurface (193,248 voxels in 16,384 columns) a 180 x 360
@@ -211,6 +212,17 @@ void far_columns_build(const int* vox, int nb, const int N[3], FarColumns& fc) {
   }
 }
 
+FarGeom far_geom(double k0, double h, const double o[3], int pad, const int N[3], double half) {
+  FarGeom g = {k0, h, {0, 0, 0}, half, {0, 0, 0}, 16};
+  for (int a = 0; a < 3; ++a) {
+    g.nmax = std::max(g.nmax, N[a]);
+    const double near = rint(pad - o[a] / h);
+    g.c[a] = near > 0.0 ? (near < N[a] - 1 ? (int)near : N[a] - 1) : 0;
+    g.o[a] = fma(h, (double)(g.c[a] - pad), o[a]);
+  }
+  return g;
+}
+
 bool far_groups(const double* theta, int nd, FarGroups& fg) {
   // open-addressed table of the distinct angles (by their bits), at most half
   // as many as directions: beyond that nothing is shared
@@ -305,8 +317,47 @@ __global__ void k_far_frames(const double* __restrict__ ang, const int* __restri
 }
 
 struct FfGeom {
-  double k0, h, o[3];
+  double kh, khl;  // -k0 h to twice the precision
+  double split;    // see FfAxes
+  int c[3];
 };
+
+// Phases per voxel along the axes, -k0 h r, each split in two parts: whole
+// multiples of a quantum (adding and taking away `split` = 3/2 of 2^52 quanta
+// leaves them) and the rest.  The quantum is such that products with voxel
+// offsets and their sums are exact in the first parts, so a block's phase and
+// an offset's inside it have no error of their own: where one takes back what
+// the other has put on (a body near the reference point) nothing is left.
+struct FfAxes {
+  double x, y, z, xl, yl, zl;
+  __device__ __forceinline__ void set(const FfGeom& g, double rx, double ry, double rz) {
+    part(g, rx, x, xl);
+    part(g, ry, y, yl);
+    part(g, rz, z, zl);
+  }
+  // (written out with fma: the same bits wherever it is inlined)
+  static __device__ __forceinline__ void part(const FfGeom& g, double r, double& hi, double& lo) {
+    hi = fma(g.kh, r, g.split) - g.split;
+    lo = fma(g.khl, r, fma(g.kh, r, -hi));
+  }
+  __device__ __forceinline__ double hi(double i, double j, double l) const {
+    return fma(z, l, fma(y, j, x * i));
+  }
+  __device__ __forceinline__ double lo(double i, double j, double l) const {
+    return fma(zl, l, fma(yl, j, xl * i));
+  }
+};
+static FfGeom ff_geom(const FarGeom& g) {
+  FfGeom f;
+  const double kh = g.k0 * g.h;
+  f.kh = -kh;
+  f.khl = -fma(g.k0, g.h, -kh);
+  int e;
+  frexp(3.0 * kh * g.nmax, &e);  // every sum is below 2^e
+  f.split = ldexp(1.5, e);
+  for (int a = 0; a < 3; ++a) f.c[a] = g.c[a];
+  return f;
+}
 
 // The tile groups of one launch: group g's K-splits start at ks0[g] and end at
 // the next group's, its tiles are tile0[g] .. + ntiles[g] - 1, its blocks bx[g] x by[g] x (16 / bx / by).
@@ -324,15 +375,9 @@ __device__ __forceinline__ double ff_round(double x, double s, int& low) {
   return t - 6755399441055744.0;
 }
 
-// sin and cos of x for |x| < 1e15: Cody-Waite reduction by pi/2 with a two-part
-// constant (FMA), then Taylor polynomials on |r| <= pi/4 through r^17 (sin)
-// and r^16 (cos); absolute error about 2e-16.  Branch-free, so it schedules
-// between the matrix instructions.
-__device__ __forceinline__ void ff_sincos(double x, double& sn, double& cs) {
-  int q;
-  const double n = ff_round(x, 0.63661977236758134308, q);  // 2 / pi
-  double r = fma(-n, 1.5707963267948966192, x);
-  r = fma(-n, 6.123233995736766036e-17, r);
+// sin and cos of q pi/2 + r, |r| <= pi/4: Taylor polynomials through r^17 (sin)
+// and r^16 (cos); absolute error about 2e-16.
+__device__ __forceinline__ void ff_quadrant(double r, int q, double& sn, double& cs) {
   const double r2 = r * r;
   double ps = 2.8114572543455207632e-15;    // 1/17!
   ps = fma(ps, r2, -7.6471637318198164759e-13);  // -1/15!
@@ -358,16 +403,33 @@ __device__ __forceinline__ void ff_sincos(double x, double& sn, double& cs) {
   cs = ((q + 1) & 2) ? -c1 : c1;
 }
 
-// exp(i x), |x| < 1e13, from a 256-entry table of exp(2 pi i k / 256) in LDS: x = k pi/128
-// + e with |e| <= pi/256 (two-part FMA reduction), then Taylor polynomials of
-// cos e through e^6 and sin e through e^7 (truncation below 1e-19) and one
-// complex product with the table entry.
+// sin and cos of x + lo for |x| < 1e15, tiny lo: Cody-Waite reduction by pi/2 with
+// a two-part constant (FMA).  Branch-free, so it schedules between the matrix
+// instructions.
+__device__ __forceinline__ void ff_sincos(double x, double lo, double& sn, double& cs) {
+  int q;
+  const double n = ff_round(x, 0.63661977236758134308, q);  // 2 / pi
+  double r = fma(-n, 1.5707963267948966192, x);
+  r = fma(-n, 6.123233995736766036e-17, r) + lo;
+  ff_quadrant(r, q, sn, cs);
+}
+
+// exp(i (x + lo)), |x| < 1e13, from a 256-entry table of exp(2 pi i k / 256) in LDS:
+// x = k pi/128 + e with |e| <= pi/256 (two-part FMA reduction), then Taylor
+// polynomials of cos e through e^6 and sin e through e^7 (truncation below
+// 1e-19) and one complex product with the table entry.
 constexpr int FF_NT = 256;
-__device__ __forceinline__ c64 ff_expi(double x, const c64* sT) {
+__device__ __forceinline__ c64 ff_table(int k) {  // the angle within pi/4 of its quadrant's
+  const int q = (k + FF_NT / 8) / (FF_NT / 4);
+  double sn, cs;
+  ff_quadrant((k - q * (FF_NT / 4)) * (2.0 * M_PI / FF_NT), q, sn, cs);
+  return mk(cs, sn);
+}
+__device__ __forceinline__ c64 ff_expi(double x, double lo, const c64* sT) {
   int k;
   const double kf = ff_round(x, 40.743665431525205957, k);  // 128 / pi
   double e = fma(-kf, 2.4543692606170259375e-02, x);  // fl(pi) / 128
-  e = fma(-kf, 9.5675531183386971e-19, e);            // (pi - fl(pi)) / 128
+  e = fma(-kf, 9.5675531183386971e-19, e) + lo;       // (pi - fl(pi)) / 128
   const c64 t = sT[k & (FF_NT - 1)];
   const double e2 = e * e;
   double pc = fma(e2, -1.3888888888888888889e-03, 4.1666666666666666667e-02);
@@ -402,16 +464,13 @@ __device__ __forceinline__ void ff_store(c64* sW, int4* sOrg, const FfPre& p) {
   if (threadIdx.x < FF_TB) sOrg[threadIdx.x] = p.o;
 }
 
-struct FfRows {
-  double p0[4], cx[4], cy[4], cz[4];
-};
-
 // G(r, b, qc) = sum_u A(r, u) W(b, u, qc) for one staged tile (complex as
 // four real products), and the block scale S(r, b) of this lane's column.
 __device__ __forceinline__ void ff_tile(const c64* sW, const int4* sOrg, const c64* sT,
                                         const double (&aR)[4],
                                         const double (&aI)[4], const double (&aIn)[4],
-                                        const FfRows& rw, int lane, d4 (&gR)[FF_QC],
+                                        const FfAxes (&rw)[4], const int (&ref)[3], int lane,
+                                        d4 (&gR)[FF_QC],
                                         d4 (&gI)[FF_QC], c64 (&S)[4]) {
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
@@ -441,11 +500,10 @@ __device__ __forceinline__ void ff_tile(const c64* sW, const int4* sOrg, const c
     }
   }
   const int4 ob = sOrg[lane & 15];
-  const double ox = ob.x, oy = ob.y, oz = ob.z;
+  const double ox = ob.x - ref[0], oy = ob.y - ref[1], oz = ob.z - ref[2];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const double ang = fma(rw.cz[r], oz, fma(rw.cy[r], oy, fma(rw.cx[r], ox, rw.p0[r])));
-    S[r] = ff_expi(ang, sT);
+    S[r] = ff_expi(rw[r].hi(ox, oy, oz), rw[r].lo(ox, oy, oz), sT);
   }
 }
 
@@ -468,14 +526,18 @@ constexpr int FF_NZ = 256;  // most z layers of a grid
 __global__ __launch_bounds__(256) void k_ff_columns(FarSrc f, const int* __restrict__ ptr,
                                                     const int2* __restrict__ ent, int ntiles,
                                                     const int* __restrict__ gfirst, int g0, int ng,
-                                                    const double* __restrict__ dirs, double k0h,
+                                                    const double* __restrict__ dirs, FfGeom fg,
                                                     int nz, c64* __restrict__ Wd) {
   __shared__ c64 sT[FF_CG][FF_NZ];
   const int gb = blockIdx.y * FF_CG;
   for (int k = threadIdx.x; k < FF_CG * nz; k += 256) {
     const int g = k / nz, z = k % nz;
     double sn = 0.0, cs = 0.0;
-    if (gb + g < ng) ff_sincos(-k0h * dirs[(int64_t)gfirst[g0 + gb + g] * 9 + 2] * z, sn, cs);
+    if (gb + g < ng) {
+      double hi, lo;
+      FfAxes::part(fg, dirs[(int64_t)gfirst[g0 + gb + g] * 9 + 2], hi, lo);
+      ff_sincos(hi * (z - fg.c[2]), lo * (z - fg.c[2]), sn, cs);
+    }
     sT[g][z] = mk(cs, sn);
   }
   __syncthreads();
@@ -542,11 +604,7 @@ __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))
   __shared__ int4 sOrg[2][FF_TB];
   __shared__ c64 sT[FF_NT];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int k = threadIdx.x; k < FF_NT; k += FF_DIRS * 4) {
-    double sn, cs;
-    ff_sincos(k * (2.0 * M_PI / FF_NT), sn, cs);
-    sT[k] = mk(cs, sn);
-  }  // visible after the first barrier of the tile loop
+  for (int k = threadIdx.x; k < FF_NT; k += FF_DIRS * 4) sT[k] = ff_table(k);  // visible after the first barrier of the tile loop
   const int dbase = first + wave * 16;
   const int t0 = ((int)blockIdx.y - ks0) * tiles_per_split;
   const int t1 = min(ntiles, t0 + tiles_per_split);
@@ -561,13 +619,14 @@ __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))
       ry = dirs[d * 9 + 1];
       rz = dirs[d * 9 + 2];
     }
+    FfAxes ax;
+    ax.set(fg, rx, ry, rz);
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       const int u = 4 * ks + (lane >> 4);
       const int du = u % bx, dv = (u / bx) % by, dw = u / (bx * by);
-      const double ang = -fg.k0 * fg.h * (rx * du + ry * dv + rz * dw);
       double sn, cs;
-      ff_sincos(ang, sn, cs);
+      ff_sincos(ax.hi(du, dv, dw), ax.lo(du, dv, dw), sn, cs);
       aR[ks] = cs;
       aI[ks] = sn;
       aIn[ks] = -sn;
@@ -575,7 +634,7 @@ __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))
   }
   // output rows of this lane (FP64 16x16x4 result layout: row lane/16 + 4 r,
   // column lane % 16): directions dbase + lane/16 + 4 r
-  FfRows rw;
+  FfAxes rw[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int d = dbase + (lane >> 4) + 4 * r;
@@ -585,10 +644,7 @@ __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))
       ry = dirs[d * 9 + 1];
       rz = dirs[d * 9 + 2];
     }
-    rw.p0[r] = -fg.k0 * (rx * fg.o[0] + ry * fg.o[1] + rz * fg.o[2]);
-    rw.cx[r] = -fg.k0 * fg.h * rx;
-    rw.cy[r] = -fg.k0 * fg.h * ry;
-    rw.cz[r] = -fg.k0 * fg.h * rz;
+    rw[r].set(fg, rx, ry, rz);
   }
   c64 acc[4][FF_QC];
 #pragma unroll
@@ -606,7 +662,7 @@ __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))
     if (t + 1 < t1) pre = ff_fetch(Wd, org, t + 1);
     __syncthreads();
     if (dbase < nd) {
-      ff_tile(sW[cb], sOrg[cb], sT, aR, aI, aIn, rw, lane, gR, gI, S);
+      ff_tile(sW[cb], sOrg[cb], sT, aR, aI, aIn, rw, fg.c, lane, gR, gI, S);
       ff_accum(gR, gI, S, acc);
     }
   }
@@ -635,10 +691,30 @@ __global__ __launch_bounds__(FF_DIRS * 4) __attribute__((amdgpu_waves_per_eu(2))
   }
 }
 
+// hi + lo += a b to twice the precision.
+__device__ __forceinline__ void ff_dot(double& hi, double& lo, double a, double b) {
+  const double p = a * b, s = hi + p, t = s - hi;
+  lo += ((hi - (s - t)) + (p - t)) + fma(a, b, -p);
+  hi = s;
+}
+// v exp(i (x + lo)) as v + v (exp - 1): a small phase's rounding stays as small as
+// the phase (and any size of phase will do).
+__device__ __forceinline__ c64 ff_turn(c64 v, double x, double lo) {
+  double s, c;
+  sincos(0.5 * x, &s, &c);
+  const double sn = 2.0 * s * c, t = -2.0 * s * s;
+  const double re = t - lo * sn, im = fma(lo, t, lo) + sn;
+  return mk(v.re + fma(re, v.re, -(im * v.im)), v.im + fma(re, v.im, im * v.re));
+}
+
 // F = scale (theta-hat . S, phi-hat . S), S = the sum of the kst partials
 // of a (right-hand side, direction position) pair, which are contiguous per
-// component; component c's points sit `half` / k0 off the block origins along
-// axis c (rooftop faces; 0 for voxels).  Position p is direction perm[p].  L lanes share a pair: 64 where there are many partials (a
+// component; the reference point's phase -k0 r.o enters here, and component c's
+// points sit g.half off the grid points along axis c (rooftop faces; 0 for
+// voxels).  What is done once per direction is not averaged over the points, so
+// its roundings would be most of the error: the phases are kept to twice the
+// precision and applied as small corrections.  Position p is direction
+// perm[p].  L lanes share a pair: 64 where there are many partials (a
 // detector scan splits the voxels into hundreds; one thread walking them took
 // 190 us at 181 directions and 341 partials), 1 where a sweep leaves a few.
 // Fixed order either way.
@@ -647,7 +723,7 @@ __global__ __launch_bounds__(256) void k_farfield_project(const c64* __restrict_
                                                           int npair, int nd,
                                                           const double* __restrict__ dirs,
                                                           const int* __restrict__ perm,
-                                                          double scale, double half,
+                                                          double scale, FarGeom g,
                                                           c64* __restrict__ F) {
   const int e = (blockIdx.x * 256 + threadIdx.x) / L, lane = threadIdx.x % L;
   if (e >= npair) return;
@@ -668,12 +744,14 @@ __global__ __launch_bounds__(256) void k_farfield_project(const c64* __restrict_
   if (lane != 0) return;
   const int pos = e % nd, q = e / nd;
   const double* D = dirs + (int64_t)pos * 9;
-  if (half != 0.0)
-    for (int c = 0; c < 3; ++c) {
-      double sn, cs;
-      ff_sincos(-half * D[c], sn, cs);
-      v[c] = v[c] * mk(cs, sn);
-    }
+  double at = 0.0, atl = 0.0;
+  for (int a = 0; a < 3; ++a) ff_dot(at, atl, D[a], g.o[a]);
+  for (int c = 0; c < 3; ++c) {
+    double x = at, xl = atl;
+    ff_dot(x, xl, D[c], g.half);
+    const double ang = -g.k0 * x;
+    v[c] = ff_turn(v[c], ang, fma(-g.k0, xl, fma(-g.k0, x, -ang)));
+  }
   c64 ft = mk(0.0, 0.0), fp = mk(0.0, 0.0);
   for (int c = 0; c < 3; ++c) {
     ft = ft + D[3 + c] * v[c];
@@ -688,13 +766,12 @@ static hipError_t far_project_sums(const c64* part, int kst, int npair, int nd,
                                    const double* dirs, const int* perm, const FarGeom& fg, c64* F,
                                    hipStream_t s) {
   const double scale = fg.k0 * fg.k0 * fg.h * fg.h * fg.h / (4.0 * M_PI);
-  const double half = fg.k0 * fg.half;
   if (kst > 8)
     k_farfield_project<64><<<(npair + 3) / 4, 256, 0, s>>>(part, kst, npair, nd, dirs, perm, scale,
-                                                           half, F);
+                                                           fg, F);
   else
     k_farfield_project<1><<<(npair + 255) / 256, 256, 0, s>>>(part, kst, npair, nd, dirs, perm,
-                                                              scale, half, F);
+                                                              scale, fg, F);
   return hipGetLastError();
 }
 
@@ -786,10 +863,9 @@ hipError_t launch_farfield_sweep(const FarSrc& src, int nr, const FarColumns& fc
   if (nz > FF_NZ) return hipErrorInvalidValue;
   const int ng = (int)gr.first.size() - 1;
   const int tps = (fc.ntiles + pl.kst - 1) / pl.kst;
-  FfGeom fg;
-  fg.k0 = geo.k0;
-  fg.h = geo.h;
-  for (int a = 0; a < 3; ++a) fg.o[a] = geo.o[a];
+  const FfGeom fz = ff_geom(geo);
+  FfGeom fg = fz;
+  fg.c[2] = 0;  // z is in the columns' sums
   FfGroups gs = {};
   gs.n = 1;
   gs.ntiles[0] = fc.ntiles;
@@ -802,7 +878,7 @@ hipError_t launch_farfield_sweep(const FarSrc& src, int nr, const FarColumns& fc
     for (int g0 = 0; g0 < ng; g0 += pl.ngc) {
       const int n = std::min(pl.ngc, ng - g0);
       k_ff_columns<<<dim3(fc.ntiles, (n + FF_CG - 1) / FF_CG, nq), 256, 0, s>>>(
-          f, ptr, (const int2*)ent, fc.ntiles, first, g0, n, dirs, geo.k0 * geo.h, nz, Wd);
+          f, ptr, (const int2*)ent, fc.ntiles, first, g0, n, dirs, fz, nz, Wd);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
       const int d0 = gr.tile0[g0], d1 = gr.tile0[g0 + n];
@@ -823,10 +899,7 @@ hipError_t launch_farfield_mfma(const FarSrc& src, int nr, const FarBlocks& fb, 
                                 const int* blk_org, const FarPlan& pl, const double* dirs, int nd,
                                 const FarGeom& geo, c64* Wd, c64* part, c64* F, hipStream_t s) {
   const int ntiles = fb.ntiles;
-  FfGeom fg;
-  fg.k0 = geo.k0;
-  fg.h = geo.h;
-  for (int a = 0; a < 3; ++a) fg.o[a] = geo.o[a];
+  const FfGeom fg = ff_geom(geo);
   const int db = (nd + FF_DIRS - 1) / FF_DIRS;
   const int64_t tot = (int64_t)ntiles * FF_TILE;
   // every block shape in one launch, all splits equally long: launched one

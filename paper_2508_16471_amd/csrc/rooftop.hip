@@ -1327,8 +1327,7 @@ extern "C" int vie_rt_farfield(vie_rt* r, const vie_c64* w, int32_t nrhs, const 
   }
   const FarSrc src = {r->fw.as<c64>(), (const int64_t*)(r->fin.as<double>() + 2 * (size_t)ndir),
                       r->q.m, r->alpha};
-  FarGeom geo = {r->k0, r->h, {0, 0, 0}, 0.5 * r->h};
-  for (int a = 0; a < 3; ++a) geo.o[a] = r->origin[a] - r->h;  // padded cell 0
+  const FarGeom geo = far_geom(r->k0, r->h, r->origin, 1, r->q.E, 0.5 * r->h);
   for (int q0 = 0; q0 < nrhs && e == hipSuccess; q0 += per) {
     const int nq = std::min(per, nrhs - q0);
     chk(hipMemcpyAsync(r->fw.p, w + q0 * n, (size_t)nq * n * sizeof(c64), hipMemcpyHostToDevice,

@@ -224,3 +224,31 @@ def test_farfield_block_shapes_share_a_launch(V, ndir):
             assert _relerr(F[q], np.stack([ft, fp], -1)) < 1e-12
     finally:
         V.vie_destroy(ctx)
+
+
+def test_phases_are_taken_about_the_coordinate_origin(V):
+    """One voxel at the coordinate origin in the middle of a box of 127 voxels of
+    k0 h = 20: no phase at all, while the box's corner is at 1300 rad.  Bar: the
+    roundings of the direction frames, the projection and the constants, 16 of
+    2^-53; relative to the corner the rounding of one phase is 1e-13."""
+    print("far field of one voxel", flush=True)
+    rng = np.random.default_rng(4)
+    n, h = (127, 63, 9), 3.25
+    origin = tuple(-h * (m // 2) for m in n)
+    eps = np.ones(n[::-1])
+    eps[4, 31, 63] = 1.5
+    theta, phi = np.arccos(rng.uniform(-1, 1, 40)), rng.uniform(-np.pi, np.pi, 40)
+    ctx = V.vie_setup([(eps, h, origin)], V.make_options(K0, tol=1e-9, max_iter=2))
+    try:
+        V.vie_solve(ctx, _channels(rng, 1), [1], allow_noconv=True)
+        F = V.vie_farfield(ctx, 0, theta, phi, 1)[0]
+        w = V.vie_get_current(ctx, 0, 0, n)[:, 4, 31, 63].astype(np.clongdouble)
+    finally:
+        V.vie_destroy(ctx)
+    t, p = theta.astype(np.longdouble), phi.astype(np.longdouble)
+    C = np.longdouble(K0) ** 2 * np.longdouble(h) ** 3 / (16 * np.arctan(np.longdouble(1)))
+    ref = C * np.stack([np.cos(t) * (np.cos(p) * w[0] + np.sin(p) * w[1]) - np.sin(t) * w[2],
+                        np.cos(p) * w[1] - np.sin(p) * w[0]], -1)
+    err = float(np.max(np.abs(F - ref)) / np.max(np.abs(ref)))
+    print(err)
+    assert err < 16 * 2.0 ** -53

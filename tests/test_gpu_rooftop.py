@@ -404,6 +404,32 @@ def _farfield_long(alpha, pos, h, k0, w, theta, phi):
     return C * np.stack([ct * cp * S[0] + ct * sp * S[1] - st * S[2], cp * S[1] - sp * S[0]], -1)
 
 
+def test_farfield_phases_are_taken_about_the_coordinate_origin(V):
+    """One cell at the coordinate origin in the middle of a box of 127 cells of
+    k0 h = 20: its phases are 10 rad, those of the box's corner 1300.  Bar: the
+    directions' roundings (3 of 2^-53 each) and those of the phase itself times
+    10 rad, 1e-14; relative to the corner the rounding of one phase is 1e-13."""
+    print("rooftop far field of one cell", flush=True)
+    rng = np.random.default_rng(4)
+    n, h = (127, 63, 9), 3.25
+    origin = tuple(-h * (m // 2) for m in n)
+    chi = np.zeros(n[::-1])
+    chi[4, 31, 63] = 1.0
+    active, alpha, _, pos = rt.face_data(chi, h, origin)
+    w = np.where(active, rng.standard_normal(active.shape) + 1j, 0)
+    theta, phi = np.arccos(rng.uniform(-1, 1, 40)), rng.uniform(-np.pi, np.pi, 40)
+    r = V.vie_rt_setup(chi + 1, h, origin, K0)
+    try:
+        ext, _ = V.vie_rt_grid(r)
+        F = V.vie_rt_farfield(r, w.reshape((1, 3) + ext[::-1]), theta, phi)[0]
+    finally:
+        V.vie_rt_destroy(r)
+    ref = _farfield_long(alpha, pos, h, K0, w, theta, phi)
+    err = float(np.max(np.abs(F - ref)) / np.max(np.abs(ref)))
+    print(err)
+    assert err < 1e-14
+
+
 @pytest.mark.parametrize("ntheta,nphi", [(11, 1), (60, 130)])
 def test_farfield_of_a_body_far_away(V, ntheta, nphi):
     """A body 2^28 wavelengths from the coordinate origin (positions exact): its
