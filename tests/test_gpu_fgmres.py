@@ -394,3 +394,41 @@ def test_steps_of_few_and_many_right_hand_sides(V):
     for q in range(16):
         assert np.linalg.norm(w[16][q] - w[17][q]) <= 1e-11 * np.linalg.norm(w[17][q])
     assert np.linalg.norm(w[1][0] - w[17][0]) <= 1e-11 * np.linalg.norm(w[17][0])
+
+
+# block boxes of every y and z FFT length (y: 25..32, 33..48, 49..64 cells; z: 16, 25..32,
+# 33..48, 49..64) and uneven x, lines full or padded
+@pytest.mark.parametrize("n", [(104, 52, 16), (108, 112, 16), (52, 70, 30), (56, 60, 64),
+                               (100, 80, 53), (54, 128, 64), (70, 99, 49), (104, 64, 41),
+                               (90, 67, 46), (128, 105, 34)])
+def test_packed_fp16_lines_of_every_length(V, n):
+    """Every line along x, y and z of a two-step block solve, against FP64 products.  An entry
+    carries the rounding of two bfloat16 vectors (2^-9 each) and a few 2^-11 of the FP16
+    transforms, of the size of its neighbours: 1e-2 of a line's own norm leaves a factor of two
+    for entries that cancel.  A line left out, doubled, or at the wrong frequency is off by 0.1
+    and more, which the norm of the whole vector would hide."""
+    print("packed lines", n, flush=True)
+    rng = np.random.default_rng(sum(n))
+    h = 0.03
+    g = Grid.centred(n, h)
+    eps = 1.0 + rng.uniform(0.5, 2.0, size=n[::-1])
+    eps[rng.random(eps.shape) < 0.3] = 1.0
+    r = rng.standard_normal((1, 3) + n[::-1]) + 1j * rng.standard_normal((1, 3) + n[::-1])
+    out = []
+    for inner in (V.VIE_FP64, V.VIE_MIXED_BF16):
+        ctx = V.vie_setup([(eps, h, g.origin)],
+                          V.make_options(K0, precision=V.VIE_MIXED, flags=V.VIE_FLAG_TIMING))
+        try:
+            out.append(V.vie_precond_apply(
+                ctx, V.fgmres_options(blocks=(2, 2), inner_iters=2, inner_precision=inner), r)[0])
+            t = V.vie_kernel_times(ctx, reset=True)
+        finally:
+            V.vie_destroy(ctx)
+        assert (t["block_fft_xy_fwd_h16"][1] > 0) == (inner == V.VIE_MIXED_BF16)
+    body = eps != 1.0
+    for ax in (1, 2, 3):
+        e = np.sqrt((np.abs(out[1] - out[0]) ** 2).sum(ax) / np.maximum(
+            (np.abs(out[0]) ** 2).sum(ax), 1e-300))
+        full = np.broadcast_to(body.sum(ax - 1) >= 6, e.shape)
+        print("axis", "zyx"[ax - 1], "largest error of a line", e[full].max())
+        assert full.any() and e[full].max() < 1e-2

@@ -80,3 +80,25 @@ def test_solves_satisfy_the_oracle_system(V, n, prec, tol):
             assert np.linalg.norm(res) <= 2 * tol * np.linalg.norm(b) * max(5 * share, 1e-3)
     finally:
         V.vie_destroy(ctx)
+
+
+@pytest.mark.parametrize("prec,tol", [(0, 1e-11), (1, 1e-9)])
+@pytest.mark.parametrize("n", [g for g in GRIDS if g != (32, 32, 20)])
+def test_solves_meet_their_tolerance_on_every_row(V, n, prec, tol):
+    """The oracle's residual over all rows: at most the tolerance, and as much again for the
+    rounding of both sides' operators."""
+    rng, g, eps = _body(n)
+    k = np.array([0.6, 0.0, 0.8])
+    chi = (eps - 1).ravel()
+    pos = vd.voxel_centres(g.n, g.h, g.origin)
+    ctx = V.vie_setup([(eps, g.h, g.origin)],
+                      V.make_options(K0, precision=prec, tol=tol, max_iter=4000))
+    try:
+        V.vie_solve(ctx, [(k, [0.8, 0.5j, -0.6])], [1])
+        w = V.vie_get_current(ctx, 0, 0, g.n).reshape(3, -1)
+    finally:
+        V.vie_destroy(ctx)
+    b = vd.rhs(chi, pos, K0, k, [0.8, 0.5j, -0.6])
+    res = np.linalg.norm(b - vd.matvec(chi, pos, g.h, K0, w)) / np.linalg.norm(b)
+    print(n, prec, res)
+    assert res <= 2 * tol
