@@ -43,8 +43,6 @@ struct Cnn {
   size_t ws_vox = 0;
   bf16raw* act[kCnnLayers] = {nullptr};  // layer inputs (act[0] = features)
   bf16raw* gbuf[2] = {nullptr, nullptr}; // activation gradients (ping-pong)
-  bf16raw* fcopy = nullptr;              // aligned copy of misaligned features
-  size_t fcopy_vox = 0;
   float* out = nullptr;                  // network output [vox][16] fp32
   float* wpart = nullptr;                // weight-gradient partials
   float* loss = nullptr;                 // [2] numerator, denominator

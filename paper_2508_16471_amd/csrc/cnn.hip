@@ -26,6 +26,13 @@ typedef short v4s __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
+// A caller's tensor may start anywhere its elements may (a view into a larger
+// one): 16- and 8-byte accesses to it claim no more.  The memory unit takes
+// them so; on aligned tensors they are the same instructions.
+typedef uint32_t u4any __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u2any __attribute__((ext_vector_type(2), aligned(2)));
+typedef float f4any __attribute__((ext_vector_type(4), aligned(4)));
+
 // One 16x16 output tile += A (16 x K) B (K x 16) over K = 32 (or 16): lane l
 // holds row / column l % 16 and the K slice 8 (l / 16) .. + 7 (4 (l / 16) .. +
 // 3) of its operands, and receives D[4 (l / 16) + i][l % 16], i = 0..3.  Only
@@ -122,13 +129,13 @@ __global__ __launch_bounds__(CNT) __attribute__((amdgpu_waves_per_eu(2))) void k
     goff[p] = ok ? (gy * cd.d0 + gx) * CIN + (i % SL) * 8 : -1;
   }
   const size_t layer = (size_t)cd.d0 * cd.d1;
-  uint4 pre[PF];
+  u4any pre[PF];
   auto fetch = [&](int z) {
     const bf16raw* src = in + (size_t)z * layer * CIN;
 #pragma unroll
     for (int p = 0; p < PF; ++p) {
-      pre[p] = make_uint4(0u, 0u, 0u, 0u);
-      if (goff[p] >= 0) pre[p] = *(const uint4*)&src[goff[p]];
+      pre[p] = u4any{0u, 0u, 0u, 0u};
+      if (goff[p] >= 0) pre[p] = *(const u4any*)&src[goff[p]];
     }
   };
   // operand addresses: activations of voxel (row0 + s + dy', r + dx'), dy', dx' = 0..2,
@@ -164,7 +171,7 @@ __global__ __launch_bounds__(CNT) __attribute__((amdgpu_waves_per_eu(2))) void k
         const v4f c = acc[s][ct];
         const float v[4] = {c[0] + bv[ct].x, c[1] + bv[ct].y, c[2] + bv[ct].z, c[3] + bv[ct].w};
         if (MODE == 1) {
-          *(float4*)&outf[at] = make_float4(v[0], v[1], v[2], v[3]);
+          *(f4any*)&outf[at] = f4any{v[0], v[1], v[2], v[3]};
         } else {
           bf16raw h[4];
           if (MODE == 0) {
@@ -196,7 +203,9 @@ __global__ __launch_bounds__(CNT) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
     for (int q = 0; q < PF; ++q) {
       const int i = tid + q * CNT, v = i / SL;
-      if (i < NP) *(uint4*)&s_p[v * RB + (((i % SL) ^ swz(v)) << 4)] = pre[q];
+      if (i < NP)
+        *(uint4*)&s_p[v * RB + (((i % SL) ^ swz(v)) << 4)] =
+            make_uint4(pre[q].x, pre[q].y, pre[q].z, pre[q].w);
     }
     if (p < p1) fetch(p + 1);
     lds_barrier();
@@ -308,7 +317,10 @@ __global__ __launch_bounds__(GNT) void k_conv3d_wgrad(const bf16raw* __restrict_
 #pragma unroll
       for (int v = 0; v < TX + 2; ++v) {
         const int gx = x0 + v - 1;
-        if (gx >= 0 && gx < cd.d0) pre[v] = *(const uint2*)&src[(size_t)gx * CIN];
+        if (gx >= 0 && gx < cd.d0) {
+          const u2any t = *(const u2any*)&src[(size_t)gx * CIN];
+          pre[v] = make_uint2(t.x, t.y);
+        }
       }
     } else if (is_g) {
       const int gy = y0 + row % TY, gz = z0 + row / TY;
@@ -699,7 +711,7 @@ hipError_t cnn_alloc(Cnn& c) {
 
 void cnn_free(Cnn& c) {
   void* ps[] = {c.p, c.m, c.v, c.g, c.wf, c.wb, c.out, c.wpart, c.loss, c.gbuf[0], c.gbuf[1],
-                c.act[1], c.act[2], c.act[3], c.fcopy};
+                c.act[1], c.act[2], c.act[3]};
   for (void* q : ps)
     if (q) (void)hipFree(q);
   if (c.hostloss) (void)hipHostFree(c.hostloss);
@@ -780,26 +792,8 @@ static void wgrad(const GradDims& cd, const bf16raw* in, const bf16raw* g, float
 
 hipError_t cnn_forward(Cnn& c, const int d[3], const bf16raw* feat, float* out, hipStream_t s) {
   const ConvDims cd = conv_dims(d);
-  const size_t nv = (size_t)d[0] * d[1] * d[2];
-  hipError_t e = cnn_ensure_ws(c, nv);
+  hipError_t e = cnn_ensure_ws(c, (size_t)d[0] * d[1] * d[2]);
   if (e != hipSuccess) return e;
-  // the convolutions move 16-byte items: a caller's tensor that does not start
-  // on such a boundary goes through the network's own buffers
-  float* dst = out ? out : c.out;
-  if ((uintptr_t)feat & 15) {
-    if (c.fcopy_vox < nv) {
-      if (c.fcopy) (void)hipFree(c.fcopy);
-      c.fcopy = nullptr;
-      c.fcopy_vox = 0;
-      if ((e = dev_malloc(&c.fcopy, nv * kCnnIn * sizeof(bf16raw))) != hipSuccess) return e;
-      c.fcopy_vox = nv;
-    }
-    if ((e = hipMemcpyAsync(c.fcopy, feat, nv * kCnnIn * sizeof(bf16raw),
-                            hipMemcpyDeviceToDevice, s)) != hipSuccess)
-      return e;
-    feat = c.fcopy;
-  }
-  if ((uintptr_t)dst & 15) dst = c.out;
   c.act[0] = const_cast<bf16raw*>(feat);
   conv<32, 32, 0>(cd, feat, c.wf + bf16_weight_offset(0), c.p + c.off.b[0], c.act[1], nullptr,
                   nullptr, s);
@@ -807,12 +801,9 @@ hipError_t cnn_forward(Cnn& c, const int d[3], const bf16raw* feat, float* out, 
                   nullptr, nullptr, s);
   conv<32, 32, 0>(cd, c.act[2], c.wf + bf16_weight_offset(2), c.p + c.off.b[2], c.act[3],
                   nullptr, nullptr, s);
-  conv<32, 16, 1>(cd, c.act[3], c.wf + bf16_weight_offset(3), c.p + c.off.b[3], nullptr, dst,
-                  nullptr, s);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (out && dst != out)
-    e = hipMemcpyAsync(out, dst, nv * 16 * sizeof(float), hipMemcpyDeviceToDevice, s);
-  return e;
+  conv<32, 16, 1>(cd, c.act[3], c.wf + bf16_weight_offset(3), c.p + c.off.b[3], nullptr,
+                  out ? out : c.out, nullptr, s);
+  return hipGetLastError();
 }
 
 hipError_t cnn_backward(Cnn& c, const int d[3], const float* target, float* loss_host,

@@ -243,3 +243,37 @@ def test_checkpoint_resume_is_exact(env, tmp_path):
     finally:
         for n in nets:
             V.vie_cnn_destroy(n)
+
+
+@pytest.mark.parametrize("shift", [2, 8, 10])
+def test_tensors_that_start_anywhere_under_capture(env, shift):
+    """Features and outputs that start on any element, in a captured call after
+    one of the same size on aligned tensors (nothing left to allocate): each
+    replay gives the aligned tensors' outputs, bit for bit."""
+    V, torch = env
+    print("network under capture, shift", shift, flush=True)
+    d = (33, 18, 11)
+    shape = d[::-1]
+    n = int(np.prod(shape))
+    net = V.vie_cnn_create(5)
+    try:
+        feat = torch.randn(n * 32, device="cuda").to(torch.bfloat16)
+        want = torch.empty(n * 16, device="cuda")
+        V.vie_cnn_infer_dev(net, d, feat.data_ptr(), want.data_ptr())
+        odd = torch.zeros(n * 32 + 16, dtype=torch.bfloat16, device="cuda")
+        out = torch.zeros(n * 16 + 16, device="cuda")
+        k, m = shift // 2, shift // 4
+        odd[k:k + feat.numel()] = feat
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            V.vie_cnn_infer_dev(net, d, odd.data_ptr() + 2 * k, out.data_ptr() + 4 * m,
+                                torch.cuda.current_stream().cuda_stream)
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out[m:m + n * 16], want) and want.abs().max() > 0
+            odd[k:k + feat.numel()] = feat
+    finally:
+        V.vie_cnn_destroy(net)
