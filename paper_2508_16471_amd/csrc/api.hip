@@ -17,6 +17,7 @@
 #include "cnn.h"
 #include "gmres.h"
 #include "green.h"
+#include "entry.h"
 #include "kernels.h"
 #include "trace.h"
 
@@ -414,7 +415,7 @@ static int build_spectrum(vie_ctx* ctx, Group& G) {
 }
 
 extern "C" int vie_setup(const vie_body* bodies, int32_t n_bodies, const vie_options* opt,
-                         vie_ctx** out) {
+                         vie_ctx** out) try {
   TraceRange trace_("vie_setup");
   if (!out) return VIE_EINVAL;
   *out = nullptr;
@@ -435,12 +436,10 @@ extern "C" int vie_setup(const vie_body* bodies, int32_t n_bodies, const vie_opt
   }
   vie_ctx* ctx = new (std::nothrow) vie_ctx();
   if (!ctx) return VIE_ENOMEM;
+  std::unique_ptr<vie_ctx, void (*)(vie_ctx*)> hold(ctx, vie_destroy);  // until it is complete
   ctx->opt = *opt;
   int rc = VIE_OK;
-  auto bail = [&](int code) {
-    vie_destroy(ctx);
-    return code;
-  };
+  auto bail = [](int code) { return code; };
   auto hip_fail = [&](hipError_t e, const char* what) {
     if (getenv("VIE_LOG"))
       fprintf(stderr, "vie: vie_setup: %s failed: %s\n", what, hipGetErrorString(e));
@@ -526,7 +525,6 @@ extern "C" int vie_setup(const vie_body* bodies, int32_t n_bodies, const vie_opt
     // one component of the y/z scratch must be addressable with 32-bit offsets
     const int64_t zl = G.g.N[2] < 16 ? G.g.N[2] : 16;
     if (((G.g.N[2] + zl - 1) / zl) * zl * G.g.P[1] * G.g.P[0] >= ((int64_t)1 << 31)) {
-      vie_destroy(ctx);
       return VIE_ENOTSUP;
     }
   }
@@ -639,9 +637,9 @@ extern "C" int vie_setup(const vie_body* bodies, int32_t n_bodies, const vie_opt
   for (int k = 0; k < 2; ++k)
     if ((he = hipEventCreateWithFlags(&ctx->flag_ev[k], hipEventDisableTiming)) != hipSuccess)
       return hip_fail(he, "hipEventCreateWithFlags");
-  *out = ctx;
+  *out = hold.release();
   return VIE_OK;
-}
+} VIE_CATCH
 
 extern "C" void vie_destroy(vie_ctx* ctx) {
   if (!ctx) return;
@@ -1322,13 +1320,18 @@ static int bind_rhs(vie_ctx* ctx, Group& G, const vie_planewave* inc,
   G.g.nrhs = nr;
   if (nr == 0) return VIE_OK;
   // without storage the bodies have no solution, not even the last one
-  auto unbind = [&](int code) {
-    for (int b : G.bodies) ctx->bodies[b]->nrhs = 0;
-    G.g.nrhs = 0;
-    return code;
-  };
+  struct Bound {
+    vie_ctx* ctx;
+    Group& G;
+    bool done;
+    ~Bound() {
+      if (done) return;
+      for (int b : G.bodies) ctx->bodies[b]->nrhs = 0;
+      G.g.nrhs = 0;
+    }
+  } bound{ctx, G, false};
   int rc = ensure_solve_storage(ctx, G, nr);
-  if (rc != VIE_OK) return unbind(rc);
+  if (rc != VIE_OK) return rc;
   G.roff_host.assign(nr, 0);
   int64_t vlen = 0;
   for (int b : G.bodies) {
@@ -1339,7 +1342,7 @@ static int bind_rhs(vie_ctx* ctx, Group& G, const vie_planewave* inc,
     }
   }
   rc = ensure_vectors(ctx, G, std::max<int64_t>(vlen, 1));
-  if (rc != VIE_OK) return unbind(rc);
+  if (rc != VIE_OK) return rc;
   VIE_HIP(hipMemcpyAsync(G.roff.p, G.roff_host.data(), nr * sizeof(int64_t),
                          hipMemcpyHostToDevice, ctx->stream));
   G.bi.vox = G.vox_all.as<int>();
@@ -1370,6 +1373,7 @@ static int bind_rhs(vie_ctx* ctx, Group& G, const vie_planewave* inc,
                          ctx->stream));
   // the host tables must outlive the copies
   VIE_HIP(hipStreamSynchronize(ctx->stream));
+  bound.done = true;
   return VIE_OK;
 }
 
@@ -1382,7 +1386,7 @@ static double done_seconds(const vie_ctx* ctx, const KState& S, bool conv,
 }
 
 extern "C" int vie_solve(vie_ctx* ctx, const vie_planewave* inc, const int32_t* nrhs_per_body,
-                         vie_stats* stats) {
+                         vie_stats* stats) try {
   TraceRange trace_("vie_solve");
   if (!ctx) return VIE_EINVAL;
   if (ctx->poisoned) return VIE_ESTATE;
@@ -1437,7 +1441,7 @@ extern "C" int vie_solve(vie_ctx* ctx, const vie_planewave* inc, const int32_t* 
   }
   timing_collect(ctx);
   return all_conv ? VIE_OK : VIE_ENOCONV;
-}
+} VIE_CATCH
 
 // ------------------------------------------------- flexible GMRES (FGMRES)
 // Restarted FGMRES with right preconditioning (Saad 1993) and the block
@@ -2144,7 +2148,7 @@ static std::vector<int> rhs_slots(vie_ctx* ctx, const Group& G) {
 
 extern "C" int vie_solve_fgmres(vie_ctx* ctx, const vie_planewave* inc,
                                 const int32_t* nrhs_per_body, const vie_fgmres_options* fo,
-                                vie_stats* stats) {
+                                vie_stats* stats) try {
   TraceRange trace_("vie_solve_fgmres");
   if (!ctx) return VIE_EINVAL;
   if (ctx->poisoned) return VIE_ESTATE;
@@ -2208,10 +2212,10 @@ extern "C" int vie_solve_fgmres(vie_ctx* ctx, const vie_planewave* inc,
   }
   timing_collect(ctx);
   return all_conv ? VIE_OK : VIE_ENOCONV;
-}
+} VIE_CATCH
 
 extern "C" int vie_precond_apply(vie_ctx* ctx, const vie_fgmres_options* fo, const vie_c64* r,
-                                 vie_c64* z, int32_t nvec) {
+                                 vie_c64* z, int32_t nvec) try {
   if (!ctx) return VIE_EINVAL;
   if (ctx->poisoned) return VIE_ESTATE;
   if (!fo || !r || !z || nvec < 1) return VIE_EINVAL;
@@ -2263,26 +2267,21 @@ extern "C" int vie_precond_apply(vie_ctx* ctx, const vie_fgmres_options* fo, con
         o.im = a.im;
       }
   return VIE_OK;
-}
+} VIE_CATCH
 
 // --------------------------------------------------------------- products
 extern "C" int vie_matvec_dev(vie_ctx* ctx, int32_t body, int32_t precision, const void* x,
-                              void* y, int32_t nvec) {
+                              void* y, int32_t nvec) try {
   if (!ctx) return VIE_EINVAL;
   if (ctx->poisoned) return VIE_ESTATE;
   if (body < 0 || body >= (int)ctx->bodies.size() || nvec < 1 || !x || !y) return VIE_EINVAL;
   if (precision != VIE_FP64 && precision != VIE_MIXED) return VIE_EINVAL;
   BodyRec& B = *ctx->bodies[body];
   Group& G = *ctx->groups[B.group];
-  const int saved = G.g.nrhs;
-  G.g.nrhs = nvec;
   // the scratch alone: the last solve's tables stay as they are for
   // vie_cnn_sample_dev, which reads them after any number of products
   int rc = ensure_product_storage(ctx, G, nvec);
-  if (rc != VIE_OK) {
-    G.g.nrhs = saved;
-    return rc;
-  }
+  if (rc != VIE_OK) return rc;
   // Box vectors come in the bodies' grid; the product runs on the compute
   // window.  Outside the window chi = 0, so there y = x.
   const bool window = G.g.n != G.n0;
@@ -2290,12 +2289,8 @@ extern "C" int vie_matvec_dev(vie_ctx* ctx, int32_t body, int32_t precision, con
   c64* ys = (c64*)y;
   if (window) {
     const size_t wb = (size_t)nvec * 3 * G.g.n * sizeof(c64);
-    hipError_t re = G.boxX.reserve(wb);
-    if (re == hipSuccess) re = G.boxY.reserve(wb);
-    if (re != hipSuccess) {
-      G.g.nrhs = saved;
-      VIE_HIP(re);
-    }
+    VIE_HIP(G.boxX.reserve(wb));
+    VIE_HIP(G.boxY.reserve(wb));
     const int64_t shift = (int64_t)G.g.N[0] * G.g.N[1] * B.zoff;
     for (int64_t r = 0; r < (int64_t)nvec * 3; ++r)  // the window of every component
       VIE_HIP(hipMemcpyAsync(G.boxX.as<c64>() + r * G.g.n, (const c64*)x + r * G.n0 + shift,
@@ -2304,10 +2299,16 @@ extern "C" int vie_matvec_dev(vie_ctx* ctx, int32_t body, int32_t precision, con
     ys = G.boxY.as<c64>();
   }
   EpiArgs e{EPI_PLAIN, nullptr, nullptr, 0, nullptr, nullptr};
-  hipError_t err = run_matvec(ctx, G, precision == VIE_MIXED ? 1 : 0, xs, ys, e, nullptr,
-                              G.chi.as<double>() + (int64_t)B.slot * G.g.n);
-  G.g.nrhs = saved;
-  VIE_HIP(err);
+  {
+    struct Vectors {  // the group's right-hand sides for this product
+      int& nrhs;
+      const int saved;
+      ~Vectors() { nrhs = saved; }
+    } vectors{G.g.nrhs, G.g.nrhs};
+    G.g.nrhs = nvec;
+    VIE_HIP(run_matvec(ctx, G, precision == VIE_MIXED ? 1 : 0, xs, ys, e, nullptr,
+                       G.chi.as<double>() + (int64_t)B.slot * G.g.n));
+  }
   if (window) {
     const int64_t shift = (int64_t)G.g.N[0] * G.g.N[1] * B.zoff;
     VIE_HIP(hipMemcpyAsync(y, x, (size_t)nvec * 3 * G.n0 * sizeof(c64), hipMemcpyDeviceToDevice,
@@ -2317,7 +2318,7 @@ extern "C" int vie_matvec_dev(vie_ctx* ctx, int32_t body, int32_t precision, con
                              G.g.n * sizeof(c64), hipMemcpyDeviceToDevice, ctx->stream));
   }
   return VIE_OK;
-}
+} VIE_CATCH
 
 // The product of vie_matvec_dev with every scratch buffer (FFT work arrays,
 // window copies) carved out of the static scratch array instead of memory the
@@ -2325,7 +2326,7 @@ extern "C" int vie_matvec_dev(vie_ctx* ctx, int32_t body, int32_t precision, con
 // 256-byte aligned: bufA, bufB, then the two window copies.  The z-pass shape
 // is the one tuned for this group if any, else the default.
 extern "C" int vie_matvec_dev_static(vie_ctx* ctx, int32_t body, int32_t precision,
-                                     const void* x, void* y, int32_t nvec) {
+                                     const void* x, void* y, int32_t nvec) try {
   if (!ctx) return VIE_EINVAL;
   if (ctx->poisoned) return VIE_ESTATE;
   if (body < 0 || body >= (int)ctx->bodies.size() || nvec < 1 || !x || !y) return VIE_EINVAL;
@@ -2382,10 +2383,10 @@ extern "C" int vie_matvec_dev_static(vie_ctx* ctx, int32_t body, int32_t precisi
                              ctx->stream));
   }
   return VIE_OK;
-}
+} VIE_CATCH
 
 extern "C" int vie_matvec(vie_ctx* ctx, int32_t body, int32_t precision, const vie_c64* x,
-                          vie_c64* y, int32_t nvec) {
+                          vie_c64* y, int32_t nvec) try {
   TraceRange trace_("vie_matvec");
   if (!ctx) return VIE_EINVAL;
   if (ctx->poisoned) return VIE_ESTATE;
@@ -2402,9 +2403,9 @@ extern "C" int vie_matvec(vie_ctx* ctx, int32_t body, int32_t precision, const v
   VIE_HIP(hipStreamSynchronize(ctx->stream));
   timing_collect(ctx);
   return VIE_OK;
-}
+} VIE_CATCH
 
-extern "C" int vie_get_current(vie_ctx* ctx, int32_t body, int32_t rhs, vie_c64* w) {
+extern "C" int vie_get_current(vie_ctx* ctx, int32_t body, int32_t rhs, vie_c64* w) try {
   if (!ctx) return VIE_EINVAL;
   if (ctx->poisoned) return VIE_ESTATE;
   if (body < 0 || body >= (int)ctx->bodies.size() || !w) return VIE_EINVAL;
@@ -2427,7 +2428,7 @@ extern "C" int vie_get_current(vie_ctx* ctx, int32_t body, int32_t rhs, vie_c64*
       w[comp * n0 + shift + vx[k]].im = c[(size_t)comp * B.nb + k].im;
     }
   return VIE_OK;
-}
+} VIE_CATCH
 
 // -------------------------------------------------------------- far field
 // Far field of every right-hand side of body B at ndir directions, given as
@@ -2529,7 +2530,7 @@ static void sph_frame(double t, double p, double* D) {
 }
 
 extern "C" int vie_farfield(vie_ctx* ctx, int32_t body, const double* theta, const double* phi,
-                            int32_t ndir, vie_c64* F) {
+                            int32_t ndir, vie_c64* F) try {
   TraceRange trace_("vie_farfield");
   if (!ctx) return VIE_EINVAL;
   if (ctx->poisoned) return VIE_ESTATE;
@@ -2544,7 +2545,7 @@ extern "C" int vie_farfield(vie_ctx* ctx, int32_t body, const double* theta, con
     ang[ndir + d] = phi[d];
   }
   return far_project(ctx, B, std::move(ang), true, ndir, F);
-}
+} VIE_CATCH
 
 // Gauss-Legendre nodes and weights on [-1, 1]: Newton iteration on P_n from
 // the cosine initial guess, P_n and P_n' by the three-term recurrence.
@@ -2574,7 +2575,7 @@ static void gauss_legendre(int n, std::vector<double>& x, std::vector<double>& w
 }
 
 extern "C" int vie_transfer_na(vie_ctx* ctx, int32_t body, const vie_na_detector* det,
-                               int32_t ndet, int32_t n_rad, int32_t n_az, vie_c64* T) {
+                               int32_t ndet, int32_t n_rad, int32_t n_az, vie_c64* T) try {
   TraceRange trace_("vie_transfer_na");
   if (!ctx) return VIE_EINVAL;
   if (ctx->poisoned) return VIE_ESTATE;
@@ -2645,7 +2646,7 @@ extern "C" int vie_transfer_na(vie_ctx* ctx, int32_t body, const vie_na_detector
       T[(size_t)q * ndet + a] = {re, im};
     }
   return VIE_OK;
-}
+} VIE_CATCH
 
 // ------------------------------------------------------- two-photon (host)
 extern "C" int hom_g2(const vie_c64 T[4], const double* omega, double sigma, const double* dtau,
@@ -2731,7 +2732,7 @@ extern "C" int hom_classical_p2(const vie_c64 T[4], double* p2) {
 // ------------------------------------------------------- network (C ABI)
 extern "C" int64_t vie_cnn_num_params(void) { return cnn_offsets().total; }
 
-extern "C" int vie_cnn_create(uint64_t seed, vie_cnn** out) {
+extern "C" int vie_cnn_create(uint64_t seed, vie_cnn** out) try {
   if (!out) return VIE_EINVAL;
   *out = nullptr;
   vie_cnn* net = new (std::nothrow) vie_cnn();
@@ -2772,7 +2773,7 @@ extern "C" int vie_cnn_create(uint64_t seed, vie_cnn** out) {
   }
   *out = net;
   return VIE_OK;
-}
+} VIE_CATCH
 
 extern "C" void vie_cnn_destroy(vie_cnn* net) {
   if (!net) return;
@@ -2833,7 +2834,7 @@ static bool valid_dims(const int32_t* d) {
 }
 
 extern "C" int vie_cnn_sample_dev(vie_ctx* ctx, int32_t body, int32_t rhs, void* feat,
-                                  void* target, int32_t* dims) {
+                                  void* target, int32_t* dims) try {
   if (!ctx || !dims) return VIE_EINVAL;
   if (ctx->poisoned) return VIE_ESTATE;
   if (body < 0 || body >= (int)ctx->bodies.size()) return VIE_EINVAL;
@@ -2871,7 +2872,7 @@ extern "C" int vie_cnn_sample_dev(vie_ctx* ctx, int32_t body, int32_t rhs, void*
   }
   VIE_HIP(hipStreamSynchronize(ctx->stream));
   return VIE_OK;
-}
+} VIE_CATCH
 
 extern "C" int vie_cnn_infer_dev(vie_cnn* net, const int32_t* dims, const void* feat, void* out,
                                  void* stream) {

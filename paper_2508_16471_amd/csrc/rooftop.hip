@@ -29,11 +29,13 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <memory>
 #include <new>
 #include <type_traits>
 #include <vector>
 
 #include "../../include/vie.h"
+#include "entry.h"
 #include "fft_common.h"
 #include "green.h"
 #include "kernels.h"
@@ -898,7 +900,7 @@ int rt_apply(vie_rt* r, const c64* x, c64* out, int nvec, bool fp32, int mode = 
 
 }  // namespace
 
-extern "C" int vie_rt_setup(const vie_body* body, double k0, vie_rt** out) {
+extern "C" int vie_rt_setup(const vie_body* body, double k0, vie_rt** out) try {
   TraceRange trace_("vie_rt_setup");
   if (!out) return VIE_EINVAL;
   *out = nullptr;
@@ -917,6 +919,7 @@ extern "C" int vie_rt_setup(const vie_body* body, double k0, vie_rt** out) {
 
   vie_rt* r = new (std::nothrow) vie_rt();
   if (!r) return VIE_ENOMEM;
+  std::unique_ptr<vie_rt, void (*)(vie_rt*)> hold(r, vie_rt_destroy);  // until it is complete
   for (int a = 0; a < 3; ++a) {
     r->N[a] = body->n[a];
     r->origin[a] = body->origin[a];
@@ -991,11 +994,7 @@ extern "C" int vie_rt_setup(const vie_body* body, double k0, vie_rt** out) {
   // the circulant and its transform, for the spectrum only, then the workspace:
   // whichever is larger is the one allocation
   chk(rt_reserve(r, 1, 2 * M * sizeof(c64)));
-  if (e != hipSuccess) {
-    rt_free(r);
-    delete r;
-    return e == hipErrorOutOfMemory ? VIE_ENOMEM : VIE_EDEVICE;
-  }
+  if (e != hipSuccess) return e == hipErrorOutOfMemory ? VIE_ENOMEM : VIE_EDEVICE;
   c64 *work = (c64*)r->w.base, *tmp = work + M;
   std::vector<c64> tab(3 * sum);
   c32* tab32 = (c32*)(tab.data() + 2 * sum);
@@ -1027,14 +1026,10 @@ extern "C" int vie_rt_setup(const vie_body* body, double k0, vie_rt** out) {
     chk(hipGetLastError());
   }
   if (e == hipSuccess) chk(hipStreamSynchronize(r->stream));
-  if (e != hipSuccess) {
-    rt_free(r);
-    delete r;
-    return VIE_EDEVICE;
-  }
-  *out = r;
+  if (e != hipSuccess) return VIE_EDEVICE;
+  *out = hold.release();
   return VIE_OK;
-}
+} VIE_CATCH
 
 extern "C" int vie_rt_grid(const vie_rt* r, int32_t* ext, int32_t* fft) {
   if (!r) return VIE_EINVAL;
@@ -1046,7 +1041,7 @@ extern "C" int vie_rt_grid(const vie_rt* r, int32_t* ext, int32_t* fft) {
 }
 
 extern "C" int vie_rt_matvec(vie_rt* r, const vie_c64* x, vie_c64* y, int32_t nvec,
-                             int32_t precision) {
+                             int32_t precision) try {
   if (!r || !x || !y || nvec < 1 || (precision != VIE_FP64 && precision != VIE_MIXED))
     return VIE_EINVAL;
   if (r->poisoned) return VIE_ESTATE;
@@ -1059,7 +1054,7 @@ extern "C" int vie_rt_matvec(vie_rt* r, const vie_c64* x, vie_c64* y, int32_t nv
     RT_HIP(r->stage.to_host(y + v * n, dy, n * sizeof(c64), r->stream));
   }
   return VIE_OK;
-}
+} VIE_CATCH
 
 // Solves nc channels as one batch (host driver of the iteration): chunks of
 // iterations run on the device, the host looks at the scalars once per chunk
@@ -1211,7 +1206,7 @@ static int rt_solve_batch(vie_rt* r, const vie_planewave* inc, int nc, double to
 }
 
 extern "C" int vie_rt_solve(vie_rt* r, const vie_planewave* inc, int32_t nrhs, double tol,
-                            int32_t max_iter, int32_t precision, vie_c64* w, vie_stats* stats) {
+                            int32_t max_iter, int32_t precision, vie_c64* w, vie_stats* stats) try {
   TraceRange trace_("vie_rt_solve");
   if (!r || !inc || !w || nrhs < 1 || !(tol > 0) || !(tol < 1) || max_iter < 1 ||
       (precision != VIE_FP64 && precision != VIE_MIXED))
@@ -1240,10 +1235,10 @@ extern "C" int vie_rt_solve(vie_rt* r, const vie_planewave* inc, int32_t nrhs, d
                           precision == VIE_MIXED, w + k * 3 * q.m, stats ? stats + k : nullptr,
                           &all));
   return all ? VIE_OK : VIE_ENOCONV;
-}
+} VIE_CATCH
 
 extern "C" int vie_rt_farfield(vie_rt* r, const vie_c64* w, int32_t nrhs, const double* theta,
-                               const double* phi, int32_t ndir, vie_c64* F) {
+                               const double* phi, int32_t ndir, vie_c64* F) try {
   TraceRange trace_("vie_rt_farfield");
   if (!r || !w || !theta || !phi || !F || nrhs < 1 || ndir < 1) return VIE_EINVAL;
   if (r->poisoned) return VIE_ESTATE;
@@ -1354,7 +1349,7 @@ extern "C" int vie_rt_farfield(vie_rt* r, const vie_c64* w, int32_t nrhs, const 
     return VIE_EDEVICE;
   }
   return VIE_OK;
-}
+} VIE_CATCH
 
 extern "C" void vie_rt_destroy(vie_rt* r) {
   if (!r) return;

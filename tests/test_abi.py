@@ -36,3 +36,31 @@ def test_binding_names_match_header():
 
     for n in _declared():
         assert hasattr(vie, n), n
+
+
+CHILD = """
+import ctypes, resource, sys
+import numpy as np
+from paper_2508_16471_amd import vie as V
+eps = np.full((128, 128, 128), 2.0)
+V.lib()
+vm = int([l for l in open("/proc/self/status") if l.startswith("VmSize")][0].split()[1]) << 10
+resource.setrlimit(resource.RLIMIT_AS, (vm + (24 << 20), resource.RLIM_INFINITY))
+try:
+    V.vie_rt_setup(eps, 0.05, (0, 0, 0), 6.28)
+except V.VieError as e:
+    print("code", e.code)
+"""
+
+
+def test_host_memory_that_runs_out_is_an_error_code():
+    """The face data of 128^3 cells take 120 MB of host memory before any device
+    call: with 24 MB left the entry point returns VIE_ENOMEM, nothing is thrown
+    across the ABI (which would end the process)."""
+    import subprocess
+    import sys
+
+    p = subprocess.run([sys.executable, "-c", CHILD], cwd=ROOT, capture_output=True, text=True,
+                       timeout=300)
+    assert p.returncode == 0 and p.stdout.split() == ["code", "-2"], (p.returncode, p.stdout,
+                                                                      p.stderr[-500:])
