@@ -36,7 +36,7 @@
 
 #include "../../include/vie.h"
 #include "entry.h"
-#include "fft_common.h"
+#include "fft_plane.h"
 #include "green.h"
 #include "kernels.h"
 #include "trace.h"
@@ -347,32 +347,8 @@ constexpr int kRtFold = 64;  // partial pairs per vector that a vector kernel su
 
 // Sum of n pairs of partials in a fixed order, to every thread.
 __device__ __forceinline__ void rt_sum(const c64* __restrict__ part, int n, c64& a, c64& b) {
-  __shared__ double red[kRtThreads / 64][4];
-  c64 s0 = mk(0.0, 0.0), s1 = mk(0.0, 0.0);
-  for (int k = threadIdx.x; k < n; k += kRtThreads) {
-    s0 = s0 + part[2 * k];
-    s1 = s1 + part[2 * k + 1];
-  }
-  for (int m = 32; m >= 1; m >>= 1) {
-    s0.re += __shfl_xor(s0.re, m, 64);
-    s0.im += __shfl_xor(s0.im, m, 64);
-    s1.re += __shfl_xor(s1.re, m, 64);
-    s1.im += __shfl_xor(s1.im, m, 64);
-  }
-  __syncthreads();  // red may still be read from an earlier sum
-  if ((threadIdx.x & 63) == 0) {
-    double* r = red[threadIdx.x >> 6];
-    r[0] = s0.re;
-    r[1] = s0.im;
-    r[2] = s1.re;
-    r[3] = s1.im;
-  }
-  __syncthreads();
-  a = b = mk(0.0, 0.0);
-  for (int w = 0; w < kRtThreads / 64; ++w) {
-    a = a + mk(red[w][0], red[w][1]);
-    b = b + mk(red[w][2], red[w][3]);
-  }
+  __shared__ double red[16];
+  fold_pairs<kRtThreads>(part, n, red, a, b);
 }
 
 // This thread's sums into the workgroup's partial pair.
@@ -422,10 +398,6 @@ struct RtScal {
   int stop;         // 0 running, 1 recursive residual reached, 2 breakdown, 3 cap
 };
 
-__device__ __forceinline__ c64 rt_cdiv(c64 a, c64 b) {
-  const double d = b.re * b.re + b.im * b.im;
-  return mk((a.re * b.re + a.im * b.im) / d, (a.im * b.re - a.re * b.im) / d);
-}
 __device__ __forceinline__ bool rt_zero(c64 a) { return a.re == 0.0 && a.im == 0.0; }
 
 // b = chi_f pol_i e^{i k0 khat . r_f}, face i of padded cell c at
@@ -510,7 +482,7 @@ __global__ void __launch_bounds__(kRtThreads) k_rt_pupd(
     if (stop) active[vec] = 0;
   }
   if (stop) return;
-  const c64 beta = rt_cdiv(rho1, rho) * rt_cdiv(alpha, om);
+  const c64 beta = kcdiv(rho1, rho) * kcdiv(alpha, om);
   for (int64_t e = (int64_t)blk * kRtThreads + threadIdx.x; e < n; e += (int64_t)vb * kRtThreads) {
     const int64_t g = vec * n + e;
     p[g] = r[g] + beta * (p[g] - om * v[g]);
@@ -529,7 +501,7 @@ __global__ void __launch_bounds__(kRtThreads) k_rt_supd(
   c64 rhv, none;
   rt_sum(part + (int64_t)vec * npart * 2, npart, rhv, none);
   const bool stop = rt_zero(rhv);
-  const c64 al = stop ? mk(0.0, 0.0) : rt_cdiv(rho1, rhv);
+  const c64 al = stop ? mk(0.0, 0.0) : kcdiv(rho1, rhv);
   if (blk == 0 && threadIdx.x == 0) {
     if (stop) {
       S->stop = 2;
