@@ -85,12 +85,13 @@ enum vie_status {
  * The block solves only approximate M^{-1}, so the basis' rounding (a few
  * 1e-3 relative) leaves the preconditioner about as good while the basis
  * traffic halves; the FP64 outer residual still decides convergence.
- * Where the block grid allows it (16-layer z tiles, padded z length 32, 48,
- * 64, 96 or 128, and an even number of threads per x line), the block
- * products' y and z transforms and the Green tensor product run in packed
- * FP16 on FP16 scratch (two columns per register); the x transforms stay
- * FP32 and convert at the scratch side, fused with the y transforms per z
- * plane where the x and y lengths are 64, 96 or 128.  Each forward transform
+ * Where the block grid allows it (16-layer z tiles, padded z length 32, 64,
+ * 96 or 128, and x lines in whole tiles of the z pass), the block products' y
+ * and z transforms and the Green tensor product run in FP16 on FP16 scratch;
+ * the x transforms stay FP32 and convert at the scratch side.  Where the x and
+ * y lengths are 64, 96 or 128, all three run as products with DFT matrices on
+ * the matrix cores (FP32 sums; y, z and the spectrum in one pass), else in
+ * packed FP16 arithmetic (two columns per register).  Each forward transform
  * scales its input by a power of two at most 1/sqrt(extent), the spectrum by
  * a power of two that brings its largest modulus into [1/2, 1), so no
  * intermediate overflows for the unit-norm basis vectors the block solves
@@ -393,9 +394,9 @@ int vie_matvec_dev(vie_ctx *ctx, int32_t body, int32_t precision, const void *x_
  * harnesses that forbid hipMalloc): same arguments, layout and result (the
  * same kernels; the z-pass launch shape is the one the context has tuned for
  * this grid, else the default).  The call allocates nothing, copies nothing
- * from host memory and records no memset: its scratch (FFT work arrays, a
- * table of nvec ints and, with the z window, two window copies of the
- * vectors) lives in a static device array of VIE_STATIC_SCRATCH_BYTES that
+ * from host memory and records no memset: its scratch (FFT work arrays,
+ * 4 bytes a vector that are not used and, with the z window, two window
+ * copies of the vectors) lives in a static device array of VIE_STATIC_SCRATCH_BYTES that
  * the library holds on every GPU it runs on until the process ends.  Bytes
  * needed, each term rounded up to 256, with c = 16 (VIE_FP64) or 8
  * (VIE_MIXED), window grid (N1, N2, N3) and FFT lengths (P1, P2, P3) as
@@ -422,9 +423,10 @@ int vie_set_stream(vie_ctx *ctx, void *hip_stream);
  * five product passes per precision ("fft_x_fwd_f64" ... "fft_x_inv_f32"),
  * Krylov vector work, reductions, far field, setup, network; the same five
  * passes of the block solves of vie_solve_fgmres ("block_fft_..."), its
- * Arnoldi vector kernels ("arnoldi"), and the five packed-FP16 passes
- * ("fft_x_fwd_h16" ... "fft_x_inv_h16", and "block_fft_..._h16").  Call with
- * *nkinds = 0 to learn the number of kinds.  reset != 0 clears the
+ * Arnoldi vector kernels ("arnoldi"), and the FP16 passes: the five packed ones
+ * ("fft_x_fwd_h16" ... "fft_x_inv_h16") or the three on the matrix cores
+ * ("fft_xy_fwd_h16", "fft_z_h16" for y, z and the spectrum, "fft_yx_inv_h16"),
+ * and "block_fft_..._h16".  Call with *nkinds = 0 to learn the number of kinds.  reset != 0 clears the
  * accumulators after reading. */
 int vie_kernel_times(vie_ctx *ctx, const char **names, double *ms, int64_t *cnt,
                      int32_t *nkinds, int32_t reset);

@@ -442,7 +442,9 @@ __global__ __launch_bounds__(GNT) void k_conv3d_wgrad(const bf16raw* __restrict_
 
 // Sum of the weight-gradient partials, in fixed order, put in parameter order
 // ([tap][co][ci], then the biases): four waves take a quarter of the blocks
-// each for 64 neighbouring elements.
+// each for 64 neighbouring elements.  Chains of 64 partials after a block's own:
+// 2.1e-7, 1.7e-7 and 1.0e-7 off the 64-bit sums on boxes of 121 x 107 x 37, 64 x 64 x
+// 37 and 30 x 25 x 16 (512 partials in one chain: 4.1e-7, 4.6e-7, 1.6e-7).
 template <int COUT>
 __global__ __launch_bounds__(256) void k_reduce_parts(const float* __restrict__ part, int nblk,
                                                       float* __restrict__ out) {

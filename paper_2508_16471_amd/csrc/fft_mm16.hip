@@ -28,7 +28,12 @@
 // bits (a bfloat16 vector times 2^14, or the FP16 plane): the products with
 // C and S split into two halves each (hi + lo, 2^-25 off) are exact and are
 // summed in FP32, 6e-8 to 7e-8 off the 64-bit transform for P = 64 to 128
-// (FP32 Stockham stages: 6e-8 to 8e-8).  The y and z transforms are FP16
+// (FP32 Stockham stages: 6e-8 to 8e-8).  The input is a vector of the block
+// solves' basis, of norm 1 in whichever form it comes: no entry reaches the 4
+// at which 2^14 times it overflows (the forward scales rest on the norm as
+// well).  Entries below 2^-31 keep 2^-39 instead of their 8 bits, at most 2^-33 in
+// a sum of 64, whose result is rounded to FP16 at the scale 1/8: 2^-36 against
+// half of that format's smallest step, 2^-25.  The y and z transforms are FP16
 // transforms: FP16 operands, FP32 sums, one rounding per transform.
 #include "fft_common.h"
 

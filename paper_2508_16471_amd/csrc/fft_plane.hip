@@ -303,8 +303,10 @@ __global__ __launch_bounds__(NT) void k_plane_inv(
 // boxes, microseconds separate / fused: FP64 16^3 x 1, 8, 32 vectors 22.9 / 15.5,
 // 32.5 / 23.5, 51.7 / 41.4; 32^3 33.6 / 27.0, 83.0 / 66.3, 285.6 / 212.0; FP32 32^3
 // 29.5 / 19.2, 50.3 / 35.7, 137.1 / 104.1.  At 96 points a plane's lines pass in
-// five batches and two workgroups fill a CU's LDS: 81 us against 56 for the
-// four separate FP32 passes of 8 vectors of 48^3.
+// three to five batches and one workgroup (FP32 two) fills a CU's LDS: 48^3 x 1,
+// 8, 32 vectors FP64 70 / 73, 349 / 335, 1397 / 1418, FP32 45 / 48, 142 / 152, 651 /
+// 653; 40 x 35 x 44 FP64 62 / 66, 273 / 293, 1126 / 1197, FP32 45 / 47, 128 / 146, 567 /
+// 593.
 static bool plane_len(int p) { return p == 24 || p == 32 || p == 48 || p == 64; }
 bool plane_ok(const GroupGeom& g) {
   return plane_len(g.P[0]) && plane_len(g.P[1]);

@@ -590,12 +590,13 @@ struct RtBuf {
 };
 }  // namespace
 
-// Pinned pieces between the device and the caller's pageable arrays.  The
-// runtime's own copy back of 12.4 MB takes 715 us; a pinned copy takes 235 us
-// and one core reads 12.4 MB that the device has just written in 400 us, so
-// with four pieces of 1 MB in turn the two overlap: 460 us (256 KB: 900, 512
-// KB: 580, 2 MB: 475 us).  The other way staging is no faster (475 us against
-// 342 us).  Kept by the handle, made by its first large copy (300 us).
+// Pinned pieces between the device and the caller's pageable arrays.  For the
+// 13.8 MB of a 64^3 body's vector the runtime's own copy back takes 940 us; a
+// pinned copy takes 256 us and one core reads what the device has just written
+// in 530 us, so with four pieces of 1 MB in turn the two overlap: 537 us (256
+// KB: 994, 512 KB: 628, 2 MB: 543 us).  The other way staging is no faster (475
+// us against 342 us for 12.4 MB).  Kept by the handle, made by its first large
+// copy (300 us).
 struct RtStage {
   static constexpr int kPieces = 4;
   static constexpr size_t kPiece = (size_t)1 << 20;

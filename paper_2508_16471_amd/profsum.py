@@ -23,9 +23,10 @@ import sqlite3
 import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-PRODUCT_SOURCES = ["paper_2508_16471_amd/csrc/fft_passes.hip", "paper_2508_16471_amd/csrc/fft_xc.hip",
-                   "paper_2508_16471_amd/csrc/fft_common.h", "paper_2508_16471_amd/csrc/fft.h",
-                   "paper_2508_16471_amd/csrc/common.h", "paper_2508_16471_amd/csrc/kernels.h"]
+# every file whose code the operator products run
+PRODUCT_SOURCES = ["paper_2508_16471_amd/csrc/" + f for f in (
+    "fft_passes.hip", "fft_xc.hip", "fft_mm16.hip", "fft_plane.hip", "fft_plane.h",
+    "fft_common.h", "fft.h", "common.h", "kernels.h")]
 COPY_BYTES = 512 << 20
 
 

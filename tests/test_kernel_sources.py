@@ -57,3 +57,15 @@ def test_lines_written_over_their_transform_are_fenced():
         if reads >= 0:
             assert "wave_fence();" in after[0][at:at + reads], name
     assert writes == 2
+
+
+def test_traffic_records_cover_every_product_source():
+    """A counter record is stamped with the sources it was taken from: all files
+    of the FFT passes, and what they include."""
+    from paper_2508_16471_amd.profsum import PRODUCT_SOURCES
+
+    want = {f for f in os.listdir(CSRC) if f.startswith("fft")}
+    for f in sorted(want):
+        with open(os.path.join(CSRC, f)) as fh:
+            want |= set(re.findall(r'#include "(\w+\.h)"', fh.read()))
+    assert {os.path.basename(f) for f in PRODUCT_SOURCES} == want
