@@ -698,12 +698,11 @@ __device__ __forceinline__ void ff_dot(double& hi, double& lo, double a, double 
   hi = s;
 }
 // v exp(i (x + lo)) as v + v (exp - 1): a small phase's rounding stays as small as
-// the phase (and any size of phase will do).
+// the phase.
 __device__ __forceinline__ c64 ff_turn(c64 v, double x, double lo) {
   double s, c;
-  sincos(0.5 * x, &s, &c);
-  const double sn = 2.0 * s * c, t = -2.0 * s * s;
-  const double re = t - lo * sn, im = fma(lo, t, lo) + sn;
+  ff_sincos(0.5 * x, 0.5 * lo, s, c);
+  const double im = 2.0 * s * c, re = -2.0 * s * s;
   return mk(v.re + fma(re, v.re, -(im * v.im)), v.im + fma(re, v.im, im * v.re));
 }
 
@@ -727,6 +726,10 @@ __global__ __launch_bounds__(256) void k_farfield_project(const c64* __restrict_
                                                           c64* __restrict__ F) {
   const int e = (blockIdx.x * 256 + threadIdx.x) / L, lane = threadIdx.x % L;
   if (e >= npair) return;
+  const int pos = e % nd, q = e / nd;
+  double D[9];  // requested before the partials
+#pragma unroll
+  for (int k = 0; k < 9; ++k) D[k] = dirs[(int64_t)pos * 9 + k];
   c64 v[3];
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
@@ -741,16 +744,25 @@ __global__ __launch_bounds__(256) void k_farfield_project(const c64* __restrict_
       v[c].re += __shfl_xor(v[c].re, m, 64);
       v[c].im += __shfl_xor(v[c].im, m, 64);
     }
-  if (lane != 0) return;
-  const int pos = e % nd, q = e / nd;
-  const double* D = dirs + (int64_t)pos * 9;
   double at = 0.0, atl = 0.0;
+#pragma unroll
   for (int a = 0; a < 3; ++a) ff_dot(at, atl, D[a], g.o[a]);
-  for (int c = 0; c < 3; ++c) {
+  auto turned = [&](double r, c64 w) {
     double x = at, xl = atl;
-    ff_dot(x, xl, D[c], g.half);
+    ff_dot(x, xl, r, g.half);
     const double ang = -g.k0 * x;
-    v[c] = ff_turn(v[c], ang, fma(-g.k0, xl, fma(-g.k0, x, -ang)));
+    return ff_turn(w, ang, fma(-g.k0, xl, fma(-g.k0, x, -ang)));
+  };
+  if constexpr (L > 1) {  // the components side by side in the first lanes
+    auto mine = [&](double a, double b, double c) { return lane == 1 ? b : lane == 2 ? c : a; };
+    const c64 t = turned(mine(D[0], D[1], D[2]), mk(mine(v[0].re, v[1].re, v[2].re),
+                                                    mine(v[0].im, v[1].im, v[2].im)));
+#pragma unroll
+    for (int c = 0; c < 3; ++c) v[c] = mk(__shfl(t.re, c, 64), __shfl(t.im, c, 64));
+    if (lane != 0) return;
+  } else {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) v[c] = turned(D[c], v[c]);
   }
   c64 ft = mk(0.0, 0.0), fp = mk(0.0, 0.0);
   for (int c = 0; c < 3; ++c) {
