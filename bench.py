@@ -638,9 +638,10 @@ def farfield_mode(args):
     V.lib()
     bodies, chans = make_workload(1, args.channels, args.grid)
     eps, h, o, g = bodies[0]
+    args.wflag = 0 if args.no_window else V.VIE_FLAG_Z_WINDOW
     ctx = V.vie_setup([(eps, h, o)], V.make_options(K0, precision=V.VIE_MIXED, tol=args.tol,
                                                    max_iter=20000, inner_tol=args.inner_tol,
-                                                   flags=V.VIE_FLAG_TIMING))
+                                                   flags=V.VIE_FLAG_TIMING | args.wflag))
     try:
         sweep = farfield_sweep(V, torch, ctx, args, chans, args.channels, eps != 1.0,
                                reps=max(1, args.steps))
