@@ -1266,7 +1266,7 @@ def main():
                 "cnn": cnn_mode, "rooftop": rooftop_mode}[args.mode](args)
     if args.gpus != 1:
         print(json.dumps({"error": "this build runs on one GPU only; the path shards by "
-                          "right-hand side / body (see DESIGN.md), --gpus must be 1"}))
+                          "right-hand side / body, --gpus must be 1"}))
         sys.exit(2)
     bodies, chans = make_workload(args.bodies, args.channels, args.grid)
     cpu_t = c1 = None

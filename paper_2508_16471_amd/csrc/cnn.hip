@@ -88,9 +88,10 @@ struct ConvDims {
 // the other's MFMAs.  Rows of 64 bytes are stored with their 16-byte slots
 // rotated by the voxel (row) index so that neighbouring lanes hit different
 // banks.  The voxels are the MFMA's columns: each lane ends with four
-// neighbouring channels of one voxel, one packed store.  Bound by LDS reads
-// and MFMAs about equally (17 and 14 us of the 35 us per 32 -> 32 layer on
-// 128 x 128 x 37, where one layer per wave with 2-byte stores took 79 us).
+// neighbouring channels of one voxel, one packed store.  41 us per 32 -> 32
+// layer on 128 x 128 x 37, where one layer per wave with 2-byte stores took 79;
+// the matrix cores are busy for 41 % of the CUs' busy cycles, the LDS for 22 %
+// (no bank conflicts): the waits between reads, products and staging bound it.
 template <int CIN, int COUT, int MODE>
 __global__ __launch_bounds__(CNT) __attribute__((amdgpu_waves_per_eu(2))) void k_conv3d(
     const bf16raw* __restrict__ in, const bf16raw* __restrict__ w, const float* __restrict__ bias,
